@@ -198,7 +198,8 @@ size_t moe_block_list_len(int T, int k, int C);
  * few microseconds of work behind a launch of similar cost; this entry point pays one launch.
  * sync_dev: moe_front_sync_len() int32 of device memory, zero before the first call; every call
  * leaves its first 33 words zero (the rest is scratch).  Calls that share sync_dev must not overlap
- * in time.  Up to 8192 requests (T*k) the call is one launch and sync_dev is one word; larger
+ * in time.  Up to 8192 requests (T*k) the call is one launch and sync_dev is one word (batches of up to 16 tokens
+ * are one workgroup and leave it alone); larger
  * batches take three launches: the routing workgroups collect the activated experts in a bitset
  * (Alg. 1, Step 1, token-parallel), the last of them runs Step 2, and Step 3 and the sort run
  * over chunks of 2048 requests, one workgroup each (per-chunk counts, then the scatter; no
@@ -264,11 +265,11 @@ int moe_scaling_solve(const moe_scaling_model *m, const double *amax_table_host,
                       const double *B_values_host, int n_B, double lambda, double slo, int n_max, int ne_min,
                       double B_max, int *n_a_out, int *n_e_out, double *B_star_out, double *tpot_out);
 
-/* ------------------------------------------------------------------ the gate in the same launch
+/* ------------------------------------------------------------------ the gate on the MoE side
  * Sec. 3.3 ("gating on the MoE side"): the MoE instance receives the complete activations and
  * runs the gate itself.  These two entry points start from the activations instead of from
  * logits: logits[i, e] = sum_c X[i, c] * W_r[e, c] (+ bias[e]), bf16 operands, fp32 products
- * and sums (MFMA), then the selection of moe_route on those fp32 logits, in one launch;
+ * and sums (MFMA), one launch, then the selection of moe_route on those fp32 logits, another;
  * moe_gate_route_schedule_permute continues through Alg. 1 and the dispatch exactly like
  * moe_route_schedule_permute.
  *   X_dev      [T, d_h] bf16, row-major, 16-byte aligned

@@ -23,27 +23,50 @@ __device__ __forceinline__ uint64_t readfirstlane_u64(uint64_t v) {
 }
 
 // ------------------------------------------------------------------ a0: one token per wavefront
-// Largest key of the wavefront, in every lane.  Data-parallel-primitive moves instead of LDS-crossbar
+// Largest unsigned key of the wavefront, as a scalar.  Data-parallel-primitive moves instead of LDS-crossbar
 // shuffles (the k selection rounds of a token are a chain of these): two exchanges inside quads, two
 // rotations inside rows of 16 lanes, then the row results travel to the last lane through the two
 // row broadcasts, and a scalar lane read hands the result to everybody.  Lanes a move does not
-// write read 0, the smallest key.
+// write read 0, the smallest key.  Keys are 32 bits so that a step is one instruction (a 64-bit key that
+// carries the id for ties takes five: the E = 256 selection was 1.5 us longer with it).
 template <int CTRL, int ROW_MASK>
-__device__ __forceinline__ uint64_t dpp_max_step(uint64_t v) {
-    const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(v & 0xffffffffu), CTRL, ROW_MASK, 0xf, false);
-    const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(v >> 32), CTRL, ROW_MASK, 0xf, false);
-    const uint64_t o = (static_cast<uint64_t>(hi) << 32) | lo;
+__device__ __forceinline__ uint32_t dpp_max_step(uint32_t v) {
+    const uint32_t o = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), CTRL, ROW_MASK, 0xf, false));
     return o > v ? o : v;
 }
 
-__device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     v = dpp_max_step<0xB1, 0xf>(v);                      // quad_perm [1,0,3,2]
     v = dpp_max_step<0x4E, 0xf>(v);                      // quad_perm [2,3,0,1]
     v = dpp_max_step<0x124, 0xf>(v);                     // row_ror:4
     v = dpp_max_step<0x128, 0xf>(v);                     // row_ror:8   -> every lane: its row's largest
     v = dpp_max_step<0x142, 0xa>(v);                     // row_bcast:15 into rows 1 and 3
     v = dpp_max_step<0x143, 0xc>(v);                     // row_bcast:31 into rows 2 and 3 -> lane 63: the largest
-    return readlane_u64(v, MOE_WAVE - 1);
+    return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), MOE_WAVE - 1));
+}
+
+// Smallest key of each row of 16 lanes, in every lane of the row; and, from that, of the wavefront.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_min_step(uint32_t v) {
+    const uint32_t o = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(-1, static_cast<int>(v), CTRL, 0xf, 0xf, false));
+    return o < v ? o : v;
+}
+
+__device__ __forceinline__ uint32_t wave_min_rows_u32(uint32_t v) {
+    v = dpp_min_step<0xB1>(v);                           // quad_perm [1,0,3,2]
+    v = dpp_min_step<0x4E>(v);                           // quad_perm [2,3,0,1]
+    v = dpp_min_step<0x124>(v);                          // row_ror:4
+    return dpp_min_step<0x128>(v);                       // row_ror:8
+}
+
+__device__ __forceinline__ uint32_t wave_min_of_rows_u32(uint32_t v) {
+    uint32_t m = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 0));
+#pragma unroll
+    for (int r = 1; r < 4; ++r) {
+        const uint32_t o = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), r * 16));
+        m = o < m ? o : m;
+    }
+    return m;
 }
 
 // Inclusive prefix sum over the 64 lanes with the same moves: three shifts of the input and two of
@@ -87,32 +110,33 @@ __device__ __forceinline__ float from_orderable(uint32_t o) {
     return __uint_as_float(u);
 }
 
-__device__ __forceinline__ uint64_t make_key(float v, int id) {
-    return (static_cast<uint64_t>(orderable(v)) << 32) | static_cast<uint32_t>(0x7fffffff - id);
-}
-
 __device__ __forceinline__ float sigmoid_f32(float x) { return 1.0f / (1.0f + expf(-x)); }
 
-// Lane l owns experts l, l+64, ...; every logit becomes a 64-bit key (order-preserving float bits
-// in the high word, ~id in the low word) so that "largest logit, lower id on ties" is an unsigned
-// comparison.  With one key per lane (E <= 64) the top-k are the keys that fewer than k other keys
-// exceed (rank counting with scalar lane broadcasts, no shuffles); with more keys per lane the k
-// selections are k maxima, each found with a 6-step cross-lane butterfly.
-// row_lds: VPL*64 floats private to this wavefront.  ROW_IN_LDS: `row` already is that LDS copy (the
-// caller passes the same address twice and has ordered its writes).  COHERENT: results are written with agent-scope
-// stores (read by another workgroup of the same launch).
+// Lane l owns experts l, l+64, ...; every logit becomes an unsigned key in the order of the floats, and the k
+// selections are k rounds: every lane's largest remaining key, the wavefront's largest of those (6 cross-lane
+// steps), the lane that holds it from a ballot.  Equal logits go to the lower id: the lowest index inside a lane,
+// and among several lanes with the same key (rare) the smallest id over them.  Experts that are taken, dropped or
+// past E have key 0 and no bit in `alive`, so that a surviving NaN whose key is 0 is still found.
+// row_lds: VPL*64 floats private to this wavefront.  COHERENT: ids are written with agent-scope stores (read by
+// another workgroup of the same launch).  ids_lds (optional): a copy of the ids in LDS.
 // mark_lds (optional): a bitset in LDS in which the selected experts are raised.
-template <int VPL, bool COHERENT, bool ROW_IN_LDS = false>
+template <int VPL, bool COHERENT>
 __device__ __forceinline__ void route_token(const float *row, int E, int k, const moe_route_cfg &cfg,
                                             float *row_lds, int lane, int32_t *ids_out, float *w_out,
-                                            uint32_t *mark_lds = nullptr) {
+                                            int32_t *ids_lds = nullptr, uint32_t *mark_lds = nullptr) {
     float v[VPL];
-    uint64_t key[VPL];
+    uint32_t key[VPL];
+    uint32_t alive = 0u;
 #pragma unroll
     for (int i = 0; i < VPL; ++i) {
         const int e = lane + i * MOE_WAVE;
         v[i] = e < E ? row[e] : 0.0f;
-        key[i] = e < E ? make_key(v[i], e) : 0ull;
+    }
+#pragma unroll
+    for (int i = 0; i < VPL; ++i) {
+        const bool ok = lane + i * MOE_WAVE < E;
+        key[i] = ok ? orderable(v[i]) : 0u;
+        alive |= ok ? 1u << i : 0u;
     }
 
     float denom_all = 0.0f;                              // softmax denominator over all experts
@@ -120,14 +144,14 @@ __device__ __forceinline__ void route_token(const float *row, int E, int k, cons
         // group score = sum of the two largest sigmoid scores of the group, in fp32
         const int per = E / cfg.n_group;
 #pragma unroll
-        for (int i = 0; i < VPL; ++i)
-            if (!ROW_IN_LDS) row_lds[lane + i * MOE_WAVE] = v[i];
+        for (int i = 0; i < VPL; ++i) row_lds[lane + i * MOE_WAVE] = v[i];
         // the row is private to this wave: a wavefront-scope fence orders its LDS writes
         // before the reads below (no block barrier: waves may be on different tokens)
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        uint64_t gkey = 0ull;
+        uint32_t gkey = 0u;
+        bool galive = false;
         int owner_shift = 0;                             // group g's key sits in lane g << owner_shift
         if (cfg.n_group <= MOE_WAVE / 8) {
             // eight lanes per group: each scans an eighth of the group, then three exchanges inside the
@@ -158,7 +182,8 @@ __device__ __forceinline__ void route_token(const float *row, int E, int k, cons
             MOE_TOP2_MERGE(0x4E);                        // quad_perm [2,3,0,1]
             MOE_TOP2_MERGE(0x141);                       // row_half_mirror: the other quad of the eight
 #undef MOE_TOP2_MERGE
-            if (sub == 0 && g < cfg.n_group) gkey = make_key(sigmoid_f32(a) + sigmoid_f32(b), g);
+            galive = sub == 0 && g < cfg.n_group;
+            if (galive) gkey = orderable(sigmoid_f32(a) + sigmoid_f32(b));
         } else if (lane < cfg.n_group) {
             float a = -INFINITY, b = -INFINITY;          // a >= b: two largest logits of the group
             for (int j = 0; j < per; ++j) {
@@ -166,27 +191,28 @@ __device__ __forceinline__ void route_token(const float *row, int E, int k, cons
                 if (x > a) { b = a; a = x; }
                 else if (x > b) { b = x; }
             }
-            const float score = sigmoid_f32(a) + sigmoid_f32(b);
-            gkey = make_key(score, lane);
+            galive = true;
+            gkey = orderable(sigmoid_f32(a) + sigmoid_f32(b));
         }
         uint64_t keep = 0ull;
         for (int j = 0; j < cfg.topk_group; ++j) {
-            const uint64_t best = wave_max_u64(gkey);
-            const int g = 0x7fffffff - static_cast<int>(best & 0xffffffffu);
-            keep |= 1ull << g;
-            if (lane == (g << owner_shift)) gkey = 0ull;
+            const uint32_t best = wave_max_u32(gkey);
+            // groups sit in ascending lanes: the lowest lane is the lowest group on ties
+            const int owner = __builtin_ctzll(__ballot(galive && gkey == best));
+            keep |= 1ull << (owner >> owner_shift);
+            if (lane == owner) { gkey = 0u; galive = false; }
         }
 #pragma unroll
         for (int i = 0; i < VPL; ++i) {
             const int e = lane + i * MOE_WAVE;
-            if (e < E && !((keep >> (e / per)) & 1ull)) key[i] = 0ull;
+            if (e < E && !((keep >> (e / per)) & 1ull)) { key[i] = 0u; alive &= ~(1u << i); }
         }
         __builtin_amdgcn_wave_barrier();                 // row_lds is reused by this wave's next token
     } else if (!cfg.renormalize) {
-        uint64_t m = 0ull;
+        uint32_t m = 0u;
 #pragma unroll
         for (int i = 0; i < VPL; ++i) m = key[i] > m ? key[i] : m;
-        const float vmax = from_orderable(static_cast<uint32_t>(wave_max_u64(m) >> 32));
+        const float vmax = from_orderable(wave_max_u32(m));
         float s = 0.0f;
 #pragma unroll
         for (int i = 0; i < VPL; ++i)
@@ -194,92 +220,58 @@ __device__ __forceinline__ void route_token(const float *row, int E, int k, cons
         denom_all = wave_sum_f32(s);
     }
 
-    if (VPL == 1) {
-        // Rank of every key among all keys of the row (keys are distinct: the id is part of the key):
-        // lane j's keys are broadcast one after the other with scalar lane reads and every lane counts
-        // the keys greater than its own.  The k keys with rank < k are the selection, already in
-        // output order; dropped or padding keys are 0 and never rank below k.
-        int rank[VPL];
-    #pragma unroll
-        for (int i = 0; i < VPL; ++i) rank[i] = 0;
-        for (int j = 0; j < MOE_WAVE; ++j) {
-    #pragma unroll
-            for (int i2 = 0; i2 < VPL; ++i2) {
-                const uint64_t other = readlane_u64(key[i2], j);
-    #pragma unroll
-                for (int i = 0; i < VPL; ++i) rank[i] += other > key[i] ? 1 : 0;
-            }
+    // k rounds of "largest remaining"
+    float sel_v = 0.0f;                // lane j keeps the j-th selected logit
+    int sel_id = 0;
+    float vmax = 0.0f;
+    for (int j = 0; j < k; ++j) {
+        uint32_t m = key[0];
+        int mi = 0;                                      // lowest index of the lane's largest key
+#pragma unroll
+        for (int i = 1; i < VPL; ++i)
+            if (key[i] > m) { m = key[i]; mi = i; }
+        const uint32_t best = wave_max_u32(m);
+        if (best == 0u) mi = __builtin_ctz(alive | 0x80000000u);     // key 0: only what is alive counts
+        uint64_t holders = __ballot(m == best && alive != 0u);
+        int src = __builtin_ctzll(holders);
+        int id = __builtin_amdgcn_readlane(mi, src) * MOE_WAVE + src;
+        holders &= holders - 1;
+        while (holders) {                                // equal logits on several lanes
+            const int l = __builtin_ctzll(holders);
+            holders &= holders - 1;
+            const int o = __builtin_amdgcn_readlane(mi, l) * MOE_WAVE + l;
+            if (o < id) { id = o; src = l; }
         }
-        float vmax = 0.0f;                                   // largest surviving logit (rank 0)
-    #pragma unroll
-        for (int i = 0; i < VPL; ++i) {
-            const uint64_t top = __ballot(rank[i] == 0 && key[i] != 0ull);
-            if (top) vmax = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v[i]), __builtin_ctzll(top)));
-        }
-        float score[VPL];
-        float local = 0.0f;
-    #pragma unroll
-        for (int i = 0; i < VPL; ++i) {
-            const bool sel = rank[i] < k && key[i] != 0ull;
-            score[i] = sel ? (cfg.mode == MOE_ROUTE_SIGMOID_GROUP ? sigmoid_f32(v[i]) : expf(v[i] - vmax)) : 0.0f;
-            local += score[i];
-        }
-        const float denom_sel = wave_sum_f32(local);
-    #pragma unroll
-        for (int i = 0; i < VPL; ++i) {
-            if (rank[i] < k && key[i] != 0ull) {
-                float w;
-                if (cfg.mode == MOE_ROUTE_SIGMOID_GROUP) w = score[i] / denom_sel * cfg.scale;
-                else if (cfg.renormalize) w = score[i] / denom_sel;
-                else w = score[i] / denom_all;
-                const int e = lane + i * MOE_WAVE;
-                if (COHERENT) {
-                    __hip_atomic_store(ids_out + rank[i], e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                } else {
-                    ids_out[rank[i]] = e;
-                }
-                if (mark_lds) atomicOr(mark_lds + (e >> 5), 1u << (e & 31));
-                w_out[rank[i]] = w;
-            }
-        }
-    } else {
-        // k rounds of "largest remaining"
-        float sel_v = 0.0f;            // lane j keeps the j-th selected logit
-        int sel_id = 0;
-        float vmax = 0.0f;
-        for (int j = 0; j < k; ++j) {
-            uint64_t m = 0ull;
-    #pragma unroll
-            for (int i = 0; i < VPL; ++i) m = key[i] > m ? key[i] : m;
-            const uint64_t best = wave_max_u64(m);
-            const int id = 0x7fffffff - static_cast<int>(best & 0xffffffffu);
-            const float val = from_orderable(static_cast<uint32_t>(best >> 32));
-            if (j == 0) vmax = val;
-            if (lane == j) { sel_v = val; sel_id = id; }
-    #pragma unroll
+        const float val = from_orderable(best);
+        if (j == 0) vmax = val;
+        if (lane == j) { sel_v = val; sel_id = id; }
+        if (lane == src) {
+            alive &= ~(1u << mi);
+#pragma unroll
             for (int i = 0; i < VPL; ++i)
-                if (lane + i * MOE_WAVE == id) key[i] = 0ull;
+                if (i == mi) key[i] = 0u;
         }
+    }
 
-        // weights of the k selected experts (lanes 0..k-1)
-        float score = 0.0f;
-        if (lane < k) {
-            score = cfg.mode == MOE_ROUTE_SIGMOID_GROUP ? sigmoid_f32(sel_v) : expf(sel_v - vmax);
+    // weights of the k selected experts (lanes 0..k-1)
+    float score = 0.0f;
+    if (lane < k) {
+        score = cfg.mode == MOE_ROUTE_SIGMOID_GROUP ? sigmoid_f32(sel_v) : expf(sel_v - vmax);
+    }
+    const float denom_sel = wave_sum_f32(score);
+    if (lane < k) {
+        float w;
+        if (cfg.mode == MOE_ROUTE_SIGMOID_GROUP) w = score / denom_sel * cfg.scale;
+        else if (cfg.renormalize) w = score / denom_sel;
+        else w = score / denom_all;
+        if (COHERENT) {
+            __hip_atomic_store(ids_out + lane, sel_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        } else {
+            ids_out[lane] = sel_id;
         }
-        const float denom_sel = wave_sum_f32(score);
-        if (lane < k) {
-            float w;
-            if (cfg.mode == MOE_ROUTE_SIGMOID_GROUP) w = score / denom_sel * cfg.scale;
-            else if (cfg.renormalize) w = score / denom_sel;
-            else w = score / denom_all;
-            if (COHERENT) {
-                __hip_atomic_store(ids_out + lane, sel_id, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            } else {
-                ids_out[lane] = sel_id;
-            }
-            if (mark_lds) atomicOr(mark_lds + (sel_id >> 5), 1u << (sel_id & 31));
-            w_out[lane] = w;
-        }
+        if (ids_lds) ids_lds[lane] = sel_id;
+        if (mark_lds) atomicOr(mark_lds + (sel_id >> 5), 1u << (sel_id & 31));
+        w_out[lane] = w;
     }
 }
 
@@ -342,55 +334,105 @@ __device__ __forceinline__ void aebs_stage_tables(const SchedTables &tb, SchedSh
     __syncthreads();
 }
 
-// Step 2 of Alg. 1 from the expert flags in LDS (first wavefront; the caller orders the flags before
-// and sh.rep after with barriers): actRep into sh.rep and act_rep (if not null), loads into load_out.
-__device__ __forceinline__ void aebs_select(const SchedTables &tb, SchedShared &sh, int E, int n_inst, int C, int n_words,
-                                            int32_t *__restrict__ act_rep, int32_t *__restrict__ load_out) {
-    const int tid = threadIdx.x;
-    if (tid < MOE_WAVE) {
-        const int lane = tid;
-        int load = 0;                                   // lane g: load[g]
-        for (int w = 0; w < n_words; ++w) {
-            const int e = w * 64 + lane;
-            const uint64_t act = __ballot(e < E && sh.flag[e] != 0u);
-            if (lane < n_inst) load += __popcll(act & sh.single_mask[lane * n_words + w]);
-        }
-        for (int w = 0; w < n_words; ++w) {
-            const int e = w * 64 + lane;
-            const uint64_t act = __ballot(e < E && sh.flag[e] != 0u);
-            const uint64_t hm = e < E ? sh.host_mask[e] : 0ull;
-            uint64_t todo = act & readfirstlane_u64(sh.multi_mask[w]);   // wave-uniform: keep the loop scalar
-            int chosen = -1;                            // lane b: instance chosen for expert w*64+b
+// Step 2 of Alg. 1 by one wavefront from the expert flags in LDS.  W >= n_words is a compile-time number of
+// 64-expert words: the flags and host masks of all words are read at once, before the greedy chain, and the
+// replica ids of all words after it, so that the LDS latencies of the words overlap (a loop over the words paid
+// them one after the other: 0.9 us per word).  In between only scalar instructions and lane reads remain.
+// rep_of(e, instance, or -1 if it has one replica): the replica id of an expert.  actRep goes to rep (LDS, if not null) and
+// act_rep (if not null); returns load[lane].
+template <int W, typename RepOf>
+__device__ __forceinline__ int aebs_select_wave(const uint32_t *flag, const uint64_t *host_mask, const uint64_t *multi_mask,
+                                                const uint64_t *single_mask, int E, int n_inst, int n_words, int lane,
+                                                RepOf rep_of, int32_t *rep, int32_t *__restrict__ act_rep) {
+    // Up to 16 instances the loads are kept four times, lane l = instance l % 16: the arg-min of
+    // (load, instance) over an expert's hosts is then four exchanges inside rows of 16 lanes with the result in
+    // every lane, and the chain never leaves the vector registers (walking the hosts one by one with scalar lane
+    // reads cost about 50 ns a host).
+    const bool rows = n_inst <= 16;                     // wave-uniform
+    const int g = rows ? lane & 15 : lane;
+    const int g_ok = g < n_inst ? g : n_inst - 1;
+    // all reads with clamped indices, none inside a branch: one LDS latency for all words
+    uint32_t fl[W];
+    uint64_t act[W], hm[W], sm[W];
+    const uint64_t mm = multi_mask[lane < n_words ? lane : n_words - 1];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        const int e = w * MOE_WAVE + lane < E ? w * MOE_WAVE + lane : E - 1;
+        fl[w] = flag[e];
+        hm[w] = host_mask[e];
+        sm[w] = single_mask[g_ok * n_words + (w < n_words ? w : n_words - 1)];
+    }
+    int load = 0;                                       // load[g]
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        act[w] = __ballot(w * MOE_WAVE + lane < E && fl[w] != 0u);
+        load += __popcll(act[w] & sm[w]);               // words past the last have no act bits
+    }
+    if (g >= n_inst) load = 0;
+    int chosen[W];                                      // lane b: instance chosen for expert w*64+b
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        chosen[w] = -1;
+        uint64_t todo = w < n_words ? act[w] & readlane_u64(mm, w) : 0ull;   // wave-uniform: keep the loop scalar
+        if (rows) {
             while (todo) {
                 const int b = __builtin_ctzll(todo);
                 todo &= todo - 1;
-                uint64_t hosts = readlane_u64(hm, b);
-                int best_g = __builtin_ctzll(hosts);
-                int best_load = __builtin_amdgcn_readlane(load, best_g);
-                hosts &= hosts - 1;
-                while (hosts) {                         // ascending instance id: strict '<' keeps the lowest on ties
-                    const int h = __builtin_ctzll(hosts);
-                    hosts &= hosts - 1;
-                    const int l = __builtin_amdgcn_readlane(load, h);
-                    if (l < best_load) { best_load = l; best_g = h; }
-                }
-                if (lane == best_g) load += 1;
-                if (lane == b) chosen = best_g;
+                const uint32_t hosts = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(hm[w] & 0xffffffffu), b));
+                // smallest load first, lowest instance on ties; loads are at most MOE_MAX_SLOTS
+                const uint32_t m = wave_min_rows_u32((hosts >> g) & 1u ? static_cast<uint32_t>(load) * MOE_MAX_INSTANCES + g : ~0u);
+                const int best = static_cast<int>(m % MOE_MAX_INSTANCES);
+                load += g == best ? 1 : 0;
+                chosen[w] = lane == b ? best : chosen[w];
             }
-            if (e < E) {
-                int rep = -1;
-                if ((act >> lane) & 1ull) {
-                    if (chosen >= 0) rep = chosen * C + tb.slot_of[e * n_inst + chosen];
-                    else rep = sh.single_rid[e];
-                }
-                sh.rep[e] = rep;
-                if (act_rep) act_rep[e] = rep;
+        } else {
+            while (todo) {
+                const int b = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                const uint64_t hosts = readlane_u64(hm[w], b);
+                const uint32_t m = wave_min_of_rows_u32(
+                    wave_min_rows_u32((hosts >> g) & 1ull ? static_cast<uint32_t>(load) * MOE_MAX_INSTANCES + g : ~0u));
+                const int best = static_cast<int>(m % MOE_MAX_INSTANCES);
+                load += g == best ? 1 : 0;
+                chosen[w] = lane == b ? best : chosen[w];
             }
         }
-        if (lane < n_inst) load_out[lane] = load;
     }
+    if (rep || act_rep) {
+        int r[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const int e = w * MOE_WAVE + lane < E ? w * MOE_WAVE + lane : E - 1;
+            r[w] = rep_of(e, chosen[w]);
+        }
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+            const int e = w * MOE_WAVE + lane;
+            r[w] = (act[w] >> lane) & 1ull ? r[w] : -1;
+            if (e < E && rep) rep[e] = r[w];
+            if (e < E && act_rep) act_rep[e] = r[w];
+        }
+    }
+    return load;
 }
 
+// Step 2 from sh.flag (first wavefront; the caller orders the flags before and sh.rep after with barriers):
+// actRep into sh.rep and act_rep (if not null), loads into load_out.
+template <int W>
+__device__ __forceinline__ void aebs_select(const SchedTables &tb, SchedShared &sh, int E, int n_inst, int C, int n_words,
+                                            int32_t *__restrict__ act_rep, int32_t *__restrict__ load_out) {
+    if (threadIdx.x >= MOE_WAVE) return;
+    const int lane = threadIdx.x;
+    const auto rep_of = [&](int e, int g) {
+        const int single = sh.single_rid[e], multi = (g < 0 ? 0 : g) * C + tb.slot_of[e * n_inst + (g < 0 ? 0 : g)];
+        return g >= 0 ? multi : single;
+    };
+    const int load = aebs_select_wave<W>(sh.flag, sh.host_mask, sh.multi_mask, sh.single_mask, E, n_inst, n_words, lane,
+                                         rep_of, sh.rep, act_rep);
+    if (lane < n_inst) load_out[lane] = load;
+}
+
+template <int W>
 __device__ __forceinline__ void aebs_block(const SchedTables &tb, SchedShared &sh, int E, int n_inst, int C,
                                            int n_words, const int32_t *__restrict__ ids, int n_pairs, int vec_ok,
                                            bool ids_coherent, int32_t *__restrict__ rid,
@@ -413,7 +455,7 @@ __device__ __forceinline__ void aebs_block(const SchedTables &tb, SchedShared &s
     __syncthreads();
 
     // ---- Step 2: select one replica per activated expert (first wavefront)
-    aebs_select(tb, sh, E, n_inst, C, n_words, act_rep, load_out);
+    aebs_select<W>(tb, sh, E, n_inst, C, n_words, act_rep, load_out);
     if (!rid) return;                                    // uniform: no barrier is skipped by part of the workgroup
     __syncthreads();
 

@@ -8,11 +8,10 @@
 // they were written on other XCDs.
 //
 // The gated variants start one step earlier (Sec. 3.3: gating runs on the MoE side, from the
-// complete activations): the logits are the router's linear layer X * W_r^T (+ bias), computed
-// in the same launch.  A workgroup owns (16 tokens) x (16 experts) of the logits: its 16
-// wavefronts split the hidden dimension, each accumulates one 16x16 MFMA tile over its share,
-// and the partial tiles are summed in LDS in wavefront order.  The workgroup that completes a
-// token group (a ticket per group) routes its 16 tokens from the logits the others published.
+// complete activations): the logits are the router's linear layer X * W_r^T (+ bias), a launch of their own
+// before the one that starts from logits.  (In one launch, with the workgroup that completed a token group
+// routing its 16 tokens, the routing shared its CU with the products: 44 us at T = 512, E = 256, d_h = 7168
+// against 25 us for the two launches, and 25 against 18 us at T = 32.)
 #include "dispatch_dev.h"
 
 namespace {
@@ -28,172 +27,235 @@ struct FrontArgs {
     int32_t *rid, *act_rep, *load, *slot_count, *slot_off, *perm, *pos, *blocks;
     int32_t *ticket;
     int block_rows;
-    // gated variants: logits = X * Wr^T (+ bias) are computed here and written to `logits_out`
-    const uint16_t *X, *Wr;              // bf16 [T,d_h], [E,d_h]
-    const float *bias;                   // [E] or null
-    float *logits_out;                   // [T,E]
-    int d_h, n_tiles;                    // n_tiles = ceil(E/16) expert tiles
-    int tail;                            // 0: stop after the gating selection
     // batches too large for the one-workgroup tail (launch from logits only): the routing workgroups
     // raise the activated experts in act_bits, the last one runs Step 2 of Alg. 1 from them, and two
     // further launches (front_count_kernel, front_scatter_kernel) rewrite and sort the requests in chunks
     uint32_t *act_bits;                  // [kBitWords], zero between calls; null = one-workgroup tail
     int32_t *hist;                       // [n_chunks][C]
     int chunk_pairs, n_chunks;
-    int tok_per_wg;                      // launch from logits: wavefronts of a workgroup that route a token (4, 8 or 16)
+    int tok_per_wg;                      // wavefronts of a workgroup that route a token (4, 8 or 16)
 };
 constexpr int kBitWords = MOE_MAX_EXPERTS / 32;
 constexpr int kChunkPairs = 2048;
 
+// ------------------------------------------------------------------ the gate's linear layer
+struct GateArgs {
+    const uint16_t *X, *Wr;              // bf16 [T,d_h], [E,d_h]
+    const float *bias;                   // [E] or null
+    float *logits;                       // [T,E]
+    int T, E, d_h;
+    int e_tiles;                         // ceil(E/16) expert tiles
+};
+constexpr int kGateWaves = 16;
 constexpr int kGateUnroll = 4;
-constexpr int kGateDepth = 4;
+constexpr int kGateDepth = 2;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Logits of token group tg (16 tokens) against expert tile j (16 experts).  MFMA 16x16x32: the
+// Logits of TT token tiles (16 tokens each) against expert tile j (16 experts).  MFMA 16x16x32: the
 // router rows are the A operand (lane l: expert l%16, 8 columns at (l/16)*8 of the K-step), the
 // token rows the B operand (same shape), and the D tile leaves lane l with experts (l/16)*4..+3
-// of token l%16.  Rows past T or E repeat the last valid row and are not stored.
+// of token l%16.  Rows past T or E repeat the last valid row and are not stored.  The 16 wavefronts split the
+// hidden dimension.
 //
 // This wavefront's share of the sum, operands read straight into the MFMA layout: every lane
 // requests its own 16 bytes of its own row, four requests per 64 bytes.  Used when the hidden
 // size is not a multiple of 64.
-__device__ __forceinline__ f32x4 gate_acc_steps(const FrontArgs &a, int tg, int j, int wave, int lane) {
+template <int TT>
+__device__ __forceinline__ void gate_acc_steps(const GateArgs &a, int t0, int j, int wave, int lane, f32x4 (&acc)[TT]) {
     const int KS = a.d_h / 32;
-    const int per = (KS + moe::kFrontWaves - 1) / moe::kFrontWaves;
+    const int per = (KS + kGateWaves - 1) / kGateWaves;
     const int k0 = wave * per;
     const int k1 = k0 + per < KS ? k0 + per : KS;
-    int tok = tg * 16 + (lane & 15);
-    tok = tok < a.T ? tok : a.T - 1;
     int e = j * 16 + (lane & 15);
     e = e < a.E ? e : a.E - 1;
-    const char *xb = reinterpret_cast<const char *>(a.X) + (static_cast<size_t>(tok) * a.d_h + (lane >> 4) * 8) * 2;
     const char *wb = reinterpret_cast<const char *>(a.Wr) + (static_cast<size_t>(e) * a.d_h + (lane >> 4) * 8) * 2;
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    const char *xb[TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) {
+        int tok = t0 + t * 16 + (lane & 15);
+        tok = tok < a.T ? tok : a.T - 1;
+        xb[t] = reinterpret_cast<const char *>(a.X) + (static_cast<size_t>(tok) * a.d_h + (lane >> 4) * 8) * 2;
+    }
     // kGateUnroll K-steps of both operands in flight; steps past the share load the last valid step
     // again and multiply by zero, so the loop has no tail
     const bf16x8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
     for (int kk = k0; kk < k1; kk += kGateUnroll) {
-        bf16x8 av[kGateUnroll], bv[kGateUnroll];
+        bf16x8 av[kGateUnroll], bv[kGateUnroll][TT];
 #pragma unroll
         for (int u = 0; u < kGateUnroll; ++u) {
             const int q = kk + u < k1 ? kk + u : k1 - 1;
             av[u] = *reinterpret_cast<const bf16x8 *>(wb + q * 64);
-            bv[u] = *reinterpret_cast<const bf16x8 *>(xb + q * 64);
+#pragma unroll
+            for (int t = 0; t < TT; ++t) bv[u][t] = *reinterpret_cast<const bf16x8 *>(xb[t] + q * 64);
         }
 #pragma unroll
         for (int u = 0; u < kGateUnroll; ++u)
-            acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[u], kk + u < k1 ? bv[u] : zero, acc, 0, 0, 0);
+#pragma unroll
+            for (int t = 0; t < TT; ++t)
+                acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kk + u < k1 ? av[u] : zero, kk + u < k1 ? bv[u][t] : zero, acc[t], 0, 0, 0);
     }
-    return acc;
 }
 
 // The same share with whole-line reads (hidden size a multiple of 64): a super-step is 64 columns =
-// one 128-byte line of each of the 16 + 16 rows; a load instruction fetches 8 whole lines (lane l:
+// one 128-byte line of each row; a load instruction fetches 8 whole lines (lane l:
 // row l/8, 16-byte chunk l%8), a quarter of the requests of the direct form, and the MFMA layout
-// comes from a round trip through a wave-private 4 KiB LDS tile (chunks XOR-swizzled by row so
+// comes from a round trip through a wave-private LDS tile (chunks XOR-swizzled by row so
 // that the row-major writes and the column-wise reads both spread over the banks).  Wavefront w
 // takes super-steps w, w+16, ...; kGateDepth of them are in flight.
-__device__ __forceinline__ f32x4 gate_acc_lines(const FrontArgs &a, int tg, int j, char *stage, int wave, int lane) {
+template <int TT>
+__device__ __forceinline__ void gate_acc_lines(const GateArgs &a, int t0, int j, char *stage, int wave, int lane,
+                                               f32x4 (&acc)[TT]) {
+    constexpr int L = 2 + 2 * TT;                                    // load instructions per super-step
     const int SS = a.d_h / 64;
-    const int n = (SS - wave + moe::kFrontWaves - 1) / moe::kFrontWaves;
-    char *st = stage + wave * 4096;                                  // [router rows | token rows][16 rows][128 bytes]
-    const char *wp[2], *xp[2];
+    const int n = (SS - wave + kGateWaves - 1) / kGateWaves;
+    char *st = stage + wave * (L * 1024);                            // [router rows | token rows][16 rows][128 bytes]
+    const char *p[L];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        int e = j * 16 + h * 8 + (lane >> 3);
-        e = e < a.E ? e : a.E - 1;
-        int t = tg * 16 + h * 8 + (lane >> 3);
-        t = t < a.T ? t : a.T - 1;
-        wp[h] = reinterpret_cast<const char *>(a.Wr) + static_cast<size_t>(e) * a.d_h * 2 + (lane & 7) * 16;
-        xp[h] = reinterpret_cast<const char *>(a.X) + static_cast<size_t>(t) * a.d_h * 2 + (lane & 7) * 16;
+    for (int h = 0; h < L; ++h) {
+        const int r = h * 8 + (lane >> 3);                           // row of the 16 router + TT*16 token rows
+        if (h < 2) {
+            int e = j * 16 + r;
+            e = e < a.E ? e : a.E - 1;
+            p[h] = reinterpret_cast<const char *>(a.Wr) + static_cast<size_t>(e) * a.d_h * 2 + (lane & 7) * 16;
+        } else {
+            int t = t0 + r - 16;
+            t = t < a.T ? t : a.T - 1;
+            p[h] = reinterpret_cast<const char *>(a.X) + static_cast<size_t>(t) * a.d_h * 2 + (lane & 7) * 16;
+        }
     }
     // LDS: row R of an operand at R*128, its 16-byte chunk c at ((c ^ (R & 7)) * 16)
     const uint32_t wr_lds = ((lane >> 3) * 128) + (((lane & 7) ^ (lane >> 3)) * 16);
     const uint32_t rd_row = (lane & 15) * 128, rd_sw = lane & 7, rd_g = lane >> 4;
-    bf16x8 ld[kGateDepth][4];
+    bf16x8 ld[kGateDepth][L];
 #define MOE_GATE_LOAD(d, i)                                                                      \
     do {                                                                                         \
-        const size_t off_ = static_cast<size_t>(wave + moe::kFrontWaves * (i)) * 128;            \
-        ld[d][0] = *reinterpret_cast<const bf16x8 *>(wp[0] + off_);                              \
-        ld[d][1] = *reinterpret_cast<const bf16x8 *>(wp[1] + off_);                              \
-        ld[d][2] = *reinterpret_cast<const bf16x8 *>(xp[0] + off_);                              \
-        ld[d][3] = *reinterpret_cast<const bf16x8 *>(xp[1] + off_);                              \
+        const size_t off_ = static_cast<size_t>(wave + kGateWaves * (i)) * 128;                  \
+        _Pragma("unroll") for (int q = 0; q < L; ++q)                                            \
+            ld[d][q] = *reinterpret_cast<const bf16x8 *>(p[q] + off_);                           \
     } while (0)
 #pragma unroll
     for (int d = 0; d < kGateDepth; ++d)
         if (d < n) MOE_GATE_LOAD(d, d);
-    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     for (int i = 0; i < n; i += kGateDepth) {
 #pragma unroll
         for (int d = 0; d < kGateDepth; ++d) {
             if (i + d < n) {                                         // wave-uniform
 #pragma unroll
-                for (int q = 0; q < 4; ++q) *reinterpret_cast<bf16x8 *>(st + q * 1024 + wr_lds) = ld[d][q];
+                for (int q = 0; q < L; ++q) *reinterpret_cast<bf16x8 *>(st + q * 1024 + wr_lds) = ld[d][q];
                 asm volatile("" ::: "memory");
                 if (i + d + kGateDepth < n) MOE_GATE_LOAD(d, i + d + kGateDepth);
 #pragma unroll
                 for (int ss = 0; ss < 2; ++ss) {
                     const uint32_t o = rd_row + (((4 * ss + rd_g) ^ rd_sw) * 16);
                     const bf16x8 av = *reinterpret_cast<const bf16x8 *>(st + o);
-                    const bf16x8 bv = *reinterpret_cast<const bf16x8 *>(st + 2048 + o);
-                    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc, 0, 0, 0);
+#pragma unroll
+                    for (int t = 0; t < TT; ++t) {
+                        const bf16x8 bv = *reinterpret_cast<const bf16x8 *>(st + (1 + t) * 2048 + o);
+                        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv, acc[t], 0, 0, 0);
+                    }
                 }
                 asm volatile("" ::: "memory");
             }
         }
     }
 #undef MOE_GATE_LOAD
-    return acc;
 }
 
-// lds: 64 KiB.  The partial tiles of the 16 wavefronts are summed in wavefront order.
-__device__ __forceinline__ void gate_tile(const FrontArgs &a, int tg, int j, char *lds, int wave, int lane) {
-    // the bias of this lane's four experts, fetched up front so that the stores at the end follow
-    // one another without a load (and its wait for the previous store) in between
+// A workgroup computes TT*16 tokens x 16 experts.  The partial tiles of the 16 wavefronts are summed in
+// wavefront order, so results are reproducible and do not depend on TT.
+// Workgroups go to the 8 XCDs round-robin: the XCDs form a grid of 4 token shares x 2 expert shares, so each L2 reads
+// a quarter of the activations and half of the router matrix.
+// Bound by the operand tiles on their way through the L1s (176 MB at T = 512, E = 256, d_h = 7168).  11.7 us there;
+// with four super-steps in flight 15.6 us (the register file spills), with three 12.5 us, with tiles of 16 x 16
+// 16.1 us.
+template <int TT, bool LINES>
+__global__ __launch_bounds__(kGateWaves * MOE_WAVE)
+void gate_kernel(GateArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[kGateWaves * (2 + 2 * TT) * 1024];
+    static_assert(TT <= 2, "the partial tiles must fit in the staging tiles");
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE), lane = moe::lane_id();
+    const int r = blockIdx.x / 8, xcd = blockIdx.x % 8, eh = (a.e_tiles + 1) / 2;
+    const int tg = xcd % 4 + 4 * (r / eh), j = r % eh + (xcd / 4) * eh;
+    if (j >= a.e_tiles) return;
+    const int t0 = tg * (TT * 16);
+    if (t0 >= a.T) return;
+    // the bias of this lane's four experts, fetched up front
     float bias[4] = {0.f, 0.f, 0.f, 0.f};
-    if (a.bias && threadIdx.x < MOE_WAVE) {
+    if (a.bias && wave < TT) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int ee = j * 16 + (lane >> 4) * 4 + i;
             bias[i] = a.bias[ee < a.E ? ee : a.E - 1];
         }
     }
-    f32x4 acc;
-    if (a.d_h % 64 == 0) {
-        acc = gate_acc_lines(a, tg, j, lds, wave, lane);
+    f32x4 acc[TT];
+#pragma unroll
+    for (int t = 0; t < TT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (LINES) {
+        gate_acc_lines<TT>(a, t0, j, lds, wave, lane, acc);
         __syncthreads();                                             // the staging tiles give way to the partial tiles
     } else {
-        acc = gate_acc_steps(a, tg, j, wave, lane);
+        gate_acc_steps<TT>(a, t0, j, wave, lane, acc);
     }
     f32x4 *part = reinterpret_cast<f32x4 *>(lds);
-    part[wave * MOE_WAVE + lane] = acc;
-    __syncthreads();
-    if (threadIdx.x < MOE_WAVE) {
-        f32x4 s = part[lane];
 #pragma unroll
-        for (int w = 1; w < moe::kFrontWaves; ++w) s += part[w * MOE_WAVE + lane];
-        const int t = tg * 16 + (lane & 15);
+    for (int t = 0; t < TT; ++t) part[(t * kGateWaves + wave) * MOE_WAVE + lane] = acc[t];
+    __syncthreads();
+    if (wave < TT) {
+        const f32x4 *mine = part + wave * kGateWaves * MOE_WAVE + lane;
+        f32x4 s = mine[0];
+#pragma unroll
+        for (int w = 1; w < kGateWaves; ++w) s += mine[w * MOE_WAVE];
+        const int t = t0 + wave * 16 + (lane & 15);
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int ee = j * 16 + (lane >> 4) * 4 + i;
-            if (t < a.T && ee < a.E)
-                __hip_atomic_store(a.logits_out + static_cast<size_t>(t) * a.E + ee, s[i] + bias[i],
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (t < a.T && ee < a.E) a.logits[static_cast<size_t>(t) * a.E + ee] = s[i] + bias[i];
         }
     }
 }
 
+// Tiles of 32 tokens read a quarter less than tiles of 16 (48 rows for 2 x 16 logits a lane instead of 64), and are
+// taken when they still give every CU a workgroup.
+constexpr long long kGateWideTiles = 256;
+int launch_gate(const void *X, const void *Wr, const float *bias, float *logits, int T, int E, int d_h, hipStream_t st) {
+    GateArgs a;
+    a.X = static_cast<const uint16_t *>(X); a.Wr = static_cast<const uint16_t *>(Wr); a.bias = bias; a.logits = logits;
+    a.T = T; a.E = E; a.d_h = d_h; a.e_tiles = (E + 15) / 16;
+    const bool lines = d_h % 64 == 0;
+    const bool wide = static_cast<long long>((T + 31) / 32) * a.e_tiles >= kGateWideTiles;
+    const int groups = wide ? (T + 31) / 32 : (T + 15) / 16;
+    const long long blocks = static_cast<long long>((groups + 3) / 4) * 8 * ((a.e_tiles + 1) / 2);
+    if (blocks > 0x7fffffffLL) return MOE_ESHAPE;
+    const dim3 grid(static_cast<unsigned>(blocks)), threads(kGateWaves * MOE_WAVE);
+    if (wide && lines) hipLaunchKernelGGL((gate_kernel<2, true>), grid, threads, 0, st, a);
+    else if (wide) hipLaunchKernelGGL((gate_kernel<2, false>), grid, threads, 0, st, a);
+    else if (lines) hipLaunchKernelGGL((gate_kernel<1, true>), grid, threads, 0, st, a);
+    else hipLaunchKernelGGL((gate_kernel<1, false>), grid, threads, 0, st, a);
+    return MOE_OK;
+}
+
+// ------------------------------------------------------------------ selection, Alg. 1 and dispatch
 // Decode-size tail (up to kRegPairs requests): Alg. 1 and the counting sort with every request id
 // held in registers.  Wavefront w owns requests [w*gpw*64, (w+1)*gpw*64), the mapping the sort needs,
-// so the ids are read from memory exactly once (one round trip together with the layout tables)
-// and everything after that runs out of LDS and registers.
-constexpr int kGpwMax = 8;                                            // 64-request groups per wavefront
+// so the ids are read from memory exactly once and everything after that runs out of LDS and registers.
+constexpr int kGpwMax = 8;                                            // 64-request groups per wavefront (compiled for 1, 2, 4 and 8)
 constexpr int kRegPairs = moe::kFrontWaves * kGpwMax * MOE_WAVE;      // 8192
 constexpr int kSlotOfLds = 8192;                                      // E*n_inst entries of slot_of kept in LDS
+// Up to this many tokens one workgroup routes the whole batch: the ids stay in LDS, and the publication, the
+// ticket and the read-back (0.3 + 0.45 + 0.9 us at T = 8) fall away.  More tokens would take turns on its wavefronts.
+constexpr int kSoloTokens = moe::kFrontWaves;
 
-// Layout tables one thread fetches at kernel entry (every workgroup does, only the last one uses
-// them): their latency hides behind the routing instead of following the ticket.
+struct SmallShared {
+    moe::SchedShared sched;
+    moe::PermShared perm;
+    alignas(16) int16_t slot_of[kSlotOfLds];
+};
+
+// The tail's layout tables in LDS, its flags and counters cleared.  Every workgroup prepares this while
+// its tokens are being routed, although only the last one uses it: nothing of it follows the ticket then.
+// Elements are dealt from the highest thread down, because the lowest wavefronts are the ones that route.
 struct TablePrefetch {
     uint64_t host_mask, multi_mask, single_mask;
     int32_t single_rid;
@@ -202,103 +264,72 @@ struct TablePrefetch {
 
 __device__ __forceinline__ TablePrefetch prefetch_tables(const FrontArgs &a) {
     TablePrefetch t{};
-    const int tid = threadIdx.x;
-    if (tid < a.E) { t.host_mask = a.tb.host_mask[tid]; t.single_rid = a.tb.single_rid[tid]; }
-    if (tid < a.n_words) t.multi_mask = a.tb.multi_mask[tid];
-    if (tid < a.n_inst * a.n_words) t.single_mask = a.tb.single_mask[tid];
+    const int i = moe::kFrontThreads - 1 - threadIdx.x;
+    if (i < a.E) { t.host_mask = a.tb.host_mask[i]; t.single_rid = a.tb.single_rid[i]; }
+    if (i < a.n_words) t.multi_mask = a.tb.multi_mask[i];
+    if (i < a.n_inst * a.n_words) t.single_mask = a.tb.single_mask[i];
     // the table is padded to a multiple of 256 bytes, so the last 16-byte read stays inside it
-    if (tid * 8 < a.E * a.n_inst) t.slot_of = reinterpret_cast<const uint4 *>(a.tb.slot_of)[tid];
+    if (i * 8 < a.E * a.n_inst) t.slot_of = reinterpret_cast<const uint4 *>(a.tb.slot_of)[i];
     return t;
 }
 
-struct SmallShared {
-    moe::SchedShared sched;
-    moe::PermShared perm;
-    alignas(16) int16_t slot_of[kSlotOfLds];
-};
+// E, n_words, n_inst*n_words <= 1024 threads and E*n_inst <= 8*1024: one element each
+__device__ __forceinline__ void stage_small(const FrontArgs &a, SmallShared &sh, const TablePrefetch &t) {
+    const int i = moe::kFrontThreads - 1 - threadIdx.x;
+    if (i < a.E) {
+        sh.sched.flag[i] = 0u;
+        sh.sched.host_mask[i] = t.host_mask;
+        sh.sched.single_rid[i] = t.single_rid;
+    }
+    if (i < a.n_words) sh.sched.multi_mask[i] = t.multi_mask;
+    if (i < a.n_inst * a.n_words) sh.sched.single_mask[i] = t.single_mask;
+    if (i * 8 < a.E * a.n_inst) reinterpret_cast<uint4 *>(sh.slot_of)[i] = t.slot_of;
+    static_assert(sizeof(sh.perm.cnt) == moe::kFrontThreads * 16, "one 16-byte store per thread clears the counters");
+    reinterpret_cast<uint4 *>(&sh.perm.cnt[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
+}
 
-__device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared &sh, int n_pairs,
-                                                 const TablePrefetch &tp) {
+// ids_lds: the batch's request ids in LDS (one-workgroup launch), or null: they were written by other
+// workgroups and are read with agent-scope loads.  VPL >= n_words; GPW >= 64-request groups per wavefront.
+template <int VPL, int GPW>
+__device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared &sh, int n_pairs, const int32_t *ids_lds) {
     const int tid = threadIdx.x;
     const int wave = tid / MOE_WAVE, lane = tid % MOE_WAVE;
-    const int E = a.E, n_inst = a.n_inst, C = a.C, n_words = a.n_words;
+    const int E = a.E, n_inst = a.n_inst, C = a.C;
     const int n_groups = (n_pairs + MOE_WAVE - 1) / MOE_WAVE;
-    const int gpw = (n_groups + moe::kFrontWaves - 1) / moe::kFrontWaves;   // <= kGpwMax
+    const int gpw = (n_groups + moe::kFrontWaves - 1) / moe::kFrontWaves;   // <= GPW
 
-    // ---- one round trip: request ids (written by other workgroups: agent-scope loads) and tables
-    int id[kGpwMax];
+    int id[GPW];
 #pragma unroll
-    for (int g = 0; g < kGpwMax; ++g) {
+    for (int g = 0; g < GPW; ++g) {
         const int p = (wave * gpw + g) * MOE_WAVE + lane;
-        id[g] = (g < gpw && p < n_pairs) ? __hip_atomic_load(a.ids + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : -1;
+        id[g] = -1;
+        if (g < gpw && p < n_pairs)
+            id[g] = ids_lds ? ids_lds[p] : __hip_atomic_load(a.ids + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // E, n_words, n_inst*n_words <= 1024 threads and E*n_inst <= 8*1024: one element each
-    if (tid < E) {
-        sh.sched.flag[tid] = 0u;
-        sh.sched.host_mask[tid] = tp.host_mask;
-        sh.sched.single_rid[tid] = tp.single_rid;
-    }
-    if (tid < n_words) sh.sched.multi_mask[tid] = tp.multi_mask;
-    if (tid < n_inst * n_words) sh.sched.single_mask[tid] = tp.single_mask;
-    if (tid * 8 < E * n_inst) reinterpret_cast<uint4 *>(sh.slot_of)[tid] = tp.slot_of;
-    for (int i = tid; i < moe::kFrontWaves * MOE_MAX_SLOTS; i += moe::kFrontThreads) (&sh.perm.cnt[0][0])[i] = 0;
-    __syncthreads();
-
     // ---- Step 1
 #pragma unroll
-    for (int g = 0; g < kGpwMax; ++g)
+    for (int g = 0; g < GPW; ++g)
         if (id[g] >= 0) sh.sched.flag[id[g]] = 1u;
     __syncthreads();
 
-    // ---- Step 2 (first wavefront), as in aebs_block but with slot_of in LDS
+    // ---- Step 2 (first wavefront), slot_of in LDS
     if (tid < MOE_WAVE) {
-        int load = 0;
-        for (int w = 0; w < n_words; ++w) {
-            const int e = w * 64 + lane;
-            const uint64_t act = __ballot(e < E && sh.sched.flag[e] != 0u);
-            if (lane < n_inst) load += __popcll(act & sh.sched.single_mask[lane * n_words + w]);
-        }
-        for (int w = 0; w < n_words; ++w) {
-            const int e = w * 64 + lane;
-            const uint64_t act = __ballot(e < E && sh.sched.flag[e] != 0u);
-            const uint64_t hm = e < E ? sh.sched.host_mask[e] : 0ull;
-            uint64_t todo = act & moe::readfirstlane_u64(sh.sched.multi_mask[w]);
-            int chosen = -1;
-            while (todo) {
-                const int b = __builtin_ctzll(todo);
-                todo &= todo - 1;
-                uint64_t hosts = moe::readlane_u64(hm, b);
-                int best_g = __builtin_ctzll(hosts);
-                int best_load = __builtin_amdgcn_readlane(load, best_g);
-                hosts &= hosts - 1;
-                while (hosts) {                         // ascending instance id: strict '<' keeps the lowest on ties
-                    const int h = __builtin_ctzll(hosts);
-                    hosts &= hosts - 1;
-                    const int l = __builtin_amdgcn_readlane(load, h);
-                    if (l < best_load) { best_load = l; best_g = h; }
-                }
-                if (lane == best_g) load += 1;
-                if (lane == b) chosen = best_g;
-            }
-            if (e < E) {
-                int rep = -1;
-                if ((act >> lane) & 1ull) {
-                    if (chosen >= 0) rep = chosen * C + sh.slot_of[e * n_inst + chosen];
-                    else rep = sh.sched.single_rid[e];
-                }
-                sh.sched.rep[e] = rep;
-                a.act_rep[e] = rep;
-            }
-        }
+        const auto rep_of = [&](int e, int g) {
+            const int single = sh.sched.single_rid[e], multi = (g < 0 ? 0 : g) * C + sh.slot_of[e * n_inst + (g < 0 ? 0 : g)];
+            return g >= 0 ? multi : single;
+        };
+        const int load = moe::aebs_select_wave<VPL>(sh.sched.flag, sh.sched.host_mask, sh.sched.multi_mask,
+                                                    sh.sched.single_mask, E, n_inst, a.n_words, lane, rep_of, sh.sched.rep,
+                                                    a.act_rep);
         if (lane < n_inst) a.load[lane] = load;
     }
     __syncthreads();
 
     // ---- Step 3 and pass A of the sort
     const int rid_lo = a.g_self * C;
-    int sl[kGpwMax];                                                  // local slot, or -1
+    int sl[GPW];                                                  // local slot, or -1
 #pragma unroll
-    for (int g = 0; g < kGpwMax; ++g) {
+    for (int g = 0; g < GPW; ++g) {
         sl[g] = -1;
         if (id[g] >= 0) {
             const int r = sh.sched.rep[id[g]];
@@ -330,7 +361,7 @@ __device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared
         // and bumps it with scalar-indexed lane accesses, no LDS round trip per slot
         int base_reg = lane < C ? sh.perm.cnt[wave][lane] + sh.perm.off[lane] : 0;
 #pragma unroll
-        for (int g = 0; g < kGpwMax; ++g) {
+        for (int g = 0; g < GPW; ++g) {
             if (g < gpw) {                                            // wave-uniform
                 const int p = (wave * gpw + g) * MOE_WAVE + lane;
                 const int s = sl[g];
@@ -356,7 +387,7 @@ __device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared
     }
     volatile int *base = &sh.perm.cnt[wave][0];
 #pragma unroll
-    for (int g = 0; g < kGpwMax; ++g) {
+    for (int g = 0; g < GPW; ++g) {
         if (g < gpw) {                                                // wave-uniform
             const int p = (wave * gpw + g) * MOE_WAVE + lane;
             const int s = sl[g];
@@ -384,102 +415,77 @@ __device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared
     }
 }
 
-template <int VPL, bool GATE>
+template <int VPL>
+__device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared &sh, int n_pairs) {
+    if (n_pairs <= kRegPairs / 8) front_tail_small<VPL, 1>(a, sh, n_pairs, nullptr);
+    else if (n_pairs <= kRegPairs / 4) front_tail_small<VPL, 2>(a, sh, n_pairs, nullptr);
+    else if (n_pairs <= kRegPairs / 2) front_tail_small<VPL, 4>(a, sh, n_pairs, nullptr);
+    else front_tail_small<VPL, kGpwMax>(a, sh, n_pairs, nullptr);
+}
+
+template <int VPL>
 __global__ __launch_bounds__(moe::kFrontThreads)
 void front_kernel(FrontArgs a) {
-    // the phases run one after another, so their LDS overlays
+    // the tails' LDS; the decode-size tail's is prepared while the tokens are routed, so the routing rows and
+    // the ids have their own
     union Shared {
-        float row[moe::kFrontWaves][VPL * MOE_WAVE];
         moe::SchedShared sched;
         moe::PermShared perm;
         SmallShared small;
-        char gate[moe::kFrontWaves * 4096];                           // gated variants: staging tiles, then partial tiles
     };
     __shared__ Shared sh;
+    __shared__ float row[moe::kFrontWaves][VPL * MOE_WAVE];
+    __shared__ int32_t s_ids[kSoloTokens * MOE_MAX_TOPK];
     __shared__ int s_last;
     __shared__ uint32_t s_bits[kBitWords];                            // experts this workgroup's tokens selected
 
-    const int wave = threadIdx.x / MOE_WAVE;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE);
     const int lane = moe::lane_id();
     const int n_pairs = a.T * a.k;
     const bool small = n_pairs <= kRegPairs && a.E * a.n_inst <= kSlotOfLds;
+    const bool solo = small && a.T <= kSoloTokens;                    // this is the only workgroup
     TablePrefetch tp{};
-    int expected = static_cast<int>(gridDim.x);                       // arrivals that complete the selection
-    if constexpr (GATE) {
-        if (a.tail && small) tp = prefetch_tables(a);
-        expected = a.T > 0 ? (a.T + 15) / 16 : 1;
-        if (a.T > 0) {
-            // workgroups go to the 8 XCDs round-robin: all expert tiles of a token group run on one XCD,
-            // so each L2 reads an eighth of the activations (and the whole router matrix)
-            const int r = blockIdx.x / 8;
-            const int tg = blockIdx.x % 8 + 8 * (r / a.n_tiles), j = r % a.n_tiles;
-            if (tg * 16 >= a.T) return;
-            gate_tile(a, tg, j, sh.gate, wave, lane);
-            __syncthreads();                                          // the partial tiles give way to the logits rows
-            // the group's ticket must not overtake the logits
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-            __syncthreads();
-            if (threadIdx.x == 0) {
-                int32_t *grp = a.ticket + 1 + tg;
-                const int old = __hip_atomic_fetch_add(grp, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                s_last = old == a.n_tiles - 1;
-                if (s_last) __hip_atomic_store(grp, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            __syncthreads();
-            if (!s_last) return;
-            const int t = tg * 16 + wave;
-            if (t < a.T) {
-                float *row = sh.row[wave];
-#pragma unroll
-                for (int i = 0; i < VPL; ++i) {
-                    const int e = lane + i * MOE_WAVE;
-                    row[e] = e < a.E ? __hip_atomic_load(a.logits_out + static_cast<size_t>(t) * a.E + e, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT)
-                                     : 0.0f;
-                }
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                moe::route_token<VPL, true, true>(row, a.E, a.k, a.cfg, row, lane,
-                                                  a.ids + static_cast<size_t>(t) * a.k, a.w + static_cast<size_t>(t) * a.k);
-            }
-        }
-        if (!a.tail) return;
-    } else {
-        if (small) tp = prefetch_tables(a);
-        if (a.act_bits) {
-            if (threadIdx.x < kBitWords) s_bits[threadIdx.x] = 0u;
-            __syncthreads();
-        }
-        // small batches route on a few wavefronts per workgroup (one or two per SIMD instead of four),
-        // spread over more CUs: the selection is a long chain of cross-lane steps that four wavefronts
-        // of one SIMD would take turns at
-        const int t = blockIdx.x * a.tok_per_wg + wave;
-        if (wave < a.tok_per_wg && t < a.T) {
-            moe::route_token<VPL, true>(a.logits + static_cast<size_t>(t) * a.E, a.E, a.k, a.cfg, sh.row[wave], lane,
-                                        a.ids + static_cast<size_t>(t) * a.k, a.w + static_cast<size_t>(t) * a.k,
-                                        a.act_bits ? s_bits : nullptr);
-        }
-        if (a.act_bits) {
-            // Step 1 of Alg. 1, spread over the routing workgroups: one atomic per non-empty word
-            __syncthreads();
-            if (threadIdx.x < kBitWords && s_bits[threadIdx.x])
-                __hip_atomic_fetch_or(a.act_bits + threadIdx.x, s_bits[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+    if (small) tp = prefetch_tables(a);
+    if (a.act_bits) {
+        if (threadIdx.x < kBitWords) s_bits[threadIdx.x] = 0u;
+        __syncthreads();
+    }
+    // small batches route on a few wavefronts per workgroup (one or two per SIMD instead of four),
+    // spread over more CUs: the selection is a long chain of cross-lane steps that four wavefronts
+    // of one SIMD would take turns at
+    const int t = blockIdx.x * a.tok_per_wg + wave;
+    if (wave < a.tok_per_wg && t < a.T) {
+        const float *lg = a.logits + static_cast<size_t>(t) * a.E;
+        int32_t *ids = a.ids + static_cast<size_t>(t) * a.k;
+        float *w = a.w + static_cast<size_t>(t) * a.k;
+        moe::route_token<VPL, true>(lg, a.E, a.k, a.cfg, row[wave], lane, ids, w, solo ? s_ids + t * a.k : nullptr,
+                                    a.act_bits ? s_bits : nullptr);
+    }
+    if (small) stage_small(a, sh.small, tp);
+    if (solo) {
+        __syncthreads();
+        front_tail_small<VPL, 1>(a, sh.small, n_pairs, s_ids);
+        return;
+    }
+    if (a.act_bits) {
+        // Step 1 of Alg. 1, spread over the routing workgroups: one atomic per non-empty word
+        __syncthreads();
+        if (threadIdx.x < kBitWords && s_bits[threadIdx.x])
+            __hip_atomic_fetch_or(a.act_bits + threadIdx.x, s_bits[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // a workgroup barrier does not wait for global stores: the ticket must not overtake the ids
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
         const int old = __hip_atomic_fetch_add(a.ticket, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        s_last = old == expected - 1;
+        s_last = old == static_cast<int>(gridDim.x) - 1;
         if (s_last) __hip_atomic_store(a.ticket, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
     }
     __syncthreads();
     if (!s_last) return;
 
     if (small) {
-        front_tail_small(a, sh.small, n_pairs, tp);
+        front_tail_small<VPL>(a, sh.small, n_pairs);
         return;
     }
     if (a.act_bits) {
@@ -492,11 +498,11 @@ void front_kernel(FrontArgs a) {
         __syncthreads();
         if (threadIdx.x < kBitWords)                                  // ready for the next call
             __hip_atomic_store(a.act_bits + threadIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        moe::aebs_select(a.tb, sh.sched, a.E, a.n_inst, a.C, a.n_words, a.act_rep, a.load);
+        moe::aebs_select<VPL>(a.tb, sh.sched, a.E, a.n_inst, a.C, a.n_words, a.act_rep, a.load);
         return;
     }
     const int vec_ok = ((reinterpret_cast<uintptr_t>(a.ids) | reinterpret_cast<uintptr_t>(a.rid)) & 15) == 0;
-    moe::aebs_block(a.tb, sh.sched, a.E, a.n_inst, a.C, a.n_words, a.ids, n_pairs, vec_ok, true,
+    moe::aebs_block<VPL>(a.tb, sh.sched, a.E, a.n_inst, a.C, a.n_words, a.ids, n_pairs, vec_ok, true,
                     a.rid, a.act_rep, a.load);
     // rid is re-read below by other wavefronts of this workgroup
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -527,18 +533,14 @@ void front_scatter_kernel(FrontArgs a) {
                        a.perm, a.pos, a.blocks, a.block_rows);
 }
 
-#ifndef MOE_TPW
-#define MOE_TPW 0
-#endif
-template <int VPL, bool GATE>
+template <int VPL>
 int launch_front(const FrontArgs &a_in, const char *what, hipStream_t st) {
     FrontArgs a = a_in;
     // every routing workgroup takes a ticket from one counter: keep them to about a hundred
-    a.tok_per_wg = MOE_TPW ? MOE_TPW : a.T <= 512 ? 4 : a.T <= 1024 ? 8 : moe::kFrontWaves;
-    int blocks = 1;
-    if (a.T > 0) blocks = GATE ? (a.T + 127) / 128 * 8 * a.n_tiles : (a.T + a.tok_per_wg - 1) / a.tok_per_wg;
-    hipLaunchKernelGGL((front_kernel<VPL, GATE>), dim3(blocks), dim3(moe::kFrontThreads), 0, st, a);
-    if (!GATE && a.act_bits) {
+    a.tok_per_wg = a.T <= kSoloTokens ? moe::kFrontWaves : a.T <= 512 ? 4 : a.T <= 1024 ? 8 : moe::kFrontWaves;
+    const int blocks = a.T > 0 ? (a.T + a.tok_per_wg - 1) / a.tok_per_wg : 1;
+    hipLaunchKernelGGL(front_kernel<VPL>, dim3(blocks), dim3(moe::kFrontThreads), 0, st, a);
+    if (a.act_bits) {
         hipLaunchKernelGGL(front_count_kernel, dim3(a.n_chunks), dim3(moe::kFrontThreads), 0, st, a);
         hipLaunchKernelGGL(front_scatter_kernel, dim3(a.n_chunks), dim3(moe::kFrontThreads), 0, st, a);
     }
@@ -551,14 +553,13 @@ bool front_is_large(const moe_placement_t *pl, int T, int k) {
     return static_cast<long long>(T) * k > kRegPairs || pl->E * pl->n_inst > kSlotOfLds;
 }
 
-template <bool GATE>
 int launch_front_for(const FrontArgs &a, const char *what, hipStream_t st) {
     const int vpl = (a.E + MOE_WAVE - 1) / MOE_WAVE;
-    if (vpl <= 1) return launch_front<1, GATE>(a, what, st);
-    if (vpl <= 2) return launch_front<2, GATE>(a, what, st);
-    if (vpl <= 4) return launch_front<4, GATE>(a, what, st);
-    if (vpl <= 8) return launch_front<8, GATE>(a, what, st);
-    return launch_front<16, GATE>(a, what, st);
+    if (vpl <= 1) return launch_front<1>(a, what, st);
+    if (vpl <= 2) return launch_front<2>(a, what, st);
+    if (vpl <= 4) return launch_front<4>(a, what, st);
+    if (vpl <= 8) return launch_front<8>(a, what, st);
+    return launch_front<16>(a, what, st);
 }
 
 int check_selection(int T, int E, int k, const moe_route_cfg *cfg) {
@@ -598,7 +599,6 @@ int fill_tail(FrontArgs &a, const moe_placement_t *pl, int g_self, int T, int32_
     a.rid = rid_dev; a.act_rep = act_rep_dev; a.load = load_dev;
     a.slot_count = slot_count_dev; a.slot_off = slot_off_dev; a.perm = perm_dev; a.pos = pos_dev; a.blocks = blocks_dev;
     a.block_rows = moe::ffn_block_rows(T);
-    a.tail = 1;
     return MOE_OK;
 }
 
@@ -628,7 +628,7 @@ extern "C" int moe_route_schedule_permute(const moe_placement_t *pl, int g_self,
         a.chunk_pairs = kChunkPairs;
         a.n_chunks = static_cast<int>((static_cast<long long>(T) * k + kChunkPairs - 1) / kChunkPairs);
     }
-    return launch_front_for<false>(a, "moe_route_schedule_permute", static_cast<hipStream_t>(stream));
+    return launch_front_for(a, "moe_route_schedule_permute", static_cast<hipStream_t>(stream));
 }
 
 extern "C" size_t moe_front_sync_len(const moe_placement_t *pl, int T, int k) {
@@ -648,15 +648,9 @@ extern "C" int moe_gate_route(const void *X_dev, const void *Wr_dev, const float
     if (!sync_dev || !moe::aligned(sync_dev, 4)) return MOE_EINVAL;
     if (T == 0) return MOE_OK;
     if (!topk_ids_dev || !topk_w_dev || !moe::aligned(topk_ids_dev, 4) || !moe::aligned(topk_w_dev, 4)) return MOE_EINVAL;
-    FrontArgs a{};
-    a.T = T; a.E = E; a.k = k; a.cfg = *cfg;
-    a.ids = topk_ids_dev; a.w = topk_w_dev;
-    a.ticket = sync_dev;
-    a.X = static_cast<const uint16_t *>(X_dev); a.Wr = static_cast<const uint16_t *>(Wr_dev); a.bias = bias_dev;
-    a.logits_out = logits_dev; a.d_h = d_h; a.n_tiles = (E + 15) / 16;
-    a.n_inst = 1;
-    a.tail = 0;
-    return launch_front_for<true>(a, "moe_gate_route", static_cast<hipStream_t>(stream));
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (const int rc = launch_gate(X_dev, Wr_dev, bias_dev, logits_dev, T, E, d_h, st)) return rc;
+    return moe_route(logits_dev, T, E, k, cfg, topk_ids_dev, topk_w_dev, stream);
 }
 
 extern "C" int moe_gate_route_schedule_permute(const moe_placement_t *pl, int g_self, const void *X_dev,
@@ -678,10 +672,11 @@ extern "C" int moe_gate_route_schedule_permute(const moe_placement_t *pl, int g_
                                  perm_dev, pos_dev, blocks_dev))
         return rc;
     a.T = T; a.E = E; a.k = k; a.cfg = *cfg;
+    a.logits = logits_dev;
     a.ids = topk_ids_dev; a.w = topk_w_dev;
     a.ticket = sync_dev;
-    a.X = static_cast<const uint16_t *>(X_dev); a.Wr = static_cast<const uint16_t *>(Wr_dev); a.bias = bias_dev;
-    a.logits_out = logits_dev; a.d_h = d_h; a.n_tiles = (E + 15) / 16;
-    return launch_front_for<true>(a, "moe_gate_route_schedule_permute", static_cast<hipStream_t>(stream));
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (T > 0)
+        if (const int rc = launch_gate(X_dev, Wr_dev, bias_dev, logits_dev, T, E, d_h, st)) return rc;
+    return launch_front_for(a, "moe_gate_route_schedule_permute", st);
 }
-

@@ -1,0 +1,111 @@
+"""GPU parity of the dispatch branches that the size rules of a0-a4 choose, at the sizes where they change over."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_13525_amd import binding as B
+from paper_2512_13525_amd import workloads as W
+from paper_2512_13525_amd.layer import LayerStep, to_device_bf16
+from oracle import dispatch, gating, routing, scheduling
+
+from helpers import expected_blocks
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("E,k,group", [(7, 7, None), (64, 12, None), (65, 9, None), (300, 32, None), (1024, 5, None),
+                                       (64, 6, (8, 3)), (250, 8, (25, 4)), (192, 4, (64, 2))])
+def test_selection_with_equal_logits(E, k, group):
+    """Logits from a handful of values (zeros of both signs, infinities): every choice falls on ties, inside a
+    lane's experts and across lanes; ids are the oracle's, weights too (fp32 exp and a sum of k: rtol 1e-5)."""
+    rng = np.random.default_rng([E, k])
+    values = np.array([-2.0, -0.0, 0.0, 0.5, 3.0], dtype=np.float32)
+    z = rng.choice(values, size=(33, E), p=[0.4, 0.2, 0.2, 0.15, 0.05])
+    z[0] = 0.5
+    if group is None:
+        z[1, : E // 2] = -np.inf
+        ids, w = routing.route_softmax(z, k)
+    else:
+        # groups of two and more whose scores tie exactly in fp32
+        ids, w, _ = routing.route_sigmoid_group(z, k, *group)
+    d_ids = torch.empty((33, k), dtype=torch.int32, device="cuda")
+    d_w = torch.empty((33, k), dtype=torch.float32, device="cuda")
+    kw = {} if group is None else dict(mode=B.MOE_ROUTE_SIGMOID_GROUP, n_group=group[0], topk_group=group[1])
+    B.moe_route(torch.from_numpy(z).cuda(), k, d_ids, d_w, **kw)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(d_ids.cpu().numpy(), ids)
+    np.testing.assert_allclose(d_w.cpu().numpy(), w, rtol=1e-5, atol=1e-30)
+
+
+@pytest.mark.parametrize("n_inst,C,E", [(3, 9, 21), (16, 5, 64), (20, 4, 60), (40, 30, 1000)])
+@pytest.mark.parametrize("T", [1, 16, 17, 600])
+def test_front_sizes(n_inst, C, E, T):
+    """One workgroup (up to 16 tokens) and several; up to 16 instances and more; 1, 2 and 4 groups of 64 requests
+    per wavefront; a table too large for LDS.  Against the oracle, twice on the same sync words."""
+    k = 7
+    cfg = W.MoEConfig("front", E=E, k=k, d_h=32, d_e=32, T=T, n_inst=n_inst, C=C, zipf_s=1.0, seed=T)
+    lay = W.build_placement(cfg)
+    pl = scheduling.make_placement(lay, E, n_inst, C)
+    logits = W.router_logits(cfg)
+    ids, _ = routing.route_softmax(logits, k)
+    O, act_rep, load = scheduling.aebs(ids, pl)
+    g = int(np.argmax(load))
+    count, off, perm = dispatch.permute(O, g, C)
+    s = LayerStep(cfg, lay, g)
+    for _ in range(2):
+        for t in (s.topk_ids, s.rid, s.act_rep, s.load, s.slot_count, s.slot_off, s.perm, s.pos, s.blocks):
+            t.fill_(-5)
+        s.front(torch.from_numpy(logits).cuda())
+        torch.cuda.synchronize()
+        for got, want in ((s.topk_ids, ids), (s.rid, O), (s.act_rep, act_rep), (s.load, load), (s.slot_count, count),
+                          (s.slot_off, off)):
+            np.testing.assert_array_equal(got.cpu().numpy().reshape(np.shape(want)), want)
+        np.testing.assert_array_equal(s.perm.cpu().numpy()[:len(perm)], perm)
+        blk = expected_blocks(off, B.moe_block_rows(T))
+        np.testing.assert_array_equal(s.blocks.cpu().numpy()[:len(blk)], blk)
+        assert int(s.sync[:33].abs().sum().item()) == 0
+
+
+@pytest.mark.parametrize("d_h", [64, 96, 1088])
+@pytest.mark.parametrize("T,E", [(31, 17), (481, 257), (897, 130)])
+def test_gate_tiles(T, E, d_h):
+    """Tiles of 16 and of 32 tokens (from 256 tiles on), ragged in tokens and experts, odd numbers of expert tiles, whole
+    lines and single K-steps.  fp32 sums of d_h products of N(0,1) and N(0,1/d_h): error below 2e-5."""
+    cfg = W.MoEConfig("gate", E=E, k=3, d_h=d_h, d_e=32, T=T, n_inst=1, C=E, zipf_s=0.7, seed=2)
+    X = W.activations(cfg)
+    Wr, bias = W.router_weights(cfg)
+    z = torch.full((T, E), float("nan"), dtype=torch.float32, device="cuda")
+    ids = torch.empty((T, 3), dtype=torch.int32, device="cuda")
+    w = torch.empty((T, 3), dtype=torch.float32, device="cuda")
+    sync = torch.zeros(B.moe_gate_sync_len(T), dtype=torch.int32, device="cuda")
+    B.moe_gate_route(to_device_bf16(X), to_device_bf16(Wr), torch.from_numpy(bias).cuda(), 3, z, ids, w, sync)
+    torch.cuda.synchronize()
+    np.testing.assert_allclose(z.cpu().numpy(), gating.gate_logits(X, Wr, bias), rtol=0, atol=2e-5)
+    np.testing.assert_array_equal(ids.cpu().numpy(), routing.route_softmax(z.cpu().numpy(), 3)[0])
+
+
+@pytest.mark.parametrize("n_inst,C,E,T,k", [(3, 9, 21, 7, 3), (16, 10, 112, 40, 4), (20, 4, 60, 5, 5), (8, 36, 256, 260, 8),
+                                            (17, 64, 1003, 33, 6)])
+@pytest.mark.parametrize("n_batches", [512, 513, 9000])
+def test_schedule_batched_loads_only(n_inst, C, E, T, k, n_batches):
+    """A wavefront per batch (more than 512 batches, loads only) against the general path, which runs when act_rep is
+    asked for, bit for bit: numbers of requests that are and are not multiples of four and of 2048."""
+    cfg = W.MoEConfig("loads", E=E, k=k, d_h=32, d_e=32, T=T, n_inst=n_inst, C=C, zipf_s=1.1, seed=3)
+    lay = W.build_placement(cfg)
+    pl = B.Placement(lay, E, n_inst, C)
+    if n_batches * T * k > 8_000_000:
+        n_batches = 700
+    g = torch.Generator(device="cuda")
+    g.manual_seed(1)
+    ids = torch.randint(0, E, (n_batches, T, k), dtype=torch.int32, device="cuda", generator=g)
+    ids[::3] = ids[::3] // 3                                        # fewer experts activated
+    load = torch.full((n_batches, n_inst), -9, dtype=torch.int32, device="cuda")
+    want = torch.full((n_batches, n_inst), -9, dtype=torch.int32, device="cuda")
+    rep = torch.empty((n_batches, E), dtype=torch.int32, device="cuda")
+    B.moe_schedule_batched(pl, ids, n_batches, T, k, None, None, load)
+    B.moe_schedule_batched(pl, ids, n_batches, T, k, None, rep, want)
+    torch.cuda.synchronize()
+    assert torch.equal(load, want)
+    opl = scheduling.make_placement(lay, E, n_inst, C)
+    for b in (0, 1, n_batches - 1):
+        np.testing.assert_array_equal(want[b].cpu().numpy(), scheduling.aebs(ids[b].cpu().numpy(), opl)[2])
