@@ -106,52 +106,67 @@ __device__ __forceinline__ void lds_barrier() {
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Partial sums of an item in LDS: [wave][fragment][lane] (a fragment = 16 channels x 16 rows), at most 2*TT fragments.
+// F fragments of NT row tiles each are stored fragment-major: f * NT + t.
+template <int F, int NT, int TT>
+__device__ __forceinline__ void put_partials(char *lds, const f32x4 (&acc)[F][NT], int wave, int lane) {
+    static_assert(F * NT <= 2 * TT, "the reduction buffer holds 2 * TT fragments per wavefront");
+    f32x4 *red = reinterpret_cast<f32x4 *>(lds) + wave * (2 * TT * MOE_WAVE) + lane;
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+        for (int t = 0; t < NT; ++t) red[(f * NT + t) * MOE_WAVE] = acc[f][t];
+}
+
+template <int TT>
+__device__ __forceinline__ f32x4 sum_partials(const char *lds, int frag, int lane) {
+    const f32x4 *red = reinterpret_cast<const f32x4 *>(lds) + frag * MOE_WAVE + lane;
+    f32x4 v = red[0];
+#pragma unroll
+    for (int wv = 1; wv < kWaves; ++wv) v += red[wv * (2 * TT * MOE_WAVE)];
+    return v;
+}
+
 // Split-K reduction over the 4 wavefronts in LDS (fixed order), then the epilogue: SiLU(gate)*up
-// rounded once to bf16 (stage 1, agent-scope stores) or the fp32 partial output rows (stage 2).
-template <bool STAGE1, int NT, int TT>
-__device__ __forceinline__ void reduce_store(const StreamArgs &a, const StageArgs &g,
-                                             f32x4 (*red)[2][TT][MOE_WAVE], f32x4 (&acc)[2][NT],
-                                             int item_id, int brow, int tile, int row0, int row_end, int wave, int lane) {
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) red[wave][h][t][lane] = acc[h][t];
-    __syncthreads();
-    if (STAGE1) {
-        // lane-slot (t, l) holds gate/up channels tile*16 + (l/16)*4 .. +3 of token row0 + t*16 + l%16
-        for (int item = threadIdx.x; item < NT * MOE_WAVE; item += kThreads) {
-            const int t = item / MOE_WAVE, l = item % MOE_WAVE;
-            f32x4 gt = red[0][0][t][l], up = red[0][1][t][l];
-#pragma unroll
-            for (int wv = 1; wv < kWaves; ++wv) { gt += red[wv][0][t][l]; up += red[wv][1][t][l]; }
-            const int r = row0 + t * 16 + (l & 15);
-            if (r < row_end) {
-                const uint64_t o = static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[0], up[0]))) |
-                                   static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[1], up[1]))) << 16 |
-                                   static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[2], up[2]))) << 32 |
-                                   static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[3], up[3]))) << 48;
-                // act block of this item: [K-step of stage 2][token tile][64 lanes][16 B], the register image of
-                // the MFMA B operand (lane: row % 16, channels (lane / 16) * 8 .. + 7 of the K-step's 32); this
-                // tile is half a K-step, and every 128-byte line of the image has one writing workgroup
-                const int fl = (l & 15) + 16 * ((tile & 1) * 2 + (l >> 5));
-                uint64_t *dst = reinterpret_cast<uint64_t *>(
-                    reinterpret_cast<char *>(a.act) + static_cast<size_t>(item_id) * a.act_block_bytes +
-                    (static_cast<size_t>(tile >> 1) * TT + (brow >> 4) + t) * 1024 +
-                    fl * 16 + ((l >> 4) & 1) * 8);
-                __hip_atomic_store(dst, o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
+// rounded once to bf16 (stage 1, agent-scope stores) or the fp32 partial output rows (stage 2).  One copy of this code
+// for all numbers of row tiles (nt): the kernel's instructions are many times the instruction cache.
+template <int TT>
+__device__ __forceinline__ void store_act(const StreamArgs &a, const char *lds, int nt, int item_id, int tile, int row0, int row_end) {
+    // lane-slot (t, l) holds gate/up channels tile*16 + (l/16)*4 .. +3 of token row0 + t*16 + l%16
+    for (int item = threadIdx.x; item < nt * MOE_WAVE; item += kThreads) {
+        const int t = item / MOE_WAVE, l = item % MOE_WAVE;
+        const f32x4 gt = sum_partials<TT>(lds, t, l), up = sum_partials<TT>(lds, nt + t, l);
+        const int r = row0 + t * 16 + (l & 15);
+        if (r < row_end) {
+            const uint64_t o = static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[0], up[0]))) |
+                               static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[1], up[1]))) << 16 |
+                               static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[2], up[2]))) << 32 |
+                               static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[3], up[3]))) << 48;
+            // act block of this item: [K-step of stage 2][token tile][64 lanes][16 B], the register image of
+            // the MFMA B operand (lane: row % 16, channels (lane / 16) * 8 .. + 7 of the K-step's 32); this
+            // tile is half a K-step, and every 128-byte line of the image has one writing workgroup
+            const int fl = (l & 15) + 16 * ((tile & 1) * 2 + (l >> 5));
+            uint64_t *dst = reinterpret_cast<uint64_t *>(
+                reinterpret_cast<char *>(a.act) + static_cast<size_t>(item_id) * a.act_block_bytes +
+                (static_cast<size_t>(tile >> 1) * TT + t) * 1024 + fl * 16 + ((l >> 4) & 1) * 8);
+            __hip_atomic_store(dst, o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-    } else {
-        // lane-slot (h, t, l) holds output channels tile*32 + h*16 + (l/16)*4 .. +3
-        for (int item = threadIdx.x; item < 2 * NT * MOE_WAVE; item += kThreads) {
-            const int h = item / (NT * MOE_WAVE), t = item / MOE_WAVE % NT, l = item % MOE_WAVE;
-            f32x4 y = red[0][h][t][l];
-#pragma unroll
-            for (int wv = 1; wv < kWaves; ++wv) y += red[wv][h][t][l];
-            const int r = row0 + t * 16 + (l & 15);
-            if (r < row_end)
-                *reinterpret_cast<f32x4 *>(a.Yp + static_cast<size_t>(r) * g.out_stride + tile * 32 + h * 16 + (l >> 4) * 4) = y;
-        }
+    }
+}
+
+// nf fragments of 16 output channels, from channel tile*32 on
+template <int TT>
+__device__ __forceinline__ void store_rows(const StreamArgs &a, const StageArgs &g, const char *lds, int nf, int nt, int tile,
+                                           int row0, int row_end) {
+    // lane-slot (f, t, l) holds output channels tile*32 + f*16 + (l/16)*4 .. +3
+    int f = 0, t = threadIdx.x / MOE_WAVE;
+    for (int item = threadIdx.x; item < nf * nt * MOE_WAVE; item += kThreads, t += kWaves) {
+        while (t >= nt) { t -= nt; ++f; }
+        const int l = item % MOE_WAVE;
+        const f32x4 y = sum_partials<TT>(lds, item / MOE_WAVE, l);
+        const int r = row0 + t * 16 + (l & 15);
+        if (r < row_end)
+            *reinterpret_cast<f32x4 *>(a.Yp + static_cast<size_t>(r) * g.out_stride + tile * 32 + f * 16 + (l >> 4) * 4) = y;
     }
 }
 
@@ -200,22 +215,24 @@ __device__ __forceinline__ void store_nan_rows(const StreamArgs &a, const StageA
         *reinterpret_cast<f32x4 *>(a.Yp + static_cast<size_t>(row0 + i / 8) * g.out_stride + tile * 32 + (i % 8) * 4) = v;
 }
 
-// One stage-1 item with an even number of K-steps.  A super-step is two K-steps = 64 columns = one
-// 128-byte line of every token row.
+// One stage-1 item.  A super-step is two K-steps = 64 columns = one 128-byte line of every token row (with an odd
+// number of K-steps, hidden sizes that are multiples of 32 but not of 64, two halves of one for every other row: still a
+// quarter of the requests of reading 16 bytes per lane straight into the MFMA layout: 52 -> 46 us for the launch at
+// d_h = 2016, d_e = 1056, T = 203).
 // A token load instruction fetches whole lines (lane l: row l/8, 16-byte chunk l%8), so no line
 // is requested twice and none by halves; the MFMA layout (lane l: row l%16, 16-byte chunk 4*step + l/16) is produced by a
 // round trip through a wave-private 2 KiB LDS tile per 16 rows (chunks XOR-swizzled by row so
 // that both the row-major writes and the column-wise reads spread over the banks).  NH = number
 // of 8-row halves that hold requests (rows past the end repeat the last row; halves past it are
 // not loaded and leave unspecified values in token columns whose results are never stored).
-template <int NH, int TT, bool STREAM>
+// EVEN: the number of K-steps is even.  Otherwise one wavefront adds the last K-step after its super-steps.
+template <int NH, int TT, bool STREAM, bool EVEN>
 __device__ __forceinline__ void stream_item_lines(const StreamArgs &a, const StageArgs &g, char *lds,
-                                                  const char *w, int item, int tile, int row0, int row_end,
+                                                  const char *w, int tile, int row0, int row_end,
                                                   int wave, int lane) {
     asm volatile("" : "+v"(lane));                             // see wide_item
     constexpr int NT = (NH + 1) / 2;
     constexpr int D = kDepthA;
-    f32x4 (*red)[2][TT][MOE_WAVE] = reinterpret_cast<f32x4 (*)[2][TT][MOE_WAVE]>(lds);
     char *stg = lds + wave * (TT * 2048);
     const uint32_t aoff = lane * 16;
     // token rows: wave-uniform base (advanced per super-step) + constant 32-bit per-lane byte offset
@@ -294,6 +311,26 @@ __device__ __forceinline__ void stream_item_lines(const StreamArgs &a, const Sta
             }                                                                                    \
         asm volatile("" ::: "memory");                                                           \
     } while (0)
+    // The last K-step of an odd number, by the wavefront that is next in turn: its operands are requested before that
+    // wavefront's last super-steps are multiplied, the token rows 16 bytes a lane in the MFMA layout (the row offsets
+    // come from the lanes that hold them for the whole-line loads).
+    const bool extra = !EVEN && wave == (g.KS >> 1) % kWaves;
+    bf16x8 xw[2], xb[NT];
+#define MOE_LOAD_EXTRA()                                                                         \
+    do {                                                                                         \
+        if (extra) {                                                                             \
+            const char *ws_ = w + static_cast<size_t>(g.KS - 1) * 2048 + aoff;                   \
+            xw[0] = load_weights<STREAM>(ws_);                                                   \
+            xw[1] = load_weights<STREAM>(ws_ + 1024);                                            \
+            _Pragma("unroll") for (int t = 0; t < NT; ++t) {                                     \
+                const uint32_t o0_ = __shfl(boff[2 * t], (lane & 7) * 8);                        \
+                const uint32_t o1_ = 2 * t + 1 < NH ? __shfl(boff[2 * t + 1 < NH ? 2 * t + 1 : 0], (lane & 7) * 8) : o0_; \
+                xb[t] = *reinterpret_cast<const bf16x8 *>(bbase + static_cast<size_t>(g.KS - 1) * 64 + (lane >> 4) * 16 + \
+                                                          ((lane & 8) ? o1_ : o0_));             \
+            }                                                                                    \
+        }                                                                                        \
+        asm volatile("" ::: "memory");                                                           \
+    } while (0)
     if (n > 0) {
         // issue order of the first loads: tokens of a super-step before its weights
 #pragma unroll
@@ -311,6 +348,7 @@ __device__ __forceinline__ void stream_item_lines(const StreamArgs &a, const Sta
                 MOE_LOAD_A(d, i + d + D);
             }
         }
+        if constexpr (!EVEN) MOE_LOAD_EXTRA();
         const int rem = n - i;                                   // 1 .. 2*D-1 super-steps left
         // the last 1 .. 2*D-1 super-steps: only those that exist are loaded, staged and multiplied
         // (wave-uniform conditions)
@@ -328,92 +366,26 @@ __device__ __forceinline__ void stream_item_lines(const StreamArgs &a, const Sta
                 MOE_MMA_STEP(d);
             }
         }
+    } else if constexpr (!EVEN) {
+        MOE_LOAD_EXTRA();
     }
+    if constexpr (!EVEN) {
+        if (extra) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+                acc[0][t] = mfma16(xw[0], xb[t], acc[0][t]);
+                acc[1][t] = mfma16(xw[1], xb[t], acc[1][t]);
+            }
+        }
+    }
+#undef MOE_LOAD_EXTRA
 #undef MOE_STEP_INDEX
 #undef MOE_LOAD_A
 #undef MOE_LOAD_B
 #undef MOE_STAGE_B
 #undef MOE_MMA_STEP
     __syncthreads();                                             // the staging tiles are reused for the reduction
-    reduce_store<true, NT, TT>(a, g, red, acc, item, 0, tile, row0, row_end, wave, lane);
-}
-
-// One stage-1 item with an odd number of K-steps (shapes that are multiples of 32 but not of 64): single
-// K-steps, token rows read 64 bytes at a time straight into the MFMA layout (lane l: row l%16,
-// 16 bytes at (l/16)*16), four steps of weights and tokens in flight.
-template <int NT, int TT>
-__device__ __forceinline__ void stream_item_steps(const StreamArgs &a, const StageArgs &g, char *lds,
-                                                  const char *w, int item, int brow, int tile, int row0, int row_end,
-                                                  int wave, int lane) {
-    asm volatile("" : "+v"(lane));                             // see wide_item
-    constexpr int D = 2 * kDepthA;
-    f32x4 (*red)[2][TT][MOE_WAVE] = reinterpret_cast<f32x4 (*)[2][TT][MOE_WAVE]>(lds);
-    const uint32_t aoff = lane * 16;
-    uint32_t boff[NT];
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        int r = row0 + t * 16 + (lane & 15);
-        r = r < row_end ? r : row_end - 1;
-        boff[t] = (static_cast<uint32_t>(a.perm[r] / a.k) * static_cast<uint32_t>(g.b_stride) + (lane >> 4) * 8) * 2;
-    }
-    const char *bbase = reinterpret_cast<const char *>(g.B);
-    constexpr int kBStep = 64;                                   // bytes a K-step advances a token row
-    const int n = (g.KS - wave + kWaves - 1) / kWaves;          // K-steps wave, wave+4, ... of this wavefront
-    f32x4 acc[2][NT];
-#pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-        for (int t = 0; t < NT; ++t) acc[h][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    if (n > 0) {
-        bf16x8 wr[D][2], br[D][NT];
-        const int last = n - 1;
-        const int rot = static_cast<int>(static_cast<unsigned>(tile) % static_cast<unsigned>(n));
-#define MOE_LOAD_STEP(d, step)                                                                   \
-        do {                                                                                     \
-            const int q_ = (step);                                                               \
-            int r_ = (q_ < last ? q_ : last) + rot;                                              \
-            r_ = r_ >= n ? r_ - n : r_;                                                          \
-            const int s_ = wave + kWaves * r_;                                                   \
-            const char *ws_ = w + static_cast<size_t>(s_) * 2048;                                \
-            const char *bs_ = bbase + static_cast<size_t>(s_) * kBStep;                            \
-            wr[d][0] = load_weights<false>(ws_ + aoff);                                          \
-            wr[d][1] = load_weights<false>(ws_ + 1024 + aoff);                                   \
-            _Pragma("unroll") for (int t = 0; t < NT; ++t)                                       \
-                br[d][t] = *reinterpret_cast<const bf16x8 *>(bs_ + boff[t]);                     \
-            asm volatile("" ::: "memory");                                                       \
-        } while (0)
-#define MOE_MMA_STEP(d)                                                                          \
-        do {                                                                                     \
-            _Pragma("unroll") for (int t = 0; t < NT; ++t) {                                     \
-                acc[0][t] = mfma16(wr[d][0], br[d][t], acc[0][t]);                               \
-                acc[1][t] = mfma16(wr[d][1], br[d][t], acc[1][t]);                               \
-            }                                                                                    \
-        } while (0)
-#pragma unroll
-        for (int d = 0; d < D; ++d)
-            if (d < n) MOE_LOAD_STEP(d, d);
-        int i = 0;
-        for (; i + 2 * D <= n; i += D) {
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-                MOE_MMA_STEP(d);
-                MOE_LOAD_STEP(d, i + d + D);
-            }
-        }
-        const int rem = n - i;                                   // 1 .. 2*D-1 steps left
-#pragma unroll
-        for (int d = 0; d < D; ++d) {
-            if (d < rem) MOE_MMA_STEP(d);
-            if (d < D - 1 && d + D < rem) MOE_LOAD_STEP(d, i + d + D);
-        }
-#pragma unroll
-        for (int d = 0; d < D - 1; ++d)
-            if (D + d < rem) MOE_MMA_STEP(d);
-#undef MOE_LOAD_STEP
-#undef MOE_MMA_STEP
-    }
-    reduce_store<true, NT, TT>(a, g, red, acc, item, brow, tile, row0, row_end, wave, lane);
+    put_partials<2, NT, TT>(lds, acc, wave, lane);
 }
 
 // Stage 2 of one item.  Stage 1 leaves the block's rows of `act` as MFMA B-operand images, so a
@@ -422,19 +394,17 @@ __device__ __forceinline__ void stream_item_steps(const StreamArgs &a, const Sta
 // K-steps is even and the token tiles leave room in the registers); the steps go round-robin over
 // the wavefronts, 4 / U or 3 of them in flight for both operands, the weights issued before the
 // wait for the block (they do not depend on stage 1).
-// NW = 2: the item is a pair of adjacent tiles (64 output channels; their weights follow each other in
-// the packed layout) multiplied with the same token fragments: half as many items and `act`
+// NW = 2: the item is a pair of adjacent tiles (64 output channels; their weights lie w_tile bytes apart) multiplied with the same token fragments: half as many items and `act`
 // loads per block, twice the weight bytes in flight per workgroup.  Blocks of up to 16 rows (32
 // in the 64-row launch) have the registers for it.  n_readers: calls of this function per block.
+// Leaves the partial sums in LDS (put_partials); false: the wait for the block ran out and nothing was computed.
 template <int NT, int TT, int U, bool STREAM, int NW>
-__device__ __forceinline__ void stream_item_down(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok,
-                                                 const char *w, int item, int tile, int n_readers, int row0, int row_end,
+__device__ __forceinline__ bool stream_item_down(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok,
+                                                 const char *w, size_t w_tile, int item, int tile, int n_readers,
                                                  int wave, int lane) {
     asm volatile("" : "+v"(lane));                             // see wide_item
     constexpr int D = U == 2 ? 2 : NT > 2 ? 3 : 4;               // steps in flight that fit the registers
     constexpr int F = 2 * NW;                                    // weight fragments per K-step
-    const size_t w_tile = static_cast<size_t>(g.KS) * 2048;     // bytes between the tiles of the pair
-    f32x4 (*red)[2][TT][MOE_WAVE] = reinterpret_cast<f32x4 (*)[2][TT][MOE_WAVE]>(lds);
     const uint32_t aoff = lane * 16;
     const char *bbase = reinterpret_cast<const char *>(g.B) + static_cast<size_t>(item) * a.act_block_bytes + aoff;
     const int n = (g.KS / U - wave + kWaves - 1) / kWaves;      // steps wave, wave+4, ... of this wavefront
@@ -481,12 +451,7 @@ __device__ __forceinline__ void stream_item_down(const StreamArgs &a, const Stag
 #pragma unroll
     for (int d = 0; d < D; ++d)
         if (d < n) MOE_LOAD_W(d, d);
-    if (!wait_block_ready(a, s_ok, item, tile, n_readers)) {
-        const int m_ = row_end - row0;
-#pragma unroll
-        for (int nw = 0; nw < NW; ++nw) store_nan_rows(a, g, tile + nw, row0, m_ < TT * 16 ? m_ : TT * 16);
-        return;
-    }
+    if (!wait_block_ready(a, s_ok, item, tile, n_readers)) return false;
     if (n > 0) {
 #pragma unroll
         for (int d = 0; d < D; ++d)
@@ -514,14 +479,8 @@ __device__ __forceinline__ void stream_item_down(const StreamArgs &a, const Stag
 #undef MOE_LOAD_W
 #undef MOE_LOAD_T
 #undef MOE_MMA_STEP
-#pragma unroll
-    for (int nw = 0; nw < NW; ++nw) {
-        if (nw) __syncthreads();                                 // the reduction buffer is reused
-        f32x4 part[2][NT];
-#pragma unroll
-        for (int t = 0; t < NT; ++t) { part[0][t] = acc[2 * nw][t]; part[1][t] = acc[2 * nw + 1][t]; }
-        reduce_store<false, NT, TT>(a, g, red, part, item, 0, tile + nw, row0, row_end, wave, lane);
-    }
+    put_partials<F, NT, TT>(lds, acc, wave, lane);
+    return true;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -775,15 +734,14 @@ __device__ __forceinline__ void run_wide(const StreamArgs &a, const StageArgs &g
     const int row0 = lo + b * WR;
     const int m = hi - row0 < WR ? hi - row0 : WR;
     const int rt = (m + 15) >> 4;
-    if (rt <= 1) wide_item<STAGE1, 1>(a, g, lds, s_ok, item, group, groups, slot, row0, m);
-    else if (rt <= 2) wide_item<STAGE1, 2>(a, g, lds, s_ok, item, group, groups, slot, row0, m);
+    if (rt <= 2) wide_item<STAGE1, 2>(a, g, lds, s_ok, item, group, groups, slot, row0, m);
     else wide_item<STAGE1, 4>(a, g, lds, s_ok, item, group, groups, slot, row0, m);
 }
 
-// LINES: this stage has an even number of K-steps
+// EVEN: this stage has an even number of K-steps
 // wide: 0 = every slot is cut into streaming items; 1 = slots with more than kWideMin requests are wide
 // blocks of this launch; 2 = those slots belong to the tiled-GEMM launches and are skipped here
-template <bool STAGE1, bool LINES, int TT, int WR>
+template <bool STAGE1, bool EVEN, int TT, int WR>
 __device__ __forceinline__ void run_item(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok, int wide,
                                          unsigned id) {
     int tile = id % g.tiles_pad;
@@ -809,62 +767,57 @@ __device__ __forceinline__ void run_item(const StreamArgs &a, const StageArgs &g
     const char *w = g.Wp + (static_cast<size_t>(slot) * g.tiles + tile) * g.KS * 2048;
     const int m = hi - row0;
     const bool single = m <= TT * 16 && row0 == ent.w;                  // the slot's only block
+    // Loads of a slot's only block carry the streaming hint; the full blocks of a slot with several do not (a slot's
+    // last, partly filled block shares the code of the single blocks: fewer instructions to fetch).
     if constexpr (!STAGE1) {
-        const int tiles16 = ((m < TT * 16 ? m : TT * 16) + 15) >> 4;     // 16-row token tiles that hold requests
-        const bool two = kPairs && tile + 1 < g.tiles;                   // an odd number of tiles leaves the last one alone
-        // blocks with few rows multiply both tiles at once (every workgroup of a block takes the same
-        // branch, so the block's readers are counted the same way by all)
-        const bool paired = kPairs && tiles16 <= 2;
-#define MOE_DOWN(NT, U, NW, t_, n_readers_)                                                          \
-        do {                                                                                         \
-            const char *w_ = w + static_cast<size_t>((t_) - tile) * g.KS * 2048;                     \
-            if (single) stream_item_down<NT, TT, U, true, NW>(a, g, lds, s_ok, w_, item, t_, n_readers_, row0, hi, wave, lane);  \
-            else stream_item_down<NT, TT, U, false, NW>(a, g, lds, s_ok, w_, item, t_, n_readers_, row0, hi, wave, lane);        \
-        } while (0)
-#define MOE_CASE_PAIR(NT, U)                                                                         \
-    case NT:                                                                                         \
-        if (two) MOE_DOWN(NT, U, 2, tile, g.items);                                                  \
-        else MOE_DOWN(NT, U, 1, tile, g.items);                                                      \
-        break;
-#define MOE_CASE_SEQ(NT, U)                                                                          \
-    case NT:                                                                                         \
-        MOE_DOWN(NT, U, 1, tile, g.tiles);                                                           \
-        if (two) {                                                                                   \
-            __syncthreads();                                             /* the LDS buffer is reused */ \
-            MOE_DOWN(NT, U, 1, tile + 1, g.tiles);                                                   \
-        }                                                                                            \
-        break;
-        if constexpr (TT == 2) {
-            switch (tiles16) { MOE_CASE_SEQ(1, LINES ? 2 : 1) MOE_CASE_SEQ(2, LINES ? 2 : 1) }
-        } else if (paired) {
-            switch (tiles16) { MOE_CASE_PAIR(1, LINES ? 2 : 1) MOE_CASE_PAIR(2, LINES ? 2 : 1) }
-        } else {
-            switch (tiles16) { MOE_CASE_SEQ(3, 1) MOE_CASE_SEQ(4, 1) }
-        }
+        const int nt = ((m < TT * 16 ? m : TT * 16) + 15) >> 4;          // 16-row token tiles that hold requests
+        constexpr int U = EVEN ? 2 : 1;
+        const size_t tile_bytes = static_cast<size_t>(g.KS) * 2048;
+        // 64-row launch: blocks of up to 32 rows multiply both tiles of the pair at once, larger ones one after the other
+        // (every workgroup of a block takes the same branch, so the block's readers are counted the same way by all).
+        // An odd number of tiles leaves the last one alone: its pair is itself and is not stored.
+        const bool two = kPairs && tile + 1 < g.tiles;
+        const bool paired = kPairs && nt <= 2;
+        const int passes = kPairs && !paired && two ? 2 : 1, n_readers = paired ? g.items : g.tiles;
+        for (int pass = 0; pass < passes; ++pass) {
+            if (pass) __syncthreads();                                   // the LDS buffer is reused
+            const int t = tile + pass;
+            const char *w_ = w + pass * tile_bytes;
+            bool ok;
+#define MOE_DOWN(NT, U_, NW, STREAM) stream_item_down<NT, TT, U_, STREAM, NW>(a, g, lds, s_ok, w_, two ? tile_bytes : 0, item, t, n_readers, wave, lane)
+            if constexpr (TT == 2) {
+                if (nt == 1) ok = MOE_DOWN(1, U, 1, true);
+                else if (single) ok = MOE_DOWN(2, U, 1, true);
+                else ok = MOE_DOWN(2, U, 1, false);
+            } else {
+                if (nt == 1) ok = MOE_DOWN(1, U, 2, true);
+                else if (nt == 2) ok = MOE_DOWN(2, U, 2, true);
+                else if (nt == 3) ok = MOE_DOWN(3, 1, 1, true);
+                else if (single) ok = MOE_DOWN(4, 1, 1, true);
+                else ok = MOE_DOWN(4, 1, 1, false);
+            }
 #undef MOE_DOWN
-#undef MOE_CASE_PAIR
-#undef MOE_CASE_SEQ
-    } else if (LINES) {
-        const int halves = ((m < TT * 16 ? m : TT * 16) + 7) >> 3;     // 8-row halves that hold requests
-#define MOE_CASE(NH)                                                                                 \
-    case NH:                                                                                         \
-        if (single) stream_item_lines<NH, TT, true>(a, g, lds, w, item, tile, row0, hi, wave, lane);    \
-        else stream_item_lines<NH, TT, false>(a, g, lds, w, item, tile, row0, hi, wave, lane);          \
-        break;
-        if constexpr (TT == 2) {
+            const int nw = paired && two ? 2 : 1;                        // tiles to store
+            if (ok) {
+                __syncthreads();
+                store_rows<TT>(a, g, lds, 2 * nw, nt, t, row0, hi);
+            } else {
+                for (int q = 0; q < nw; ++q) store_nan_rows(a, g, t + q, row0, m < TT * 16 ? m : TT * 16);
+            }
+        }
+    } else {
+        const int halves = ((m < TT * 16 ? m : TT * 16) + 7) >> 3;       // 8-row halves that hold requests
+#define MOE_CASE(NH) case NH: stream_item_lines<NH, TT, true, EVEN>(a, g, lds, w, tile, row0, hi, wave, lane); break;
+        if (halves == 2 * TT && !single) {
+            stream_item_lines<2 * TT, TT, false, EVEN>(a, g, lds, w, tile, row0, hi, wave, lane);
+        } else if constexpr (TT == 2) {
             switch (halves) { MOE_CASE(1) MOE_CASE(2) MOE_CASE(3) MOE_CASE(4) }
         } else {
             switch (halves) { MOE_CASE(1) MOE_CASE(2) MOE_CASE(3) MOE_CASE(4) MOE_CASE(5) MOE_CASE(6) MOE_CASE(7) MOE_CASE(8) }
         }
 #undef MOE_CASE
-    } else {
-        // passes of 32 rows (rows [row0 + brow, ...) of the block)
-        const int end = m < TT * 16 ? hi : row0 + TT * 16;
-        for (int brow = 0; row0 + brow < end; brow += 32) {
-            if (brow) __syncthreads();                           // the reduction buffer is reused
-            if (end - (row0 + brow) <= 16) stream_item_steps<1, TT>(a, g, lds, w, item, brow, tile, row0 + brow, end, wave, lane);
-            else stream_item_steps<2, TT>(a, g, lds, w, item, brow, tile, row0 + brow, end, wave, lane);
-        }
+        __syncthreads();
+        store_act<TT>(a, lds, (halves + 1) >> 1, item, tile, row0, hi);
     }
     if (STAGE1) {
         // announce the tile: every thread waits for its own act stores to be acknowledged, then
@@ -889,10 +842,10 @@ __device__ __forceinline__ void run_item(const StreamArgs &a, const StageArgs &g
 // stage-2 workgroup is started after every stage-1 workgroup, and go to the XCDs round-robin, so
 // the blocks of one tile of a slot (ids tiles_pad apart, a multiple of 8) run on the same XCD at
 // about the same time: the tile's weights come from HBM once and are shared through that XCD's
-// L2.  LINES1 / LINES2 select the whole-line token path of a stage (even number of K-steps).
+// L2.  EVEN1 / EVEN2: a stage has an even number of K-steps.
 // TT = token tiles per block (2: blocks of 32 rows, 4 workgroups per CU; 4: blocks of 64 rows, whose
-// larger register set allows 3 per CU).
-template <bool LINES1, bool LINES2, int TT, int WR>
+// larger register set allows 3 per CU).  WRAP: the list can be longer than kFfnLaneBlocks.
+template <bool EVEN1, bool EVEN2, int TT, int WR, bool WRAP>
 __global__ __launch_bounds__(kThreads, TT == 2 ? 4 : 3)
 void ffn_stream_kernel(StreamArgs a) {
     // split-K reduction buffer [4 waves][2][TT][64] x 16 B, which the whole-line path also uses as
@@ -900,7 +853,7 @@ void ffn_stream_kernel(StreamArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[kWaves * 2 * TT * MOE_WAVE * 16];
     static_assert(kWaves * TT * 2048 <= sizeof(lds), "staging tiles must fit in the reduction buffer");
     static_assert(2 * WR * 128 <= sizeof(lds), "the two token tiles of a wide block must fit");
-    __shared__ unsigned long long s_visit;
+    __shared__ unsigned long long s_visit;                       // WRAP
     __shared__ int s_ok;
     {
         // ids are decoded with the number of blocks the batch really has, so that the surplus of
@@ -924,54 +877,64 @@ void ffn_stream_kernel(StreamArgs a) {
         const unsigned n_blocks = static_cast<unsigned>(head.x);
         const unsigned lanes = n_blocks < moe::kFfnLaneBlocks ? n_blocks : moe::kFfnLaneBlocks;
         const unsigned n1 = lanes * a.s[0].tiles_pad, n2 = lanes * a.s[1].tiles_pad;
-        if (n_blocks <= lanes) {
-            if (blockIdx.x < n1) run_item<true, LINES1, TT, WR>(a, a.s[0], lds, &s_ok, wide, blockIdx.x);
-            else if (blockIdx.x - n1 < n2) run_item<false, LINES2, TT, WR>(a, a.s[1], lds, &s_ok, wide, blockIdx.x - n1);
-        } else if (blockIdx.x < n1 + n2) {
-            // a long list: the first wavefront looks at all the blocks of this workgroup at once (lane l:
-            // block + l*lanes) and the workgroup then visits only those that are its own to compute
+        if constexpr (!WRAP) {
+            if (blockIdx.x < n1) run_item<true, EVEN1, TT, WR>(a, a.s[0], lds, &s_ok, wide, blockIdx.x);
+            else if (blockIdx.x - n1 < n2) run_item<false, EVEN2, TT, WR>(a, a.s[1], lds, &s_ok, wide, blockIdx.x - n1);
+        } else {
+            if (blockIdx.x >= n1 + n2) return;
             const bool s1 = blockIdx.x < n1;
             const unsigned id0 = s1 ? blockIdx.x : blockIdx.x - n1;
-            const unsigned tp = s1 ? a.s[0].tiles_pad : a.s[1].tiles_pad;
-            // (ids that pad the tiles to a multiple of 8 stay: the wide slots use them)
-            if (threadIdx.x < MOE_WAVE) {
-                const unsigned b = id0 / tp + threadIdx.x * lanes;
-                // entries of wide slots that lead no block are not visited
-                bool mine = false;
-                if (b < n_blocks) {
-                    const int4 e = reinterpret_cast<const int4 *>(a.blocks)[1 + b];
-                    mine = !wide || e.z - e.w <= kWideMin || (wide == 1 && (e.y - e.w) % WR == 0);
+            unsigned long long visit = 1ull;
+            if (n_blocks > lanes) {
+                // a long list: the first wavefront looks at all the blocks of this workgroup at once (lane l:
+                // block + l*lanes) and the workgroup then visits only those that are its own to compute
+                const unsigned tp = s1 ? a.s[0].tiles_pad : a.s[1].tiles_pad;
+                // (ids that pad the tiles to a multiple of 8 stay: the wide slots use them)
+                if (threadIdx.x < MOE_WAVE) {
+                    const unsigned b = id0 / tp + threadIdx.x * lanes;
+                    // entries of wide slots that lead no block are not visited
+                    bool mine = false;
+                    if (b < n_blocks) {
+                        const int4 e = reinterpret_cast<const int4 *>(a.blocks)[1 + b];
+                        mine = !wide || e.z - e.w <= kWideMin || (wide == 1 && (e.y - e.w) % WR == 0);
+                    }
+                    const unsigned long long m = __ballot(mine);
+                    if (threadIdx.x == 0) s_visit = m;
                 }
-                const unsigned long long m = __ballot(mine);
-                if (threadIdx.x == 0) s_visit = m;
+                __syncthreads();
+                visit = s_visit;
             }
-            __syncthreads();
-            unsigned long long visit = s_visit;
             bool first = true;
+#pragma unroll 1
             while (visit) {
                 const unsigned l = static_cast<unsigned>(__builtin_ctzll(visit));
                 visit &= visit - 1;
                 if (!first) __syncthreads();                         // the LDS buffer is reused
                 first = false;
-                if (s1) run_item<true, LINES1, TT, WR>(a, a.s[0], lds, &s_ok, wide, id0 + l * n1);
-                else run_item<false, LINES2, TT, WR>(a, a.s[1], lds, &s_ok, wide, id0 + l * n2);
+                // opaque copies: what the items derive from these is not to be computed ahead of the loop for all kinds
+                // of items at once (hundreds of spilled scalars)
+                StageArgs g = s1 ? a.s[0] : a.s[1];
+                asm volatile("" : "+s"(g.KS), "+s"(g.tiles), "+s"(g.tiles_pad), "+s"(g.items));
+                if (s1) run_item<true, EVEN1, TT, WR>(a, g, lds, &s_ok, wide, id0 + l * n1);
+                else run_item<false, EVEN2, TT, WR>(a, g, lds, &s_ok, wide, id0 + l * n2);
             }
         }
     }
 }
 
-template <bool L1, bool L2>
+template <bool L1, bool L2, bool WRAP>
 void launch(const StreamArgs &a, int block_rows, unsigned blocks, hipStream_t st) {
-    if (block_rows == 32) hipLaunchKernelGGL((ffn_stream_kernel<L1, L2, 2, 64>), dim3(blocks), dim3(kThreads), 0, st, a);
-    else hipLaunchKernelGGL((ffn_stream_kernel<L1, L2, 4, 64>), dim3(blocks), dim3(kThreads), 0, st, a);
+    if (block_rows == 32) hipLaunchKernelGGL((ffn_stream_kernel<L1, L2, 2, 64, WRAP>), dim3(blocks), dim3(kThreads), 0, st, a);
+    else hipLaunchKernelGGL((ffn_stream_kernel<L1, L2, 4, 64, WRAP>), dim3(blocks), dim3(kThreads), 0, st, a);
 }
 
-void launch_lines(const StreamArgs &a, int block_rows, unsigned blocks, hipStream_t st) {
+template <bool WRAP>
+void launch_even(const StreamArgs &a, int block_rows, unsigned blocks, hipStream_t st) {
     const bool l1 = a.s[0].KS % 2 == 0, l2 = a.s[1].KS % 2 == 0;
-    if (l1 && l2) launch<true, true>(a, block_rows, blocks, st);
-    else if (l1) launch<true, false>(a, block_rows, blocks, st);
-    else if (l2) launch<false, true>(a, block_rows, blocks, st);
-    else launch<false, false>(a, block_rows, blocks, st);
+    if (l1 && l2) launch<true, true, WRAP>(a, block_rows, blocks, st);
+    else if (l1) launch<true, false, WRAP>(a, block_rows, blocks, st);
+    else if (l2) launch<false, true, WRAP>(a, block_rows, blocks, st);
+    else launch<false, false, WRAP>(a, block_rows, blocks, st);
 }
 
 }  // namespace
@@ -1001,7 +964,9 @@ int launch_ffn_stream(const void *X, const void *W13p, const void *W2p, int T, i
     const long long lanes = items < kFfnLaneBlocks ? items : kFfnLaneBlocks;
     const long long n1 = lanes * a.s[0].tiles_pad, n2 = lanes * a.s[1].tiles_pad;
     if (n1 + n2 > 0x7fffffffLL) return MOE_ESHAPE;
-    launch_lines(a, block_rows, static_cast<unsigned>(n1 + n2), st);
+    // only a batch whose list can be longer than the lanes needs the code that walks it
+    if (items > kFfnLaneBlocks) launch_even<true>(a, block_rows, static_cast<unsigned>(n1 + n2), st);
+    else launch_even<false>(a, block_rows, static_cast<unsigned>(n1 + n2), st);
     return MOE_OK;
 }
 
