@@ -32,34 +32,79 @@ void shared_dispatch_kernel(int T, int block_rows, int32_t *__restrict__ slot_of
     for (int b = tid; b < n_blocks; b += n) reinterpret_cast<int4 *>(blocks)[1 + b] = make_int4(0, b * block_rows, T, 0);
 }
 
-// One workgroup per (token, 1024-column chunk); each thread owns 4 consecutive columns.
+// One workgroup per (token, chunk of 256*V columns); each thread owns V consecutive columns (V = 8: one 16-byte store of
+// bf16; V = 4 where the columns or the output's alignment ask for it).  Bound by memory: the output once, the local rows of Yp once.
+// The token's k places and weights are read by the first lanes of every wavefront at once and handed round with lane
+// reads, so a token without a local request stores its zeros after one load, and the rows of one with several follow
+// each other without a load of pos in between (two in flight).  T = 8192, d_h = 4096, k = 8: 22 us against 34 with a loop
+// over k that reads pos[j] before every row.
 // Ys (optional): rows of a shared expert's output, added with weight 1 after the routed sum.
-template <bool OUT_BF16>
+template <bool OUT_BF16, int V>
 __global__ __launch_bounds__(256)
 void combine_kernel(const float *__restrict__ Yp, const int32_t *__restrict__ pos,
                     const float *__restrict__ w, const float *__restrict__ Ys, int k, int d_h, void *__restrict__ Y) {
+    constexpr int N = V / 4;
+    typedef float f32x4 __attribute__((ext_vector_type(4)));
     const int i = blockIdx.x;
-    const int col = (blockIdx.y * 256 + threadIdx.x) * 4;
-    if (col >= d_h) return;
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int j = 0; j < k; ++j) {
-        const int r = pos[i * k + j];
-        if (r < 0) continue;
-        const float wj = w[i * k + j];
-        const float4 y = *reinterpret_cast<const float4 *>(Yp + static_cast<size_t>(r) * d_h + col);
-        acc.x += wj * y.x; acc.y += wj * y.y; acc.z += wj * y.z; acc.w += wj * y.w;
+    const int col0 = (blockIdx.y * 256 + threadIdx.x) * V;
+    const bool on = col0 < d_h;                                       // threads past the columns stay for the lane reads
+    const int col = on ? col0 : 0;
+    const int lane = moe::lane_id();
+    int r_l = -1;
+    float w_l = 0.f;
+    if (lane < k) {                                                   // k <= 32
+        r_l = pos[static_cast<size_t>(i) * k + lane];
+        w_l = w[static_cast<size_t>(i) * k + lane];
+    }
+    uint64_t todo = __ballot(r_l >= 0);
+    f32x4 acc[N];
+#pragma unroll
+    for (int n = 0; n < N; ++n) acc[n] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const auto row = [&](int j, f32x4 (&y)[N]) {
+        const float *p = Yp + static_cast<size_t>(__builtin_amdgcn_readlane(r_l, j)) * d_h + col;
+#pragma unroll
+        for (int n = 0; n < N; ++n) y[n] = *reinterpret_cast<const f32x4 *>(p + 4 * n);
+    };
+    const auto add = [&](int j, const f32x4 (&y)[N]) {
+        const float wj = __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(w_l)), j)));
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[n][q] += wj * y[n][q];
+    };
+    while (todo) {                                                    // ascending j
+        const int j0 = __builtin_ctzll(todo);
+        todo &= todo - 1;
+        f32x4 y0[N], y1[N];
+        row(j0, y0);
+        if (todo) {
+            const int j1 = __builtin_ctzll(todo);
+            todo &= todo - 1;
+            row(j1, y1);
+            add(j0, y0);
+            add(j1, y1);
+        } else {
+            add(j0, y0);
+        }
     }
     if (Ys) {
-        const float4 y = *reinterpret_cast<const float4 *>(Ys + static_cast<size_t>(i) * d_h + col);
-        acc.x += y.x; acc.y += y.y; acc.z += y.z; acc.w += y.w;
+        const float *p = Ys + static_cast<size_t>(i) * d_h + col;
+#pragma unroll
+        for (int n = 0; n < N; ++n) acc[n] += *reinterpret_cast<const f32x4 *>(p + 4 * n);
     }
+    if (!on) return;
     if (OUT_BF16) {
-        ushort4 o;
-        o.x = moe::f32_to_bf16(acc.x); o.y = moe::f32_to_bf16(acc.y);
-        o.z = moe::f32_to_bf16(acc.z); o.w = moe::f32_to_bf16(acc.w);
-        *reinterpret_cast<ushort4 *>(static_cast<uint16_t *>(Y) + static_cast<size_t>(i) * d_h + col) = o;
+        typedef uint16_t u16xV __attribute__((ext_vector_type(V)));
+        u16xV o;
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) o[n * 4 + q] = moe::f32_to_bf16(acc[n][q]);
+        *reinterpret_cast<u16xV *>(static_cast<uint16_t *>(Y) + static_cast<size_t>(i) * d_h + col) = o;
     } else {
-        *reinterpret_cast<float4 *>(static_cast<float *>(Y) + static_cast<size_t>(i) * d_h + col) = acc;
+#pragma unroll
+        for (int n = 0; n < N; ++n)
+            *reinterpret_cast<f32x4 *>(static_cast<float *>(Y) + static_cast<size_t>(i) * d_h + col + 4 * n) = acc[n];
     }
 }
 
@@ -97,6 +142,9 @@ extern "C" size_t moe_block_list_len(int T, int k, int C) {
 
 namespace {
 
+// from this many outputs on (T = 8192, d_h = 4096: 22 us with eight columns a thread, 27 with four; level at T = 512, d_h = 7168)
+constexpr long long kCombineWide = 4 << 20;
+
 int combine(const float *Yp_dev, const int32_t *pos_dev, const float *topk_w_dev, const float *Ys_dev, bool shared,
             int T, int k, int d_h, int dtype, void *Y_dev, void *stream, const char *what) {
     if (T < 0 || k < 1 || d_h < 1) return MOE_EINVAL;
@@ -107,12 +155,18 @@ int combine(const float *Yp_dev, const int32_t *pos_dev, const float *topk_w_dev
     if (!moe::aligned(Yp_dev, 16) || !moe::aligned(pos_dev, 4) || !moe::aligned(topk_w_dev, 4) ||
         !moe::aligned(Ys_dev, 16) || !moe::aligned(Y_dev, dtype == MOE_DTYPE_BF16 ? 8 : 16))
         return MOE_EINVAL;
-    const dim3 grid(T, (d_h + 1023) / 1024);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (dtype == MOE_DTYPE_BF16)
-        hipLaunchKernelGGL(combine_kernel<true>, grid, dim3(256), 0, st, Yp_dev, pos_dev, topk_w_dev, Ys_dev, k, d_h, Y_dev);
+    // eight columns a thread once that still gives every CU several workgroups; rows of d_h bf16 keep their 16-byte
+    // alignment when d_h is a multiple of 8
+    const bool wide = dtype == MOE_DTYPE_BF16 && d_h % 8 == 0 && moe::aligned(Y_dev, 16) && static_cast<long long>(T) * d_h >= kCombineWide;
+    const int cols = wide ? 2048 : 1024;
+    const dim3 grid(T, (d_h + cols - 1) / cols);
+    if (wide)
+        hipLaunchKernelGGL((combine_kernel<true, 8>), grid, dim3(256), 0, st, Yp_dev, pos_dev, topk_w_dev, Ys_dev, k, d_h, Y_dev);
+    else if (dtype == MOE_DTYPE_BF16)
+        hipLaunchKernelGGL((combine_kernel<true, 4>), grid, dim3(256), 0, st, Yp_dev, pos_dev, topk_w_dev, Ys_dev, k, d_h, Y_dev);
     else
-        hipLaunchKernelGGL(combine_kernel<false>, grid, dim3(256), 0, st, Yp_dev, pos_dev, topk_w_dev, Ys_dev, k, d_h, Y_dev);
+        hipLaunchKernelGGL((combine_kernel<false, 4>), grid, dim3(256), 0, st, Yp_dev, pos_dev, topk_w_dev, Ys_dev, k, d_h, Y_dev);
     return moe::check_launch(what);
 }
 

@@ -109,3 +109,52 @@ def test_schedule_batched_loads_only(n_inst, C, E, T, k, n_batches):
     opl = scheduling.make_placement(lay, E, n_inst, C)
     for b in (0, 1, n_batches - 1):
         np.testing.assert_array_equal(want[b].cpu().numpy(), scheduling.aebs(ids[b].cpu().numpy(), opl)[2])
+
+
+@pytest.mark.parametrize("T,k,d_h,dtype,shift", [(5, 1, 4, "f32", 0), (7, 32, 1028, "bf16", 0), (3, 8, 2052, "f32", 0),
+                                                 (1030, 6, 4104, "bf16", 0), (1030, 3, 4100, "bf16", 0), (1030, 6, 4104, "bf16", 4)])
+@pytest.mark.parametrize("shared", [False, True])
+def test_combine_columns(T, k, d_h, dtype, shift, shared):
+    """Four and eight columns a thread (from 4 Mi outputs on, d_h a multiple of 8, output 16-byte aligned; shift moves it by
+    8 bytes), columns past a multiple of a workgroup's, tokens with no, some and all k local requests.  fp32 sums of up
+    to 33 terms: 1e-6 relative, and one rounding to bf16 (2^-8)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(T + d_h)
+    local = torch.rand((T, k), device="cuda", generator=g) < 0.5
+    local[0], local[1] = False, True
+    n = int(local.sum().item())
+    pos = torch.full((T, k), -1, dtype=torch.int32, device="cuda")
+    pos[local] = torch.randperm(n, device="cuda", generator=g).to(torch.int32)
+    w = torch.rand((T, k), device="cuda", generator=g)
+    Yp = torch.randn((n, d_h), device="cuda", generator=g)
+    Ys = torch.randn((T, d_h), device="cuda", generator=g)
+    tdt, code = (torch.bfloat16, B.MOE_DTYPE_BF16) if dtype == "bf16" else (torch.float32, B.MOE_DTYPE_F32)
+    buf = torch.full((T * d_h + 16,), 77.0, dtype=tdt, device="cuda")
+    Y = buf[shift:shift + T * d_h].view(T, d_h)
+    if shared:
+        B.moe_combine_shared(Yp, pos, w, Ys, T, k, d_h, code, Y)
+    else:
+        B.moe_combine(Yp, pos, w, T, k, d_h, code, Y)
+    torch.cuda.synchronize()
+    want = Ys.double() if shared else torch.zeros((T, d_h), dtype=torch.float64, device="cuda")
+    size = want.abs()
+    for j in range(k):
+        term = torch.where(local[:, j:j + 1], Yp[pos[:, j].clamp(min=0).long()].double() * w[:, j:j + 1].double(), 0.0)
+        want, size = want + term, size + term.abs()
+    bound = 2e-6 * size + (2.0 ** -8 * want.abs() if dtype == "bf16" else 0.0)
+    assert ((Y.double() - want).abs() <= bound + 1e-30).all()
+    assert (buf[:shift] == 77.0).all() and (buf[shift + T * d_h:] == 77.0).all()
+
+
+@pytest.mark.parametrize("C,d_h,d_e", [(1, 32, 32), (3, 160, 96), (2, 544, 672)])
+def test_pack_weights_layout(C, d_h, d_e):
+    """The packed images against their definition, for numbers of K-steps around a wavefront's four."""
+    W13 = torch.arange(C * 2 * d_e * d_h, dtype=torch.int32, device="cuda").to(torch.int16).view(C, 2 * d_e, d_h)
+    W2 = torch.arange(C * d_h * d_e, dtype=torch.int32, device="cuda").mul_(7).to(torch.int16).view(C, d_h, d_e)
+    p13, p2 = torch.zeros_like(W13), torch.zeros_like(W2)
+    B.moe_pack_weights_bf16(W13, W2, C, d_h, d_e, p13, p2)
+    torch.cuda.synchronize()
+    # [C][tile][K-step][half][16-byte group of the K-step][row of the tile][8]
+    w13 = W13.view(C, 2, d_e // 16, 16, d_h // 32, 4, 8).permute(0, 2, 4, 1, 5, 3, 6)
+    w2 = W2.view(C, d_h // 32, 2, 16, d_e // 32, 4, 8).permute(0, 1, 4, 2, 5, 3, 6)
+    assert torch.equal(p13.view(-1), w13.reshape(-1)) and torch.equal(p2.view(-1), w2.reshape(-1))
