@@ -659,7 +659,8 @@ __device__ __forceinline__ void scatter_chunk(PermShared &sh, int *__restrict__ 
     // slot totals over all chunks, and the requests of the chunks before this one
     for (int s = tid; s < C; s += kFrontThreads) {
         int tot = 0, low = 0;
-        for (int c = 0; c < n_chunks; ++c) {
+#pragma unroll 16
+        for (int c = 0; c < n_chunks; ++c) {                          // the loads of sixteen chunks at once
             const int v = hist[c * C + s];
             tot += v;
             low += c < chunk ? v : 0;
