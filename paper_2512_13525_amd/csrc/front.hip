@@ -33,6 +33,7 @@ struct FrontArgs {
     uint32_t *act_bits;                  // [kBitWords], zero between calls; null = one-workgroup tail
     int32_t *hist;                       // [n_chunks][C]
     int chunk_pairs, n_chunks;
+    int tok_per_wave;                    // tokens such a wavefront routes one after the other
     int tok_per_wg;                      // wavefronts of a workgroup that route a token (4, 8 or 16)
 };
 constexpr int kBitWords = MOE_MAX_EXPERTS / 32;
@@ -453,13 +454,15 @@ void front_kernel(FrontArgs a) {
     // small batches route on a few wavefronts per workgroup (one or two per SIMD instead of four),
     // spread over more CUs: the selection is a long chain of cross-lane steps that four wavefronts
     // of one SIMD would take turns at
-    const int t = blockIdx.x * a.tok_per_wg + wave;
-    if (wave < a.tok_per_wg && t < a.T) {
-        const float *lg = a.logits + static_cast<size_t>(t) * a.E;
-        int32_t *ids = a.ids + static_cast<size_t>(t) * a.k;
-        float *w = a.w + static_cast<size_t>(t) * a.k;
-        moe::route_token<VPL, true>(lg, a.E, a.k, a.cfg, row[wave], lane, ids, w, solo ? s_ids + t * a.k : nullptr,
-                                    a.act_bits ? s_bits : nullptr);
+    for (int u = 0; u < a.tok_per_wave; ++u) {
+        const int t = (blockIdx.x * a.tok_per_wave + u) * a.tok_per_wg + wave;
+        if (wave < a.tok_per_wg && t < a.T) {
+            const float *lg = a.logits + static_cast<size_t>(t) * a.E;
+            int32_t *ids = a.ids + static_cast<size_t>(t) * a.k;
+            float *w = a.w + static_cast<size_t>(t) * a.k;
+            moe::route_token<VPL, true>(lg, a.E, a.k, a.cfg, row[wave], lane, ids, w, solo ? s_ids + t * a.k : nullptr,
+                                        a.act_bits ? s_bits : nullptr);
+        }
     }
     if (small) stage_small(a, sh.small, tp);
     if (solo) {
@@ -533,12 +536,17 @@ void front_scatter_kernel(FrontArgs a) {
                        a.perm, a.pos, a.blocks, a.block_rows);
 }
 
+constexpr int kFrontTwoTokens = 256 * moe::kFrontWaves;
 template <int VPL>
 int launch_front(const FrontArgs &a_in, const char *what, hipStream_t st) {
     FrontArgs a = a_in;
     // every routing workgroup takes a ticket from one counter: keep them to about a hundred
     a.tok_per_wg = a.T <= kSoloTokens ? moe::kFrontWaves : a.T <= 512 ? 4 : a.T <= 1024 ? 8 : moe::kFrontWaves;
-    const int blocks = a.T > 0 ? (a.T + a.tok_per_wg - 1) / a.tok_per_wg : 1;
+    // past one workgroup per CU the counter and the bit set cost more than a second token on every wavefront
+    // (T = 8192, E = 256: front 32 -> 28 us; E = 128 30 -> 26)
+    a.tok_per_wave = a.act_bits && a.T > kFrontTwoTokens ? 2 : 1;
+    const int per = a.tok_per_wg * a.tok_per_wave;
+    const int blocks = a.T > 0 ? (a.T + per - 1) / per : 1;
     hipLaunchKernelGGL(front_kernel<VPL>, dim3(blocks), dim3(moe::kFrontThreads), 0, st, a);
     if (a.act_bits) {
         hipLaunchKernelGGL(front_count_kernel, dim3(a.n_chunks), dim3(moe::kFrontThreads), 0, st, a);

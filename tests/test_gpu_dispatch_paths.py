@@ -38,10 +38,10 @@ def test_selection_with_equal_logits(E, k, group):
 
 
 @pytest.mark.parametrize("n_inst,C,E", [(3, 9, 21), (16, 5, 64), (20, 4, 60), (40, 30, 1000)])
-@pytest.mark.parametrize("T", [1, 16, 17, 600])
+@pytest.mark.parametrize("T", [1, 16, 17, 600, 4107])
 def test_front_sizes(n_inst, C, E, T):
     """One workgroup (up to 16 tokens) and several; up to 16 instances and more; 1, 2 and 4 groups of 64 requests
-    per wavefront; a table too large for LDS.  Against the oracle, twice on the same sync words."""
+    per wavefront, the chunked tail with two tokens a wavefront; a table too large for LDS.  Against the oracle, twice on the same sync words."""
     k = 7
     cfg = W.MoEConfig("front", E=E, k=k, d_h=32, d_e=32, T=T, n_inst=n_inst, C=C, zipf_s=1.0, seed=T)
     lay = W.build_placement(cfg)
