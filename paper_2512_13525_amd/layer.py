@@ -91,7 +91,7 @@ class LayerStep:
                                      c.n_group if group else 1, c.topk_group if group else 1, 1.0, stream=stream)
 
     def front_gate(self, X, Wr, bias=None, stream=None):
-        """gate (X * Wr^T + bias) + route + schedule + permute in one launch; returns the logits."""
+        """gate (X * Wr^T + bias), then route + schedule + permute in one launch; returns the logits."""
         c = self.cfg
         group = c.route != "softmax"
         B.moe_gate_route_schedule_permute(self.pl, self.g_self, X, Wr, bias, c.k, self.gate_logits, self.topk_ids,
