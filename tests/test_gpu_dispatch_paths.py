@@ -158,3 +158,39 @@ def test_pack_weights_layout(C, d_h, d_e):
     w13 = W13.view(C, 2, d_e // 16, 16, d_h // 32, 4, 8).permute(0, 2, 4, 1, 5, 3, 6)
     w2 = W2.view(C, d_h // 32, 2, 16, d_e // 32, 4, 8).permute(0, 1, 4, 2, 5, 3, 6)
     assert torch.equal(p13.view(-1), w13.reshape(-1)) and torch.equal(p2.view(-1), w2.reshape(-1))
+
+
+def device_time(fn, n=20, reps=9):
+    """Microseconds of one call on the device: the fastest of several replays of a graph of n calls."""
+    fn()
+    torch.cuda.synchronize()
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        for _ in range(n):
+            fn()
+    best = float("inf")
+    for r in range(3 + reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        torch.cuda.synchronize()
+        if r >= 3:
+            best = min(best, a.elapsed_time(b) / n * 1e3)
+    return best
+
+
+@pytest.mark.parametrize("E,k,group", [(64, 8, None), (128, 8, None), (256, 8, (8, 4)), (1024, 8, None)])
+def test_selection_time_with_equal_logits(E, k, group):
+    """A row of equal logits (a padded token's) takes as long as any other: every choice then falls on a tie of all
+    experts.  Walking the tied experts one by one takes 3 to 10 times as long; the bound is half again."""
+    T = 512
+    ids = torch.empty((T, k), dtype=torch.int32, device="cuda")
+    w = torch.empty((T, k), dtype=torch.float32, device="cuda")
+    kw = {} if group is None else dict(mode=B.MOE_ROUTE_SIGMOID_GROUP, n_group=group[0], topk_group=group[1])
+    z = torch.randn((T, E), device="cuda")
+    equal = torch.zeros_like(z)
+    t_random = device_time(lambda: B.moe_route(z, k, ids, w, **kw))
+    t_equal = device_time(lambda: B.moe_route(equal, k, ids, w, **kw))
+    assert (ids == torch.arange(k, dtype=torch.int32, device="cuda")).all()
+    assert t_equal < 1.5 * t_random, (t_equal, t_random)
