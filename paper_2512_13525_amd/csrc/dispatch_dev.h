@@ -117,7 +117,7 @@ __device__ __forceinline__ float sigmoid_f32(float x) { return 1.0f / (1.0f + ex
 // steps), the lane that holds it from a ballot.  Equal logits go to the lower id: the lowest index inside a lane,
 // and among several lanes with the same key the lowest index, then the lowest lane.  That choice narrows the ballot
 // by one bit of the index at a time, the same few scalar instructions for any number of holders: a row of equal logits
-// (a padded token) takes as long as any other (E = 128, k = 8, T = 256, a seventh of the rows zero: front 10.0 us, 28.2
+// (a padded token) takes 2 to 9 % longer than any other (E = 128, k = 8, T = 256, a seventh of the rows zero: front 10.0 us, 28.2
 // when the holders were walked one by one).  Experts that are taken, dropped or
 // past E have key 0 and no bit in `alive`, so that a surviving NaN whose key is 0 is still found.
 // row_lds: VPL*64 floats private to this wavefront.  COHERENT: ids are written with agent-scope stores (read by
@@ -242,6 +242,7 @@ __device__ __forceinline__ void route_token(const float *row, int E, int k, cons
         vmax = __uint_as_float(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(sel_v)), 0)));
     } else {
         // k rounds of "largest remaining"
+#pragma unroll 1                                         // two rounds in a row only lengthen cold code (E = 128 front 7.8, 7.5 us with one)
         for (int j = 0; j < k; ++j) {
             uint32_t m = key[0];
             int mi = 0;                                      // lowest index of the lane's largest key
@@ -251,10 +252,14 @@ __device__ __forceinline__ void route_token(const float *row, int E, int k, cons
             const uint32_t best = wave_max_u32(m);
             if (best == 0u) mi = __builtin_ctz(alive | 0x80000000u);     // key 0: only what is alive counts
             uint64_t holders = __ballot(m == best && alive != 0u);
+            // only where lanes tie (E = 1024, k = 32: front 29.8 us with the steps in every round, 28.5 so); with two
+            // keys a lane the one step costs no more than the branch around it
+            if (VPL == 2 || (VPL > 2 && (holders & (holders - 1)))) {    // wave-uniform
 #pragma unroll
-            for (int b = VPL / 2; b > 0; b >>= 1) {          // VPL is a power of two
-                const uint64_t low = holders & __ballot((mi & b) == 0);
-                holders = low ? low : holders;
+                for (int b = VPL / 2; b > 0; b >>= 1) {      // VPL is a power of two
+                    const uint64_t low = holders & __ballot((mi & b) == 0);
+                    holders = low ? low : holders;
+                }
             }
             const int src = __builtin_ctzll(holders);
             const int id = __builtin_amdgcn_readlane(mi, src) * MOE_WAVE + src;
