@@ -198,8 +198,8 @@ size_t moe_block_list_len(int T, int k, int C);
  * few microseconds of work behind a launch of similar cost; this entry point pays one launch.
  * sync_dev: moe_front_sync_len() int32 of device memory, zero before the first call; every call
  * leaves its first 33 words zero (the rest is scratch).  Calls that share sync_dev must not overlap
- * in time.  Up to 8192 requests (T*k) the call is one launch and sync_dev is one word (batches of up to 16 tokens
- * are one workgroup and leave it alone); larger
+ * in time.  Up to 8192 requests (T*k) the call is one launch and sync_dev is one word (batches of a few tokens,
+ * 12 at most, are one workgroup and leave it alone); larger
  * batches take three launches: the routing workgroups collect the activated experts in a bitset
  * (Alg. 1, Step 1, token-parallel), the last of them runs Step 2, and Step 3 and the sort run
  * over chunks of 2048 requests, one workgroup each (per-chunk counts, then the scatter; no

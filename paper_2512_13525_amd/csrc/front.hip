@@ -33,6 +33,7 @@ struct FrontArgs {
     uint32_t *act_bits;                  // [kBitWords], zero between calls; null = one-workgroup tail
     int32_t *hist;                       // [n_chunks][C]
     int chunk_pairs, n_chunks;
+    int solo;                            // one workgroup routes the batch and goes on without a ticket
     int tok_per_wave;                    // tokens such a wavefront routes one after the other
     int tok_per_wg;                      // wavefronts of a workgroup that route a token (4, 8 or 16)
 };
@@ -244,9 +245,13 @@ int launch_gate(const void *X, const void *Wr, const float *bias, float *logits,
 constexpr int kGpwMax = 8;                                            // 64-request groups per wavefront (compiled for 1, 2, 4 and 8)
 constexpr int kRegPairs = moe::kFrontWaves * kGpwMax * MOE_WAVE;      // 8192
 constexpr int kSlotOfLds = 8192;                                      // E*n_inst entries of slot_of kept in LDS
-// Up to this many tokens one workgroup routes the whole batch: the ids stay in LDS, and the publication, the
-// ticket and the read-back (0.3 + 0.45 + 0.9 us at T = 8) fall away.  More tokens would take turns on its wavefronts.
-constexpr int kSoloTokens = moe::kFrontWaves;
+// A batch of a few tokens is routed by one workgroup: the ids stay in LDS, and the publication, the ticket and the
+// read-back (0.3 + 0.45 + 0.9 us at T = 8) fall away.  Its wavefronts take turns on the four SIMDs, so each further four
+// tokens add a selection to the chain, and the line falls with the selection's length, about E * k
+// (one workgroup against several, us: E = 128, k = 8, T = 12 7.4 and 7.6, T = 16 8.0 and 7.6; E = 512, k = 8, T = 8
+// 9.1 and 9.7, T = 12 10.2 and 9.4; E = 1024, k = 32, T = 4 27.2 and 28.4, T = 16 39.9 and 29.6).
+constexpr int kSoloTokens = 12;
+int solo_tokens(int E, int k) { return E * k <= 2048 ? kSoloTokens : E * k <= 8192 ? 8 : 4; }
 
 struct SmallShared {
     moe::SchedShared sched;
@@ -444,7 +449,7 @@ void front_kernel(FrontArgs a) {
     const int lane = moe::lane_id();
     const int n_pairs = a.T * a.k;
     const bool small = n_pairs <= kRegPairs && a.E * a.n_inst <= kSlotOfLds;
-    const bool solo = small && a.T <= kSoloTokens;                    // this is the only workgroup
+    const bool solo = a.solo != 0;                                    // this is the only workgroup
     TablePrefetch tp{};
     if (small) tp = prefetch_tables(a);
     if (a.act_bits) {
@@ -541,7 +546,8 @@ template <int VPL>
 int launch_front(const FrontArgs &a_in, const char *what, hipStream_t st) {
     FrontArgs a = a_in;
     // every routing workgroup takes a ticket from one counter: keep them to about a hundred
-    a.tok_per_wg = a.T <= kSoloTokens ? moe::kFrontWaves : a.T <= 512 ? 4 : a.T <= 1024 ? 8 : moe::kFrontWaves;
+    a.solo = static_cast<long long>(a.T) * a.k <= kRegPairs && a.E * a.n_inst <= kSlotOfLds && a.T <= solo_tokens(a.E, a.k);
+    a.tok_per_wg = a.solo ? moe::kFrontWaves : a.T <= 512 ? 4 : a.T <= 1024 ? 8 : moe::kFrontWaves;
     // past one workgroup per CU the counter and the bit set cost more than a second token on every wavefront
     // (T = 8192, E = 256: front 32 -> 28 us; E = 128 30 -> 26)
     a.tok_per_wave = a.act_bits && a.T > kFrontTwoTokens ? 2 : 1;

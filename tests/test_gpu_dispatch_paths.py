@@ -206,3 +206,17 @@ def test_selection_time_with_many_selections():
     t8 = device_time(lambda: B.moe_route(z, 8, ids, w))
     t32 = device_time(lambda: B.moe_route(z, 32, ids, w))
     assert t32 < 1.5 * t8, (t32, t8)
+
+
+@pytest.mark.parametrize("E,n_inst,C,k", [(1024, 16, 64, 32), (256, 16, 16, 32), (128, 8, 17, 8)])
+def test_front_time_of_few_tokens(E, n_inst, C, k):
+    """Batches of a few tokens, some of them routed by one workgroup, take no longer than one of a few tokens more that
+    several workgroups route (0.9 to 1.0 of it; sixteen long selections in one workgroup take 1.4)."""
+    def front_time(T):
+        cfg = W.MoEConfig("few", E=E, k=k, d_h=32, d_e=32, T=T, n_inst=n_inst, C=C, zipf_s=1.0, seed=T)
+        s = LayerStep(cfg, W.build_placement(cfg), 0)
+        z = torch.from_numpy(W.router_logits(cfg)).cuda()
+        return device_time(lambda: s.front(z))
+    several = front_time(20)
+    times = {T: front_time(T) for T in (4, 8, 12, 16)}
+    assert all(t < 1.15 * several for t in times.values()), (times, several)
