@@ -23,12 +23,12 @@ void aebs_kernel(SchedTables tb, int E, int n_inst, int C, int n_words,
 
 // Loads only, many batches: one wavefront per batch, no barrier, no rewriting.  The four wavefronts of a workgroup
 // share the layout tables and walk the batches with a stride of the whole grid.  A batch is one pass over its ids
-// (16-byte loads, eight in flight a lane), flags in wave-private LDS, then the same selection as aebs_kernel.
+// (16-byte loads, eight in flight a lane, whatever the batch's own alignment), flags in wave-private LDS, then the same selection as aebs_kernel.
 constexpr int kLoadsWaves = 4;
 template <int W>
 __global__ __launch_bounds__(kLoadsWaves * MOE_WAVE)
 void aebs_loads_kernel(SchedTables tb, int E, int n_inst, int n_words, const int32_t *__restrict__ ids, int n_batches,
-                       int n_pairs, int vec_ok, int32_t *__restrict__ load_out) {
+                       int n_pairs, int32_t *__restrict__ load_out) {
     __shared__ uint64_t host_mask[W * MOE_WAVE], multi_mask[W], single_mask[MOE_MAX_INSTANCES * W];
     __shared__ uint32_t flags[kLoadsWaves][W * MOE_WAVE];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE), lane = moe::lane_id();
@@ -43,23 +43,22 @@ void aebs_loads_kernel(SchedTables tb, int E, int n_inst, int n_words, const int
 #pragma unroll
         for (int w = 0; w < W; ++w) flag[w * MOE_WAVE + lane] = 0u;
         __builtin_amdgcn_wave_barrier();                             // LDS operations of a wavefront stay in order
-        int done = 0;
-        if (vec_ok) {
-            const int n4 = n_pairs >> 2;
-            const int4 *my4 = reinterpret_cast<const int4 *>(my);
-            for (int i0 = 0; i0 < n4; i0 += kAhead * MOE_WAVE) {
-                int4 v[kAhead];
+        // whole 16 bytes from the first aligned one on; up to three ids before them and after them
+        const int lead = static_cast<int>(-(reinterpret_cast<uintptr_t>(my) >> 2) & 3);
+        const int head = lead < n_pairs ? lead : n_pairs, n4 = (n_pairs - head) >> 2, tail = head + (n4 << 2);
+        if (lane < head) flag[my[lane]] = 1u;
+        if (lane < n_pairs - tail) flag[my[tail + lane]] = 1u;
+        const int4 *my4 = reinterpret_cast<const int4 *>(my + head);
+        for (int i0 = 0; i0 < n4; i0 += kAhead * MOE_WAVE) {
+            int4 v[kAhead];
 #pragma unroll
-                for (int u = 0; u < kAhead; ++u) {
-                    const int i = i0 + u * MOE_WAVE + lane;
-                    v[u] = my4[i < n4 ? i : n4 - 1];                 // past the end: the last four again
-                }
-#pragma unroll
-                for (int u = 0; u < kAhead; ++u) { flag[v[u].x] = 1u; flag[v[u].y] = 1u; flag[v[u].z] = 1u; flag[v[u].w] = 1u; }
+            for (int u = 0; u < kAhead; ++u) {
+                const int i = i0 + u * MOE_WAVE + lane;
+                v[u] = my4[i < n4 ? i : n4 - 1];                     // past the end: the last four again
             }
-            done = n4 << 2;
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) { flag[v[u].x] = 1u; flag[v[u].y] = 1u; flag[v[u].z] = 1u; flag[v[u].w] = 1u; }
         }
-        for (int i = done + lane; i < n_pairs; i += MOE_WAVE) flag[my[i]] = 1u;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -122,16 +121,16 @@ void launch_aebs(const moe_placement_t *pl, int n_batches, const int32_t *ids, i
 }
 
 // A workgroup per batch keeps two batches on each CU, 512 in all; from the second round on a wavefront per batch
-// is faster: 2000 batches of 2048 requests 5.7 us a call against 10.6, 600 of 4096 4.5 against 5.2, 3000 of 4096 11.0
-// against 19.5, but 512 of 16384 8.7 against 8.4 (sixteen wavefronts read one batch's ids faster).
-constexpr int kLoadsMinBatches = 513;
-void launch_loads(const moe_placement_t *pl, int n_batches, const int32_t *ids, int n_pairs, int vec_ok, int32_t *load,
-                  hipStream_t st) {
+// is faster as long as its pass over the ids (2048 at a time, one such step after the other) is short against the rounds
+// it replaces (2000 batches of 2048 requests 4.7 us a call against 9.8, 5000 of 8192 28 against 37, 600 of 4096 4.7 against
+// 5.8; but 513 of 8192 6.6 against 6.1, 2000 of 32768 44 against 40).
+bool loads_by_wavefront(int n_batches, int n_pairs) { return n_batches > 512 && n_pairs <= 8192 && n_pairs / 8 <= n_batches; }
+void launch_loads(const moe_placement_t *pl, int n_batches, const int32_t *ids, int n_pairs, int32_t *load, hipStream_t st) {
     const SchedTables tb{pl->host_mask_d, pl->slot_of_d, pl->single_rid_d, pl->multi_mask_d, pl->single_mask_d};
     const long long wanted = (static_cast<long long>(n_batches) + kLoadsWaves - 1) / kLoadsWaves;
     const unsigned grid = static_cast<unsigned>(wanted < 2048 ? wanted : 2048);
 #define MOE_LOADS(W) hipLaunchKernelGGL(aebs_loads_kernel<W>, dim3(grid), dim3(kLoadsWaves * MOE_WAVE), 0, st, tb, pl->E, pl->n_inst, \
-                                        pl->n_words, ids, n_batches, n_pairs, vec_ok, load)
+                                        pl->n_words, ids, n_batches, n_pairs, load)
     if (pl->n_words <= 1) MOE_LOADS(1);
     else if (pl->n_words <= 2) MOE_LOADS(2);
     else if (pl->n_words <= 4) MOE_LOADS(4);
@@ -191,8 +190,8 @@ extern "C" int moe_schedule_batched(const moe_placement_t *pl, const int32_t *to
     const int vec_ok = moe::aligned(topk_ids_dev, 16) && (!rid_dev || moe::aligned(rid_dev, 16)) &&
                        (static_cast<long long>(T) * k) % 4 == 0;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (!rid_dev && !act_rep_dev && n_batches >= kLoadsMinBatches)
-        launch_loads(pl, n_batches, topk_ids_dev, T * k, vec_ok, load_dev, st);
+    if (!rid_dev && !act_rep_dev && loads_by_wavefront(n_batches, T * k))
+        launch_loads(pl, n_batches, topk_ids_dev, T * k, load_dev, st);
     else
         launch_aebs(pl, n_batches, topk_ids_dev, T * k, vec_ok, rid_dev, act_rep_dev, load_dev, st);
     return moe::check_launch("moe_schedule_batched");
