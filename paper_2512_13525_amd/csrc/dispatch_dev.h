@@ -357,15 +357,18 @@ __device__ __forceinline__ void aebs_stage_tables(const SchedTables &tb, SchedSh
 }
 
 // Step 2 of Alg. 1 by one wavefront from the expert flags in LDS.  W >= n_words is a compile-time number of
-// 64-expert words: the flags and host masks of all words are read at once, before the greedy chain, and the
-// replica ids of all words after it, so that the LDS latencies of the words overlap (a loop over the words paid
-// them one after the other: 0.9 us per word).  In between only scalar instructions and lane reads remain.
+// 64-expert words: the flags and masks of G words are read at once, before the greedy chain, and the
+// replica ids of these words after it, so that the LDS latencies of the words overlap (a loop over the words paid
+// them one after the other: 0.9 us per word).  In between only scalar instructions and lane reads remain.  G: the words of
+// a group.  All at once is the fastest chain; where many workgroups share the CUs groups of four keep them at 64 registers
+// and two to a CU (E = 1024, 512 batches: all sixteen words at once take 128 registers and 11.6 us, groups 8.6).
 // rep_of(e, instance, or -1 if it has one replica): the replica id of an expert.  actRep goes to rep (LDS, if not null) and
 // act_rep (if not null); returns load[lane].
-template <int W, typename RepOf>
+template <int W, int G, typename RepOf>
 __device__ __forceinline__ int aebs_select_wave(const uint32_t *flag, const uint64_t *host_mask, const uint64_t *multi_mask,
                                                 const uint64_t *single_mask, int E, int n_inst, int n_words, int lane,
                                                 RepOf rep_of, int32_t *rep, int32_t *__restrict__ act_rep) {
+    static_assert(W % G == 0, "whole groups");
     // Up to 16 instances the loads are kept four times, lane l = instance l % 16: the arg-min of
     // (load, instance) over an expert's hosts is then four exchanges inside rows of 16 lanes with the result in
     // every lane, and the chain never leaves the vector registers (walking the hosts one by one with scalar lane
@@ -373,66 +376,85 @@ __device__ __forceinline__ int aebs_select_wave(const uint32_t *flag, const uint
     const bool rows = n_inst <= 16;                     // wave-uniform
     const int g = rows ? lane & 15 : lane;
     const int g_ok = g < n_inst ? g : n_inst - 1;
-    // all reads with clamped indices, none inside a branch: one LDS latency for all words
-    uint32_t fl[W];
-    uint64_t act[W], hm[W], sm[W];
+    // all reads with clamped indices, none inside a branch: one LDS latency for the words of a group
+    uint64_t act[G];                                    // the activated experts of a word: scalars of the only group,
+    uint64_t act_l = 0ull;                              // or in lane w
     const uint64_t mm = multi_mask[lane < n_words ? lane : n_words - 1];
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-        const int e = w * MOE_WAVE + lane < E ? w * MOE_WAVE + lane : E - 1;
-        fl[w] = flag[e];
-        hm[w] = host_mask[e];
-        sm[w] = single_mask[g_ok * n_words + (w < n_words ? w : n_words - 1)];
-    }
     int load = 0;                                       // load[g]
+#pragma unroll 1                                        // groups of one shape: less cold code, no reads ahead of a group
+    for (int w0 = 0; w0 < (W == G ? G : n_words); w0 += G) {
+        uint32_t fl[G];
+        uint64_t sm[G];
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-        act[w] = __ballot(w * MOE_WAVE + lane < E && fl[w] != 0u);
-        load += __popcll(act[w] & sm[w]);               // words past the last have no act bits
+        for (int i = 0; i < G; ++i) {
+            const int w = w0 + i, e = w * MOE_WAVE + lane < E ? w * MOE_WAVE + lane : E - 1;
+            fl[i] = flag[e];
+            sm[i] = single_mask[g_ok * n_words + (w < n_words ? w : n_words - 1)];
+        }
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            act[i] = __ballot((w0 + i) * MOE_WAVE + lane < E && fl[i] != 0u);
+            load += __popcll(act[i] & sm[i]);           // words past the last have no act bits
+            if (W > G) act_l = lane == w0 + i ? act[i] : act_l;
+        }
     }
     if (g >= n_inst) load = 0;
-    int chosen[W];                                      // lane b: instance chosen for expert w*64+b
+#pragma unroll 1
+    for (int w0 = 0; w0 < (W == G ? G : n_words); w0 += G) {
+        uint64_t hm[G];
+        if (W > G) {
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-        chosen[w] = -1;
-        uint64_t todo = w < n_words ? act[w] & readlane_u64(mm, w) : 0ull;   // wave-uniform: keep the loop scalar
-        if (rows) {
-            while (todo) {
-                const int b = __builtin_ctzll(todo);
-                todo &= todo - 1;
-                const uint32_t hosts = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(hm[w] & 0xffffffffu), b));
-                // smallest load first, lowest instance on ties; loads are at most MOE_MAX_SLOTS
-                const uint32_t m = wave_min_rows_u32((hosts >> g) & 1u ? static_cast<uint32_t>(load) * MOE_MAX_INSTANCES + g : ~0u);
-                const int best = static_cast<int>(m % MOE_MAX_INSTANCES);
-                load += g == best ? 1 : 0;
-                chosen[w] = lane == b ? best : chosen[w];
-            }
-        } else {
-            while (todo) {
-                const int b = __builtin_ctzll(todo);
-                todo &= todo - 1;
-                const uint64_t hosts = readlane_u64(hm[w], b);
-                const uint32_t m = wave_min_of_rows_u32(
-                    wave_min_rows_u32((hosts >> g) & 1ull ? static_cast<uint32_t>(load) * MOE_MAX_INSTANCES + g : ~0u));
-                const int best = static_cast<int>(m % MOE_MAX_INSTANCES);
-                load += g == best ? 1 : 0;
-                chosen[w] = lane == b ? best : chosen[w];
-            }
-        }
-    }
-    if (rep || act_rep) {
-        int r[W];
-#pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const int e = w * MOE_WAVE + lane < E ? w * MOE_WAVE + lane : E - 1;
-            r[w] = rep_of(e, chosen[w]);
+            for (int i = 0; i < G; ++i) act[i] = readlane_u64(act_l, w0 + i);
         }
 #pragma unroll
-        for (int w = 0; w < W; ++w) {
-            const int e = w * MOE_WAVE + lane;
-            r[w] = (act[w] >> lane) & 1ull ? r[w] : -1;
-            if (e < E && rep) rep[e] = r[w];
-            if (e < E && act_rep) act_rep[e] = r[w];
+        for (int i = 0; i < G; ++i) {
+            const int e = (w0 + i) * MOE_WAVE + lane < E ? (w0 + i) * MOE_WAVE + lane : E - 1;
+            hm[i] = host_mask[e];
+        }
+        int chosen[G];                                  // lane b: instance chosen for expert w*64+b
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            const int w = w0 + i;
+            chosen[i] = -1;
+            uint64_t todo = w < n_words ? act[i] & readlane_u64(mm, w) : 0ull;   // wave-uniform: keep the loop scalar
+            if (rows) {
+                while (todo) {
+                    const int b = __builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    const uint32_t hosts = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(hm[i] & 0xffffffffu), b));
+                    // smallest load first, lowest instance on ties; loads are at most MOE_MAX_SLOTS
+                    const uint32_t m = wave_min_rows_u32((hosts >> g) & 1u ? static_cast<uint32_t>(load) * MOE_MAX_INSTANCES + g : ~0u);
+                    const int best = static_cast<int>(m % MOE_MAX_INSTANCES);
+                    load += g == best ? 1 : 0;
+                    chosen[i] = lane == b ? best : chosen[i];
+                }
+            } else {
+                while (todo) {
+                    const int b = __builtin_ctzll(todo);
+                    todo &= todo - 1;
+                    const uint64_t hosts = readlane_u64(hm[i], b);
+                    const uint32_t m = wave_min_of_rows_u32(
+                        wave_min_rows_u32((hosts >> g) & 1ull ? static_cast<uint32_t>(load) * MOE_MAX_INSTANCES + g : ~0u));
+                    const int best = static_cast<int>(m % MOE_MAX_INSTANCES);
+                    load += g == best ? 1 : 0;
+                    chosen[i] = lane == b ? best : chosen[i];
+                }
+            }
+        }
+        if (rep || act_rep) {
+            int r[G];
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                const int e = (w0 + i) * MOE_WAVE + lane < E ? (w0 + i) * MOE_WAVE + lane : E - 1;
+                r[i] = rep_of(e, chosen[i]);
+            }
+#pragma unroll
+            for (int i = 0; i < G; ++i) {
+                const int e = (w0 + i) * MOE_WAVE + lane;
+                r[i] = (act[i] >> lane) & 1ull ? r[i] : -1;
+                if (e < E && rep) rep[e] = r[i];
+                if (e < E && act_rep) act_rep[e] = r[i];
+            }
         }
     }
     return load;
@@ -440,7 +462,7 @@ __device__ __forceinline__ int aebs_select_wave(const uint32_t *flag, const uint
 
 // Step 2 from sh.flag (first wavefront; the caller orders the flags before and sh.rep after with barriers):
 // actRep into sh.rep and act_rep (if not null), loads into load_out.
-template <int W>
+template <int W, int G = W>
 __device__ __forceinline__ void aebs_select(const SchedTables &tb, SchedShared &sh, int E, int n_inst, int C, int n_words,
                                             int32_t *__restrict__ act_rep, int32_t *__restrict__ load_out) {
     if (threadIdx.x >= MOE_WAVE) return;
@@ -449,12 +471,12 @@ __device__ __forceinline__ void aebs_select(const SchedTables &tb, SchedShared &
         const int single = sh.single_rid[e], multi = (g < 0 ? 0 : g) * C + tb.slot_of[e * n_inst + (g < 0 ? 0 : g)];
         return g >= 0 ? multi : single;
     };
-    const int load = aebs_select_wave<W>(sh.flag, sh.host_mask, sh.multi_mask, sh.single_mask, E, n_inst, n_words, lane,
+    const int load = aebs_select_wave<W, G>(sh.flag, sh.host_mask, sh.multi_mask, sh.single_mask, E, n_inst, n_words, lane,
                                          rep_of, sh.rep, act_rep);
     if (lane < n_inst) load_out[lane] = load;
 }
 
-template <int W>
+template <int W, int G = W>
 __device__ __forceinline__ void aebs_block(const SchedTables &tb, SchedShared &sh, int E, int n_inst, int C,
                                            int n_words, const int32_t *__restrict__ ids, int n_pairs, int vec_ok,
                                            bool ids_coherent, int32_t *__restrict__ rid,
@@ -477,7 +499,7 @@ __device__ __forceinline__ void aebs_block(const SchedTables &tb, SchedShared &s
     __syncthreads();
 
     // ---- Step 2: select one replica per activated expert (first wavefront)
-    aebs_select<W>(tb, sh, E, n_inst, C, n_words, act_rep, load_out);
+    aebs_select<W, G>(tb, sh, E, n_inst, C, n_words, act_rep, load_out);
     if (!rid) return;                                    // uniform: no barrier is skipped by part of the workgroup
     __syncthreads();
 

@@ -324,7 +324,7 @@ __device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared
             const int single = sh.sched.single_rid[e], multi = (g < 0 ? 0 : g) * C + sh.slot_of[e * n_inst + (g < 0 ? 0 : g)];
             return g >= 0 ? multi : single;
         };
-        const int load = moe::aebs_select_wave<VPL>(sh.sched.flag, sh.sched.host_mask, sh.sched.multi_mask,
+        const int load = moe::aebs_select_wave<VPL, VPL>(sh.sched.flag, sh.sched.host_mask, sh.sched.multi_mask,
                                                     sh.sched.single_mask, E, n_inst, a.n_words, lane, rep_of, sh.sched.rep,
                                                     a.act_rep);
         if (lane < n_inst) a.load[lane] = load;

@@ -7,17 +7,20 @@ namespace {
 using moe::SchedTables;
 constexpr int kSchedThreads = moe::kFrontThreads;
 
+template <int W>
+constexpr int kGroup = W < 4 ? W : 4;                    // words that aebs_select_wave reads at once
+
 // One workgroup per batch (blockIdx.x): batch b reads ids + b*n_pairs and writes rid + b*n_pairs,
 // act_rep + b*E, load_out + b*n_inst.  The single-batch call is a grid of one.
 // W: 64-expert words the selection is compiled for (n_words <= W).
 template <int W>
-__global__ __launch_bounds__(kSchedThreads)
+__global__ __launch_bounds__(kSchedThreads, 8)           // 8 wavefronts a SIMD: two workgroups a CU
 void aebs_kernel(SchedTables tb, int E, int n_inst, int C, int n_words,
                  const int32_t *__restrict__ ids, int n_pairs, int vec_ok,
                  int32_t *__restrict__ rid, int32_t *__restrict__ act_rep, int32_t *__restrict__ load_out) {
     __shared__ moe::SchedShared sh;
     const size_t b = blockIdx.x;
-    moe::aebs_block<W>(tb, sh, E, n_inst, C, n_words, ids + b * n_pairs, n_pairs, vec_ok, false,
+    moe::aebs_block<W, kGroup<W>>(tb, sh, E, n_inst, C, n_words, ids + b * n_pairs, n_pairs, vec_ok, false,
                     rid ? rid + b * n_pairs : nullptr, act_rep ? act_rep + b * E : nullptr, load_out + b * n_inst);
 }
 
@@ -63,7 +66,7 @@ void aebs_loads_kernel(SchedTables tb, int E, int n_inst, int n_words, const int
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const auto no_rep = [](int, int) { return -1; };
-        const int load = moe::aebs_select_wave<W>(flag, host_mask, multi_mask, single_mask, E, n_inst, n_words, lane,
+        const int load = moe::aebs_select_wave<W, kGroup<W>>(flag, host_mask, multi_mask, single_mask, E, n_inst, n_words, lane,
                                                   no_rep, static_cast<int32_t *>(nullptr), static_cast<int32_t *>(nullptr));
         if (lane < n_inst) load_out[static_cast<size_t>(b) * n_inst + lane] = load;
         __builtin_amdgcn_wave_barrier();
@@ -115,8 +118,7 @@ void launch_aebs(const moe_placement_t *pl, int n_batches, const int32_t *ids, i
     if (pl->n_words <= 1) MOE_AEBS(1);
     else if (pl->n_words <= 2) MOE_AEBS(2);
     else if (pl->n_words <= 4) MOE_AEBS(4);
-    else if (pl->n_words <= 8) MOE_AEBS(8);
-    else MOE_AEBS(16);
+    else MOE_AEBS(16);                                   // more than four words: groups of four, the same code for all
 #undef MOE_AEBS
 }
 

@@ -237,3 +237,18 @@ def test_schedule_batched_loads_only_time(T, k):
         loads = device_time(lambda: B.moe_schedule_batched(pl, ids, n, T, k, None, None, load))
         general = device_time(lambda: B.moe_schedule_batched(pl, ids, n, T, k, None, rep, load))
         assert loads < 1.1 * general, (n, loads, general)
+
+
+@pytest.mark.parametrize("E,n_inst,C", [(300, 4, 80), (1024, 16, 64)])
+def test_schedule_batched_two_workgroups_a_cu(E, n_inst, C):
+    """More than 256 experts: 512 batches still run two to a CU, so they take little longer than 256 (1.1 times; 1.7 when a
+    workgroup's registers leave room for one)."""
+    pl = B.Placement(np.arange(E, dtype=np.int32) if n_inst * C == E else np.r_[np.arange(E), np.full(n_inst * C - E, -1)].astype(np.int32),
+                     E, n_inst, C)
+    t = {}
+    for n in (256, 512):
+        ids = torch.randint(0, E, (n, 16, 8), dtype=torch.int32, device="cuda")
+        rid, rep = torch.empty_like(ids), torch.empty((n, E), dtype=torch.int32, device="cuda")
+        load = torch.empty((n, n_inst), dtype=torch.int32, device="cuda")
+        t[n] = device_time(lambda: B.moe_schedule_batched(pl, ids, n, 16, 8, rid, rep, load))
+    assert t[512] < 1.4 * t[256], t
