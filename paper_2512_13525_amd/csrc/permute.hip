@@ -46,6 +46,7 @@ void combine_kernel(const float *__restrict__ Yp, const int32_t *__restrict__ po
     constexpr int N = V / 4;
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     const int i = blockIdx.x;
+    if ((blockIdx.y * 256 + (threadIdx.x & ~(MOE_WAVE - 1))) * V >= static_cast<unsigned>(d_h)) return;   // wavefronts past the columns
     const int col0 = (blockIdx.y * 256 + threadIdx.x) * V;
     const bool on = col0 < d_h;                                       // threads past the columns stay for the lane reads
     const int col = on ? col0 : 0;
@@ -142,8 +143,11 @@ extern "C" size_t moe_block_list_len(int T, int k, int C) {
 
 namespace {
 
-// from this many outputs on (T = 8192, d_h = 4096: 22 us with eight columns a thread, 27 with four; level at T = 512, d_h = 7168)
+// Eight columns a thread from this many outputs on (T = 8192, d_h = 4096: 22 us with eight, 27 with four; level at T = 512,
+// d_h = 7168; 6 to 16 % faster with 5 to 12 % of the requests local, 1 to 6 % slower with 30 to 60 %), where a row fills a
+// wavefront of them (T = 33000, d_h = 128, 60 % local: 42 us with eight columns and all wavefronts kept, 20 so).
 constexpr long long kCombineWide = 4 << 20;
+constexpr int kCombineWideMinCols = MOE_WAVE * 8;
 
 int combine(const float *Yp_dev, const int32_t *pos_dev, const float *topk_w_dev, const float *Ys_dev, bool shared,
             int T, int k, int d_h, int dtype, void *Y_dev, void *stream, const char *what) {
@@ -156,9 +160,9 @@ int combine(const float *Yp_dev, const int32_t *pos_dev, const float *topk_w_dev
         !moe::aligned(Ys_dev, 16) || !moe::aligned(Y_dev, dtype == MOE_DTYPE_BF16 ? 8 : 16))
         return MOE_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // eight columns a thread once that still gives every CU several workgroups; rows of d_h bf16 keep their 16-byte
-    // alignment when d_h is a multiple of 8
-    const bool wide = dtype == MOE_DTYPE_BF16 && d_h % 8 == 0 && moe::aligned(Y_dev, 16) && static_cast<long long>(T) * d_h >= kCombineWide;
+    // rows of d_h bf16 keep their 16-byte alignment when d_h is a multiple of 8
+    const bool wide = dtype == MOE_DTYPE_BF16 && d_h % 8 == 0 && d_h >= kCombineWideMinCols && moe::aligned(Y_dev, 16) &&
+                      static_cast<long long>(T) * d_h >= kCombineWide;
     const int cols = wide ? 2048 : 1024;
     const dim3 grid(T, (d_h + cols - 1) / cols);
     if (wide)

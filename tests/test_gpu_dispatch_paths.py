@@ -148,6 +148,21 @@ def test_combine_columns(T, k, d_h, dtype, shift, shared):
     assert (buf[:shift] == 77.0).all() and (buf[shift + T * d_h:] == 77.0).all()
 
 
+def test_combine_time_of_short_rows():
+    """Rows shorter than a wavefront: as many outputs take 1.3 times as long as rows of 512 columns do (more workgroups);
+    2.8 times when the wavefronts past the columns stay and the others are a quarter full."""
+    k, t = 8, {}
+    for T, d_h in ((8250, 512), (33000, 128)):
+        local = torch.rand((T, k), device="cuda") < 0.6
+        pos = torch.full((T, k), -1, dtype=torch.int32, device="cuda")
+        n = int(local.sum().item())
+        pos[local] = torch.randperm(n, device="cuda").to(torch.int32)
+        Yp, w = torch.randn((n, d_h), device="cuda"), torch.rand((T, k), device="cuda")
+        Y = torch.empty((T, d_h), dtype=torch.bfloat16, device="cuda")
+        t[d_h] = device_time(lambda: B.moe_combine(Yp, pos, w, T, k, d_h, B.MOE_DTYPE_BF16, Y))
+    assert t[128] < 2.0 * t[512], t
+
+
 @pytest.mark.parametrize("C,d_h,d_e", [(1, 32, 32), (3, 160, 96), (2, 544, 672)])
 def test_pack_weights_layout(C, d_h, d_e):
     """The packed images against their definition, for numbers of K-steps around a wavefront's four."""
