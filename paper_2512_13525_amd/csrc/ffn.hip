@@ -34,40 +34,57 @@ constexpr size_t kCtrlBytes = moe::kFfnCtrlBytes;
 // row of a tile's half h: s*rows_per_slot + h*half_stride + tile*tile_stride.
 //   W13 [C, 2*d_e, d_h] -> halves gate, up:   tile_stride 16, half_stride d_e
 //   W2  [C, d_h, d_e]   -> rows 0-15, 16-31:  tile_stride 32, half_stride 16
-// A copy: one workgroup per tile pair, a wavefront moves kPackSteps K-steps of both halves at a time (both 64-byte halves
-// of each source line, 2 KiB of contiguous stores per K-step).  At C = 17, d_h = 2048, d_e = 1408 (588 MB moved) 122 us for both
-// matrices (4.8 TB/s; a plain device copy reaches 4.95) against 134 for a flat index of 16-byte pieces taken apart with
-// 64-bit divisions, 1225 against 1537 us at C = 36, d_h = 7168, d_e = 2048.  The stores carry the streaming hint
-// (132 us without); on the loads it costs the other half of each line (147 us).
+// A copy: a wavefront moves STEPS K-steps of both halves of a tile pair (four: both 64-byte halves of each source line, 2 KiB
+// of contiguous stores per K-step); the wavefronts of a slot are dealt over its K-steps and tiles alike, so that a matrix of
+// few tiles or few K-steps still has its wavefronts everywhere.  At C = 17, d_h = 2048, d_e = 1408 (588 MB moved) 107 us for
+// both matrices (5.5 TB/s with part of the source in the last-level cache from the call before; a plain device copy reaches
+// 4.95) against 134 for a flat index of 16-byte pieces taken apart with 64-bit divisions; at C = 36, d_h = 7168, d_e = 2048
+// 1136 against 1537 us.  The stores carry the streaming hint (132 us without); on the loads it costs the other half of each
+// line (147 us).
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kPackWaves = 4;
-constexpr int kPackSteps = 4;
+template <int STEPS>
 __global__ __launch_bounds__(kPackWaves * MOE_WAVE)
-void pack_kernel(const u32x4 *__restrict__ src, u32x4 *__restrict__ dst, int tiles, int cols, int rows_per_slot,
+void pack_kernel(const u32x4 *__restrict__ src, u32x4 *__restrict__ dst, int tiles, int chunks, int cols, int rows_per_slot,
                  int tile_stride, int half_stride) {
-    const int tile = blockIdx.x, s = blockIdx.y;
+    const int s = blockIdx.y;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE), lane = moe::lane_id();
     const int KS = cols / 32;
+    const int unit = blockIdx.x * kPackWaves + wave;
+    if (unit >= tiles * chunks) return;
+    const int tile = unit / chunks, k0 = (unit - tile * chunks) * STEPS;
     const size_t row0 = static_cast<size_t>(s) * rows_per_slot + static_cast<size_t>(tile) * tile_stride + (lane & 15);
-    const u32x4 *p[2];
+    u32x4 v[STEPS][2];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) p[h] = src + (row0 + static_cast<size_t>(h) * half_stride) * (cols / 8) + (lane >> 4);
-    u32x4 *out = dst + (static_cast<size_t>(s) * tiles + tile) * KS * 2 * MOE_WAVE + lane;
-    for (int k0 = wave * kPackSteps; k0 < KS; k0 += kPackWaves * kPackSteps) {
-        u32x4 v[kPackSteps][2];
+    for (int u = 0; u < STEPS; ++u) {
+        const size_t kk = k0 + u < KS ? k0 + u : KS - 1;              // past the last K-step: that one again, not stored
 #pragma unroll
-        for (int u = 0; u < kPackSteps; ++u) {
-            const size_t kk = k0 + u < KS ? k0 + u : KS - 1;          // past the last K-step: that one again, not stored
-#pragma unroll
-            for (int h = 0; h < 2; ++h) v[u][h] = p[h][kk * 4];
-        }
-#pragma unroll
-        for (int u = 0; u < kPackSteps; ++u)
-            if (k0 + u < KS) {
-#pragma unroll
-                for (int h = 0; h < 2; ++h) __builtin_nontemporal_store(v[u][h], out + (static_cast<size_t>(k0 + u) * 2 + h) * MOE_WAVE);
-            }
+        for (int h = 0; h < 2; ++h)
+            v[u][h] = src[(row0 + static_cast<size_t>(h) * half_stride) * (cols / 8) + (lane >> 4) + kk * 4];
     }
+    u32x4 *out = dst + ((static_cast<size_t>(s) * tiles + tile) * KS + k0) * 2 * MOE_WAVE + lane;
+#pragma unroll
+    for (int u = 0; u < STEPS; ++u)
+        if (k0 + u < KS) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) __builtin_nontemporal_store(v[u][h], out + (u * 2 + h) * MOE_WAVE);
+        }
+}
+
+// Four K-steps a wavefront when that gives every SIMD four of them, else one (C = 4, d_h = 64, d_e = 4096 and the other way round
+// 5.4 us, 14 with a workgroup per tile pair; C = 1, d_h = 7168, d_e = 2048 29, 35).
+constexpr long long kPackFour = 4096;
+void launch_pack(const void *src, void *dst, int C, int tiles, int cols, int rows_per_slot, int tile_stride, int half_stride,
+                 hipStream_t st) {
+    const int KS = cols / 32, four = (KS + 3) / 4;
+    const bool wide = KS >= 4 && static_cast<long long>(C) * tiles * four >= kPackFour;
+    const int chunks = wide ? four : KS;
+    const int gx = (tiles * chunks + kPackWaves - 1) / kPackWaves;
+    const dim3 grid(gx, C), threads(kPackWaves * MOE_WAVE);
+    const auto *in = static_cast<const u32x4 *>(src);
+    auto *out = static_cast<u32x4 *>(dst);
+    if (wide) hipLaunchKernelGGL(pack_kernel<4>, grid, threads, 0, st, in, out, tiles, chunks, cols, rows_per_slot, tile_stride, half_stride);
+    else hipLaunchKernelGGL(pack_kernel<1>, grid, threads, 0, st, in, out, tiles, chunks, cols, rows_per_slot, tile_stride, half_stride);
 }
 
 __global__ void fill_zero_kernel(int *p, int n) {
@@ -187,10 +204,8 @@ extern "C" int moe_pack_weights_bf16(const void *W13_dev, const void *W2_dev, in
         !moe::aligned(W2_packed_dev, 16))
         return MOE_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    hipLaunchKernelGGL(pack_kernel, dim3(d_e / 16, C), dim3(kPackWaves * MOE_WAVE), 0, st, static_cast<const u32x4 *>(W13_dev),
-                       static_cast<u32x4 *>(W13_packed_dev), d_e / 16, d_h, 2 * d_e, 16, d_e);
-    hipLaunchKernelGGL(pack_kernel, dim3(d_h / 32, C), dim3(kPackWaves * MOE_WAVE), 0, st, static_cast<const u32x4 *>(W2_dev),
-                       static_cast<u32x4 *>(W2_packed_dev), d_h / 32, d_e, d_h, 32, 16);
+    launch_pack(W13_dev, W13_packed_dev, C, d_e / 16, d_h, 2 * d_e, 16, d_e, st);
+    launch_pack(W2_dev, W2_packed_dev, C, d_h / 32, d_e, d_h, 32, 16, st);
     return moe::check_launch("moe_pack_weights_bf16");
 }
 

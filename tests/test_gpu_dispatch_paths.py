@@ -163,9 +163,10 @@ def test_combine_time_of_short_rows():
     assert t[128] < 2.0 * t[512], t
 
 
-@pytest.mark.parametrize("C,d_h,d_e", [(1, 32, 32), (3, 160, 96), (2, 544, 672)])
+@pytest.mark.parametrize("C,d_h,d_e", [(1, 32, 32), (3, 160, 96), (2, 544, 672), (64, 160, 1024), (64, 1056, 224)])
 def test_pack_weights_layout(C, d_h, d_e):
-    """The packed images against their definition, for numbers of K-steps around a wavefront's four."""
+    """The packed images against their definition, for numbers of K-steps around a wavefront's four, with one step and with
+    four a wavefront."""
     W13 = torch.arange(C * 2 * d_e * d_h, dtype=torch.int32, device="cuda").to(torch.int16).view(C, 2 * d_e, d_h)
     W2 = torch.arange(C * d_h * d_e, dtype=torch.int32, device="cuda").mul_(7).to(torch.int16).view(C, d_h, d_e)
     p13, p2 = torch.zeros_like(W13), torch.zeros_like(W2)
@@ -267,3 +268,15 @@ def test_schedule_batched_two_workgroups_a_cu(E, n_inst, C):
         load = torch.empty((n, n_inst), dtype=torch.int32, device="cuda")
         t[n] = device_time(lambda: B.moe_schedule_batched(pl, ids, n, 16, 8, rid, rep, load))
     assert t[512] < 1.4 * t[256], t
+
+
+@pytest.mark.parametrize("d_h,d_e", [(64, 4096), (4096, 64)])
+def test_pack_time_of_few_tiles(d_h, d_e):
+    """Matrices of few tiles or few K-steps take as long to pack as square ones of their size (2.6 times when a tile pair is
+    one workgroup's)."""
+    C, t = 4, []
+    for a, b in ((512, 512), (d_h, d_e)):
+        W13, W2 = (torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_() for shape in ((C, 2 * b, a), (C, a, b)))
+        p13, p2 = torch.empty_like(W13), torch.empty_like(W2)
+        t.append(device_time(lambda: B.moe_pack_weights_bf16(W13, W2, C, a, b, p13, p2)))
+    assert t[1] < 1.6 * t[0], t
