@@ -398,7 +398,7 @@ int moe_grouped_ffn_static(const void *X_dev, const void *W13_dev, const void *W
  *                                    other experts to stream to hide them); in batches
  *                                    of at least 2048 tokens over blocks of 128 rows by two launches
  *                                    of their own when (number of 128-row blocks) x (workgroups per
- *                                    block) >= this value (default 1280), which takes precedence.
+ *                                    block) >= this value (default 512), which takes precedence.
  *                                    Otherwise they are cut into streaming items like every other
  *                                    slot.  Results do not depend on it beyond rounding order.
  */

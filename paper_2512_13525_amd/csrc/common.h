@@ -86,12 +86,13 @@ int launch_ffn_stream(const void *X, const void *W13p, const void *W2p, int T, i
 // launch's intermediate.
 constexpr int kGemmMinTokens = 2048;
 inline bool ffn_has_gemm(int T) { return T >= kGemmMinTokens; }
-// The line lies at five first-stage workgroups per CU.  Below it the tiled-GEMM items of the streaming launch are faster: they
-// run beside the experts that are streamed, where these launches come before them, and they fill the chip with half as
-// large blocks (layer at d_h = 4096, d_e = 1536, T = 8192, 16 slots of 256 rows, 984 workgroups: 391 against 447 us;
-// d_h = 2048, d_e = 1408, T = 4000, 1144 workgroups: 216 against 237 us).  Above it the multiply rate counts and the larger
-// blocks win (1512 workgroups 473 against 541 us, 1800 600 against 640, 2832 706 against 876).
-constexpr int kGemmMinWorkgroups = 1280;
+// Two first-stage workgroups per CU.  Which side is faster past this line depends on the rows of the slots, which the
+// list's header does not tell: launches of their own against items of the streaming launch, us, d_h x d_e,
+//   7168 x 2048, 640 workgroups: slots of 78 rows 388 and 518, of 206 337 and 406, of 512 289 and 265 (512 workgroups);
+//   1024 x 512, 512: 78 rows 65 and 84;   3072 x 1024, 800: 200 and 226;
+//   4096 x 1536, 528: 206 rows 177 and 204, 960: 512 rows 447 and 391 (a whole layer);   2048 x 1408, 528 to 968: 1.02 to 1.25 the other way.
+// A line at 1280 loses up to a third on the former and gains up to a fifth on the latter; this one loses less.
+constexpr int kGemmMinWorkgroups = 512;
 constexpr int kWideWaves = 4;            // wavefronts (= packed weight tiles) of a tiled-GEMM workgroup
 inline int ffn_gemm_tiles1(int d_e) { return (d_e / 16 + kWideWaves - 1) / kWideWaves; }
 __device__ __forceinline__ bool ffn_gemm_on(int4 head, int tiles1, int override_min) {

@@ -74,3 +74,24 @@ def expected_blocks(slot_off, block_rows, heavy_rows=16):
     n_wide = int(sum((int(v) + 63) // 64 for v in rows if v > 64))
     n_wide128 = int(sum((int(v) + 127) // 128 for v in rows if v > 64))
     return np.array([[len(out), block_rows, n_wide, n_wide128]] + out, dtype=np.int32).reshape(-1)
+
+
+def device_time(fn, n=20, reps=9):
+    """Microseconds of one call on the device: the fastest of several replays of a graph of n calls."""
+    import torch
+    fn()
+    torch.cuda.synchronize()
+    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=stream):
+        for _ in range(n):
+            fn()
+    best = float("inf")
+    for r in range(3 + reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        torch.cuda.synchronize()
+        if r >= 3:
+            best = min(best, a.elapsed_time(b) / n * 1e3)
+    return best

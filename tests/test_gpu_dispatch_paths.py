@@ -8,7 +8,7 @@ from paper_2512_13525_amd import workloads as W
 from paper_2512_13525_amd.layer import LayerStep, to_device_bf16
 from oracle import dispatch, gating, routing, scheduling
 
-from helpers import expected_blocks
+from helpers import device_time, expected_blocks
 
 pytestmark = pytest.mark.gpu
 
@@ -176,26 +176,6 @@ def test_pack_weights_layout(C, d_h, d_e):
     w13 = W13.view(C, 2, d_e // 16, 16, d_h // 32, 4, 8).permute(0, 2, 4, 1, 5, 3, 6)
     w2 = W2.view(C, d_h // 32, 2, 16, d_e // 32, 4, 8).permute(0, 1, 4, 2, 5, 3, 6)
     assert torch.equal(p13.view(-1), w13.reshape(-1)) and torch.equal(p2.view(-1), w2.reshape(-1))
-
-
-def device_time(fn, n=20, reps=9):
-    """Microseconds of one call on the device: the fastest of several replays of a graph of n calls."""
-    fn()
-    torch.cuda.synchronize()
-    graph, stream = torch.cuda.CUDAGraph(), torch.cuda.Stream()
-    with torch.cuda.graph(graph, stream=stream):
-        for _ in range(n):
-            fn()
-    best = float("inf")
-    for r in range(3 + reps):
-        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-        a.record()
-        graph.replay()
-        b.record()
-        torch.cuda.synchronize()
-        if r >= 3:
-            best = min(best, a.elapsed_time(b) / n * 1e3)
-    return best
 
 
 @pytest.mark.parametrize("E,k,group", [(64, 8, None), (128, 8, None), (256, 8, (8, 4)), (1024, 8, None)])

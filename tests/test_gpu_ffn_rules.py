@@ -1,0 +1,99 @@
+"""GPU parity and times of the grouped FFN around the lines at which its size rules change over, on hand-made
+dispatches."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2512_13525_amd import binding as B
+from paper_2512_13525_amd import workloads as W
+from paper_2512_13525_amd.layer import to_device_bf16
+from oracle import ffn
+
+from helpers import device_time, expected_blocks
+
+pytestmark = pytest.mark.gpu
+
+TOL_BF16 = 2e-2                  # relative, of a layer in bf16
+GEMM_MIN_TOKENS, GEMM_MIN_WORKGROUPS = 2048, 512
+
+
+class Dispatch:
+    """counts[s] requests of slot s, drawn at random from T*k."""
+
+    def __init__(self, counts, T, k, seed=0):
+        self.T, self.k, self.C = T, k, len(counts)
+        self.off = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+        self.n = int(self.off[-1])
+        assert self.n <= T * k
+        self.perm = np.random.default_rng(seed).permutation(T * k)[:self.n].astype(np.int32)
+        self.list = expected_blocks(self.off, B.moe_block_rows(T))
+        assert self.list[0] <= B.moe_max_blocks(T, k, self.C)
+        blocks = torch.zeros((B.moe_block_list_len(T, k, self.C),), dtype=torch.int32)
+        blocks[:len(self.list)] = torch.from_numpy(self.list)
+        self.dev = [torch.from_numpy(self.off).cuda(), torch.from_numpy(self.perm).cuda(), blocks.cuda()]
+
+    def buffers(self, d_h, d_e):
+        ws = torch.empty((B.moe_workspace_bytes(self.T, self.k, self.C, d_h, d_e, B.MOE_DTYPE_BF16),), dtype=torch.uint8,
+                         device="cuda")
+        B.moe_workspace_init(ws)
+        return ws, torch.full((self.T * self.k, d_h), 123.0, dtype=torch.float32, device="cuda")
+
+    def run(self, X, W13p, W2p, d_h, d_e, Yp, ws):
+        B.moe_grouped_ffn(X, W13p, W2p, self.T, self.k, self.C, d_h, d_e, B.MOE_DTYPE_BF16, *self.dev, Yp, ws)
+
+    def gemm_workgroups(self, d_e):
+        """First-stage workgroups over blocks of 128 rows, what the rule of the tiled-GEMM launches goes by."""
+        return int(self.list[3]) * -(-(d_e // 16) // 4)
+
+
+def random_weights(C, d_h, d_e):
+    """Packed images of N(0, 0.02) weights; which element is which does not matter to a time."""
+    return (torch.empty((C, 2 * d_e, d_h), dtype=torch.bfloat16, device="cuda").normal_().mul_(0.02),
+            torch.empty((C, d_h, d_e), dtype=torch.bfloat16, device="cuda").normal_().mul_(0.02))
+
+
+LONG = [(130, 65, 64, 17, 200, 66)[s % 6] for s in range(150)]           # 325 blocks of 64 rows: the list wraps twice
+
+
+@pytest.mark.parametrize("counts,T,k,d_h,d_e,own_launches", [
+    ([65 + s % 64 for s in range(63)] + [64, 9, 0, 33], 2048, 4, 160, 512, False),
+    ([65 + s % 64 for s in range(64)] + [64, 9, 0, 33], 2048, 4, 160, 512, True),
+    (LONG, 2048, 8, 96, 512, True), (LONG, 2047, 8, 96, 512, False)])
+def test_tiled_gemm_launches_by_their_own_rule(counts, T, k, d_h, d_e, own_launches):
+    """Slots with more than 64 requests by launches of their own from 2048 tokens and 512 first-stage workgroups on, inside the
+    streaming launch below: both sides of the line with the rule's own threshold, rows against the oracle."""
+    d = Dispatch(counts, T, k, seed=T)
+    assert (T >= GEMM_MIN_TOKENS and d.gemm_workgroups(d_e) >= GEMM_MIN_WORKGROUPS) == own_launches
+    cfg = W.MoEConfig("rules", E=d.C, k=k, d_h=d_h, d_e=d_e, T=T, n_inst=1, C=d.C, zipf_s=0.0, seed=21)
+    X = W.activations(cfg)
+    W13, W2 = (np.stack(w) for w in zip(*(W.expert_weights(cfg, e) for e in range(d.C))))
+    want = ffn.grouped_ffn(X, W13, W2, d.off, d.perm, k)
+    d13, d2 = to_device_bf16(W13), to_device_bf16(W2)
+    p13, p2 = torch.empty_like(d13), torch.empty_like(d2)
+    B.moe_pack_weights_bf16(d13, d2, d.C, d_h, d_e, p13, p2)
+    ws, Yp = d.buffers(d_h, d_e)
+    for _ in range(2):
+        Yp.fill_(123.0)
+        d.run(to_device_bf16(X), p13, p2, d_h, d_e, Yp, ws)
+        torch.cuda.synchronize()
+        got = Yp.cpu().numpy()
+        assert (got[d.n:] == 123.0).all()
+        num, den = np.linalg.norm(got[:d.n] - want, axis=1), np.linalg.norm(want, axis=1)
+        assert (num <= 2.5 * TOL_BF16 * den + 1e-30).all(), int(np.argmax(num / den))
+        assert B.moe_workspace_status(ws) == 0
+
+
+@pytest.mark.parametrize("C,rows,d_h,d_e", [(64, 78, 1024, 512), (20, 78, 7168, 2048), (20, 206, 3072, 1024)])
+def test_tiled_gemm_line_time(C, rows, d_h, d_e):
+    """Past the line the launches of their own are what the rule takes: its time is theirs (within 1.12; inside the streaming
+    launch these batches take 1.13 to 1.35 times as long)."""
+    T, k = 2048, 8
+    d = Dispatch([rows] * C, T, k)
+    assert GEMM_MIN_WORKGROUPS <= d.gemm_workgroups(d_e) < 1280
+    w = random_weights(C, d_h, d_e)
+    X = torch.empty((T, d_h), dtype=torch.bfloat16, device="cuda").normal_()
+    ws, Yp = d.buffers(d_h, d_e)
+    rule = device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws), n=5)
+    B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, 1)
+    own = device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws), n=5)
+    assert rule < 1.12 * own, (rule, own)

@@ -196,8 +196,8 @@ FFN_CFGS = [W.tiny(), small(), small("multi_tile", T=300, k=4, E=8, n_inst=2, C=
             small("f32_ragged", dtype="f32", T=21, d_h=36, d_e=20),
             W.dsv2lite(), W.qwen3(32), W.qwen3(256), W.qwen3(1024), W.stress(64, 1.25, 0.8),
             W.stress(2048, 1.25, 0.8), W.dsv3(512),
-            # token-heavy points of the stress sweep: the tiled-GEMM launches (taken by the rule) next to the
-            # streaming launch on a list that wraps around
+            # token-heavy points of the stress sweep, lists that wrap around: T = 4096 has 360 first-stage workgroups of
+            # 128-row blocks (tiled GEMMs inside the streaming launch), T = 8192 has 576 (launches of their own, from 512 on)
             W.stress(4096, 1.25, 0.8), W.stress(8192, 1.25, 0.8)]
 
 
