@@ -90,8 +90,9 @@ __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
 // streaming hint (STREAM), so that on their way through an L2 they do not push out the token rows,
 // which every tile of a block reads again (7 MB of rows against a 4 MB L2 at d_h = 7168, T = 512:
 // 237 -> 227 us for that launch).  The blocks of a slot with several share their tiles through L2
-// and keep the plain loads (with the hint on those too, all-slot batches of 128 to 512 tokens
-// were 20 % slower).
+// and keep the plain loads, the last, partly filled one too (with the hint on those all-slot batches of 128 to 512 tokens
+// were 20 % slower; with it on the last block alone, slots of 36 to 60 rows at d_h = 2048, d_e = 768 43 us, 33 without,
+// 47.7 and 42.6 with the weights out of the caches).
 template <bool STREAM>
 __device__ __forceinline__ bf16x8 load_weights(const char *p) {
     if constexpr (STREAM) return __builtin_nontemporal_load(reinterpret_cast<const bf16x8 *>(p));
@@ -767,10 +768,11 @@ __device__ __forceinline__ void run_item(const StreamArgs &a, const StageArgs &g
     const char *w = g.Wp + (static_cast<size_t>(slot) * g.tiles + tile) * g.KS * 2048;
     const int m = hi - row0;
     const bool single = m <= TT * 16 && row0 == ent.w;                  // the slot's only block
-    // Loads of a slot's only block carry the streaming hint; the full blocks of a slot with several do not (a slot's
-    // last, partly filled block shares the code of the single blocks: fewer instructions to fetch).
+    // Loads of a slot's only block carry the streaming hint, those of a slot with several do not (load_weights): its last,
+    // partly filled block is computed with its row tiles rounded up to a power of two, to keep the instructions few.
     if constexpr (!STAGE1) {
-        const int nt = ((m < TT * 16 ? m : TT * 16) + 15) >> 4;          // 16-row token tiles that hold requests
+        int nt = ((m < TT * 16 ? m : TT * 16) + 15) >> 4;                // 16-row token tiles that hold requests
+        if (TT == 4 && !single) nt = nt <= 2 ? 2 : 4;
         constexpr int U = EVEN ? 2 : 1;
         const size_t tile_bytes = static_cast<size_t>(g.KS) * 2048;
         // 64-row launch: blocks of up to 32 rows multiply both tiles of the pair at once, larger ones one after the other
@@ -786,15 +788,15 @@ __device__ __forceinline__ void run_item(const StreamArgs &a, const StageArgs &g
             bool ok;
 #define MOE_DOWN(NT, U_, NW, STREAM) stream_item_down<NT, TT, U_, STREAM, NW>(a, g, lds, s_ok, w_, two ? tile_bytes : 0, item, t, n_readers, wave, lane)
             if constexpr (TT == 2) {
-                if (nt == 1) ok = MOE_DOWN(1, U, 1, true);
-                else if (single) ok = MOE_DOWN(2, U, 1, true);
-                else ok = MOE_DOWN(2, U, 1, false);
-            } else {
+                if (single) ok = nt == 1 ? MOE_DOWN(1, U, 1, true) : MOE_DOWN(2, U, 1, true);
+                else ok = nt == 1 ? MOE_DOWN(1, U, 1, false) : MOE_DOWN(2, U, 1, false);
+            } else if (single) {
                 if (nt == 1) ok = MOE_DOWN(1, U, 2, true);
                 else if (nt == 2) ok = MOE_DOWN(2, U, 2, true);
                 else if (nt == 3) ok = MOE_DOWN(3, 1, 1, true);
-                else if (single) ok = MOE_DOWN(4, 1, 1, true);
-                else ok = MOE_DOWN(4, 1, 1, false);
+                else ok = MOE_DOWN(4, 1, 1, true);
+            } else {
+                ok = nt == 2 ? MOE_DOWN(2, U, 2, false) : MOE_DOWN(4, 1, 1, false);
             }
 #undef MOE_DOWN
             const int nw = paired && two ? 2 : 1;                        // tiles to store
@@ -806,14 +808,16 @@ __device__ __forceinline__ void run_item(const StreamArgs &a, const StageArgs &g
             }
         }
     } else {
-        const int halves = ((m < TT * 16 ? m : TT * 16) + 7) >> 3;       // 8-row halves that hold requests
-#define MOE_CASE(NH) case NH: stream_item_lines<NH, TT, true, EVEN>(a, g, lds, w, tile, row0, hi, wave, lane); break;
-        if (halves == 2 * TT && !single) {
-            stream_item_lines<2 * TT, TT, false, EVEN>(a, g, lds, w, tile, row0, hi, wave, lane);
-        } else if constexpr (TT == 2) {
-            switch (halves) { MOE_CASE(1) MOE_CASE(2) MOE_CASE(3) MOE_CASE(4) }
+        int halves = ((m < TT * 16 ? m : TT * 16) + 7) >> 3;             // 8-row halves that hold requests
+        if (!single) halves = halves <= 2 ? 2 : halves <= 4 ? 4 : 8;
+#define MOE_CASE(NH, STREAM) case NH: stream_item_lines<NH, TT, STREAM, EVEN>(a, g, lds, w, tile, row0, hi, wave, lane); break;
+        if constexpr (TT == 2) {
+            if (single) switch (halves) { MOE_CASE(1, true) MOE_CASE(2, true) MOE_CASE(3, true) MOE_CASE(4, true) }
+            else switch (halves) { MOE_CASE(2, false) MOE_CASE(4, false) }
         } else {
-            switch (halves) { MOE_CASE(1) MOE_CASE(2) MOE_CASE(3) MOE_CASE(4) MOE_CASE(5) MOE_CASE(6) MOE_CASE(7) MOE_CASE(8) }
+            if (single) switch (halves) { MOE_CASE(1, true) MOE_CASE(2, true) MOE_CASE(3, true) MOE_CASE(4, true)
+                                          MOE_CASE(5, true) MOE_CASE(6, true) MOE_CASE(7, true) MOE_CASE(8, true) }
+            else switch (halves) { MOE_CASE(2, false) MOE_CASE(4, false) MOE_CASE(8, false) }
         }
 #undef MOE_CASE
         __syncthreads();

@@ -97,3 +97,18 @@ def test_tiled_gemm_line_time(C, rows, d_h, d_e):
     B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, 1)
     own = device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws), n=5)
     assert rule < 1.12 * own, (rule, own)
+
+
+@pytest.mark.parametrize("rows", [36, 48])
+def test_partly_filled_last_block_time(rows):
+    """Slots of one full block of 32 rows and a part of another share their tiles through L2 like slots of two full blocks: no
+    slower than those (1.1 allowed; with the streaming hint on the last block's loads 1.25 times as long)."""
+    T, k, C, d_h, d_e = 136, 8, 17, 2048, 768
+    w = random_weights(C, d_h, d_e)
+    X = torch.empty((T, d_h), dtype=torch.bfloat16, device="cuda").normal_()
+    t = {}
+    for m in (64, rows):
+        d = Dispatch([m] * C, T, k)
+        ws, Yp = d.buffers(d_h, d_e)
+        t[m] = device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws))
+    assert t[rows] < 1.1 * t[64], t
