@@ -112,3 +112,18 @@ def test_partly_filled_last_block_time(rows):
         ws, Yp = d.buffers(d_h, d_e)
         t[m] = device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws))
     assert t[rows] < 1.1 * t[64], t
+
+
+def test_short_list_of_a_batch_that_could_have_a_long_one_time():
+    """The same slots in a batch whose list could be longer than the workgroups' own blocks (128) take little longer (1.04
+    times, token rows spread over more tokens; 1.14 when they run through the loop that walks long lists)."""
+    C, rows, k, d_h, d_e = 36, 100, 8, 7168, 2048
+    w = random_weights(C, d_h, d_e)
+    t = {}
+    for T in (600, 1500):
+        d = Dispatch([rows] * C, T, k)
+        assert d.list[0] <= 128 and (B.moe_max_blocks(T, k, C) > 128) == (T == 1500)
+        X = torch.empty((T, d_h), dtype=torch.bfloat16, device="cuda").normal_()
+        ws, Yp = d.buffers(d_h, d_e)
+        t[T] = device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws), n=5)
+    assert t[1500] < 1.09 * t[600], t
