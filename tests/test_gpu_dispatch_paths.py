@@ -37,11 +37,13 @@ def test_selection_with_equal_logits(E, k, group):
     np.testing.assert_allclose(d_w.cpu().numpy(), w, rtol=1e-5, atol=1e-30)
 
 
-@pytest.mark.parametrize("n_inst,C,E", [(3, 9, 21), (16, 5, 64), (20, 4, 60), (40, 30, 1000)])
-@pytest.mark.parametrize("T", [1, 16, 17, 600, 4107])
+@pytest.mark.parametrize("n_inst,C,E", [(3, 9, 21), (16, 5, 64), (20, 4, 60), (40, 30, 1000), (3, 80, 210)])
+@pytest.mark.parametrize("T", [1, 8, 9, 12, 13, 16, 17, 146, 147, 292, 293, 585, 586, 600, 1170, 1171, 4107])
 def test_front_sizes(n_inst, C, E, T):
-    """One workgroup (up to 16 tokens) and several; up to 16 instances and more; 1, 2 and 4 groups of 64 requests
-    per wavefront, the chunked tail with two tokens a wavefront; a table too large for LDS.  Against the oracle, twice on the same sync words."""
+    """One workgroup (up to 12 tokens, 8 at E = 1000) and several; up to 16 instances and more; 1, 2, 4 and 8 groups of 64
+    requests per wavefront (k = 7: the tokens lie on both sides of 1024, 2048, 4096 and 8192 requests), up to 64 slots and
+    more; the chunked tail with one token and with two a wavefront; a table too large for LDS.  Against the oracle, twice on
+    the same sync words."""
     k = 7
     cfg = W.MoEConfig("front", E=E, k=k, d_h=32, d_e=32, T=T, n_inst=n_inst, C=C, zipf_s=1.0, seed=T)
     lay = W.build_placement(cfg)
