@@ -86,7 +86,7 @@ def main() -> None:
                          "activated set with an even and a Zipf split of the requests; batch_sweep: layer "
                          "us vs batch size with every slot activated; amax: Monte-Carlo a_max of AEBS and the "
                          "baseline policies over sampled batches, against the exact optimum and Eq. 5; gate: the front "
-                         "launch with and without the router's linear layer in it; placement: a_max of AEBS over the "
+                         "with and without the router's linear layer before it; placement: a_max of AEBS over the "
                          "layout of Alg. 3 (Appendix B) against the contiguous layout on traces with topics; scaling: "
                          "Alg. 2 fed with the measured MoE-side coefficients and a_max table; shared: the step with a "
                          "shared expert run on the instance; graph: the step queued eagerly against the same steps "
@@ -641,8 +641,8 @@ def sched_sweep(args) -> None:
 
 
 def gate_front(args) -> None:
-    """The front of the step with the router's linear layer inside the launch (Sec. 3.3: the gate
-    runs on the MoE side): us per launch of logits -> a0-a4 (moe_route_schedule_permute), of
+    """The front of the step with the router's linear layer before it (Sec. 3.3: the gate
+    runs on the MoE side): us per call of logits -> a0-a4 (moe_route_schedule_permute), of
     X, W_r -> selection (moe_gate_route) and of X, W_r -> a0-a4 (moe_gate_route_schedule_permute),
     one JSON line per workload.  Inputs rotate over 8 batches."""
     import torch

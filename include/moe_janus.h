@@ -275,11 +275,17 @@ int moe_scaling_solve(const moe_scaling_model *m, const double *amax_table_host,
  *   X_dev      [T, d_h] bf16, row-major, 16-byte aligned
  *   Wr_dev     [E, d_h] bf16, row-major (one row per logical expert), 16-byte aligned
  *   bias_dev   [E] float, or NULL
- *   logits_dev [T, E] float, OUTPUT (the selection reads it back inside the launch)
- *   sync_dev   moe_gate_sync_len(T) int32, zero before the first call; every call leaves them
- *              zero.  Calls that share sync_dev must not overlap in time.
+ *   logits_dev [T, E] float, OUTPUT (the second launch reads it)
+ *   sync_dev   moe_gate_sync_len(T) int32, zero before the first call.
+ *              moe_gate_route_schedule_permute uses the first word and leaves it zero; the others,
+ *              and all of them in moe_gate_route, are not used.  Calls that share sync_dev must not
+ *              overlap in time.
+ * moe_gate_route_schedule_permute runs Alg. 1 and the sort in one workgroup for every batch: above
+ * 8192 requests (or 8192 (expert, instance) pairs) the chunked launches of moe_route_schedule_permute
+ * on the logits of moe_gate_route are faster.
  * Needs d_h % 32 == 0 (MOE_ESHAPE otherwise).  The sum over c is taken in a fixed order
- * (16 contiguous shares of the hidden dimension, added in ascending order), so results are
+ * (16 shares of the hidden dimension, added in ascending order: share w holds the 64-column steps
+ * w, w + 16, ... when d_h is a multiple of 64, else a contiguous run of 32-column steps), so results are
  * reproducible; it is not the order of a sequential dot product, so a logit can differ from one
  * in the last bits and a selection between logits closer than that can differ too.
  */

@@ -16,12 +16,6 @@ __device__ __forceinline__ uint64_t readlane_u64(uint64_t v, int l) {
     return (static_cast<uint64_t>(hi) << 32) | lo;
 }
 
-__device__ __forceinline__ uint64_t readfirstlane_u64(uint64_t v) {
-    const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<int>(v & 0xffffffffu));
-    const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32));
-    return (static_cast<uint64_t>(hi) << 32) | lo;
-}
-
 // ------------------------------------------------------------------ a0: one token per wavefront
 // Largest unsigned key of the wavefront, as a scalar.  Data-parallel-primitive moves instead of LDS-crossbar
 // shuffles (the k selection rounds of a token are a chain of these): two exchanges inside quads, two
@@ -337,8 +331,7 @@ __device__ __forceinline__ int load_id(const int32_t *p, bool coherent) {
 //                     experts are popcounts of (ballot & per-instance mask); lane g holds load[g]
 //                     in a register.  Multi-replica experts are walked in ascending id by peeling
 //                     bits off (ballot & multi-replica mask); the arg-min over the expert's hosts
-//                     reads the candidate lanes' loads with scalar-indexed lane reads, so one greedy
-//                     step costs a few scalar instructions per host;
+//                     is a minimum of (load, instance) over the lanes, in the vector registers;
 //   Step 3 (rewrite)  every thread maps its share of requests through actRep held in LDS.
 // The layout tables are staged into LDS first.  ids_coherent: the ids were written by other
 // workgroups of the same launch.  rid and act_rep may be null (the batched launch of the a_max

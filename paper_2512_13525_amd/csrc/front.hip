@@ -174,8 +174,8 @@ __device__ __forceinline__ void gate_acc_lines(const GateArgs &a, int t0, int j,
 template <int TT, bool LINES>
 __global__ __launch_bounds__(kGateWaves * MOE_WAVE)
 void gate_kernel(GateArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[kGateWaves * (2 + 2 * TT) * 1024];
-    static_assert(TT <= 2, "the partial tiles must fit in the staging tiles");
+    // staging tiles of the line form, then the partial tiles
+    __shared__ __attribute__((aligned(16))) char lds[kGateWaves * (LINES ? 2 + 2 * TT : TT) * 1024];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE), lane = moe::lane_id();
     const int r = blockIdx.x / 8, xcd = blockIdx.x % 8, eh = (a.e_tiles + 1) / 2;
     const int tg = xcd % 4 + 4 * (r / eh), j = r % eh + (xcd / 4) * eh;
