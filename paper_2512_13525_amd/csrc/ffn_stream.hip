@@ -219,7 +219,7 @@ __device__ __forceinline__ void store_nan_rows(const StreamArgs &a, const StageA
 // One stage-1 item.  A super-step is two K-steps = 64 columns = one 128-byte line of every token row (with an odd
 // number of K-steps, hidden sizes that are multiples of 32 but not of 64, two halves of one for every other row: still a
 // quarter of the requests of reading 16 bytes per lane straight into the MFMA layout: 52 -> 46 us for the launch at
-// d_h = 2016, d_e = 1056, T = 203).
+// d_h = 2016, d_e = 1056, T = 203; a layer whose weights stay in the last-level cache loses at 16 to 32 rows a slot, 36 -> 39).
 // A token load instruction fetches whole lines (lane l: row l/8, 16-byte chunk l%8), so no line
 // is requested twice and none by halves; the MFMA layout (lane l: row l%16, 16-byte chunk 4*step + l/16) is produced by a
 // round trip through a wave-private 2 KiB LDS tile per 16 rows (chunks XOR-swizzled by row so
@@ -735,6 +735,8 @@ __device__ __forceinline__ void run_wide(const StreamArgs &a, const StageArgs &g
     const int row0 = lo + b * WR;
     const int m = hi - row0 < WR ? hi - row0 : WR;
     const int rt = (m + 15) >> 4;
+    // up to 16 rows as two row tiles (one kind of item less; slots of 72 rows: 58 -> 61 us at d_h = 2048, d_e = 768, 173 -> 163 at
+    // d_h = 4096, d_e = 1536)
     if (rt <= 2) wide_item<STAGE1, 2>(a, g, lds, s_ok, item, group, groups, slot, row0, m);
     else wide_item<STAGE1, 4>(a, g, lds, s_ok, item, group, groups, slot, row0, m);
 }
