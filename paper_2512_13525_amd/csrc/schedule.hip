@@ -7,20 +7,17 @@ namespace {
 using moe::SchedTables;
 constexpr int kSchedThreads = moe::kFrontThreads;
 
-template <int W>
-constexpr int kGroup = W < 4 ? W : 4;                    // words that aebs_select_wave reads at once
-
 // One workgroup per batch (blockIdx.x): batch b reads ids + b*n_pairs and writes rid + b*n_pairs,
 // act_rep + b*E, load_out + b*n_inst.  The single-batch call is a grid of one.
-// W: 64-expert words the selection is compiled for (n_words <= W).
-template <int W>
-__global__ __launch_bounds__(kSchedThreads, 8)           // 8 wavefronts a SIMD: two workgroups a CU
+// W: 64-expert words the selection is compiled for (n_words <= W); G: words it reads at once.
+template <int W, int G>
+__global__ __launch_bounds__(kSchedThreads, G <= 4 ? 8 : 4)           // 8 wavefronts a SIMD: two workgroups a CU
 void aebs_kernel(SchedTables tb, int E, int n_inst, int C, int n_words,
                  const int32_t *__restrict__ ids, int n_pairs, int vec_ok,
                  int32_t *__restrict__ rid, int32_t *__restrict__ act_rep, int32_t *__restrict__ load_out) {
     __shared__ moe::SchedShared sh;
     const size_t b = blockIdx.x;
-    moe::aebs_block<W, kGroup<W>>(tb, sh, E, n_inst, C, n_words, ids + b * n_pairs, n_pairs, vec_ok, false,
+    moe::aebs_block<W, G>(tb, sh, E, n_inst, C, n_words, ids + b * n_pairs, n_pairs, vec_ok, false,
                     rid ? rid + b * n_pairs : nullptr, act_rep ? act_rep + b * E : nullptr, load_out + b * n_inst);
 }
 
@@ -66,7 +63,7 @@ void aebs_loads_kernel(SchedTables tb, int E, int n_inst, int n_words, const int
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         const auto no_rep = [](int, int) { return -1; };
-        const int load = moe::aebs_select_wave<W, kGroup<W>>(flag, host_mask, multi_mask, single_mask, E, n_inst, n_words, lane,
+        const int load = moe::aebs_select_wave<W, W < 4 ? W : 4>(flag, host_mask, multi_mask, single_mask, E, n_inst, n_words, lane,
                                                   no_rep, static_cast<int32_t *>(nullptr), static_cast<int32_t *>(nullptr));
         if (lane < n_inst) load_out[static_cast<size_t>(b) * n_inst + lane] = load;
         __builtin_amdgcn_wave_barrier();
@@ -113,12 +110,16 @@ void baseline_kernel(const uint64_t *__restrict__ host_mask, const int16_t *__re
 void launch_aebs(const moe_placement_t *pl, int n_batches, const int32_t *ids, int n_pairs, int vec_ok, int32_t *rid,
                  int32_t *act_rep, int32_t *load, hipStream_t st) {
     const SchedTables tb{pl->host_mask_d, pl->slot_of_d, pl->single_rid_d, pl->multi_mask_d, pl->single_mask_d};
-#define MOE_AEBS(W) hipLaunchKernelGGL(aebs_kernel<W>, dim3(n_batches), dim3(kSchedThreads), 0, st, tb, pl->E, pl->n_inst, pl->C, \
-                                       pl->n_words, ids, n_pairs, vec_ok, rid, act_rep, load)
-    if (pl->n_words <= 1) MOE_AEBS(1);
-    else if (pl->n_words <= 2) MOE_AEBS(2);
-    else if (pl->n_words <= 4) MOE_AEBS(4);
-    else MOE_AEBS(16);                                   // more than four words: groups of four, the same code for all
+#define MOE_AEBS(W, G) hipLaunchKernelGGL((aebs_kernel<W, G>), dim3(n_batches), dim3(kSchedThreads), 0, st, tb, pl->E, pl->n_inst, \
+                                          pl->C, pl->n_words, ids, n_pairs, vec_ok, rid, act_rep, load)
+    // more than four words: all at once takes a workgroup 68 to 128 registers, so only where one workgroup has a CU to itself
+    // (E = 312, k = 4, one batch of 11 tokens: 3.8 us, 4.5 in groups of four; E = 1024, 512 batches: 11.6 and 8.6)
+    if (pl->n_words <= 1) MOE_AEBS(1, 1);
+    else if (pl->n_words <= 2) MOE_AEBS(2, 2);
+    else if (pl->n_words <= 4) MOE_AEBS(4, 4);
+    else if (n_batches > 256) MOE_AEBS(16, 4);
+    else if (pl->n_words <= 8) MOE_AEBS(8, 8);
+    else MOE_AEBS(16, 16);
 #undef MOE_AEBS
 }
 
