@@ -694,13 +694,21 @@ __device__ __forceinline__ void scatter_chunk(PermShared &sh, int *__restrict__ 
     const int lane = tid % MOE_WAVE;
     for (int i = tid; i < kFrontWaves * MOE_MAX_SLOTS; i += kFrontThreads) (&sh.cnt[0][0])[i] = 0;
     // slot totals over all chunks, and the requests of the chunks before this one
+    // (front with 5, 8 and 32 chunks 17.5, 19.1 and 27.9 us; with a loop unrolled by 16, whose remainder is one load after the
+    // other, 18.1, 20.4 and 27.5: E = 128, T = 1040, 2048 and 8192)
+    constexpr int kAhead = 8;
     for (int s = tid; s < C; s += kFrontThreads) {
         int tot = 0, low = 0;
-#pragma unroll 16
-        for (int c = 0; c < n_chunks; ++c) {                          // the loads of sixteen chunks at once
-            const int v = hist[c * C + s];
-            tot += v;
-            low += c < chunk ? v : 0;
+        for (int c0 = 0; c0 < n_chunks; c0 += kAhead) {               // the loads of eight chunks at once
+            int v[kAhead];
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) v[u] = hist[(c0 + u < n_chunks ? c0 + u : n_chunks - 1) * C + s];   // past the last: that one again
+#pragma unroll
+            for (int u = 0; u < kAhead; ++u) {
+                const int x = c0 + u < n_chunks ? v[u] : 0;
+                tot += x;
+                low += c0 + u < chunk ? x : 0;
+            }
         }
         sh.total[s] = tot;
         lower[s] = low;

@@ -265,6 +265,20 @@ def test_schedule_time_of_one_batch():
     assert t[320] < 1.25 * t[256], t
 
 
+def layer_front_time(E, n_inst, C, k, T):
+    cfg = W.MoEConfig("front", E=E, k=k, d_h=32, d_e=32, T=T, n_inst=n_inst, C=C, zipf_s=0.8, seed=T)
+    s = LayerStep(cfg, W.build_placement(cfg), 0)
+    z = torch.from_numpy(W.router_logits(cfg)).cuda()
+    return device_time(lambda: s.front(z))
+
+
+def test_front_time_of_partial_groups_of_chunks():
+    """The tail with 14 chunks (no multiple of the chunks read at once) takes 0.92 of the time with 16
+    (level when the remainder is read one after the other)."""
+    t14, t16 = layer_front_time(128, 8, 17, 8, 3511), layer_front_time(128, 8, 17, 8, 4096)
+    assert t14 < 0.96 * t16, (t14, t16)
+
+
 @pytest.mark.parametrize("d_h,d_e", [(64, 4096), (4096, 64)])
 def test_pack_time_of_few_tiles(d_h, d_e):
     """Matrices of few tiles or few K-steps take as long to pack as square ones of their size (2.6 times when a tile pair is
