@@ -250,7 +250,7 @@ __device__ __forceinline__ void route_token(const float *row, int E, int k, cons
             // keys a lane the one step costs no more than the branch around it
             if (VPL == 2 || (VPL > 2 && (holders & (holders - 1)))) {    // wave-uniform
 #pragma unroll
-                for (int b = VPL / 2; b > 0; b >>= 1) {      // VPL is a power of two
+                for (int b = VPL > 8 ? 8 : VPL / 2; b > 0; b >>= 1) {   // indices below VPL = 1, 2, 4, 8, 12 or 16
                     const uint64_t low = holders & __ballot((mi & b) == 0);
                     holders = low ? low : holders;
                 }
