@@ -39,12 +39,12 @@ def test_selection_with_equal_logits(E, k, group):
 
 @pytest.mark.parametrize("n_inst,C,E", [(3, 9, 21), (16, 5, 64), (20, 4, 60), (40, 30, 1000), (3, 80, 210),
                                            (10, 70, 680)])
-@pytest.mark.parametrize("T", [1, 8, 9, 12, 13, 16, 17, 146, 147, 292, 293, 585, 586, 600, 1170, 1171, 4107])
+@pytest.mark.parametrize("T", [1, 8, 9, 12, 13, 16, 17, 146, 147, 292, 293, 585, 586, 600, 1025, 1170, 1171, 2340, 2341, 4107])
 def test_front_sizes(n_inst, C, E, T):
     """One workgroup (up to 12 tokens, 8 at E = 1000) and several; up to 16 instances and more; 1, 2, 4 and 8 groups of 64
     requests per wavefront (k = 7: the tokens lie on both sides of 1024, 2048, 4096 and 8192 requests), up to 64 slots and
-    more; the chunked tail with one token and with two a wavefront; a table too large for LDS.  Against the oracle, twice on
-    the same sync words."""
+    more; wavefronts that route nothing and none (from 1025 tokens on); the chunked tail with one token and with two a wavefront
+    and on both sides of eight chunks; a table too large for LDS.  Against the oracle, twice on the same sync words."""
     k = 7
     cfg = W.MoEConfig("front", E=E, k=k, d_h=32, d_e=32, T=T, n_inst=n_inst, C=C, zipf_s=1.0, seed=T)
     lay = W.build_placement(cfg)
