@@ -61,10 +61,27 @@ constexpr int kCtrlCopies = 7;
 constexpr int kCtrlBlockInts = (1 + kCtrlCopies) * kCtrlLineInts;
 constexpr int kMaxItems = static_cast<int>(moe::kFfnCtrlBytes / 4) / kCtrlBlockInts - 1;
 
+// Division of 0 <= x < 2^31 by a divisor that the host knows: x / d = (2x * mul) >> (32 + shift), exact with
+// mul = ceil(2^(31 + shift) / d) and 2^shift >= d (the excess mul * d - 2^(31 + shift) stays below d <= 2^shift, so it adds
+// less than 1 / d to the quotient).
+struct FastDiv {
+    uint32_t mul;
+    int shift;
+    __device__ __forceinline__ uint32_t operator()(uint32_t x) const { return __umulhi(x << 1, mul) >> shift; }
+};
+
+FastDiv fast_div(uint32_t d) {
+    FastDiv f{0, 0};
+    while ((1ull << f.shift) < d) ++f.shift;
+    f.mul = static_cast<uint32_t>(((1ull << (31 + f.shift)) + d - 1) / d);
+    return f;
+}
+
 struct StageArgs {
     const uint16_t *B;                   // token operand: X (stage 1, rows through perm) or act (stage 2, blocks)
     const char *Wp;                      // packed weights: [C][tiles][KS][2][64] fragments of 16 bytes
     int tiles, items, tiles_pad, KS;     // items = workgroups per block (stage 2: one per pair of tiles); tiles_pad = items rounded up to a multiple of 8
+    FastDiv pad_div;                     // division by tiles_pad
     int b_stride;                        // elements between rows of X (stage 1)
     int out_stride;                      // elements between rows of Yp (stage 2)
 };
@@ -76,11 +93,21 @@ struct StreamArgs {
     uint16_t *act;                       // stage-1 output
     float *Yp;                           // stage-2 output
     int *ctrl;
-    int k, C;
+    FastDiv k_div;                       // division by k: token of a request
     int spin_limit;
+    unsigned list_last;                  // index of the last entry the work list has room for
     uint32_t act_block_bytes;            // bytes of `act` per entry of the work list: R rows x d_e rounded up to 64 channels
     int has_gemm;                        // the batch is large enough for the separate tiled-GEMM launches (common.h)
 };
+
+// The work list and the header of the control region do not change while the launch runs: read through the constant address
+// space, they are scalar loads that the compiler may issue together, ahead of everything else.  (As plain loads they were
+// vector loads behind the stores and atomics of the kernel, four dependent round trips before a workgroup's first operand.)
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ int4 load_const(const int32_t *p, unsigned i) {
+    const i32x4 v = reinterpret_cast<const __attribute__((address_space(4))) i32x4 *>(reinterpret_cast<uintptr_t>(p))[i];
+    return make_int4(v[0], v[1], v[2], v[3]);
+}
 
 __device__ __forceinline__ f32x4 mfma16(bf16x8 a, bf16x8 b, f32x4 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -183,7 +210,7 @@ __device__ __forceinline__ bool wait_block_ready(const StreamArgs &a, int *s_ok,
         int *blk = a.ctrl + (item + 1) * kCtrlBlockInts;
         const int *flag = blk + (1 + tile % kCtrlCopies) * kCtrlLineInts;
         // header word 2: a spin limit for this workspace (tests of the overrun path); 0 = the default
-        const int lim_ws = a.ctrl[moe::kCtrlSpinLimit];
+        const int lim_ws = load_const(a.ctrl, 0).z;
         const int limit = lim_ws > 0 ? lim_ws : a.spin_limit;
         int spins = 0, ok = 1;
         while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0) {
@@ -242,8 +269,9 @@ __device__ __forceinline__ void stream_item_lines(const StreamArgs &a, const Sta
     for (int h = 0; h < NH; ++h) {
         int r = row0 + h * 8 + (lane >> 3);
         r = r < row_end ? r : row_end - 1;
-        boff[h] = static_cast<uint32_t>(a.perm[r] / a.k) * static_cast<uint32_t>(g.b_stride) * 2 + (lane & 7) * 16;
+        boff[h] = static_cast<uint32_t>(a.perm[r]);                  // the request; its row's offset below
     }
+    asm volatile("" ::: "memory");
     // LDS: row R of a tile at R*128, its 16-byte chunk c at ((c ^ ((R >> 1) & 7)) * 16): the 16 rows a
     // fragment read touches fall into 16 different bank groups.  wr_lds[p]: rows of an even / odd half.
     const uint32_t wr_lds[2] = {static_cast<uint32_t>(((lane >> 3) * 128) + (((lane & 7) ^ (lane >> 4)) * 16)),
@@ -332,13 +360,17 @@ __device__ __forceinline__ void stream_item_lines(const StreamArgs &a, const Sta
         }                                                                                        \
         asm volatile("" ::: "memory");                                                           \
     } while (0)
-    if (n > 0) {
-        // issue order of the first loads: tokens of a super-step before its weights
+    // issue order of the first loads: the weights do not wait for the requests' tokens to be known
 #pragma unroll
-        for (int d = 0; d < D; ++d) {
-            if (d < DB && d < n) MOE_LOAD_B(d, d);
-            if (d < n) MOE_LOAD_A(d, d);
-        }
+    for (int d = 0; d < D; ++d)
+        if (d < n) MOE_LOAD_A(d, d);
+#pragma unroll
+    for (int h = 0; h < NH; ++h)
+        boff[h] = a.k_div(boff[h]) * static_cast<uint32_t>(g.b_stride) * 2 + (lane & 7) * 16;
+    if (n > 0) {
+#pragma unroll
+        for (int d = 0; d < DB; ++d)
+            if (d < n) MOE_LOAD_B(d, d);
         int i = 0;
         for (; i + 2 * D <= n; i += D) {
 #pragma unroll
@@ -539,18 +571,16 @@ __device__ __forceinline__ void wide_item(const StreamArgs &a, const StageArgs &
 
     // token rows this thread fetches: piece q*256 + tid = row (q*32 + tid/8), 16-byte chunk tid%8 of the line
     const bool loader = kPieces >= kThreads || tid < kPieces;
-    const char *bp[kLoadsB];
-    const size_t kt_stride = STAGE1 ? 128 : static_cast<size_t>(rows_pad) * 128;   // bytes a K-tile advances a row
+    int req[kLoadsB];
 #pragma unroll
     for (int q = 0; q < kLoadsB; ++q) {
         int r = q * (kThreads / 8) + (tid >> 3);
         r = r < m ? r : m - 1;
-        if constexpr (STAGE1)
-            bp[q] = reinterpret_cast<const char *>(g.B) +
-                    static_cast<size_t>(a.perm[row0 + r] / a.k) * static_cast<uint32_t>(g.b_stride) * 2 + (tid & 7) * 16;
-        else
-            bp[q] = act_blk + static_cast<size_t>(r) * 128 + (tid & 7) * 16;
+        req[q] = STAGE1 ? a.perm[row0 + r] : r;
     }
+    asm volatile("" ::: "memory");
+    const char *bp[kLoadsB];
+    const size_t kt_stride = STAGE1 ? 128 : static_cast<size_t>(rows_pad) * 128;   // bytes a K-tile advances a row
     // LDS: row R at R*128, its 16-byte chunk c at ((c ^ ((R >> 1) & 7)) * 16): the 16 rows that one
     // fragment read touches then fall into 16 different bank groups (rows R and R+8 share R & 7)
     const uint32_t wr_lds = (tid >> 3) * 128 + (((tid & 7) ^ ((tid >> 4) & 7)) * 16);
@@ -629,8 +659,19 @@ __device__ __forceinline__ void wide_item(const StreamArgs &a, const StageArgs &
 
     const int n_full = g.KS >> 1;                                    // K-tiles with both K-steps
     int i = 0;
-    MOE_WIDE_LOAD_A(0, 0); MOE_WIDE_LOAD_B(0, 0);
-    MOE_WIDE_LOAD_A(1, 1); MOE_WIDE_LOAD_B(1, 1);
+    // the weights do not wait for the requests' tokens to be known
+    MOE_WIDE_LOAD_A(0, 0);
+    MOE_WIDE_LOAD_A(1, 1);
+#pragma unroll
+    for (int q = 0; q < kLoadsB; ++q) {
+        if constexpr (STAGE1)
+            bp[q] = reinterpret_cast<const char *>(g.B) +
+                    static_cast<size_t>(a.k_div(req[q])) * static_cast<uint32_t>(g.b_stride) * 2 + (tid & 7) * 16;
+        else
+            bp[q] = act_blk + static_cast<size_t>(req[q]) * 128 + (tid & 7) * 16;
+    }
+    MOE_WIDE_LOAD_B(0, 0);
+    MOE_WIDE_LOAD_B(1, 1);
     for (; i + 2 <= n_full; i += 2) {
         MOE_WIDE_STEP(0, i, true);
         MOE_WIDE_STEP(1, i + 1, true);
@@ -746,15 +787,8 @@ __device__ __forceinline__ void run_wide(const StreamArgs &a, const StageArgs &g
 // blocks of this launch; 2 = those slots belong to the tiled-GEMM launches and are skipped here
 template <bool STAGE1, bool EVEN, int TT, int WR>
 __device__ __forceinline__ void run_item(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok, int wide,
-                                         unsigned id) {
-    int tile = id % g.tiles_pad;
-    const int item = id / g.tiles_pad;
-    // work list entry: {slot, first row, end of the slot's rows, first of the slot's rows}; entry 0 holds the number of blocks
-    // (both are wave-uniform scalar loads issued together; an entry past the end is never used)
-    const int4 *list = reinterpret_cast<const int4 *>(a.blocks);
-    const int n_blocks = list[0].x;
-    const int4 ent = list[1 + item];
-    if (item >= n_blocks) return;                                // past the last block: nothing else is read
+                                         int item, int tile, int4 ent) {
+    // ent, the block's work list entry: {slot, first row, end of the slot's rows, first of the slot's rows}
     // a slot with more than kWideRows requests is computed as tiled GEMMs over blocks of kWideRows rows
     if (wide && ent.z - ent.w > kWideMin) {
         if (wide == 1) run_wide<STAGE1, WR, TT * 16>(a, g, lds, s_ok, item, tile, ent);
@@ -864,7 +898,16 @@ void ffn_stream_kernel(StreamArgs a) {
     {
         // ids are decoded with the number of blocks the batch really has, so that the surplus of
         // the worst-case grid comes after all the work of both stages
-        const int4 head = reinterpret_cast<const int4 *>(a.blocks)[0];
+        // The header, the workspace's options and the entry this workgroup has if it is a stage-1 workgroup of a block with
+        // workgroups of its own, all requested at once (an entry past the end of the list is never used).  One after the other,
+        // with the weights behind the requests' tokens and divisions in between, they kept every workgroup from its first
+        // operand for another 1.5 us: a layer step at d_h = 2048 with 17 blocks of up to 32 rows 37.1 -> 36.5 us, with odd numbers of
+        // K-steps 59.1 -> 57.7.
+        const unsigned item1 = a.s[0].pad_div(blockIdx.x);
+        const int4 head = load_const(a.blocks, 0);
+        const int4 ent1 = load_const(a.blocks, 1 + item1 < a.list_last ? 1 + item1 : a.list_last);
+        const int wide_min = load_const(a.ctrl, 0).w;
+        asm volatile("" ::"s"(head.x), "s"(ent1.x), "s"(ent1.y), "s"(ent1.z), "s"(ent1.w), "s"(wide_min));   // here, not behind the branches
         if (head.y != TT * 16) {
             // the list was cut for another block size (made for a different T): refuse, visibly
             if (threadIdx.x == 0 && blockIdx.x == 0)
@@ -876,21 +919,25 @@ void ffn_stream_kernel(StreamArgs a) {
         // workgroup of block b also takes blocks b + kFfnLaneBlocks, ..., at most 64 of them), which
         // keeps the worst-case grid of large batches small.  A stage-1 workgroup never waits, and all of them are started
         // before any stage-2 workgroup, so every flag a stage-2 workgroup waits for is raised.
-        // header word 3 of the workspace: the caller's threshold for wide blocks (0 = default)
-        const int wide_min = a.ctrl[moe::kCtrlWideMin];
+        // header word 3 of the workspace (wide_min): the caller's threshold for wide blocks (0 = default)
         const int wide = a.has_gemm && moe::ffn_gemm_on(head, (a.s[0].tiles + kWaves - 1) / kWaves, wide_min) ? 2
                          : wide_on(head, (a.s[0].tiles + kWaves - 1) / kWaves, wide_min, a.s[0].KS, a.s[1].KS) ? 1 : 0;
         const unsigned n_blocks = static_cast<unsigned>(head.x);
         const unsigned lanes = n_blocks < moe::kFfnLaneBlocks ? n_blocks : moe::kFfnLaneBlocks;
         const unsigned n1 = lanes * a.s[0].tiles_pad, n2 = lanes * a.s[1].tiles_pad;
+        const auto own_item = [&] {
+            if (blockIdx.x < n1) {
+                run_item<true, EVEN1, TT, WR>(a, a.s[0], lds, &s_ok, wide, item1, blockIdx.x - item1 * a.s[0].tiles_pad, ent1);
+            } else if (blockIdx.x - n1 < n2) {
+                const unsigned id = blockIdx.x - n1, item = a.s[1].pad_div(id);
+                run_item<false, EVEN2, TT, WR>(a, a.s[1], lds, &s_ok, wide, item, id - item * a.s[1].tiles_pad, load_const(a.blocks, 1 + item));
+            }
+        };
         if constexpr (!WRAP) {
-            if (blockIdx.x < n1) run_item<true, EVEN1, TT, WR>(a, a.s[0], lds, &s_ok, wide, blockIdx.x);
-            else if (blockIdx.x - n1 < n2) run_item<false, EVEN2, TT, WR>(a, a.s[1], lds, &s_ok, wide, blockIdx.x - n1);
+            own_item();
         } else {
             if (n_blocks <= lanes) {
-                // as without WRAP: the loop's copy of the items is up to 14 % slower on full 64-row blocks
-                if (blockIdx.x < n1) run_item<true, EVEN1, TT, WR>(a, a.s[0], lds, &s_ok, wide, blockIdx.x);
-                else if (blockIdx.x - n1 < n2) run_item<false, EVEN2, TT, WR>(a, a.s[1], lds, &s_ok, wide, blockIdx.x - n1);
+                own_item();              // as without WRAP: the loop's copy of the items is up to 14 % slower on full 64-row blocks
                 return;
             }
             if (blockIdx.x >= n1 + n2) return;
@@ -898,10 +945,10 @@ void ffn_stream_kernel(StreamArgs a) {
             const unsigned id0 = s1 ? blockIdx.x : blockIdx.x - n1;
             // a long list: the first wavefront looks at all the blocks of this workgroup at once (lane l:
             // block + l*lanes) and the workgroup then visits only those that are its own to compute
-            const unsigned tp = s1 ? a.s[0].tiles_pad : a.s[1].tiles_pad;
+            const unsigned tp = s1 ? a.s[0].tiles_pad : a.s[1].tiles_pad, item0 = s1 ? item1 : a.s[1].pad_div(id0);
             // (ids that pad the tiles to a multiple of 8 stay: the wide slots use them)
             if (threadIdx.x < MOE_WAVE) {
-                const unsigned b = id0 / tp + threadIdx.x * lanes;
+                const unsigned b = item0 + threadIdx.x * lanes;
                 // entries of wide slots that lead no block are not visited
                 bool mine = false;
                 if (b < n_blocks) {
@@ -924,8 +971,10 @@ void ffn_stream_kernel(StreamArgs a) {
                 // of items at once (hundreds of spilled scalars)
                 StageArgs g = s1 ? a.s[0] : a.s[1];
                 asm volatile("" : "+s"(g.KS), "+s"(g.tiles), "+s"(g.tiles_pad), "+s"(g.items));
-                if (s1) run_item<true, EVEN1, TT, WR>(a, g, lds, &s_ok, wide, id0 + l * n1);
-                else run_item<false, EVEN2, TT, WR>(a, g, lds, &s_ok, wide, id0 + l * n2);
+                const unsigned item = item0 + l * lanes;
+                const int4 ent = load_const(a.blocks, 1 + item);
+                if (s1) run_item<true, EVEN1, TT, WR>(a, g, lds, &s_ok, wide, item, id0 - item0 * tp, ent);
+                else run_item<false, EVEN2, TT, WR>(a, g, lds, &s_ok, wide, item, id0 - item0 * tp, ent);
             }
         }
     }
@@ -957,7 +1006,8 @@ int launch_ffn_stream(const void *X, const void *W13p, const void *W2p, int T, i
     const long long items = ffn_max_blocks(T, k, C);
     if (items > kMaxItems) return MOE_ESHAPE;
     StreamArgs a;
-    a.blocks = blocks; a.perm = perm; a.act = act; a.Yp = Yp; a.ctrl = ctrl; a.k = k; a.C = C;
+    a.blocks = blocks; a.perm = perm; a.act = act; a.Yp = Yp; a.ctrl = ctrl; a.k_div = fast_div(k);
+    a.list_last = static_cast<unsigned>(items);
     a.spin_limit = 1 << 20;
     a.act_block_bytes = static_cast<uint32_t>(ffn_act_block_bytes(T, d_e));
     a.has_gemm = ffn_has_gemm(T) ? 1 : 0;
@@ -969,7 +1019,10 @@ int launch_ffn_stream(const void *X, const void *W13p, const void *W2p, int T, i
     a.s[1].tiles = d_h / 32; a.s[1].KS = d_e / 32; a.s[1].b_stride = 0; a.s[1].out_stride = d_h;
     a.s[0].items = a.s[0].tiles;
     a.s[1].items = block_rows == 32 ? a.s[1].tiles : (a.s[1].tiles + 1) / 2;   // 64-row launch: a stage-2 workgroup owns a pair of tiles
-    for (int i = 0; i < 2; ++i) a.s[i].tiles_pad = (a.s[i].items + 7) / 8 * 8;
+    for (int i = 0; i < 2; ++i) {
+        a.s[i].tiles_pad = (a.s[i].items + 7) / 8 * 8;
+        a.s[i].pad_div = fast_div(a.s[i].tiles_pad);
+    }
     const long long lanes = items < kFfnLaneBlocks ? items : kFfnLaneBlocks;
     const long long n1 = lanes * a.s[0].tiles_pad, n2 = lanes * a.s[1].tiles_pad;
     if (n1 + n2 > 0x7fffffffLL) return MOE_ESHAPE;
