@@ -147,7 +147,7 @@ __device__ __forceinline__ void put_partials(char *lds, const f32x4 (&acc)[F][NT
 }
 
 template <int TT>
-__device__ __forceinline__ f32x4 sum_partials(const char *lds, int frag, int lane) {
+__device__ __forceinline__ f32x4 sum_partials4(const char *lds, int frag, int lane) {
     const f32x4 *red = reinterpret_cast<const f32x4 *>(lds) + frag * MOE_WAVE + lane;
     f32x4 v = red[0];
 #pragma unroll
@@ -155,30 +155,48 @@ __device__ __forceinline__ f32x4 sum_partials(const char *lds, int frag, int lan
     return v;
 }
 
+// One value of a fragment's 256 (value v: lane v / 4, element v % 4).
+template <int TT>
+__device__ __forceinline__ float sum_partials(const char *lds, int frag, int v) {
+    const float *red = reinterpret_cast<const float *>(lds) + frag * (4 * MOE_WAVE) + v;
+    float s = red[0];
+#pragma unroll
+    for (int wv = 1; wv < kWaves; ++wv) s += red[wv * (2 * TT * MOE_WAVE * 4)];
+    return s;
+}
+
+// The value of another lane of the same four.
+template <int A, int B, int C, int D>
+__device__ __forceinline__ uint32_t quad_perm(uint32_t v) {
+    return static_cast<uint32_t>(__builtin_amdgcn_update_dpp(0, static_cast<int>(v), A | B << 2 | C << 4 | D << 6, 0xf, 0xf, false));
+}
+template <int A, int B, int C, int D>
+__device__ __forceinline__ float quad_perm(float v) { return __uint_as_float(quad_perm<A, B, C, D>(__float_as_uint(v))); }
+
 // Split-K reduction over the 4 wavefronts in LDS (fixed order), then the epilogue: SiLU(gate)*up
 // rounded once to bf16 (stage 1, agent-scope stores) or the fp32 partial output rows (stage 2).  One copy of this code
 // for all numbers of row tiles (nt): the kernel's instructions are many times the instruction cache.
 template <int TT>
 __device__ __forceinline__ void store_act(const StreamArgs &a, const char *lds, int nt, int item_id, int tile, int row0, int row_end) {
-    // lane-slot (t, l) holds gate/up channels tile*16 + (l/16)*4 .. +3 of token row0 + t*16 + l%16
-    for (int item = threadIdx.x; item < nt * MOE_WAVE; item += kThreads) {
-        const int t = item / MOE_WAVE, l = item % MOE_WAVE;
-        const f32x4 gt = sum_partials<TT>(lds, t, l), up = sum_partials<TT>(lds, nt + t, l);
-        const int r = row0 + t * 16 + (l & 15);
-        if (r < row_end) {
-            const uint64_t o = static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[0], up[0]))) |
-                               static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[1], up[1]))) << 16 |
-                               static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[2], up[2]))) << 32 |
-                               static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[3], up[3]))) << 48;
-            // act block of this item: [K-step of stage 2][token tile][64 lanes][16 B], the register image of
-            // the MFMA B operand (lane: row % 16, channels (lane / 16) * 8 .. + 7 of the K-step's 32); this
-            // tile is half a K-step, and every 128-byte line of the image has one writing workgroup
-            const int fl = (l & 15) + 16 * ((tile & 1) * 2 + (l >> 5));
-            uint64_t *dst = reinterpret_cast<uint64_t *>(
-                reinterpret_cast<char *>(a.act) + static_cast<size_t>(item_id) * a.act_block_bytes +
-                (static_cast<size_t>(tile >> 1) * TT + t) * 1024 + fl * 16 + ((l >> 4) & 1) * 8);
-            __hip_atomic_store(dst, o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+    // Value v of a fragment (v / 4 = lane l, v % 4 = i) is gate/up channel tile*16 + (l/16)*4 + i of token row0 + t*16 + l%16: a
+    // thread takes one value of each row tile, so that all wavefronts share the work however few the rows are (with four
+    // values a thread a block of up to 16 rows was one wavefront's, 0.7 us of a chain that stage 2 waits for: four layer
+    // steps with five blocks of up to 5 rows 92.2 -> 91.0 us, with 12 of up to 32 rows 114.3 -> 112.9).
+    const int l = threadIdx.x >> 2, i = threadIdx.x & 3;
+    // act block of this item: [K-step of stage 2][token tile][64 lanes][16 B], the register image of
+    // the MFMA B operand (lane: row % 16, channels (lane / 16) * 8 .. + 7 of the K-step's 32); this
+    // tile is half a K-step, and every 128-byte line of the image has one writing workgroup
+    const int fl = (l & 15) + 16 * ((tile & 1) * 2 + (l >> 5));
+    char *dst = reinterpret_cast<char *>(a.act) + static_cast<size_t>(item_id) * a.act_block_bytes +
+                static_cast<size_t>(tile >> 1) * (TT * 1024) + fl * 16 + ((l >> 4) & 1) * 8;
+#pragma unroll 1
+    for (int t = 0; t < nt; ++t) {
+        const float act = silu_mul(sum_partials<TT>(lds, t, threadIdx.x), sum_partials<TT>(lds, nt + t, threadIdx.x));
+        // the four channels of a quad of threads, stored by its first
+        const uint32_t hi = moe::f32x2_to_bf16x2(act, quad_perm<1, 1, 3, 3>(act));   // lanes 0 and 2 of the quad: channels i, i+1
+        const uint64_t o = hi | static_cast<uint64_t>(quad_perm<2, 2, 2, 2>(hi)) << 32;
+        if (i == 0 && row0 + t * 16 + (l & 15) < row_end)
+            __hip_atomic_store(reinterpret_cast<uint64_t *>(dst + t * 1024), o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
@@ -191,7 +209,7 @@ __device__ __forceinline__ void store_rows(const StreamArgs &a, const StageArgs 
     for (int item = threadIdx.x; item < nf * nt * MOE_WAVE; item += kThreads, t += kWaves) {
         while (t >= nt) { t -= nt; ++f; }
         const int l = item % MOE_WAVE;
-        const f32x4 y = sum_partials<TT>(lds, item / MOE_WAVE, l);
+        const f32x4 y = sum_partials4<TT>(lds, item / MOE_WAVE, l);
         const int r = row0 + t * 16 + (l & 15);
         if (r < row_end)
             *reinterpret_cast<f32x4 *>(a.Yp + static_cast<size_t>(r) * g.out_stride + tile * 32 + f * 16 + (l >> 4) * 4) = y;
@@ -696,10 +714,8 @@ __device__ __forceinline__ void wide_item(const StreamArgs &a, const StageArgs &
             if (r >= m) continue;
             if constexpr (STAGE1) {
                 const f32x4 gt = acc[rt][0], up = acc[rt][1];
-                const uint64_t o = static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[0], up[0]))) |
-                                   static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[1], up[1]))) << 16 |
-                                   static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[2], up[2]))) << 32 |
-                                   static_cast<uint64_t>(moe::f32_to_bf16(silu_mul(gt[3], up[3]))) << 48;
+                const uint64_t o = moe::f32x2_to_bf16x2(silu_mul(gt[0], up[0]), silu_mul(gt[1], up[1])) |
+                                   static_cast<uint64_t>(moe::f32x2_to_bf16x2(silu_mul(gt[2], up[2]), silu_mul(gt[3], up[3]))) << 32;
                 uint64_t *dst = reinterpret_cast<uint64_t *>(act_blk + (static_cast<size_t>(group) * rows_pad + r) * 128 +
                                                              wave * 32 + (lane >> 4) * 8);
                 __hip_atomic_store(dst, o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
