@@ -435,6 +435,21 @@ int moe_shared_dispatch(int T, int32_t *slot_off_dev, int32_t *perm_dev, int32_t
 int moe_combine_shared(const float *Yp_dev, const int32_t *pos_dev, const float *topk_w_dev, const float *Ys_dev,
                        int T, int k, int d_h, int dtype, void *Y_dev, void *stream);
 
+/* moe_grouped_ffn for the routed experts and for the shared expert (width d_s, the dispatch of moe_shared_dispatch, a
+ * workspace of moe_workspace_bytes(T, 1, 1, d_h, d_s, dtype) bytes of its own, initialised like the other): Yp and Ys are what the
+ * two calls give, up to the order in which a slot's K-steps are added.  One launch where it can be (bf16, T < 2048,
+ * moe_max_blocks(T, k, C) <= 224, d_e / 32 and d_s / 32 both even or both odd), so that the shared expert runs beside the
+ * routed experts' weight stream; otherwise the two calls one after the other.  Nothing is launched when an argument of
+ * either set is refused.
+ */
+int moe_grouped_ffn_shared(const void *X_dev, const void *W13_dev, const void *W2_dev,
+                           int T, int k, int C, int d_h, int d_e, int dtype,
+                           const int32_t *slot_off_dev, const int32_t *perm_dev, const int32_t *blocks_dev,
+                           float *Yp_dev, void *workspace_dev, size_t workspace_bytes,
+                           const void *W13s_dev, const void *W2s_dev, int d_s,
+                           const int32_t *s_slot_off_dev, const int32_t *s_perm_dev, const int32_t *s_blocks_dev,
+                           float *Ys_dev, void *s_workspace_dev, size_t s_workspace_bytes, void *stream);
+
 #ifdef __cplusplus
 }
 #endif

@@ -31,6 +31,7 @@ EXPORTS = [
     "moe_pack_weights_bf16",
     "moe_workspace_bytes", "moe_workspace_init", "moe_workspace_status", "moe_grouped_ffn", "moe_combine",
     "moe_shared_dispatch", "moe_combine_shared", "moe_workspace_set_option", "moe_grouped_ffn_static",
+    "moe_grouped_ffn_shared",
 ]
 MOE_FFN_STATIC_SCRATCH_BYTES = 32 << 20
 BENCH_EXPORTS = ["moe_read_probe"]
@@ -127,6 +128,8 @@ def lib() -> ctypes.CDLL:
     L.moe_grouped_ffn.argtypes = [vp, vp, vp, ci, ci, ci, ci, ci, ci, vp, vp, vp, vp, vp, cs, vp]
     L.moe_grouped_ffn_static.restype = ci
     L.moe_grouped_ffn_static.argtypes = [vp, vp, vp, ci, ci, ci, ci, ci, ci, vp, vp, vp, vp, vp]
+    L.moe_grouped_ffn_shared.restype = ci
+    L.moe_grouped_ffn_shared.argtypes = [vp, vp, vp, ci, ci, ci, ci, ci, ci, vp, vp, vp, vp, vp, cs, vp, vp, ci, vp, vp, vp, vp, vp, cs, vp]
     L.moe_combine.restype = ci
     L.moe_combine.argtypes = [vp, vp, vp, ci, ci, ci, ci, vp, vp]
     L.moe_workspace_set_option.restype = ci
@@ -395,6 +398,17 @@ def moe_grouped_ffn_static(X, W13, W2, T: int, k: int, C: int, d_h: int, d_e: in
     _check(lib().moe_grouped_ffn_static(_ptr(X), _ptr(W13), _ptr(W2), T, k, C, d_h, d_e, dtype, _ptr(slot_off),
                                         _ptr(perm), _ptr(blocks), _ptr(Yp), _stream(stream)),
            "moe_grouped_ffn_static")
+
+
+def moe_grouped_ffn_shared(X, W13, W2, T: int, k: int, C: int, d_h: int, d_e: int, dtype: int, slot_off, perm, blocks, Yp,
+                           workspace, W13s, W2s, d_s: int, s_slot_off, s_perm, s_blocks, Ys, s_workspace, stream=None) -> None:
+    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+    s_ws_bytes = 0 if s_workspace is None else s_workspace.numel() * s_workspace.element_size()
+    _check(lib().moe_grouped_ffn_shared(_ptr(X), _ptr(W13), _ptr(W2), T, k, C, d_h, d_e, dtype, _ptr(slot_off),
+                                        _ptr(perm), _ptr(blocks), _ptr(Yp), _ptr(workspace), ws_bytes, _ptr(W13s), _ptr(W2s), d_s,
+                                        _ptr(s_slot_off), _ptr(s_perm), _ptr(s_blocks), _ptr(Ys), _ptr(s_workspace), s_ws_bytes,
+                                        _stream(stream)),
+           "moe_grouped_ffn_shared")
 
 
 def moe_combine(Yp, pos, topk_w, T: int, k: int, d_h: int, dtype: int, Y, stream=None) -> None:

@@ -71,12 +71,22 @@ inline size_t ffn_stream_act_bytes(int T, int k, int C, int d_e) {
     return (b + 255) / 256 * 256;
 }
 
+// One set of experts of a bf16 grouped FFN: C slots of width d_e, k requests a token.
+struct FfnCall {
+    const void *X, *W13p, *W2p;
+    int k, C, d_e;
+    const int32_t *blocks, *perm;
+    int *ctrl;                           // the workspace's control region
+    uint16_t *act;                       // ffn_stream_act_bytes(T, k, C, d_e) bytes
+    float *Yp;
+};
+
 // bf16 grouped FFN (ffn_stream.hip); shapes validated by the caller.  `ctrl` is the zero-initialised
-// control region of the workspace, `act` holds ffn_stream_act_bytes(T, k, C, d_e) bytes.  Returns MOE_OK
-// or MOE_ESHAPE (too many blocks).
-int launch_ffn_stream(const void *X, const void *W13p, const void *W2p, int T, int k, int C, int d_h, int d_e,
-                      const int32_t *blocks, const int32_t *perm, int *ctrl, uint16_t *act,
-                      float *Yp, hipStream_t st);
+// control region of the workspace.  Returns MOE_OK or MOE_ESHAPE (too many blocks).
+int launch_ffn_stream(const FfnCall &c, int T, int d_h, hipStream_t st);
+// The same for two sets of experts over the same token rows in one launch, where ffn_stream_takes_shared() says so.
+bool ffn_stream_takes_shared(const FfnCall &c, const FfnCall &sh, int T, int d_h);
+void launch_ffn_stream_shared(const FfnCall &c, const FfnCall &sh, int T, int d_h, hipStream_t st);
 
 // Batches of at least kGemmMinTokens tokens: slots with more than 64 requests as blocks of 128 rows in
 // two tiled-GEMM launches of their own (ffn_wide.hip, three workgroups of 168 registers per CU),

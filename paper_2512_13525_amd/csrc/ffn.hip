@@ -211,10 +211,10 @@ extern "C" int moe_pack_weights_bf16(const void *W13_dev, const void *W2_dev, in
 
 namespace {
 
-int grouped_ffn(const void *X_dev, const void *W13_dev, const void *W2_dev,
-                int T, int k, int C, int d_h, int d_e, int dtype,
-                const int32_t *slot_off_dev, const int32_t *perm_dev, const int32_t *blocks_dev,
-                float *Yp_dev, void *workspace_dev, size_t workspace_bytes, void *stream) {
+// The checks of one set of experts; MOE_OK with T == 0 means that nothing is to be done.
+int check_ffn(const void *X_dev, const void *W13_dev, const void *W2_dev, int T, int k, int C, int d_h, int d_e, int dtype,
+              const int32_t *slot_off_dev, const int32_t *perm_dev, const int32_t *blocks_dev, const float *Yp_dev,
+              const void *workspace_dev, size_t workspace_bytes) {
     if (T < 0 || k < 1 || C < 1 || d_h < 1 || d_e < 1) return MOE_EINVAL;
     if (dtype != MOE_DTYPE_BF16 && dtype != MOE_DTYPE_F32) return MOE_EINVAL;
     if (C > MOE_MAX_SLOTS || k > MOE_MAX_TOPK) return MOE_ESHAPE;
@@ -229,6 +229,23 @@ int grouped_ffn(const void *X_dev, const void *W13_dev, const void *W2_dev,
         return MOE_EINVAL;
     if (dtype == MOE_DTYPE_BF16 && (!blocks_dev || !moe::aligned(blocks_dev, 16))) return MOE_EINVAL;
     if (workspace_bytes < moe_workspace_bytes(T, k, C, d_h, d_e, dtype)) return MOE_EWORKSPACE;
+    return MOE_OK;
+}
+
+moe::FfnCall ffn_call(const void *X_dev, const void *W13_dev, const void *W2_dev, int k, int C, int d_e, const int32_t *perm_dev,
+                      const int32_t *blocks_dev, float *Yp_dev, void *workspace_dev) {
+    char *ws = static_cast<char *>(workspace_dev);
+    return {X_dev, W13_dev, W2_dev, k, C, d_e, blocks_dev, perm_dev, reinterpret_cast<int *>(ws),
+            reinterpret_cast<uint16_t *>(ws + kCtrlBytes), Yp_dev};
+}
+
+int grouped_ffn(const void *X_dev, const void *W13_dev, const void *W2_dev,
+                int T, int k, int C, int d_h, int d_e, int dtype,
+                const int32_t *slot_off_dev, const int32_t *perm_dev, const int32_t *blocks_dev,
+                float *Yp_dev, void *workspace_dev, size_t workspace_bytes, void *stream) {
+    const int bad = check_ffn(X_dev, W13_dev, W2_dev, T, k, C, d_h, d_e, dtype, slot_off_dev, perm_dev, blocks_dev, Yp_dev,
+                              workspace_dev, workspace_bytes);
+    if (bad != MOE_OK || T == 0) return bad;
     hipStream_t st = static_cast<hipStream_t>(stream);
     char *ws = static_cast<char *>(workspace_dev);
     if (dtype == MOE_DTYPE_BF16) {
@@ -240,9 +257,8 @@ int grouped_ffn(const void *X_dev, const void *W13_dev, const void *W2_dev,
                                                  perm_dev, reinterpret_cast<const int *>(ws), act_rows, Yp_dev, st);
             if (rcw != MOE_OK) return rcw;
         }
-        const int rc = moe::launch_ffn_stream(X_dev, W13_dev, W2_dev, T, k, C, d_h, d_e, blocks_dev, perm_dev,
-                                              reinterpret_cast<int *>(ws), reinterpret_cast<uint16_t *>(ws + kCtrlBytes),
-                                              Yp_dev, st);
+        const int rc = moe::launch_ffn_stream(
+            ffn_call(X_dev, W13_dev, W2_dev, k, C, d_e, perm_dev, blocks_dev, Yp_dev, workspace_dev), T, d_h, st);
         if (rc != MOE_OK) return rc;
     } else {
         // one grid row per possible request row; rows >= n_local leave at once
@@ -296,6 +312,35 @@ extern "C" int moe_grouped_ffn(const void *X_dev, const void *W13_dev, const voi
                                float *Yp_dev, void *workspace_dev, size_t workspace_bytes, void *stream) {
     return grouped_ffn(X_dev, W13_dev, W2_dev, T, k, C, d_h, d_e, dtype, slot_off_dev, perm_dev, blocks_dev, Yp_dev,
                        workspace_dev, workspace_bytes, stream);
+}
+
+extern "C" int moe_grouped_ffn_shared(const void *X_dev, const void *W13_dev, const void *W2_dev,
+                                      int T, int k, int C, int d_h, int d_e, int dtype,
+                                      const int32_t *slot_off_dev, const int32_t *perm_dev, const int32_t *blocks_dev,
+                                      float *Yp_dev, void *workspace_dev, size_t workspace_bytes,
+                                      const void *W13s_dev, const void *W2s_dev, int d_s,
+                                      const int32_t *s_slot_off_dev, const int32_t *s_perm_dev, const int32_t *s_blocks_dev,
+                                      float *Ys_dev, void *s_workspace_dev, size_t s_workspace_bytes, void *stream) {
+    int rc = check_ffn(X_dev, W13_dev, W2_dev, T, k, C, d_h, d_e, dtype, slot_off_dev, perm_dev, blocks_dev, Yp_dev,
+                       workspace_dev, workspace_bytes);
+    if (rc == MOE_OK)
+        rc = check_ffn(X_dev, W13s_dev, W2s_dev, T, 1, 1, d_h, d_s, dtype, s_slot_off_dev, s_perm_dev, s_blocks_dev, Ys_dev,
+                       s_workspace_dev, s_workspace_bytes);
+    if (rc != MOE_OK || T == 0) return rc;
+    if (workspace_dev == s_workspace_dev) return MOE_EINVAL;         // the two sets hand over through control lines of their own
+    if (dtype == MOE_DTYPE_BF16 && static_cast<long long>(T) * d_h * 2 <= 0xffffffffLL) {
+        const moe::FfnCall routed = ffn_call(X_dev, W13_dev, W2_dev, k, C, d_e, perm_dev, blocks_dev, Yp_dev, workspace_dev);
+        const moe::FfnCall shared = ffn_call(X_dev, W13s_dev, W2s_dev, 1, 1, d_s, s_perm_dev, s_blocks_dev, Ys_dev, s_workspace_dev);
+        if (moe::ffn_stream_takes_shared(routed, shared, T, d_h)) {
+            moe::launch_ffn_stream_shared(routed, shared, T, d_h, static_cast<hipStream_t>(stream));
+            return moe::check_launch("moe_grouped_ffn_shared");
+        }
+    }
+    rc = grouped_ffn(X_dev, W13_dev, W2_dev, T, k, C, d_h, d_e, dtype, slot_off_dev, perm_dev, blocks_dev, Yp_dev,
+                     workspace_dev, workspace_bytes, stream);
+    if (rc != MOE_OK) return rc;
+    return grouped_ffn(X_dev, W13s_dev, W2s_dev, T, 1, 1, d_h, d_s, dtype, s_slot_off_dev, s_perm_dev, s_blocks_dev, Ys_dev,
+                       s_workspace_dev, s_workspace_bytes, stream);
 }
 
 extern "C" int moe_grouped_ffn_static(const void *X_dev, const void *W13_dev, const void *W2_dev,

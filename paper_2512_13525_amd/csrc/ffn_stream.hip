@@ -758,15 +758,18 @@ constexpr int kWideMin = 64;
 constexpr int kWideMinWorkgroups = 256;
 constexpr int kWideMinHidden = 64;
 constexpr long long kWideTileNs = 900, kStreamBytesPerNs = 7000;
-__device__ __forceinline__ bool wide_on(int4 head, int groups1, int override_min, int ks1, int ks2) {
+// beside_ns: the same for the other expert set of a launch that runs two.
+__device__ __forceinline__ long long stream_ns(int blocks, int ks1, int ks2) {
+    // an expert's three matrices: 3 * d_h * d_e bf16 = ks1 * ks2 * 32 * 32 * 6 bytes
+    return static_cast<long long>(blocks) * ks1 * ks2 * (32 * 32 * 6) / kStreamBytesPerNs;
+}
+__device__ __forceinline__ bool wide_on(int4 head, int groups1, int override_min, int ks1, int ks2, long long beside_ns = 0) {
     const int wgs = head.z * groups1;
     if (override_min > 0) return wgs >= override_min;
     if (wgs >= kWideMinWorkgroups) return true;
     if (wgs < kWideMinHidden) return false;
-    // an expert's three matrices: 3 * d_h * d_e bf16 = ks1 * ks2 * 32 * 32 * 6 bytes
-    const long long stream_ns = static_cast<long long>(head.x) * ks1 * ks2 * (32 * 32 * 6) / kStreamBytesPerNs;
     const long long chain_ns = static_cast<long long>((ks1 + 1) / 2 + (ks2 + 1) / 2) * kWideTileNs;
-    return 4 * stream_ns >= 5 * chain_ns;
+    return 4 * (stream_ns(head.x, ks1, ks2) + beside_ns) >= 5 * chain_ns;
 }
 // The workgroups of a wide slot's leading entries (one entry per block of WR rows; ids tile = 0 .. tiles_pad-1
 // each) run the slot's blocks x groups of 4 tiles; all other workgroups of the slot's entries leave.
@@ -996,6 +999,72 @@ void ffn_stream_kernel(StreamArgs a) {
     }
 }
 
+// The routed experts (set 0) and a shared expert (set 1, one slot that every token visits: k = 1) in one launch.  On its own
+// the shared expert's few hundred rows are a chain of K-tiles that neither the memory nor the matrix cores limit; here it
+// runs beside the routed experts' stream, which leaves both idle (T = 256, d_h = 7168, d_e = 2048, shared width 2048: the
+// two launches 168 + 77 us).  Its first-stage workgroups have the lowest ids, because their chains are the longest, and
+// the numbers of its blocks and of those ids follow from T; then the routed first stage, and the second stages in
+// the same order, so that again no workgroup waits for one with a higher id.  Every block has workgroups of its own, and
+// the second stages have the same parity of K-steps.  Layer steps with a shared expert, two FFN launches and one, us: T = 256
+// as above 285 -> 243, T = 8 96 -> 83; d_h = 2048, d_e = 1408, shared width 1408: T = 8 (two layers) 88 -> 69, T = 128 67 -> 59,
+// T = 512 107 -> 89, T = 1000 140 -> 119.
+struct SharedArgs {
+    StreamArgs set[2];
+    unsigned shared_blocks;              // the shared list's number of blocks, at most
+};
+
+// Reports a list that was cut for another block size.
+__device__ __forceinline__ bool list_fits(int4 head, int rows, int *ctrl) {
+    if (head.y == rows) return true;
+    if (threadIdx.x == 0 && blockIdx.x == 0)
+        __hip_atomic_fetch_or(ctrl + moe::kCtrlStatus, 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return false;
+}
+
+template <bool EVEN1, bool EVEN2, int TT, int WR>
+__global__ __launch_bounds__(kThreads, TT == 2 ? 4 : 3)
+void ffn_stream_shared_kernel(SharedArgs p) {
+    __shared__ __attribute__((aligned(16))) char lds[kWaves * 2 * TT * MOE_WAVE * 16];
+    __shared__ int s_ok;
+    // The arguments by set, without a copy: a load from the kernel's argument segment with a computed offset.
+    const StreamArgs *sets = (const StreamArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+    const unsigned id = blockIdx.x, n1s = p.shared_blocks * p.set[1].s[0].tiles_pad;
+    const bool first = id < n1s;                                     // of the shared expert's first stage
+    const unsigned item1 = first ? p.set[1].s[0].pad_div(id) : p.set[0].s[0].pad_div(id - n1s);
+    const unsigned guess = 1 + item1, last = first ? p.set[1].list_last : p.set[0].list_last;
+    const int4 head_r = load_const(p.set[0].blocks, 0), head_s = load_const(p.set[1].blocks, 0);
+    const int4 ent1 = load_const(first ? p.set[1].blocks : p.set[0].blocks, guess < last ? guess : last);
+    const int min_r = load_const(p.set[0].ctrl, 0).w, min_s = load_const(p.set[1].ctrl, 0).w;
+    asm volatile("" ::"s"(head_r.x), "s"(head_s.x), "s"(ent1.x), "s"(ent1.y), "s"(ent1.z), "s"(ent1.w), "s"(min_r), "s"(min_s));
+    const bool ok_r = list_fits(head_r, TT * 16, p.set[0].ctrl), ok_s = list_fits(head_s, TT * 16, p.set[1].ctrl);
+    const unsigned blocks_r = ok_r ? static_cast<unsigned>(head_r.x) : 0u, blocks_s = ok_s ? static_cast<unsigned>(head_s.x) : 0u;
+    const int ks1 = p.set[0].s[0].KS, ks2_r = p.set[0].s[1].KS, ks2_s = p.set[1].s[1].KS;
+    const unsigned n1r = blocks_r * p.set[0].s[0].tiles_pad, n2s = blocks_s * p.set[1].s[1].tiles_pad,
+                   n2r = blocks_r * p.set[0].s[1].tiles_pad;
+    bool shared = first;
+    if (id >= n1s + n1r) shared = id - (n1s + n1r) < n2s;
+    const StreamArgs &a = sets[shared ? 1 : 0];
+    // the routed slots are cut as in a launch of their own; the shared slot's chain may also hide behind the routed stream
+    const int wide = shared ? wide_on(head_s, (p.set[1].s[0].tiles + kWaves - 1) / kWaves, min_s, ks1, ks2_s, stream_ns(blocks_r, ks1, ks2_r))
+                            : wide_on(head_r, (p.set[0].s[0].tiles + kWaves - 1) / kWaves, min_r, ks1, ks2_r);
+    if (id < n1s + n1r) {
+        if (item1 >= (first ? blocks_s : blocks_r)) return;
+        const unsigned tile = (first ? id : id - n1s) - item1 * a.s[0].tiles_pad;
+        run_item<true, EVEN1, TT, WR>(a, a.s[0], lds, &s_ok, wide, item1, tile, ent1);
+    } else {
+        const unsigned id2 = id - (n1s + n1r) - (shared ? 0 : n2s);
+        if (!shared && id2 >= n2r) return;
+        const unsigned item = a.s[1].pad_div(id2);
+        run_item<false, EVEN2, TT, WR>(a, a.s[1], lds, &s_ok, wide, item, id2 - item * a.s[1].tiles_pad, load_const(a.blocks, 1 + item));
+    }
+}
+
+template <bool L1, bool L2>
+void launch_shared(const SharedArgs &p, int block_rows, unsigned blocks, hipStream_t st) {
+    if (block_rows == 32) hipLaunchKernelGGL((ffn_stream_shared_kernel<L1, L2, 2, 64>), dim3(blocks), dim3(kThreads), 0, st, p);
+    else hipLaunchKernelGGL((ffn_stream_shared_kernel<L1, L2, 4, 64>), dim3(blocks), dim3(kThreads), 0, st, p);
+}
+
 template <bool L1, bool L2, bool WRAP>
 void launch(const StreamArgs &a, int block_rows, unsigned blocks, hipStream_t st) {
     if (block_rows == 32) hipLaunchKernelGGL((ffn_stream_kernel<L1, L2, 2, 64, WRAP>), dim3(blocks), dim3(kThreads), 0, st, a);
@@ -1011,42 +1080,72 @@ void launch_even(const StreamArgs &a, int block_rows, unsigned blocks, hipStream
     else launch<false, false, WRAP>(a, block_rows, blocks, st);
 }
 
-}  // namespace
-
-namespace moe {
-
-int launch_ffn_stream(const void *X, const void *W13p, const void *W2p, int T, int k, int C, int d_h, int d_e,
-                      const int32_t *blocks, const int32_t *perm, int *ctrl, uint16_t *act,
-                      float *Yp, hipStream_t st) {
-    const int block_rows = ffn_block_rows(T);
-    const long long items = ffn_max_blocks(T, k, C);
-    if (items > kMaxItems) return MOE_ESHAPE;
+StreamArgs stream_args(const moe::FfnCall &c, int T, int d_h) {
+    const int block_rows = moe::ffn_block_rows(T);
     StreamArgs a;
-    a.blocks = blocks; a.perm = perm; a.act = act; a.Yp = Yp; a.ctrl = ctrl; a.k_div = fast_div(k);
-    a.list_last = static_cast<unsigned>(items);
+    a.blocks = c.blocks; a.perm = c.perm; a.act = c.act; a.Yp = c.Yp; a.ctrl = c.ctrl; a.k_div = fast_div(c.k);
+    a.list_last = static_cast<unsigned>(moe::ffn_max_blocks(T, c.k, c.C));
     a.spin_limit = 1 << 20;
-    a.act_block_bytes = static_cast<uint32_t>(ffn_act_block_bytes(T, d_e));
-    a.has_gemm = ffn_has_gemm(T) ? 1 : 0;
-    a.s[0].B = static_cast<const uint16_t *>(X);
-    a.s[0].Wp = static_cast<const char *>(W13p);
-    a.s[0].tiles = d_e / 16; a.s[0].KS = d_h / 32; a.s[0].b_stride = d_h; a.s[0].out_stride = 0;
-    a.s[1].B = act;
-    a.s[1].Wp = static_cast<const char *>(W2p);
-    a.s[1].tiles = d_h / 32; a.s[1].KS = d_e / 32; a.s[1].b_stride = 0; a.s[1].out_stride = d_h;
+    a.act_block_bytes = static_cast<uint32_t>(moe::ffn_act_block_bytes(T, c.d_e));
+    a.has_gemm = moe::ffn_has_gemm(T) ? 1 : 0;
+    a.s[0].B = static_cast<const uint16_t *>(c.X);
+    a.s[0].Wp = static_cast<const char *>(c.W13p);
+    a.s[0].tiles = c.d_e / 16; a.s[0].KS = d_h / 32; a.s[0].b_stride = d_h; a.s[0].out_stride = 0;
+    a.s[1].B = c.act;
+    a.s[1].Wp = static_cast<const char *>(c.W2p);
+    a.s[1].tiles = d_h / 32; a.s[1].KS = c.d_e / 32; a.s[1].b_stride = 0; a.s[1].out_stride = d_h;
     a.s[0].items = a.s[0].tiles;
     a.s[1].items = block_rows == 32 ? a.s[1].tiles : (a.s[1].tiles + 1) / 2;   // 64-row launch: a stage-2 workgroup owns a pair of tiles
     for (int i = 0; i < 2; ++i) {
         a.s[i].tiles_pad = (a.s[i].items + 7) / 8 * 8;
         a.s[i].pad_div = fast_div(a.s[i].tiles_pad);
     }
+    return a;
+}
+
+}  // namespace
+
+namespace moe {
+
+int launch_ffn_stream(const FfnCall &c, int T, int d_h, hipStream_t st) {
+    const long long items = ffn_max_blocks(T, c.k, c.C);
+    if (items > kMaxItems) return MOE_ESHAPE;
+    const StreamArgs a = stream_args(c, T, d_h);
     const long long lanes = items < kFfnLaneBlocks ? items : kFfnLaneBlocks;
     const long long n1 = lanes * a.s[0].tiles_pad, n2 = lanes * a.s[1].tiles_pad;
     if (n1 + n2 > 0x7fffffffLL) return MOE_ESHAPE;
     // only a batch whose list can be longer than the lanes needs the code that walks it
-    if (items > kFfnLaneBlocks) launch_even<true>(a, block_rows, static_cast<unsigned>(n1 + n2), st);
-    else launch_even<false>(a, block_rows, static_cast<unsigned>(n1 + n2), st);
+    if (items > kFfnLaneBlocks) launch_even<true>(a, ffn_block_rows(T), static_cast<unsigned>(n1 + n2), st);
+    else launch_even<false>(a, ffn_block_rows(T), static_cast<unsigned>(n1 + n2), st);
     return MOE_OK;
 }
 
-}  // namespace moe
+// Routed blocks that the launch of two sets has workgroups for.  It has no loop over a long list, and the surplus of its grid
+// costs more the larger the bound is (us a step with the shared expert, two launches and one: bound 131, d_h = 7168,
+// T = 380 330 and 271; 161, T = 900 392 and 380; 204, d_h = 2048, d_e = 768, T = 1500 97.0 and 90.5; 195, d_e = 1408,
+// T = 1900 172.5 and 164.1; 267, d_e = 768, T = 2000 110.8 and 113.0; 286, d_h = 7168, T = 2000 608 and 616).
+constexpr long long kSharedMaxBlocks = 224;
+bool ffn_stream_takes_shared(const FfnCall &c, const FfnCall &sh, int T, int d_h) {
+    const long long items = ffn_max_blocks(T, c.k, c.C), items_s = ffn_max_blocks(T, sh.k, sh.C);
+    if (ffn_has_gemm(T) || items > kSharedMaxBlocks || items_s > kFfnLaneBlocks || (c.d_e / 32) % 2 != (sh.d_e / 32) % 2) return false;
+    const StreamArgs r = stream_args(c, T, d_h), s = stream_args(sh, T, d_h);
+    return items * (r.s[0].tiles_pad + r.s[1].tiles_pad) + items_s * (s.s[0].tiles_pad + s.s[1].tiles_pad) <= 0x7fffffffLL;
+}
 
+void launch_ffn_stream_shared(const FfnCall &c, const FfnCall &sh, int T, int d_h, hipStream_t st) {
+    SharedArgs p;
+    p.set[0] = stream_args(c, T, d_h);
+    p.set[1] = stream_args(sh, T, d_h);
+    const unsigned items = static_cast<unsigned>(ffn_max_blocks(T, c.k, c.C));
+    p.shared_blocks = static_cast<unsigned>(ffn_max_blocks(T, sh.k, sh.C));
+    const unsigned blocks = items * (p.set[0].s[0].tiles_pad + p.set[0].s[1].tiles_pad) +
+                            p.shared_blocks * (p.set[1].s[0].tiles_pad + p.set[1].s[1].tiles_pad);
+    const int block_rows = ffn_block_rows(T);
+    const bool l1 = p.set[0].s[0].KS % 2 == 0, l2 = p.set[0].s[1].KS % 2 == 0;
+    if (l1 && l2) launch_shared<true, true>(p, block_rows, blocks, st);
+    else if (l1) launch_shared<true, false>(p, block_rows, blocks, st);
+    else if (l2) launch_shared<false, true>(p, block_rows, blocks, st);
+    else launch_shared<false, false>(p, block_rows, blocks, st);
+}
+
+}  // namespace moe

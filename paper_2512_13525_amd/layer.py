@@ -151,11 +151,11 @@ class LayerStep:
         B.moe_shared_dispatch(c.T, self.s_slot_off, self.s_perm, self.s_blocks)
 
     def step_fused_shared(self, logits, X, stream=None, W13=None, W2=None):
-        """front, routed FFN, shared-expert FFN, combine of both (four launches)."""
+        """front, routed and shared-expert FFN, combine of both (three launches; four where the two FFNs cannot share one)."""
         c = self.cfg
         self.front(logits, stream)
-        self.ffn(X, stream, W13, W2)
-        B.moe_grouped_ffn(X, self.s_W13, self.s_W2, c.T, 1, 1, c.d_h, self.d_s, self.dtype, self.s_slot_off,
-                          self.s_perm, self.s_blocks, self.s_Yp, self.s_workspace, stream=stream)
+        B.moe_grouped_ffn_shared(X, self.W13 if W13 is None else W13, self.W2 if W2 is None else W2, c.T, c.k, c.C, c.d_h, c.d_e,
+                                 self.dtype, self.slot_off, self.perm, self.blocks, self.Yp, self.workspace, self.s_W13, self.s_W2,
+                                 self.d_s, self.s_slot_off, self.s_perm, self.s_blocks, self.s_Yp, self.s_workspace, stream=stream)
         B.moe_combine_shared(self.Yp, self.pos, self.topk_w, self.s_Yp, c.T, c.k, c.d_h, self.dtype, self.Y, stream=stream)
         return self.Y

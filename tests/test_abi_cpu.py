@@ -90,6 +90,11 @@ def test_argument_validation_without_launch():
     assert L.moe_grouped_ffn(None, None, None, 4, 2, 5, 128, 64, 7, None, None, None, None, None, 0, None) == B.MOE_EINVAL
     assert L.moe_grouped_ffn(None, None, None, 0, 2, 5, 128, 64, B.MOE_DTYPE_BF16, None, None, None, None, None, 0,
                              None) == B.MOE_OK
+    # both sets of experts are checked before anything is launched
+    both = lambda T, d_h, d_e, d_s, dt=B.MOE_DTYPE_BF16: L.moe_grouped_ffn_shared(
+        None, None, None, T, 2, 5, d_h, d_e, dt, None, None, None, None, None, 0, None, None, d_s, None, None, None, None, None, 0, None)
+    assert both(4, 128, 64, 100) == B.MOE_EINVAL and both(4, 100, 64, 64) == B.MOE_ESHAPE and both(4, 128, 64, 64, 7) == B.MOE_EINVAL
+    assert both(0, 128, 64, 100) == B.MOE_ESHAPE and both(0, 128, 64, 0) == B.MOE_EINVAL and both(0, 128, 64, 64) == B.MOE_OK
     assert L.moe_combine(None, None, None, 4, 2, 130, B.MOE_DTYPE_F32, None, None) == B.MOE_ESHAPE
     assert L.moe_combine(None, None, None, 4, 2, 128, B.MOE_DTYPE_F32, None, None) == B.MOE_EINVAL
     assert L.moe_pack_weights_bf16(None, None, 2, 100, 64, None, None, None) == B.MOE_ESHAPE

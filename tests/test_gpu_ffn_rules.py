@@ -127,3 +127,61 @@ def test_short_list_of_a_batch_that_could_have_a_long_one_time():
         ws, Yp = d.buffers(d_h, d_e)
         t[T] = device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws), n=5)
     assert t[1500] < 1.09 * t[600], t
+
+
+@pytest.mark.parametrize("counts,T,k,d_h,d_e,d_s,wide_min", [
+    ([1, 0, 2], 2, 2, 64, 64, 128, 0),                                   # smallest; a slot without requests
+    ([0, 0], 33, 1, 96, 96, 160, 0),                                     # nothing routed here, two shared blocks, odd K-steps
+    ([31, 32, 33, 64, 65, 100], 383, 1, 160, 96, 32, 0),                 # last batch in blocks of 32 rows
+    ([31, 32, 33, 64, 65, 100], 383, 1, 160, 96, 32, 1),                 # both sets' long slots as tiled-GEMM blocks
+    ([63, 64, 65, 129, 0, 17], 384, 2, 128, 192, 64, 1),                 # first batch in blocks of 64 rows
+    ([700, 5, 64, 130], 1000, 1, 64, 64, 192, 0),
+    ([28 + s for s in range(100)], 1984, 4, 64, 64, 64, 0),              # bound of 224 blocks: one launch
+    ([28 + s for s in range(101)], 1984, 4, 64, 64, 64, 0),              # 225: two
+    ([40, 9], 50, 1, 64, 96, 64, 0),                                     # parity of the second stages differs: two
+])
+def test_routed_and_shared_experts_in_one_call(counts, T, k, d_h, d_e, d_s, wide_min):
+    """moe_grouped_ffn_shared: both sets' rows against the oracle, twice on the same workspaces, and a list that was cut for
+    another block size is refused without touching the other set."""
+    d, sh = Dispatch(counts, T, k, seed=T), Dispatch([T], T, 1)
+    B.moe_shared_dispatch(T, *sh.dev)
+    if d.n == 0:
+        d.dev[1] = torch.zeros((1,), dtype=torch.int32, device="cuda")     # an empty tensor has no address
+    cfg = W.MoEConfig("shared", E=d.C, k=k, d_h=d_h, d_e=d_e, T=T, n_inst=1, C=d.C, zipf_s=0.0, seed=5)
+    X = W.activations(cfg)
+    W13, W2 = (np.stack(w) for w in zip(*(W.expert_weights(cfg, e) for e in range(d.C))))
+    ws13, ws2 = W.shared_expert_weights(cfg, d_s)
+    want = [ffn.grouped_ffn(X, W13, W2, d.off, d.perm, k), ffn.expert_ffn(X, ws13, ws2)]
+    packed = []
+    for w13, w2, n, width in ((W13, W2, d.C, d_e), (ws13[None], ws2[None], 1, d_s)):
+        a, b = to_device_bf16(w13), to_device_bf16(w2)
+        packed.append((torch.empty_like(a), torch.empty_like(b)))
+        B.moe_pack_weights_bf16(a, b, n, d_h, width, *packed[-1])
+    (ws, Yp), (s_ws, Ys) = d.buffers(d_h, d_e), sh.buffers(d_h, d_s)
+    X = to_device_bf16(X)
+    for w in (ws, s_ws):
+        B.moe_workspace_set_option(w, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, wide_min)
+
+    def call(s_list):
+        Yp.fill_(123.0)
+        Ys.fill_(123.0)
+        B.moe_grouped_ffn_shared(X, *packed[0], T, k, d.C, d_h, d_e, B.MOE_DTYPE_BF16, *d.dev, Yp, ws, *packed[1], d_s,
+                                 *sh.dev[:2], s_list, Ys, s_ws)
+        torch.cuda.synchronize()
+        return Yp.cpu().numpy(), Ys.cpu().numpy()
+
+    def check(got, ref):
+        num, den = np.linalg.norm(got - ref, axis=1), np.linalg.norm(ref, axis=1)
+        assert (num <= 2.5 * TOL_BF16 * den + 1e-30).all()
+
+    for _ in range(2):
+        y, s = call(sh.dev[2])
+        assert (y[d.n:] == 123.0).all()
+        check(y[:d.n], want[0])
+        check(s, want[1])
+        assert B.moe_workspace_status(ws) == 0 and B.moe_workspace_status(s_ws) == 0
+    other = sh.dev[2].clone()
+    other[1] = 96 - other[1]
+    y, s = call(other)
+    check(y[:d.n], want[0])
+    assert (s == 123.0).all() and B.moe_workspace_status(ws) == 0 and B.moe_workspace_status(s_ws) == 2
