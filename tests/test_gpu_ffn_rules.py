@@ -185,3 +185,31 @@ def test_routed_and_shared_experts_in_one_call(counts, T, k, d_h, d_e, d_s, wide
     y, s = call(other)
     check(y[:d.n], want[0])
     assert (s == 123.0).all() and B.moe_workspace_status(ws) == 0 and B.moe_workspace_status(s_ws) == 2
+
+
+@pytest.mark.parametrize("counts,T,k,d_h,d_e", [
+    ([1], 1, 1, 4, 4),                                                   # one K-step of four columns, one channel tile of four
+    ([15, 0, 16, 17, 33, 1], 41, 2, 20, 36),
+    ([2 + s % 30 for s in range(70)] + [0, 40], 700, 2, 68, 12),         # slots over two rounds of the scan
+    ([100, 3], 103, 1, 640, 132),                                        # more K-steps than a round of the wavefronts takes
+    ([0, 0, 5], 9, 1, 516, 1028),
+])
+def test_f32_row_tiles(counts, T, k, d_h, d_e):
+    """The fp32 path at the edges of its tiles of 16 rows and 16 channels and of its K-steps of 16 columns, rows against the oracle.
+    Each sum rounds once per level of a tree of at most 4 + 7 levels per 512 columns, twice over (both matrices): some 30 roundings of
+    6e-8 on sums whose terms are some 3 times as large as the result."""
+    d = Dispatch(counts, T, k, seed=T)
+    cfg = W.MoEConfig("rows32", E=d.C, k=k, d_h=d_h, d_e=d_e, T=T, n_inst=1, C=d.C, zipf_s=0.0, dtype="f32", seed=9)
+    X = W.activations(cfg)
+    W13, W2 = (np.stack(w) for w in zip(*(W.expert_weights(cfg, e) for e in range(d.C))))
+    want = ffn.grouped_ffn(X, W13, W2, d.off, d.perm, k)
+    ws = torch.empty((B.moe_workspace_bytes(T, k, d.C, d_h, d_e, B.MOE_DTYPE_F32),), dtype=torch.uint8, device="cuda")
+    B.moe_workspace_init(ws)
+    Yp = torch.full((T * k, d_h), 123.0, dtype=torch.float32, device="cuda")
+    B.moe_grouped_ffn(torch.from_numpy(X).cuda(), torch.from_numpy(W13).cuda(), torch.from_numpy(W2).cuda(), T, k, d.C, d_h, d_e,
+                      B.MOE_DTYPE_F32, d.dev[0], d.dev[1], None, Yp, ws)
+    torch.cuda.synchronize()
+    got = Yp.cpu().numpy()
+    assert (got[d.n:] == 123.0).all()
+    num, den = np.linalg.norm(got[:d.n] - want, axis=1), np.linalg.norm(want, axis=1)
+    assert (num <= 6e-6 * den + 1e-30).all(), float((num / den).max())
