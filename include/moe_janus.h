@@ -397,16 +397,18 @@ int moe_grouped_ffn_static(const void *X_dev, const void *W13_dev, const void *W
  *                                    before it gives up (default 2^20).  For tests of the overrun path.
  *   MOE_WS_OPT_WIDE_MIN_WORKGROUPS   slots with more than 64 requests are computed as tiled GEMMs,
  *                                    but only when the batch has enough blocks of them to fill the
- *                                    chip: over blocks of 64 rows by workgroups of the same launch
- *                                    when (number of 64-row blocks of those slots) x (ceil(d_e / 64)
+ *                                    chip: over blocks of 64 rows when
+ *                                    (number of 64-row blocks of those slots) x (ceil(d_e / 64)
  *                                    workgroups per block) >= this value (default 256; by default
  *                                    also from 64 such workgroups on when the launch has enough
- *                                    other experts to stream to hide them); in batches
- *                                    of at least 2048 tokens over blocks of 128 rows by two launches
- *                                    of their own when (number of 128-row blocks) x (workgroups per
- *                                    block) >= this value (default 512), which takes precedence.
+ *                                    other experts to stream to hide them).
  *                                    Otherwise they are cut into streaming items like every other
- *                                    slot.  Results do not depend on it beyond rounding order.
+ *                                    slot.  In large batches (from 2048 tokens on, and below where
+ *                                    T x d_h x d_e >= 12e9) they are tiled GEMMs unless they are a few blocks that
+ *                                    nothing hides, over blocks of 128 rows when
+ *                                    (number of 128-row blocks) x ceil(d_e / 128) >= this
+ *                                    value (default 176), else of 64 rows; any value > 0 makes
+ *                                    them tiled GEMMs.  Results do not depend on it beyond rounding order.
  */
 #define MOE_WS_OPT_SPIN_LIMIT            0
 #define MOE_WS_OPT_WIDE_MIN_WORKGROUPS   1

@@ -75,7 +75,7 @@ inline size_t ffn_stream_act_bytes(int T, int k, int C, int d_e) {
 struct FfnCall {
     const void *X, *W13p, *W2p;
     int k, C, d_e;
-    const int32_t *blocks, *perm;
+    const int32_t *slot_off, *blocks, *perm;
     int *ctrl;                           // the workspace's control region
     uint16_t *act;                       // ffn_stream_act_bytes(T, k, C, d_e) bytes
     float *Yp;
@@ -88,29 +88,16 @@ int launch_ffn_stream(const FfnCall &c, int T, int d_h, hipStream_t st);
 bool ffn_stream_takes_shared(const FfnCall &c, const FfnCall &sh, int T, int d_h);
 void launch_ffn_stream_shared(const FfnCall &c, const FfnCall &sh, int T, int d_h, hipStream_t st);
 
-// Batches of at least kGemmMinTokens tokens: slots with more than 64 requests as blocks of 128 rows in
-// two tiled-GEMM launches of their own (ffn_wide.hip, three workgroups of 168 registers per CU),
-// when the list counts enough 128-row blocks (header word 3) for kGemmMinWorkgroups first-stage
-// workgroups; the streaming launch then skips those slots.  Every kernel takes the decision from
-// the list's header in the same way.  `act_rows` holds T*k rows of d_e bf16 behind the streaming
-// launch's intermediate.
-constexpr int kGemmMinTokens = 2048;
-inline bool ffn_has_gemm(int T) { return T >= kGemmMinTokens; }
-// Two first-stage workgroups per CU.  Which side is faster past this line depends on the rows of the slots, which the
-// list's header does not tell: launches of their own against items of the streaming launch, us, d_h x d_e,
-//   7168 x 2048, 640 workgroups: slots of 78 rows 388 and 518, of 206 337 and 406, of 512 289 and 265 (512 workgroups);
-//   1024 x 512, 512: 78 rows 65 and 84;   3072 x 1024, 800: 200 and 226;
-//   4096 x 1536, 528: 206 rows 177 and 204, 960: 512 rows 447 and 391 (a whole layer);   2048 x 1408, 528 to 968: 1.02 to 1.25 the other way.
-// A line at 1280 loses up to a third on the former and gains up to a fifth on the latter; this one loses less.
-constexpr int kGemmMinWorkgroups = 512;
-constexpr int kWideWaves = 4;            // wavefronts (= packed weight tiles) of a tiled-GEMM workgroup
-inline int ffn_gemm_tiles1(int d_e) { return (d_e / 16 + kWideWaves - 1) / kWideWaves; }
-__device__ __forceinline__ bool ffn_gemm_on(int4 head, int tiles1, int override_min) {
-    return head.y == 64 && head.w > 0 && head.w * tiles1 >= (override_min > 0 ? override_min : kGemmMinWorkgroups);
+// Batches that take the launch for large batches (ffn_big_kernel; block lists of 64 rows): from 2048 tokens on, and below
+// where T x d_h x d_e is large.  Us a layer in that launch and in the streaming launch: T = 2000, d_h = 4096, d_e = 1536 204 and 223;
+// T = 1000, d_h = 7168, d_e = 2048 259 and 263; but T = 1000, d_h = 4096, d_e = 1536 155 and 152; d_h = 2048, d_e = 1408 97 and 89; T = 2000
+// 120 and 114.  From 2048 tokens on it is the faster one where the batch has many wide blocks, which the host cannot know (64 slots of 250
+// rows, d_h = 1024, d_e = 512 102 and 131; T = 4000, d_h = 2048, d_e = 768, zipf 1 90 and 86).
+constexpr int kBigMinTokens = 2048;
+constexpr long long kBigWork = 12000000000LL;
+inline bool ffn_is_big(int T, int d_h, int d_e) {
+    return T >= kBigMinTokens || (ffn_block_rows(T) == 64 && static_cast<long long>(d_h) * d_e >= kBigWork / T);
 }
-int launch_ffn_wide(const void *X, const void *W13p, const void *W2p, int T, int k, int C, int d_h, int d_e,
-                    const int32_t *blocks, const int32_t *perm, const int *ctrl, uint16_t *act_rows,
-                    float *Yp, hipStream_t st);
 
 inline bool aligned(const void *p, size_t a) { return (reinterpret_cast<uintptr_t>(p) % a) == 0; }
 

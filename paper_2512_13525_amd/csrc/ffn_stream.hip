@@ -25,7 +25,8 @@
 // blocks of 64 rows by workgroups of the same launch instead (wide_item): a workgroup takes four
 // channel tiles through the whole K dimension, shares the token rows of the block between them
 // through LDS, and the blocks of a slot are dealt to the workgroups so that they find the
-// expert's tiles in their XCD's L2 (run_wide).
+// expert's tiles in their XCD's L2 (run_wide).  Large batches have a launch of their own kind
+// (ffn_big_kernel): the same two stages and hand-off, larger wide blocks first, streaming items for the rest.
 //
 // Both stages run in ONE launch: the stage-2 workgroups have the higher ids, so the hardware
 // starts them only after every stage-1 workgroup has been started, and they fill the compute
@@ -39,7 +40,7 @@
 // writing workgroup, and no workgroup reads a line before its block is ready, so plain loads see
 // the data; counters and flags are agent-scope atomics.  The last stage-2 workgroup of a block to
 // get through the wait clears the block's control lines for the next call.
-#include "common.h"
+#include "dispatch_dev.h"
 
 namespace {
 
@@ -97,7 +98,6 @@ struct StreamArgs {
     int spin_limit;
     unsigned list_last;                  // index of the last entry the work list has room for
     uint32_t act_block_bytes;            // bytes of `act` per entry of the work list: R rows x d_e rounded up to 64 channels
-    int has_gemm;                        // the batch is large enough for the separate tiled-GEMM launches (common.h)
 };
 
 // The work list and the header of the control region do not change while the launch runs: read through the constant address
@@ -250,6 +250,22 @@ __device__ __forceinline__ bool wait_block_ready(const StreamArgs &a, int *s_ok,
     }
     lds_barrier();
     return *s_ok != 0;
+}
+
+// A stage-1 workgroup announces its part of a block (one of n): every thread waits for its own act stores to be
+// acknowledged, then one thread bumps the block's counter and, if it completes the count, raises the ready flags (every other
+// part's stores were acknowledged before its bump).
+__device__ __forceinline__ void announce_tiles(const StreamArgs &a, int item, int n) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int *blk = a.ctrl + (item + 1) * kCtrlBlockInts;
+        if (__hip_atomic_fetch_add(blk, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n - 1) {
+#pragma unroll
+            for (int c = 1; c <= kCtrlCopies; ++c)
+                __hip_atomic_store(blk + c * kCtrlLineInts, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
 }
 
 // The rows of a stage-2 item whose block never became ready: quiet NaNs, so that the combine
@@ -726,24 +742,209 @@ __device__ __forceinline__ void wide_item(const StreamArgs &a, const StageArgs &
             }
         }
     }
-    if constexpr (STAGE1) {
-        // announce the tile group: stores acknowledged, then the counter of the leading entry
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (tid == 0) {
-            int *blk = a.ctrl + (item + 1) * kCtrlBlockInts;
-            if (__hip_atomic_fetch_add(blk, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_groups - 1) {
+    if constexpr (STAGE1) announce_tiles(a, item, n_groups);
+}
+
+// The same in the launch of large batches (ffn_big_kernel: two workgroups a CU): blocks of up to 64 or 128 rows, two packed tiles a
+// wavefront, eight a workgroup.  A token fragment read from LDS then serves four matrix instructions, and a K-tile's operands
+// serve twice as many: matrix cores : L1 : LDS = 512 : 640 : 320 cycles a K-tile with 64 rows and 1024 : 768 : 640 with 128, where
+// one packed tile a wavefront and 64 rows need 256 : 384 : 320 and such workgroups mostly add the three up.  Weights: a ring of four
+// (128 rows: two) K-tiles in registers, each K-step's part requested again as soon as it is multiplied.  Token rows: two (one)
+// K-tiles ahead in registers, a double buffer in LDS that is written between the two K-steps of the K-tile before; one barrier a K-tile.
+template <bool STAGE1, int RT>
+__device__ __forceinline__ void wide_item2(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok,
+                                           int item, int group, int n_groups, int slot, int row0, int m) {
+    constexpr int P = 2;                                             // packed tiles of a wavefront
+    constexpr int F = 2 * P;                                         // weight fragments of a K-step
+    constexpr int kLoadsB = RT * 16 * 8 / kThreads;                  // 16-byte pieces of a K-tile of the token rows per thread
+    constexpr int kBufBytes = RT * 16 * 128;
+    constexpr int kRing = RT == 4 ? 4 : 2;                           // K-tiles of weights in flight
+    constexpr int kRingB = RT == 4 ? 2 : 1;                      // K-tiles of token rows in flight
+    static_assert(RT % 4 == 0, "whole loads per thread, row tiles in groups of four");
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));                                    // see wide_item
+    const int wave = __builtin_amdgcn_readfirstlane(tid / MOE_WAVE), lane = tid % MOE_WAVE;
+    const int pt0 = (group * kWaves + wave) * P;
+    const char *w[P];
 #pragma unroll
-                for (int c = 1; c <= kCtrlCopies; ++c)
-                    __hip_atomic_store(blk + c * kCtrlLineInts, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int p = 0; p < P; ++p) {
+        const int pt = pt0 + p < g.tiles ? pt0 + p : g.tiles - 1;
+        w[p] = g.Wp + (static_cast<size_t>(slot) * g.tiles + pt) * g.KS * 2048;
+    }
+    const uint32_t aoff = lane * 16;
+    const int rows_pad = (m + 15) & ~15;
+    char *act_blk = reinterpret_cast<char *>(a.act) + static_cast<size_t>(item) * a.act_block_bytes;
+
+    if constexpr (!STAGE1) {
+        if (!wait_block_ready(a, s_ok, item, group, n_groups)) {
+            const float qnan = __uint_as_float(0x7fc00000u);
+            const f32x4 v = {qnan, qnan, qnan, qnan};
+            const int cols = kWaves * P * 32, c0 = group * cols, nc = (g.tiles * 32 - c0 < cols ? g.tiles * 32 - c0 : cols) / 4;
+            for (int i = tid; i < m * nc; i += kThreads)
+                *reinterpret_cast<f32x4 *>(a.Yp + static_cast<size_t>(row0 + i / nc) * g.out_stride + c0 + (i % nc) * 4) = v;
+            return;
+        }
+    }
+    // token rows this thread fetches: piece q*256 + tid = row (q*32 + tid/8), 16-byte chunk tid%8 of the line
+    uint32_t boff[kLoadsB];
+#pragma unroll
+    for (int q = 0; q < kLoadsB; ++q) {
+        int r = q * (kThreads / 8) + (tid >> 3);
+        r = r < m ? r : m - 1;
+        boff[q] = STAGE1 ? static_cast<uint32_t>(a.perm[row0 + r]) : static_cast<uint32_t>(r) * 128 + (tid & 7) * 16;
+    }
+    asm volatile("" ::: "memory");
+    const char *bbase = STAGE1 ? reinterpret_cast<const char *>(g.B) : act_blk;
+    const size_t kt_stride = STAGE1 ? 128 : static_cast<size_t>(rows_pad) * 128;   // bytes a K-tile advances a row
+    // LDS as in wide_item
+    const uint32_t wr_lds = (tid >> 3) * 128 + (((tid & 7) ^ ((tid >> 4) & 7)) * 16);
+    const uint32_t rd_row = (lane & 15) * 128, rd_sw = (lane >> 1) & 7, rd_g = lane >> 4;
+    const uint32_t half_back = (tid & 7) >= 4 ? 64 : 0;              // see MOE_W2_LOAD_B
+
+    const int NKT = (g.KS + 1) >> 1;                                 // K-tiles of two K-steps (the last may hold one); >= 1
+    const int last = NKT - 1;
+    f32x4 acc[RT][F];
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+        for (int f = 0; f < F; ++f) acc[rt][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    bf16x8 areg[kRing][2][F];                                        // [K-tile % kRing][K-step][fragment]
+    bf16x8 breg[kRingB][kLoadsB];
+    // Loads past the last K-tile fetch the last one again; the second K-step of a last half K-tile repeats the first.
+#define MOE_W2_LOAD_A(set, ss, j)                                                                \
+    do {                                                                                         \
+        const int j_ = (j) < last ? (j) : last;                                                  \
+        const int s_ = 2 * j_ + (ss) < g.KS ? 2 * j_ + (ss) : 2 * j_;                            \
+        _Pragma("unroll") for (int p = 0; p < P; ++p) {                                          \
+            const char *ws_ = w[p] + static_cast<size_t>(s_) * 2048;                             \
+            areg[set][ss][2 * p] = load_weights<false>(ws_ + aoff);                              \
+            areg[set][ss][2 * p + 1] = load_weights<false>(ws_ + 1024 + aoff);                   \
+        }                                                                                        \
+        asm volatile("" ::: "memory");                                                           \
+    } while (0)
+    // chunks 4..7 of the line of a half K-tile, which lie past the row or were never written, repeat chunks 0..3
+#define MOE_W2_LOAD_B(d, j)                                                                       \
+    do {                                                                                         \
+        const int j_ = (j) < last ? (j) : last;                                                  \
+        const char *bs_ = bbase + static_cast<size_t>(j_) * kt_stride;                           \
+        const uint32_t back_ = 2 * j_ + 1 >= g.KS ? half_back : 0;                               \
+        _Pragma("unroll") for (int q = 0; q < kLoadsB; ++q)                                      \
+            breg[(d) % kRingB][q] = *reinterpret_cast<const bf16x8 *>(bs_ + (boff[q] - back_));  \
+        asm volatile("" ::: "memory");                                                           \
+    } while (0)
+#define MOE_W2_STAGE(buf, d)                                                                        \
+    do {                                                                                         \
+        _Pragma("unroll") for (int q = 0; q < kLoadsB; ++q)                                      \
+            *reinterpret_cast<bf16x8 *>(lds + (buf) * kBufBytes + q * (kThreads * 16) + wr_lds) = breg[(d) % kRingB][q]; \
+        asm volatile("" ::: "memory");                                                           \
+    } while (0)
+#define MOE_W2_MMA(set, ss)                                                                      \
+    do {                                                                                         \
+        _Pragma("unroll") for (int r0_ = 0; r0_ < RT; r0_ += 4) {                                \
+            bf16x8 b_[4];                                                                        \
+            _Pragma("unroll") for (int r4 = 0; r4 < 4; ++r4)                                     \
+                b_[r4] = *reinterpret_cast<const bf16x8 *>(                                      \
+                    lds + ((set) & 1) * kBufBytes + (r0_ + r4) * 2048 + rd_row + (((4 * (ss) + rd_g) ^ rd_sw) * 16)); \
+            _Pragma("unroll") for (int r4 = 0; r4 < 4; ++r4)                                     \
+                _Pragma("unroll") for (int f = 0; f < F; ++f)                                    \
+                    acc[r0_ + r4][f] = mfma16(areg[set][ss][f], b_[r4], acc[r0_ + r4][f]);       \
+        }                                                                                        \
+        asm volatile("" ::: "memory");                                                           \
+    } while (0)
+    // The buffer written here was last read in K-tile i-1, which every wavefront finished before the barrier at its end.
+    // set = i % kRing, a literal.
+#define MOE_W2_STEP(set, i)                                                                      \
+    do {                                                                                         \
+        MOE_W2_MMA(set, 0);                                                                      \
+        MOE_W2_LOAD_A(set, 0, (i) + kRing);                                                      \
+        MOE_W2_STAGE(1 - ((set) & 1), (set) + 1);                                                \
+        MOE_W2_LOAD_B((set) + 1, (i) + 1 + kRingB);                                              \
+        MOE_W2_MMA(set, 1);                                                                      \
+        MOE_W2_LOAD_A(set, 1, (i) + kRing);                                                      \
+        lds_barrier();                                                                           \
+    } while (0)
+
+    MOE_W2_LOAD_A(0, 0, 0);
+    MOE_W2_LOAD_A(0, 1, 0);
+    if constexpr (STAGE1) {
+#pragma unroll
+        for (int q = 0; q < kLoadsB; ++q)
+            boff[q] = a.k_div(boff[q]) * static_cast<uint32_t>(g.b_stride) * 2 + (tid & 7) * 16;
+    }
+    MOE_W2_LOAD_B(0, 0);
+#pragma unroll
+    for (int d = 1; d < kRing; ++d) {
+        MOE_W2_LOAD_A(d, 0, d);
+        MOE_W2_LOAD_A(d, 1, d);
+        if (d < kRingB) MOE_W2_LOAD_B(d, d);
+    }
+    MOE_W2_STAGE(0, 0);
+    MOE_W2_LOAD_B(0, kRingB);
+    lds_barrier();
+    // the last K-tiles: their weights have been requested, the last one may be half
+#define MOE_W2_TAIL(set, i)                                                                      \
+    do {                                                                                         \
+        MOE_W2_MMA(set, 0);                                                                      \
+        if ((i) < last) {                                                                        \
+            MOE_W2_STAGE(1 - ((set) & 1), (set) + 1);                                            \
+            if (kRing > kRingB + 1) MOE_W2_LOAD_B((set) + 1, (i) + 1 + kRingB);                  \
+        }                                                                                        \
+        if (2 * (i) + 1 < g.KS) MOE_W2_MMA(set, 1);                                              \
+        lds_barrier();                                                                           \
+    } while (0)
+    const int n_full = g.KS >> 1;                                    // K-tiles with both K-steps
+    int i = 0;
+    for (; i + kRing <= n_full; i += kRing) {
+        MOE_W2_STEP(0, i);
+        MOE_W2_STEP(1, i + 1);
+        if constexpr (kRing == 4) {
+            MOE_W2_STEP(2, i + 2);
+            MOE_W2_STEP(3, i + 3);
+        }
+    }
+    // at most kRing K-tiles are left, wave-uniform
+    if (i <= last) MOE_W2_TAIL(0, i);
+    if (i + 1 <= last) MOE_W2_TAIL(1, i + 1);
+    if constexpr (kRing == 4) {
+        if (i + 2 <= last) MOE_W2_TAIL(2, i + 2);
+        if (i + 3 <= last) MOE_W2_TAIL(3, i + 3);
+    }
+#undef MOE_W2_TAIL
+#undef MOE_W2_LOAD_A
+#undef MOE_W2_LOAD_B
+#undef MOE_W2_STAGE
+#undef MOE_W2_MMA
+#undef MOE_W2_STEP
+
+    // lane l holds, per row tile, 4 consecutive channels (l/16)*4.. of row (l%16) of each fragment
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+        const int r = rt * 16 + (lane & 15);
+        if (r >= m) continue;
+#pragma unroll
+        for (int p = 0; p < P; ++p) {
+            if (pt0 + p >= g.tiles) continue;
+            if constexpr (STAGE1) {
+                const f32x4 gt = acc[rt][2 * p], up = acc[rt][2 * p + 1];
+                const uint64_t o = moe::f32x2_to_bf16x2(silu_mul(gt[0], up[0]), silu_mul(gt[1], up[1])) |
+                                   static_cast<uint64_t>(moe::f32x2_to_bf16x2(silu_mul(gt[2], up[2]), silu_mul(gt[3], up[3]))) << 32;
+                // [K-tile of stage 2 = 4 packed tiles][row][128 bytes]
+                uint64_t *dst = reinterpret_cast<uint64_t *>(act_blk + (static_cast<size_t>((pt0 + p) >> 2) * rows_pad + r) * 128 +
+                                                             ((pt0 + p) & 3) * 32 + (lane >> 4) * 8);
+                __hip_atomic_store(dst, o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else {
+                float *dst = a.Yp + static_cast<size_t>(row0 + r) * g.out_stride + (pt0 + p) * 32 + (lane >> 4) * 4;
+                *reinterpret_cast<f32x4 *>(dst) = acc[rt][2 * p];
+                *reinterpret_cast<f32x4 *>(dst + 16) = acc[rt][2 * p + 1];
             }
         }
     }
+    if constexpr (STAGE1) announce_tiles(a, item, n_groups);
 }
 
 // A slot with more than kWideMin requests is wide.  Its rows are cut into blocks of WR = 64 rows (a block
 // of 128 rows needs 64 accumulator registers more than the streaming items leave at three workgroups
-// per CU; batches of thousands of tokens take the tiled-GEMM launches of ffn_wide.hip instead).
+// per CU; large batches take ffn_big_kernel instead).
 constexpr int kWideMin = 64;
 // A wavefront of a wide workgroup runs its tile's whole K dimension, one round trip per K-tile (about
 // kWideTileNs each), so a wide workgroup lasts much longer than a streaming item.  Wide blocks pay off
@@ -771,48 +972,51 @@ __device__ __forceinline__ bool wide_on(int4 head, int groups1, int override_min
     const long long chain_ns = static_cast<long long>((ks1 + 1) / 2 + (ks2 + 1) / 2) * kWideTileNs;
     return 4 * (stream_ns(head.x, ks1, ks2) + beside_ns) >= 5 * chain_ns;
 }
-// The workgroups of a wide slot's leading entries (one entry per block of WR rows; ids tile = 0 .. tiles_pad-1
-// each) run the slot's blocks x groups of 4 tiles; all other workgroups of the slot's entries leave.
+// The workgroups of a wide slot (ids in groups of ids8 * 8 per block: the block's, tile = 0 .. ids8 * 8 - 1) run the slot's nb blocks
+// x groups of tiles; the others leave.
 // Workgroup ids go round-robin over the eight XCDs, so tile % 8 is the XCD and (leader index, tile / 8)
-// the place in that XCD's start order.  That order is walked block-fastest: the blocks of one group of
-// tiles start next to each other on one XCD, walk the expert's tiles side by side, and all but the first
+// the place in that XCD's start order.  The XCDs take runs of the pairs (group, block), block-fastest, as even as they
+// come and the longer ones first from XCD `turn` on (slots of few pairs would otherwise meet on the first XCDs: 20 slots of 150 rows,
+// d_h = 4096, d_e = 1536, T = 700 303 -> 266 us): the blocks of one group of tiles start next to each other on one XCD, walk the expert's tiles side by side, and all but the first
 // find them in that L2.  (Group-fastest, the natural order of the ids, put the sibling blocks tiles_pad / 8
 // starts apart: on a busy chip that is longer than a line survives in a streaming L2, and every block of a
-// slot fetched the expert from memory again.)  BR = rows per list entry.
+// slot fetched the expert from memory again.)  False: this workgroup has none.
+struct WidePair { int group, block; };
+__device__ __forceinline__ bool deal_wide(int leader, int tile, int ids8, int nb, int groups, int turn, WidePair &pair) {
+    const int place = leader * ids8 + (tile >> 3);                   // in the XCD's start order, within the slot
+    const int pairs = nb * groups, x = (tile - turn) & 7, each = pairs >> 3, more = pairs & 7;
+    if (place >= each + (x < more ? 1 : 0)) return false;
+    const int idx = x * each + (x < more ? x : more) + place;
+    pair = {idx / nb, idx % nb};
+    return true;
+}
+
+// In the launches of smaller batches: one entry leads each block of WR rows; all other workgroups of the slot's entries leave.
+// BR = rows per list entry.
 template <bool STAGE1, int WR, int BR>
 __device__ __forceinline__ void run_wide(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok, int item,
                                          int tile, int4 ent) {
     const int slot = ent.x, hi = ent.z, lo = ent.w;
     if ((ent.y - lo) % WR != 0) return;                              // not the leading entry of a wide block
     const int groups = (g.tiles + kWaves - 1) / kWaves;              // workgroups of a block in this stage
-    const int nb = (hi - lo + WR - 1) / WR;                          // blocks of the slot
-    const int leader = (ent.y - lo) / WR;                            // which of them this entry leads
-    const int xcd = tile & 7;
-    const int place = leader * (g.tiles_pad >> 3) + (tile >> 3);     // in the XCD's start order, within the slot
-    const int group = xcd + 8 * (place / nb), b = place % nb;
-    if (group >= groups) return;
-    item += (b - leader) * (WR / BR);                                // the block's leading entry: its control lines and `act`
-    const int row0 = lo + b * WR;
+    const int leader = (ent.y - lo) / WR;                            // which of the slot's blocks this entry leads
+    WidePair pair;
+    if (!deal_wide(leader, tile, g.tiles_pad >> 3, (hi - lo + WR - 1) / WR, groups, (item / (WR / BR) - leader) * groups, pair)) return;
+    item += (pair.block - leader) * (WR / BR);                       // the block's leading entry: its control lines and `act`
+    const int row0 = lo + pair.block * WR;
     const int m = hi - row0 < WR ? hi - row0 : WR;
     const int rt = (m + 15) >> 4;
     // up to 16 rows as two row tiles (one kind of item less; slots of 72 rows: 58 -> 61 us at d_h = 2048, d_e = 768, 173 -> 163 at
     // d_h = 4096, d_e = 1536)
-    if (rt <= 2) wide_item<STAGE1, 2>(a, g, lds, s_ok, item, group, groups, slot, row0, m);
-    else wide_item<STAGE1, 4>(a, g, lds, s_ok, item, group, groups, slot, row0, m);
+    if (rt <= 2) wide_item<STAGE1, 2>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m);
+    else wide_item<STAGE1, 4>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m);
 }
 
 // EVEN: this stage has an even number of K-steps
-// wide: 0 = every slot is cut into streaming items; 1 = slots with more than kWideMin requests are wide
-// blocks of this launch; 2 = those slots belong to the tiled-GEMM launches and are skipped here
-template <bool STAGE1, bool EVEN, int TT, int WR>
-__device__ __forceinline__ void run_item(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok, int wide,
-                                         int item, int tile, int4 ent) {
-    // ent, the block's work list entry: {slot, first row, end of the slot's rows, first of the slot's rows}
-    // a slot with more than kWideRows requests is computed as tiled GEMMs over blocks of kWideRows rows
-    if (wide && ent.z - ent.w > kWideMin) {
-        if (wide == 1) run_wide<STAGE1, WR, TT * 16>(a, g, lds, s_ok, item, tile, ent);
-        return;
-    }
+// ent, the block's work list entry: {slot, first row, end of the slot's rows, first of the slot's rows}
+template <bool STAGE1, bool EVEN, int TT>
+__device__ __forceinline__ void run_stream_item(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok, int item, int tile,
+                                                int4 ent) {
     if (tile >= g.items) return;                                 // ids that pad the tiles to a multiple of 8
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE), lane = threadIdx.x % MOE_WAVE;
     const int slot = ent.x, row0 = ent.y, hi = ent.z;
@@ -878,21 +1082,15 @@ __device__ __forceinline__ void run_item(const StreamArgs &a, const StageArgs &g
         __syncthreads();
         store_act<TT>(a, lds, (halves + 1) >> 1, item, tile, row0, hi);
     }
-    if (STAGE1) {
-        // announce the tile: every thread waits for its own act stores to be acknowledged, then
-        // one thread bumps the block's counter and, if it completes the count, raises the ready flags
-        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            int *blk = a.ctrl + (item + 1) * kCtrlBlockInts;
-            if (__hip_atomic_fetch_add(blk, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == g.tiles - 1) {
-                // last tile of the block: every other tile's stores were acknowledged before its bump
-#pragma unroll
-                for (int c = 1; c <= kCtrlCopies; ++c)
-                    __hip_atomic_store(blk + c * kCtrlLineInts, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-        }
-    }
+    if (STAGE1) announce_tiles(a, item, g.tiles);
+}
+
+// wide: slots with more than kWideMin requests are wide blocks; otherwise every slot is cut into streaming items.
+template <bool STAGE1, bool EVEN, int TT, int WR>
+__device__ __forceinline__ void run_item(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok, int wide,
+                                         int item, int tile, int4 ent) {
+    if (wide && ent.z - ent.w > kWideMin) run_wide<STAGE1, WR, TT * 16>(a, g, lds, s_ok, item, tile, ent);
+    else run_stream_item<STAGE1, EVEN, TT>(a, g, lds, s_ok, item, tile, ent);
 }
 
 // 1-D grid sized for the worst case (at most kFfnLaneBlocks blocks).  With B = min(the batch's number of
@@ -939,8 +1137,7 @@ void ffn_stream_kernel(StreamArgs a) {
         // keeps the worst-case grid of large batches small.  A stage-1 workgroup never waits, and all of them are started
         // before any stage-2 workgroup, so every flag a stage-2 workgroup waits for is raised.
         // header word 3 of the workspace (wide_min): the caller's threshold for wide blocks (0 = default)
-        const int wide = a.has_gemm && moe::ffn_gemm_on(head, (a.s[0].tiles + kWaves - 1) / kWaves, wide_min) ? 2
-                         : wide_on(head, (a.s[0].tiles + kWaves - 1) / kWaves, wide_min, a.s[0].KS, a.s[1].KS) ? 1 : 0;
+        const int wide = wide_on(head, (a.s[0].tiles + kWaves - 1) / kWaves, wide_min, a.s[0].KS, a.s[1].KS);
         const unsigned n_blocks = static_cast<unsigned>(head.x);
         const unsigned lanes = n_blocks < moe::kFfnLaneBlocks ? n_blocks : moe::kFfnLaneBlocks;
         const unsigned n1 = lanes * a.s[0].tiles_pad, n2 = lanes * a.s[1].tiles_pad;
@@ -972,13 +1169,15 @@ void ffn_stream_kernel(StreamArgs a) {
                 bool mine = false;
                 if (b < n_blocks) {
                     const int4 e = reinterpret_cast<const int4 *>(a.blocks)[1 + b];
-                    mine = !wide || e.z - e.w <= kWideMin || (wide == 1 && (e.y - e.w) % WR == 0);
+                    mine = !wide || e.z - e.w <= kWideMin || (e.y - e.w) % WR == 0;
                 }
                 const unsigned long long m = __ballot(mine);
                 if (threadIdx.x == 0) s_visit = m;
             }
             __syncthreads();
-            unsigned long long visit = s_visit;
+            unsigned long long visit = static_cast<unsigned>(__builtin_amdgcn_readfirstlane(static_cast<int>(s_visit))) |
+                                       static_cast<unsigned long long>(static_cast<unsigned>(
+                                           __builtin_amdgcn_readfirstlane(static_cast<int>(s_visit >> 32)))) << 32;
             bool first = true;
 #pragma unroll 1
             while (visit) {
@@ -1065,6 +1264,126 @@ void launch_shared(const SharedArgs &p, int block_rows, unsigned blocks, hipStre
     else hipLaunchKernelGGL((ffn_stream_shared_kernel<L1, L2, 4, 64>), dim3(blocks), dim3(kThreads), 0, st, p);
 }
 
+// ---------------------------------------------------------------------------------------------
+// Batches of at least kBigMinTokens tokens: every slot with more than kWideMin requests as wide blocks of two packed tiles a
+// wavefront, the others as streaming items (one block each), in one launch of two workgroups a CU with the registers for both.
+// The blocks are found from the slots' offsets, not from the list: a wide block has as many ids as it has groups of tiles, and
+// only a slot can have a streaming block, so the worst-case grid stays small (32000 workgroups at T = 8192, k = 8, C = 16,
+// d_h = 4096, d_e = 1536, where ids for every tile of every block of 64 rows would be 166000) and no workgroup has to walk a list.
+// Wide blocks come first: their chains are the longest and hide behind the streams.  Against blocks of 128 rows x four tiles in two
+// launches of their own before the streaming launch, us a layer: T = 8192, d_h = 4096,
+// d_e = 1536 388 -> 303, T = 3000 232 -> 193; d_h = 2048, d_e = 1408, T = 2500 151 -> 128; d_e = 768, T = 4000 98 -> 90; 64 slots of 250 rows,
+// d_h = 1024, d_e = 512 144 -> 102.  Slower where nothing is wide and the slots are many (128 slots of 64 rows, d_h = 2048, d_e = 768
+// 307 -> 317; 200 of 20 rows, d_h = 512, d_e = 256 54 -> 58).
+struct BigArgs {
+    StreamArgs a;
+    const int32_t *slot_off;
+    int C;
+    int groups[2];                       // workgroups of a wide block: groups of eight packed tiles of a stage
+};
+
+// Blocks of 128 rows from this many first-stage workgroups of them on, else of 64 rows (us, blocks of 128 and of 64 rows:
+// 192 such workgroups, d_h = 2048, d_e = 768 79 and 94; 240, d_h = 4096, d_e = 1536 207 and 220; 360 248 and 290; but 154, d_h = 2048,
+// d_e = 1408 108 and 98; 120, d_h = 4096 178 and 169; 36 168 and 144)
+constexpr int kBigMinWorkgroups = 176;
+constexpr int kBigMaxCut = 8;            // blocks of 64 rows of slots with more than kWideMin requests that may be streaming items
+
+struct BigItem { int slot, lo, hi, at, item; };
+// The slot of work item b, slot by slot in order: `groups` items for every block of 2^wr_shift rows of a slot with more than `cut` requests
+// (wide), or one for every 64 rows of the others.  at = which of the slot's items b is, item = the blocks of 64 rows of
+// the wide slots before it (a block's own number names its control lines and its part of `act`).  Uniform over the wavefront; b is in range.
+__device__ __forceinline__ BigItem find_item(const int32_t *slot_off, int C, bool wide, int cut, int wr_shift, int groups, int b, int lane) {
+    constexpr int kRounds = MOE_MAX_SLOTS / MOE_WAVE;
+    int lo[kRounds], hi[kRounds];
+#pragma unroll
+    for (int q = 0; q < kRounds; ++q) {                              // all requested at once
+        lo[q] = hi[q] = 0;
+        if (q * MOE_WAVE < C) {
+            const int s = q * MOE_WAVE + lane;
+            lo[q] = slot_off[s < C ? s : C];
+            hi[q] = slot_off[s < C ? s + 1 : C];
+        }
+    }
+    int item0 = 0;
+#pragma unroll
+    for (int q = 0; q < kRounds; ++q) {
+        if (q * MOE_WAVE >= C) break;
+        const int m = hi[q] - lo[q];
+        const bool mine = (m > cut) == wide;
+        const int n64 = mine ? (m + 63) >> 6 : 0;                    // blocks of 64 rows, items
+        const int n = wide ? (mine ? ((m + (1 << wr_shift) - 1) >> wr_shift) * groups : 0) : n64;
+        const int incl = moe::wave_incl_scan_i32(n), incl64 = moe::wave_incl_scan_i32(n64);
+        const int total = __builtin_amdgcn_readlane(incl, MOE_WAVE - 1);
+        if (b < total) {
+            const int src = __builtin_ctzll(__ballot(incl > b));
+            return {q * MOE_WAVE + src, __builtin_amdgcn_readlane(lo[q], src), __builtin_amdgcn_readlane(hi[q], src),
+                    b - __builtin_amdgcn_readlane(incl - n, src), item0 + __builtin_amdgcn_readlane(incl64 - n64, src)};
+        }
+        b -= total;
+        item0 += __builtin_amdgcn_readlane(incl64, MOE_WAVE - 1);
+    }
+    return {0, 0, 0, 0, 0};
+}
+
+// n_wide: blocks of the wide slots, n_wide64: their blocks of 64 rows; id: of the stage's wide or streaming ids.
+template <bool STAGE1, bool EVEN>
+__device__ __forceinline__ void run_big(const BigArgs &p, char *lds, int *s_ok, bool wide, int cut, bool rows128, int n_wide,
+                                        int n_wide64, unsigned id) {
+    const StreamArgs &a = p.a;
+    const StageArgs &g = a.s[STAGE1 ? 0 : 1];
+    const int groups = p.groups[STAGE1 ? 0 : 1];
+    int b = static_cast<int>(g.pad_div(id));                         // streaming: block, and tile below
+    if (wide) {
+        // Ids go round-robin over the eight XCDs; each takes an eighth of the wide items as one run, a slot's items block-fastest:
+        // the blocks of one group of tiles start next to each other on one XCD and share the expert's tiles in that L2, and the
+        // XCD needs the rows and weights of few slots.
+        const int n = n_wide * groups, x = id & 7, each = n >> 3, more = n & 7, place = static_cast<int>(id >> 3);
+        if (place >= each + (x < more ? 1 : 0)) return;
+        b = x * each + (x < more ? x : more) + place;
+    }
+    const BigItem it = find_item(p.slot_off, p.C, wide, cut, rows128 ? 7 : 6, groups, b, moe::lane_id());
+    if (!wide) {
+        run_stream_item<STAGE1, EVEN, 4>(a, g, lds, s_ok, n_wide64 + b, static_cast<int>(id) - b * g.tiles_pad,
+                                         make_int4(it.slot, it.lo + it.at * 64, it.hi, it.lo));
+        return;
+    }
+    const int wr = rows128 ? 128 : 64, nb = (it.hi - it.lo + wr - 1) / wr, group = it.at / nb, block = it.at % nb;
+    const int row0 = it.lo + block * wr, m = it.hi - row0 < wr ? it.hi - row0 : wr;
+    const int item = it.item + block * (wr / 64);
+    if (m > 64) wide_item2<STAGE1, 8>(a, g, lds, s_ok, item, group, groups, it.slot, row0, m);
+    else wide_item2<STAGE1, 4>(a, g, lds, s_ok, item, group, groups, it.slot, row0, m);
+}
+
+template <bool EVEN1, bool EVEN2>
+__global__ __launch_bounds__(kThreads, 2)
+void ffn_big_kernel(BigArgs p) {
+    __shared__ __attribute__((aligned(16))) char lds[kWaves * 2 * 4 * MOE_WAVE * 16];
+    static_assert(2 * 128 * 128 <= sizeof(lds), "the two token tiles of a wide block must fit");
+    __shared__ int s_ok;
+    const int4 head = load_const(p.a.blocks, 0);
+    const int wide_min = load_const(p.a.ctrl, 0).w;
+    if (!list_fits(head, 64, p.a.ctrl)) return;
+    const bool rows128 = head.w * p.groups[0] >= (wide_min > 0 ? wide_min : kBigMinWorkgroups);
+    // a few blocks that nothing hides are cut into streaming items as in the other launches (wide_on)
+    const bool any = wide_min > 0 || head.z > kBigMaxCut || wide_on(head, (p.a.s[0].tiles + kWaves - 1) / kWaves, 0, p.a.s[0].KS, p.a.s[1].KS);
+    const int cut = any ? kWideMin : 0x7fffffff, n_wide64 = any ? head.z : 0;
+    const int n_wide = any ? (rows128 ? head.w : head.z) : 0;
+    const unsigned n_stream = head.x - n_wide64;
+    unsigned id = blockIdx.x;
+    const unsigned w1 = (n_wide * p.groups[0] + 7u) & ~7u, s1 = n_stream * p.a.s[0].tiles_pad;
+    if (id < w1 + s1) {
+        const bool wide = id < w1;
+        run_big<true, EVEN1>(p, lds, &s_ok, wide, cut, rows128, n_wide, n_wide64, wide ? id : id - w1);
+        return;
+    }
+    id -= w1 + s1;
+    const unsigned w2 = (n_wide * p.groups[1] + 7u) & ~7u, s2 = n_stream * p.a.s[1].tiles_pad;
+    if (id < w2 + s2) {
+        const bool wide = id < w2;
+        run_big<false, EVEN2>(p, lds, &s_ok, wide, cut, rows128, n_wide, n_wide64, wide ? id : id - w2);
+    }
+}
+
 template <bool L1, bool L2, bool WRAP>
 void launch(const StreamArgs &a, int block_rows, unsigned blocks, hipStream_t st) {
     if (block_rows == 32) hipLaunchKernelGGL((ffn_stream_kernel<L1, L2, 2, 64, WRAP>), dim3(blocks), dim3(kThreads), 0, st, a);
@@ -1087,7 +1406,6 @@ StreamArgs stream_args(const moe::FfnCall &c, int T, int d_h) {
     a.list_last = static_cast<unsigned>(moe::ffn_max_blocks(T, c.k, c.C));
     a.spin_limit = 1 << 20;
     a.act_block_bytes = static_cast<uint32_t>(moe::ffn_act_block_bytes(T, c.d_e));
-    a.has_gemm = moe::ffn_has_gemm(T) ? 1 : 0;
     a.s[0].B = static_cast<const uint16_t *>(c.X);
     a.s[0].Wp = static_cast<const char *>(c.W13p);
     a.s[0].tiles = c.d_e / 16; a.s[0].KS = d_h / 32; a.s[0].b_stride = d_h; a.s[0].out_stride = 0;
@@ -1111,6 +1429,22 @@ int launch_ffn_stream(const FfnCall &c, int T, int d_h, hipStream_t st) {
     const long long items = ffn_max_blocks(T, c.k, c.C);
     if (items > kMaxItems) return MOE_ESHAPE;
     const StreamArgs a = stream_args(c, T, d_h);
+    if (ffn_is_big(T, d_h, c.d_e)) {
+        BigArgs p;
+        p.a = a;
+        p.slot_off = c.slot_off; p.C = c.C;
+        for (int i = 0; i < 2; ++i) p.groups[i] = (a.s[i].tiles + 2 * kWaves - 1) / (2 * kWaves);
+        if (items * p.groups[0] > 0x7fffffffLL || items * p.groups[1] > 0x7fffffffLL) return MOE_ESHAPE;
+        const long long grid = items * (p.groups[0] + p.groups[1]) + 16 + static_cast<long long>(c.C + kBigMaxCut) * (a.s[0].tiles_pad + a.s[1].tiles_pad);
+        if (grid > 0x7fffffffLL) return MOE_ESHAPE;
+        const bool l1 = a.s[0].KS % 2 == 0, l2 = a.s[1].KS % 2 == 0;
+        const dim3 blocks(static_cast<unsigned>(grid)), threads(kThreads);
+        if (l1 && l2) hipLaunchKernelGGL((ffn_big_kernel<true, true>), blocks, threads, 0, st, p);
+        else if (l1) hipLaunchKernelGGL((ffn_big_kernel<true, false>), blocks, threads, 0, st, p);
+        else if (l2) hipLaunchKernelGGL((ffn_big_kernel<false, true>), blocks, threads, 0, st, p);
+        else hipLaunchKernelGGL((ffn_big_kernel<false, false>), blocks, threads, 0, st, p);
+        return MOE_OK;
+    }
     const long long lanes = items < kFfnLaneBlocks ? items : kFfnLaneBlocks;
     const long long n1 = lanes * a.s[0].tiles_pad, n2 = lanes * a.s[1].tiles_pad;
     if (n1 + n2 > 0x7fffffffLL) return MOE_ESHAPE;
@@ -1127,7 +1461,7 @@ int launch_ffn_stream(const FfnCall &c, int T, int d_h, hipStream_t st) {
 constexpr long long kSharedMaxBlocks = 224;
 bool ffn_stream_takes_shared(const FfnCall &c, const FfnCall &sh, int T, int d_h) {
     const long long items = ffn_max_blocks(T, c.k, c.C), items_s = ffn_max_blocks(T, sh.k, sh.C);
-    if (ffn_has_gemm(T) || items > kSharedMaxBlocks || items_s > kFfnLaneBlocks || (c.d_e / 32) % 2 != (sh.d_e / 32) % 2) return false;
+    if (ffn_is_big(T, d_h, c.d_e) || ffn_is_big(T, d_h, sh.d_e) || items > kSharedMaxBlocks || items_s > kFfnLaneBlocks || (c.d_e / 32) % 2 != (sh.d_e / 32) % 2) return false;
     const StreamArgs r = stream_args(c, T, d_h), s = stream_args(sh, T, d_h);
     return items * (r.s[0].tiles_pad + r.s[1].tiles_pad) + items_s * (s.s[0].tiles_pad + s.s[1].tiles_pad) <= 0x7fffffffLL;
 }

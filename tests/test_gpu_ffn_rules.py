@@ -213,3 +213,37 @@ def test_f32_row_tiles(counts, T, k, d_h, d_e):
     assert (got[d.n:] == 123.0).all()
     num, den = np.linalg.norm(got[:d.n] - want, axis=1), np.linalg.norm(want, axis=1)
     assert (num <= 6e-6 * den + 1e-30).all(), float((num / den).max())
+
+
+@pytest.mark.parametrize("wide_min", [0, 1, 1 << 20])                    # the rule's choice, blocks of 128 rows, blocks of 64 rows
+@pytest.mark.parametrize("counts,k,d_h,d_e", [
+    ([64, 65, 0, 128, 129, 1, 192, 193, 257], 1, 64, 32),                # edges of both kinds of block; fewest K-steps
+    ([66, 63, 300, 17, 130], 1, 96, 160),                                # odd numbers of K-steps: a half K-tile at the end
+    ([400], 1, 224, 288),                                                # one slot: its few blocks are streaming items by the rule
+    ([70 + s % 90 for s in range(65)] + [0] * 60 + [500], 4, 320, 96),   # slots beyond the first 64; groups of tiles not full
+    ([s % 65 for s in range(130)], 4, 128, 64),                          # no wide slot
+    ([2048], 1, 512, 1056),                                              # many blocks of one slot on every XCD
+])
+def test_launch_for_large_batches(counts, k, d_h, d_e, wide_min):
+    """Batches from 2048 tokens on: wide blocks of 64 and of 128 rows and streaming items found from the slots' offsets, rows
+    against the oracle, three times on one workspace."""
+    T = 2048
+    d = Dispatch(counts, T, k, seed=len(counts))
+    cfg = W.MoEConfig("large", E=d.C, k=k, d_h=d_h, d_e=d_e, T=T, n_inst=1, C=d.C, zipf_s=0.0, seed=13)
+    X = W.activations(cfg)
+    W13, W2 = (np.stack(w) for w in zip(*(W.expert_weights(cfg, e) for e in range(d.C))))
+    want = ffn.grouped_ffn(X, W13, W2, d.off, d.perm, k)
+    d13, d2 = to_device_bf16(W13), to_device_bf16(W2)
+    p13, p2 = torch.empty_like(d13), torch.empty_like(d2)
+    B.moe_pack_weights_bf16(d13, d2, d.C, d_h, d_e, p13, p2)
+    ws, Yp = d.buffers(d_h, d_e)
+    B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, wide_min)
+    for _ in range(3):
+        Yp.fill_(123.0)
+        d.run(to_device_bf16(X), p13, p2, d_h, d_e, Yp, ws)
+        torch.cuda.synchronize()
+        got = Yp.cpu().numpy()
+        assert (got[d.n:] == 123.0).all()
+        num, den = np.linalg.norm(got[:d.n] - want, axis=1), np.linalg.norm(want, axis=1)
+        assert (num <= 2.5 * TOL_BF16 * den + 1e-30).all(), int(np.argmax(num / den))
+        assert B.moe_workspace_status(ws) == 0
