@@ -6,6 +6,7 @@ library is missing or a call fails, an exception is raised.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional
 
@@ -157,15 +158,29 @@ def _ptr(t) -> Optional[int]:
     return t.data_ptr()
 
 
+_raw_stream = _device = None
+
+
 def _stream(stream) -> Optional[int]:
     """hipStream_t of a torch stream (None = torch's current stream)."""
-    import torch
+    global _raw_stream, _device
     if stream is None:
-        raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-        if raw is not None:                   # the fast path: no Stream object is built
-            return raw(torch.cuda.current_device()) or None
+        if _raw_stream is not None:           # the fast path: no Stream object is built
+            return _raw_stream(_device()) or None
+        import torch
+        device = torch.cuda.current_device()  # initialises torch's side of the GPU
+        raw, dev = getattr(torch._C, "_cuda_getCurrentRawStream", None), getattr(torch._C, "_cuda_getDevice", None)
+        if raw is not None and dev is not None:
+            _device, _raw_stream = dev, raw
+            return raw(device) or None
         stream = torch.cuda.current_stream()
     return stream.cuda_stream or None
+
+
+@functools.lru_cache(maxsize=64)
+def _route_cfg(mode: int, renormalize: int, n_group: int, topk_group: int, scale: float):
+    """A moe_route_cfg by reference; the library only reads it."""
+    return ctypes.byref(moe_route_cfg(mode, renormalize, n_group, topk_group, scale))
 
 
 class Placement:
@@ -202,8 +217,8 @@ class Placement:
 def moe_route(logits, k: int, topk_ids, topk_w, mode: int = MOE_ROUTE_SOFTMAX, renormalize: bool = True,
               n_group: int = 1, topk_group: int = 1, scale: float = 1.0, stream=None) -> None:
     T, E = logits.shape
-    cfg = moe_route_cfg(mode, int(renormalize), n_group, topk_group, scale)
-    _check(lib().moe_route(_ptr(logits), T, E, k, ctypes.byref(cfg), _ptr(topk_ids), _ptr(topk_w),
+    cfg = _route_cfg(mode, int(renormalize), n_group, topk_group, scale)
+    _check(lib().moe_route(_ptr(logits), T, E, k, cfg, _ptr(topk_ids), _ptr(topk_w),
                            _stream(stream)), "moe_route")
 
 
@@ -251,8 +266,8 @@ def moe_route_schedule_permute(pl: Placement, g_self: int, logits, k: int, topk_
                                renormalize: bool = True, n_group: int = 1, topk_group: int = 1, scale: float = 1.0,
                                stream=None) -> None:
     T = logits.shape[0]
-    cfg = moe_route_cfg(mode, int(renormalize), n_group, topk_group, scale)
-    _check(lib().moe_route_schedule_permute(pl.handle, g_self, _ptr(logits), T, k, ctypes.byref(cfg),
+    cfg = _route_cfg(mode, int(renormalize), n_group, topk_group, scale)
+    _check(lib().moe_route_schedule_permute(pl.handle, g_self, _ptr(logits), T, k, cfg,
                                             _ptr(topk_ids), _ptr(topk_w), _ptr(rid), _ptr(act_rep), _ptr(load),
                                             _ptr(slot_count), _ptr(slot_off), _ptr(perm), _ptr(pos), _ptr(blocks),
                                             _ptr(sync),                                             _stream(stream)), "moe_route_schedule_permute")
@@ -324,8 +339,8 @@ def moe_gate_route(X, Wr, bias, k: int, logits, topk_ids, topk_w, sync, mode: in
                    stream=None) -> None:
     T, d_h = X.shape
     E = Wr.shape[0]
-    cfg = moe_route_cfg(mode, int(renormalize), n_group, topk_group, scale)
-    _check(lib().moe_gate_route(_ptr(X), _ptr(Wr), _ptr(bias), T, E, d_h, k, ctypes.byref(cfg), _ptr(logits),
+    cfg = _route_cfg(mode, int(renormalize), n_group, topk_group, scale)
+    _check(lib().moe_gate_route(_ptr(X), _ptr(Wr), _ptr(bias), T, E, d_h, k, cfg, _ptr(logits),
                                 _ptr(topk_ids), _ptr(topk_w), _ptr(sync), _stream(stream)), "moe_gate_route")
 
 
@@ -334,9 +349,9 @@ def moe_gate_route_schedule_permute(pl: Placement, g_self: int, X, Wr, bias, k: 
                                     mode: int = MOE_ROUTE_SOFTMAX, renormalize: bool = True, n_group: int = 1,
                                     topk_group: int = 1, scale: float = 1.0, stream=None) -> None:
     T, d_h = X.shape
-    cfg = moe_route_cfg(mode, int(renormalize), n_group, topk_group, scale)
+    cfg = _route_cfg(mode, int(renormalize), n_group, topk_group, scale)
     _check(lib().moe_gate_route_schedule_permute(pl.handle, g_self, _ptr(X), _ptr(Wr), _ptr(bias), T, d_h, k,
-                                                 ctypes.byref(cfg), _ptr(logits), _ptr(topk_ids), _ptr(topk_w),
+                                                 cfg, _ptr(logits), _ptr(topk_ids), _ptr(topk_w),
                                                  _ptr(rid), _ptr(act_rep), _ptr(load), _ptr(slot_count),
                                                  _ptr(slot_off), _ptr(perm), _ptr(pos), _ptr(blocks), _ptr(sync),
                                                  _stream(stream)), "moe_gate_route_schedule_permute")
