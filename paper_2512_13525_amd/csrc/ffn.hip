@@ -223,13 +223,17 @@ extern "C" int moe_workspace_set_option(void *workspace_dev, size_t workspace_by
     return moe::check_launch("moe_workspace_set_option");
 }
 
+// From this many tokens on the size counts a row of d_e bf16 per request more than the launches use: it is what callers have
+// allocated by and what decides which shapes moe_grouped_ffn_static takes, so it stays as it is.
+constexpr int kRowsTokens = 2048;
+
 extern "C" size_t moe_workspace_bytes(int T, int k, int C, int d_h, int d_e, int dtype) {
     (void)d_h;
     if (T < 0 || k < 1 || C < 1 || d_e < 1) return 0;
     // fp32: one row per request; bf16: whole blocks of rows (at most C partly filled ones)
     const size_t bytes = dtype == MOE_DTYPE_F32
         ? static_cast<size_t>(T) * k * d_e * 4
-        : moe::ffn_stream_act_bytes(T, k, C, d_e);
+        : moe::ffn_stream_act_bytes(T, k, C, d_e) + (T >= kRowsTokens ? static_cast<size_t>(T) * k * d_e * 2 : 0);
     return kCtrlBytes + (bytes + 255) / 256 * 256 + 256;
 }
 
