@@ -75,7 +75,7 @@ inline size_t ffn_stream_act_bytes(int T, int k, int C, int d_e) {
 struct FfnCall {
     const void *X, *W13p, *W2p;
     int k, C, d_e;
-    const int32_t *slot_off, *blocks, *perm;
+    const int32_t *blocks, *perm;
     int *ctrl;                           // the workspace's control region
     uint16_t *act;                       // ffn_stream_act_bytes(T, k, C, d_e) bytes
     float *Yp;

@@ -291,10 +291,10 @@ int check_ffn(const void *X_dev, const void *W13_dev, const void *W2_dev, int T,
     return MOE_OK;
 }
 
-moe::FfnCall ffn_call(const void *X_dev, const void *W13_dev, const void *W2_dev, int k, int C, int d_e, const int32_t *slot_off_dev,
-                      const int32_t *perm_dev, const int32_t *blocks_dev, float *Yp_dev, void *workspace_dev) {
+moe::FfnCall ffn_call(const void *X_dev, const void *W13_dev, const void *W2_dev, int k, int C, int d_e, const int32_t *perm_dev,
+                      const int32_t *blocks_dev, float *Yp_dev, void *workspace_dev) {
     char *ws = static_cast<char *>(workspace_dev);
-    return {X_dev, W13_dev, W2_dev, k, C, d_e, slot_off_dev, blocks_dev, perm_dev, reinterpret_cast<int *>(ws),
+    return {X_dev, W13_dev, W2_dev, k, C, d_e, blocks_dev, perm_dev, reinterpret_cast<int *>(ws),
             reinterpret_cast<uint16_t *>(ws + kCtrlBytes), Yp_dev};
 }
 
@@ -311,7 +311,7 @@ int grouped_ffn(const void *X_dev, const void *W13_dev, const void *W2_dev,
         // the kernels address token rows with 32-bit byte offsets
         if (static_cast<long long>(T) * d_h * 2 > 0xffffffffLL) return MOE_ESHAPE;
         const int rc = moe::launch_ffn_stream(
-            ffn_call(X_dev, W13_dev, W2_dev, k, C, d_e, slot_off_dev, perm_dev, blocks_dev, Yp_dev, workspace_dev), T, d_h, st);
+            ffn_call(X_dev, W13_dev, W2_dev, k, C, d_e, perm_dev, blocks_dev, Yp_dev, workspace_dev), T, d_h, st);
         if (rc != MOE_OK) return rc;
     } else {
         const long long rows = static_cast<long long>(T) * k;
@@ -383,8 +383,8 @@ extern "C" int moe_grouped_ffn_shared(const void *X_dev, const void *W13_dev, co
     if (rc != MOE_OK || T == 0) return rc;
     if (workspace_dev == s_workspace_dev) return MOE_EINVAL;         // the two sets hand over through control lines of their own
     if (dtype == MOE_DTYPE_BF16 && static_cast<long long>(T) * d_h * 2 <= 0xffffffffLL) {
-        const moe::FfnCall routed = ffn_call(X_dev, W13_dev, W2_dev, k, C, d_e, slot_off_dev, perm_dev, blocks_dev, Yp_dev, workspace_dev);
-        const moe::FfnCall shared = ffn_call(X_dev, W13s_dev, W2s_dev, 1, 1, d_s, s_slot_off_dev, s_perm_dev, s_blocks_dev, Ys_dev, s_workspace_dev);
+        const moe::FfnCall routed = ffn_call(X_dev, W13_dev, W2_dev, k, C, d_e, perm_dev, blocks_dev, Yp_dev, workspace_dev);
+        const moe::FfnCall shared = ffn_call(X_dev, W13s_dev, W2s_dev, 1, 1, d_s, s_perm_dev, s_blocks_dev, Ys_dev, s_workspace_dev);
         if (moe::ffn_stream_takes_shared(routed, shared, T, d_h)) {
             moe::launch_ffn_stream_shared(routed, shared, T, d_h, static_cast<hipStream_t>(stream));
             return moe::check_launch("moe_grouped_ffn_shared");

@@ -1267,8 +1267,8 @@ void launch_shared(const SharedArgs &p, int block_rows, unsigned blocks, hipStre
 // ---------------------------------------------------------------------------------------------
 // Batches of at least kBigMinTokens tokens: every slot with more than kWideMin requests as wide blocks of two packed tiles a
 // wavefront, the others as streaming items (one block each), in one launch of two workgroups a CU with the registers for both.
-// The blocks are found from the slots' offsets, not from the list: a wide block has as many ids as it has groups of tiles, and
-// only a slot can have a streaming block, so the worst-case grid stays small (32000 workgroups at T = 8192, k = 8, C = 16,
+// The blocks are looked up in the list by their number among the wide or the streaming ones (find_entry), not by their place in it: a wide
+// block has as many ids as it has groups of tiles, and only a slot can have a streaming block, so the worst-case grid stays small (32000 workgroups at T = 8192, k = 8, C = 16,
 // d_h = 4096, d_e = 1536, where ids for every tile of every block of 64 rows would be 166000) and no workgroup has to walk a list.
 // Wide blocks come first: their chains are the longest and hide behind the streams.  Against blocks of 128 rows x four tiles in two
 // launches of their own before the streaming launch, us a layer: T = 8192, d_h = 4096,
@@ -1277,9 +1277,8 @@ void launch_shared(const SharedArgs &p, int block_rows, unsigned blocks, hipStre
 // 307 -> 317; 200 of 20 rows, d_h = 512, d_e = 256 54 -> 58).
 struct BigArgs {
     StreamArgs a;
-    const int32_t *slot_off;
-    int C;
     int groups[2];                       // workgroups of a wide block: groups of eight packed tiles of a stage
+    FastDiv group_div[2];                // division by groups
 };
 
 // Blocks of 128 rows from this many first-stage workgroups of them on, else of 64 rows (us, blocks of 128 and of 64 rows:
@@ -1288,51 +1287,50 @@ struct BigArgs {
 constexpr int kBigMinWorkgroups = 176;
 constexpr int kBigMaxCut = 8;            // blocks of 64 rows of slots with more than kWideMin requests that may be streaming items
 
-struct BigItem { int slot, lo, hi, at, item; };
-// The slot of work item b, slot by slot in order: `groups` items for every block of 2^wr_shift rows of a slot with more than `cut` requests
-// (wide), or one for every 64 rows of the others.  at = which of the slot's items b is, item = the blocks of 64 rows of
-// the wide slots before it (a block's own number names its control lines and its part of `act`).  Uniform over the wavefront; b is in range.
-__device__ __forceinline__ BigItem find_item(const int32_t *slot_off, int C, bool wide, int cut, int wr_shift, int groups, int b, int lane) {
-    constexpr int kRounds = MOE_MAX_SLOTS / MOE_WAVE;
-    int lo[kRounds], hi[kRounds];
+struct BigItem { int4 ent; int index; };   // an entry of the work list and its place in it; index -1: none
+// The r-th entry of a list of n that is a streaming block (a slot with at most `cut` requests) or, `wide`, that leads a block of
+// wr rows (64 or 128) of a slot with more.  A slot's entries are neighbours.  Uniform over the wavefront.  Lists of up to 512 blocks
+// are one round trip; the 1000 blocks of a batch that is local as a whole are two, of a launch of several hundred microseconds.
+__device__ __forceinline__ BigItem find_entry(const int32_t *blocks, int n, bool wide, int cut, int wr, int r, int lane) {
+    constexpr int kGroups = 8;                                       // groups of 64 entries that are requested at once
+    const int4 *list = reinterpret_cast<const int4 *>(blocks) + 1;
+    for (int j0 = 0; j0 < n; j0 += kGroups * MOE_WAVE) {
+        int4 e[kGroups];
 #pragma unroll
-    for (int q = 0; q < kRounds; ++q) {                              // all requested at once
-        lo[q] = hi[q] = 0;
-        if (q * MOE_WAVE < C) {
-            const int s = q * MOE_WAVE + lane;
-            lo[q] = slot_off[s < C ? s : C];
-            hi[q] = slot_off[s < C ? s + 1 : C];
+        for (int q = 0; q < kGroups; ++q) {
+            const int g0 = j0 + q * MOE_WAVE, j = g0 + lane;
+            e[q] = make_int4(0, 0, 0, 0);
+            if (g0 < n) e[q] = list[j < n ? j : n - 1];
+        }
+#pragma unroll
+        for (int q = 0; q < kGroups; ++q) {
+            const int g0 = j0 + q * MOE_WAVE;
+            if (g0 >= n) break;
+            const bool over = e[q].z - e[q].w > cut;
+            const bool mine = g0 + lane < n && over == wide && (!wide || ((e[q].y - e[q].w) & (wr - 1)) == 0);
+            const unsigned long long m = __ballot(mine);
+            const int count = __popcll(m);
+            if (r < count) {
+                const int before = __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32), __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0));
+                const int src = __builtin_ctzll(__ballot(mine && before == r));
+                return {make_int4(__builtin_amdgcn_readlane(e[q].x, src), __builtin_amdgcn_readlane(e[q].y, src),
+                                  __builtin_amdgcn_readlane(e[q].z, src), __builtin_amdgcn_readlane(e[q].w, src)), g0 + src};
+            }
+            r -= count;
         }
     }
-    int item0 = 0;
-#pragma unroll
-    for (int q = 0; q < kRounds; ++q) {
-        if (q * MOE_WAVE >= C) break;
-        const int m = hi[q] - lo[q];
-        const bool mine = (m > cut) == wide;
-        const int n64 = mine ? (m + 63) >> 6 : 0;                    // blocks of 64 rows, items
-        const int n = wide ? (mine ? ((m + (1 << wr_shift) - 1) >> wr_shift) * groups : 0) : n64;
-        const int incl = moe::wave_incl_scan_i32(n), incl64 = moe::wave_incl_scan_i32(n64);
-        const int total = __builtin_amdgcn_readlane(incl, MOE_WAVE - 1);
-        if (b < total) {
-            const int src = __builtin_ctzll(__ballot(incl > b));
-            return {q * MOE_WAVE + src, __builtin_amdgcn_readlane(lo[q], src), __builtin_amdgcn_readlane(hi[q], src),
-                    b - __builtin_amdgcn_readlane(incl - n, src), item0 + __builtin_amdgcn_readlane(incl64 - n64, src)};
-        }
-        b -= total;
-        item0 += __builtin_amdgcn_readlane(incl64, MOE_WAVE - 1);
-    }
-    return {0, 0, 0, 0, 0};
+    return {make_int4(0, 0, 0, 0), -1};
 }
 
-// n_wide: blocks of the wide slots, n_wide64: their blocks of 64 rows; id: of the stage's wide or streaming ids.
+// n_blocks: entries of the list; n_wide: blocks of the wide slots; id: of the stage's wide or streaming ids.  A block is named by its
+// first entry of the list: that entry's control lines and, with 128 rows, the `act` of that entry and the next.
 template <bool STAGE1, bool EVEN>
-__device__ __forceinline__ void run_big(const BigArgs &p, char *lds, int *s_ok, bool wide, int cut, bool rows128, int n_wide,
-                                        int n_wide64, unsigned id) {
+__device__ __forceinline__ void run_big(const BigArgs &p, char *lds, int *s_ok, bool wide, int cut, bool rows128, int n_blocks,
+                                        int n_wide, unsigned id) {
     const StreamArgs &a = p.a;
     const StageArgs &g = a.s[STAGE1 ? 0 : 1];
     const int groups = p.groups[STAGE1 ? 0 : 1];
-    int b = static_cast<int>(g.pad_div(id));                         // streaming: block, and tile below
+    int b = static_cast<int>(g.pad_div(id)), r = b;                  // streaming: block, and tile below
     if (wide) {
         // Ids go round-robin over the eight XCDs; each takes an eighth of the wide items as one run, a slot's items block-fastest:
         // the blocks of one group of tiles start next to each other on one XCD and share the expert's tiles in that L2, and the
@@ -1340,18 +1338,21 @@ __device__ __forceinline__ void run_big(const BigArgs &p, char *lds, int *s_ok, 
         const int n = n_wide * groups, x = id & 7, each = n >> 3, more = n & 7, place = static_cast<int>(id >> 3);
         if (place >= each + (x < more ? 1 : 0)) return;
         b = x * each + (x < more ? x : more) + place;
+        r = static_cast<int>(p.group_div[STAGE1 ? 0 : 1](b));        // a slot of nb blocks has nb * groups items: its block r has the slot of item b
     }
-    const BigItem it = find_item(p.slot_off, p.C, wide, cut, rows128 ? 7 : 6, groups, b, moe::lane_id());
+    const int wr = rows128 ? 128 : 64;
+    const BigItem it = find_entry(a.blocks, n_blocks, wide, cut, wr, r, moe::lane_id());
+    if (it.index < 0) return;
+    const int lo = it.ent.w, hi = it.ent.z;
     if (!wide) {
-        run_stream_item<STAGE1, EVEN, 4>(a, g, lds, s_ok, n_wide64 + b, static_cast<int>(id) - b * g.tiles_pad,
-                                         make_int4(it.slot, it.lo + it.at * 64, it.hi, it.lo));
+        run_stream_item<STAGE1, EVEN, 4>(a, g, lds, s_ok, it.index, static_cast<int>(id) - b * g.tiles_pad, it.ent);
         return;
     }
-    const int wr = rows128 ? 128 : 64, nb = (it.hi - it.lo + wr - 1) / wr, group = it.at / nb, block = it.at % nb;
-    const int row0 = it.lo + block * wr, m = it.hi - row0 < wr ? it.hi - row0 : wr;
-    const int item = it.item + block * (wr / 64);
-    if (m > 64) wide_item2<STAGE1, 8>(a, g, lds, s_ok, item, group, groups, it.slot, row0, m);
-    else wide_item2<STAGE1, 4>(a, g, lds, s_ok, item, group, groups, it.slot, row0, m);
+    const int nb = (hi - lo + wr - 1) / wr, nth = (it.ent.y - lo) / wr, at = b - (r - nth) * groups, group = at / nb, block = at % nb;
+    const int row0 = lo + block * wr, m = hi - row0 < wr ? hi - row0 : wr;
+    const int item = it.index + (block - nth) * (wr / 64);
+    if (m > 64) wide_item2<STAGE1, 8>(a, g, lds, s_ok, item, group, groups, it.ent.x, row0, m);
+    else wide_item2<STAGE1, 4>(a, g, lds, s_ok, item, group, groups, it.ent.x, row0, m);
 }
 
 template <bool EVEN1, bool EVEN2>
@@ -1366,21 +1367,21 @@ void ffn_big_kernel(BigArgs p) {
     const bool rows128 = head.w * p.groups[0] >= (wide_min > 0 ? wide_min : kBigMinWorkgroups);
     // a few blocks that nothing hides are cut into streaming items as in the other launches (wide_on)
     const bool any = wide_min > 0 || head.z > kBigMaxCut || wide_on(head, (p.a.s[0].tiles + kWaves - 1) / kWaves, 0, p.a.s[0].KS, p.a.s[1].KS);
-    const int cut = any ? kWideMin : 0x7fffffff, n_wide64 = any ? head.z : 0;
+    const int cut = any ? kWideMin : 0x7fffffff;
     const int n_wide = any ? (rows128 ? head.w : head.z) : 0;
-    const unsigned n_stream = head.x - n_wide64;
+    const unsigned n_stream = head.x - (any ? head.z : 0);
     unsigned id = blockIdx.x;
     const unsigned w1 = (n_wide * p.groups[0] + 7u) & ~7u, s1 = n_stream * p.a.s[0].tiles_pad;
     if (id < w1 + s1) {
         const bool wide = id < w1;
-        run_big<true, EVEN1>(p, lds, &s_ok, wide, cut, rows128, n_wide, n_wide64, wide ? id : id - w1);
+        run_big<true, EVEN1>(p, lds, &s_ok, wide, cut, rows128, head.x, n_wide, wide ? id : id - w1);
         return;
     }
     id -= w1 + s1;
     const unsigned w2 = (n_wide * p.groups[1] + 7u) & ~7u, s2 = n_stream * p.a.s[1].tiles_pad;
     if (id < w2 + s2) {
         const bool wide = id < w2;
-        run_big<false, EVEN2>(p, lds, &s_ok, wide, cut, rows128, n_wide, n_wide64, wide ? id : id - w2);
+        run_big<false, EVEN2>(p, lds, &s_ok, wide, cut, rows128, head.x, n_wide, wide ? id : id - w2);
     }
 }
 
@@ -1432,8 +1433,10 @@ int launch_ffn_stream(const FfnCall &c, int T, int d_h, hipStream_t st) {
     if (ffn_is_big(T, d_h, c.d_e)) {
         BigArgs p;
         p.a = a;
-        p.slot_off = c.slot_off; p.C = c.C;
-        for (int i = 0; i < 2; ++i) p.groups[i] = (a.s[i].tiles + 2 * kWaves - 1) / (2 * kWaves);
+        for (int i = 0; i < 2; ++i) {
+            p.groups[i] = (a.s[i].tiles + 2 * kWaves - 1) / (2 * kWaves);
+            p.group_div[i] = fast_div(p.groups[i]);
+        }
         if (items * p.groups[0] > 0x7fffffffLL || items * p.groups[1] > 0x7fffffffLL) return MOE_ESHAPE;
         const long long grid = items * (p.groups[0] + p.groups[1]) + 16 + static_cast<long long>(c.C + kBigMaxCut) * (a.s[0].tiles_pad + a.s[1].tiles_pad);
         if (grid > 0x7fffffffLL) return MOE_ESHAPE;

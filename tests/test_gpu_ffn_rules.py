@@ -247,3 +247,34 @@ def test_launch_for_large_batches(counts, k, d_h, d_e, wide_min):
         num, den = np.linalg.norm(got[:d.n] - want, axis=1), np.linalg.norm(want, axis=1)
         assert (num <= 2.5 * TOL_BF16 * den + 1e-30).all(), int(np.argmax(num / den))
         assert B.moe_workspace_status(ws) == 0
+
+
+@pytest.mark.parametrize("counts,k", [
+    ([64, 65, 0, 128, 129, 1, 192, 193, 257, 17, 16], 1),                # streaming and wide entries, light slots last in the list
+    ([40 + s % 5 for s in range(100)], 4),                               # nothing wide, entries in two groups of 64
+    ([(190, 66, 64, 300, 0, 30, 129, 131)[s % 8] for s in range(256)], 16),   # 768 entries: the search takes a second round
+])
+def test_large_batch_takes_its_rows_from_the_list(counts, k):
+    """The bf16 path takes every row range from the block list, in large batches too: offsets that say something else change
+    nothing (blocks of 128 rows, of 64 rows and the rule's choice)."""
+    T, d_h, d_e = 2048, 64, 96
+    d = Dispatch(counts, T, k, seed=3)
+    cfg = W.MoEConfig("list", E=d.C, k=k, d_h=d_h, d_e=d_e, T=T, n_inst=1, C=d.C, zipf_s=0.0, seed=17)
+    X = W.activations(cfg)
+    W13, W2 = (np.stack(w) for w in zip(*(W.expert_weights(cfg, e) for e in range(d.C))))
+    want = ffn.grouped_ffn(X, W13, W2, d.off, d.perm, k)
+    d13, d2, dX = to_device_bf16(W13), to_device_bf16(W2), to_device_bf16(X)
+    p13, p2 = torch.empty_like(d13), torch.empty_like(d2)
+    B.moe_pack_weights_bf16(d13, d2, d.C, d_h, d_e, p13, p2)
+    ws, Yp = d.buffers(d_h, d_e)
+    other = torch.zeros_like(d.dev[0])
+    for wide_min in (0, 1, int(d.list[3]) * 2 + 1):
+        B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, wide_min)
+        Yp.fill_(123.0)
+        B.moe_grouped_ffn(dX, p13, p2, T, k, d.C, d_h, d_e, B.MOE_DTYPE_BF16, other, *d.dev[1:], Yp, ws)
+        torch.cuda.synchronize()
+        got = Yp.cpu().numpy()
+        assert (got[d.n:] == 123.0).all()
+        num, den = np.linalg.norm(got[:d.n] - want, axis=1), np.linalg.norm(want, axis=1)
+        assert (num <= 2.5 * TOL_BF16 * den + 1e-30).all(), int(np.argmax(num / den))
+        assert B.moe_workspace_status(ws) == 0
