@@ -177,10 +177,17 @@ def _stream(stream) -> Optional[int]:
     return stream.cuda_stream or None
 
 
-@functools.lru_cache(maxsize=64)
 def _route_cfg(mode: int, renormalize: int, n_group: int, topk_group: int, scale: float):
-    """A moe_route_cfg by reference; the library only reads it."""
+    """A moe_route_cfg by reference; the library only reads it.  One of plain numbers is built once: anything else that ctypes
+    takes (arrays, tensors) may change its value, compare equal to a number or have no hash, and so do 0.0 and -0.0."""
+    if type(scale) is float and scale and type(mode) is int and type(n_group) is int and type(topk_group) is int:
+        return _plain_route_cfg(mode, renormalize, n_group, topk_group, scale)
     return ctypes.byref(moe_route_cfg(mode, renormalize, n_group, topk_group, scale))
+
+
+@functools.lru_cache(maxsize=64)
+def _plain_route_cfg(*fields):
+    return ctypes.byref(moe_route_cfg(*fields))
 
 
 class Placement:

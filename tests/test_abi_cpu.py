@@ -110,3 +110,22 @@ def test_argument_validation_without_launch():
     ws = L.moe_workspace_bytes(128, 6, 17, 2048, 1408, B.MOE_DTYPE_BF16)
     assert ws >= 128 * 6 * 1408 * 2 and ws % 256 == 0
     assert L.moe_workspace_bytes(64, 2, 5, 256, 512, B.MOE_DTYPE_F32) >= 64 * 2 * 512 * 4
+
+
+def test_routing_options_are_taken_by_value():
+    """Options that compare equal, change their value or have no hash get a structure of their own."""
+    import torch
+    cfg = lambda *a: B._route_cfg(*a)._obj
+    assert cfg(0, 1, 1, 1, 2.0).scale == 2.0 and cfg(1, 0, 8, 4, 2.0).n_group == 8
+    assert cfg(0, 1, 1, 1, np.array(0.5)).scale == 0.5
+    scale, groups = torch.tensor(2.0), torch.tensor(4)
+    assert cfg(0, 1, groups, 1, scale).scale == 2.0
+    scale.fill_(3.0)
+    groups.fill_(8)
+    got = cfg(0, 1, groups, 1, scale)
+    assert got.scale == 3.0 and got.n_group == 8
+    assert str(cfg(0, 1, 1, 1, 0.0).scale) == "0.0" and str(cfg(0, 1, 1, 1, -0.0).scale) == "-0.0"
+    for _ in range(2):
+        assert cfg(0, 1, 1, 1, 1.0).topk_group == 1
+        with pytest.raises(TypeError):
+            cfg(0, 1, 1.0, 1, 1.0)
