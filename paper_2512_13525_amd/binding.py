@@ -161,6 +161,14 @@ def _ptr(t) -> Optional[int]:
 _raw_stream = _device = None
 
 
+def _forget_stream_lookup() -> None:
+    global _raw_stream, _device
+    _raw_stream = _device = None
+
+
+os.register_at_fork(after_in_child=_forget_stream_lookup)      # a forked child asks torch, which refuses to use the GPU there
+
+
 def _stream(stream) -> Optional[int]:
     """hipStream_t of a torch stream (None = torch's current stream)."""
     global _raw_stream, _device

@@ -129,3 +129,23 @@ def test_routing_options_are_taken_by_value():
         assert cfg(0, 1, 1, 1, 1.0).topk_group == 1
         with pytest.raises(TypeError):
             cfg(0, 1, 1.0, 1, 1.0)
+
+
+def test_forked_child_looks_the_stream_up_anew():
+    """The stream lookup that skips torch's initialisation check is not inherited by a forked child, which torch refuses the
+    GPU (here there is none, which torch says as well)."""
+    kept = B._raw_stream, B._device
+    B._raw_stream, B._device = (lambda device: 0x1000), (lambda: 0)
+    try:
+        assert B._stream(None) == 0x1000
+        pid = os.fork()
+        if pid == 0:
+            code = 1
+            try:
+                B._stream(None)
+            except BaseException:
+                code = 7
+            os._exit(code)
+        assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 7
+    finally:
+        B._raw_stream, B._device = kept
