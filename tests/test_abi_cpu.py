@@ -131,21 +131,25 @@ def test_routing_options_are_taken_by_value():
             cfg(0, 1, 1.0, 1, 1.0)
 
 
-def test_forked_child_looks_the_stream_up_anew():
-    """The stream lookup that skips torch's initialisation check is not inherited by a forked child, which torch refuses the
-    GPU (here there is none, which torch says as well)."""
-    kept = B._raw_stream, B._device
-    B._raw_stream, B._device = (lambda device: 0x1000), (lambda: 0)
-    try:
-        assert B._stream(None) == 0x1000
-        pid = os.fork()
-        if pid == 0:
-            code = 1
-            try:
-                B._stream(None)
-            except BaseException:
-                code = 7
+def test_forked_child_looks_the_stream_up_anew(monkeypatch):
+    """The stream lookup that skips torch's initialisation check is not inherited by a forked child: it asks torch first, which
+    refuses the GPU to a child of a process that uses it."""
+    import torch
+
+    def refuse():
+        raise RuntimeError("no GPU in a forked child")
+
+    monkeypatch.setattr(torch.cuda, "current_device", refuse)
+    monkeypatch.setattr(B, "_raw_stream", lambda device: 0x1000)
+    monkeypatch.setattr(B, "_device", lambda: 0)
+    assert B._stream(None) == 0x1000
+    pid = os.fork()
+    if pid == 0:
+        code = 1
+        try:
+            B._stream(None)
+        except RuntimeError:
+            code = 7
+        finally:
             os._exit(code)
-        assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 7
-    finally:
-        B._raw_stream, B._device = kept
+    assert os.waitstatus_to_exitcode(os.waitpid(pid, 0)[1]) == 7
