@@ -128,6 +128,12 @@ __device__ __forceinline__ bf16x8 load_weights(const char *p) {
 
 __device__ __forceinline__ float silu_mul(float g, float u) { return g / (1.0f + __expf(-g)) * u; }
 
+// Waits until at most N of this wavefront's loads are outstanding.
+template <int N>
+__device__ __forceinline__ void wait_loads() {
+    __builtin_amdgcn_s_waitcnt((N & 15) | (N >> 4) << 14 | 7 << 4 | 15 << 8);
+}
+
 // Workgroup barrier for LDS exchange only: waits for this wavefront's LDS traffic, not for its
 // global loads (prefetched weights stay in flight across it).
 __device__ __forceinline__ void lds_barrier() {
@@ -574,7 +580,7 @@ __device__ __forceinline__ bool stream_item_down(const StreamArgs &a, const Stag
 // the one of the streaming items: counter and flags of the leading entry.
 template <bool STAGE1, int RT>
 __device__ __forceinline__ void wide_item(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok,
-                                          int item, int group, int n_groups, int slot, int row0, int m) {
+                                          int item, int group, int n_groups, int slot, int row0, int m, bool drain) {
     constexpr int kRing = 2;                                         // K-tiles of both operands in flight
     constexpr bool STREAM = false;                                   // a wide slot has several blocks: they share the tiles through L2
     constexpr int kPieces = RT * 16 * 8;                             // 16-byte pieces of one K-tile of the token tile
@@ -706,7 +712,12 @@ __device__ __forceinline__ void wide_item(const StreamArgs &a, const StageArgs &
     }
     MOE_WIDE_LOAD_B(0, 0);
     MOE_WIDE_LOAD_B(1, 1);
+    // The first token rows are waited for here: inside the loop the compiler would leave as few loads in flight in every round as
+    // there are behind these rows now (the weights of both K-tiles are in front of them, in the loop one K-tile's are).
+    // drain: just that is wanted (kWideDrainWorkgroups).
+    wait_loads<kLoadsB>();
     for (; i + 2 <= n_full; i += 2) {
+        if (drain) wait_loads<kLoadsB>();
         MOE_WIDE_STEP(0, i, true);
         MOE_WIDE_STEP(1, i + 1, true);
     }
@@ -972,6 +983,20 @@ __device__ __forceinline__ bool wide_on(int4 head, int groups1, int override_min
     const long long chain_ns = static_cast<long long>((ks1 + 1) / 2 + (ks2 + 1) / 2) * kWideTileNs;
     return 4 * (stream_ns(head.x, ks1, ks2) + beside_ns) >= 5 * chain_ns;
 }
+// Wide items let their ring of loads run empty every two K-tiles (drain) when there are more workgroups of their second stage than
+// this; at most that many are a chain of round trips to memory each, which an empty ring lengthens (us, drained and not: 256 and 128
+// workgroups of the two stages, d_h = d_e = 2048, 500 rows of one slot 34.7 and 29.4; 256 and 256, 4096 x 2048 48.7 and 40.2; 512 and
+// 128, 2048 x 4096 52.7 and 47.5; 240 and 320, 4096 x 1536 60.6 and 57.5).  With more of them the blocks of a slot drift apart without
+// it and fetch the expert's tiles one by one (768 and 768, 4096 x 2048 130 and 148; 384 and 1536, 8192 x 1024 160 and 171; 544 and
+// 816, 3072 x 1024 88 and 90).  So they do where as many streaming blocks hide the wide ones and want the memory for themselves
+// (d_h = 7168, d_e = 2048, T = 512 236 and 240).  Taken by the wide items alone: ahead of all items the rule costs those 1-3 %.
+constexpr int kWideDrainWorkgroups = 352;
+struct WideBlocks { int all, wide; };    // entries of the list (and of one beside it), 64-row blocks of the wide slots
+// BR: rows of a list entry
+template <int BR>
+__device__ __forceinline__ bool wide_drains(WideBlocks n, int tiles2) {
+    return n.wide * ((tiles2 + kWaves - 1) / kWaves) > kWideDrainWorkgroups || n.all - n.wide * (64 / BR) >= n.wide;
+}
 // The workgroups of a wide slot (ids in groups of ids8 * 8 per block: the block's, tile = 0 .. ids8 * 8 - 1) run the slot's nb blocks
 // x groups of tiles; the others leave.
 // Workgroup ids go round-robin over the eight XCDs, so tile % 8 is the XCD and (leader index, tile / 8)
@@ -995,7 +1020,7 @@ __device__ __forceinline__ bool deal_wide(int leader, int tile, int ids8, int nb
 // BR = rows per list entry.
 template <bool STAGE1, int WR, int BR>
 __device__ __forceinline__ void run_wide(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok, int item,
-                                         int tile, int4 ent) {
+                                         int tile, int4 ent, WideBlocks n) {
     const int slot = ent.x, hi = ent.z, lo = ent.w;
     if ((ent.y - lo) % WR != 0) return;                              // not the leading entry of a wide block
     const int groups = (g.tiles + kWaves - 1) / kWaves;              // workgroups of a block in this stage
@@ -1006,10 +1031,11 @@ __device__ __forceinline__ void run_wide(const StreamArgs &a, const StageArgs &g
     const int row0 = lo + pair.block * WR;
     const int m = hi - row0 < WR ? hi - row0 : WR;
     const int rt = (m + 15) >> 4;
+    const bool drain = wide_drains<BR>(n, a.s[1].tiles);
     // up to 16 rows as two row tiles (one kind of item less; slots of 72 rows: 58 -> 61 us at d_h = 2048, d_e = 768, 173 -> 163 at
     // d_h = 4096, d_e = 1536)
-    if (rt <= 2) wide_item<STAGE1, 2>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m);
-    else wide_item<STAGE1, 4>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m);
+    if (rt <= 2) wide_item<STAGE1, 2>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m, drain);
+    else wide_item<STAGE1, 4>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m, drain);
 }
 
 // EVEN: this stage has an even number of K-steps
@@ -1085,11 +1111,11 @@ __device__ __forceinline__ void run_stream_item(const StreamArgs &a, const Stage
     if (STAGE1) announce_tiles(a, item, g.tiles);
 }
 
-// wide: slots with more than kWideMin requests are wide blocks; otherwise every slot is cut into streaming items.
+// wide: slots with more than kWideMin requests are wide blocks (n of them); otherwise every slot is cut into streaming items.
 template <bool STAGE1, bool EVEN, int TT, int WR>
 __device__ __forceinline__ void run_item(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok, int wide,
-                                         int item, int tile, int4 ent) {
-    if (wide && ent.z - ent.w > kWideMin) run_wide<STAGE1, WR, TT * 16>(a, g, lds, s_ok, item, tile, ent);
+                                         WideBlocks n, int item, int tile, int4 ent) {
+    if (wide && ent.z - ent.w > kWideMin) run_wide<STAGE1, WR, TT * 16>(a, g, lds, s_ok, item, tile, ent, n);
     else run_stream_item<STAGE1, EVEN, TT>(a, g, lds, s_ok, item, tile, ent);
 }
 
@@ -1138,15 +1164,16 @@ void ffn_stream_kernel(StreamArgs a) {
         // before any stage-2 workgroup, so every flag a stage-2 workgroup waits for is raised.
         // header word 3 of the workspace (wide_min): the caller's threshold for wide blocks (0 = default)
         const int wide = wide_on(head, (a.s[0].tiles + kWaves - 1) / kWaves, wide_min, a.s[0].KS, a.s[1].KS);
+        const WideBlocks n = {head.x, head.z};
         const unsigned n_blocks = static_cast<unsigned>(head.x);
         const unsigned lanes = n_blocks < moe::kFfnLaneBlocks ? n_blocks : moe::kFfnLaneBlocks;
         const unsigned n1 = lanes * a.s[0].tiles_pad, n2 = lanes * a.s[1].tiles_pad;
         const auto own_item = [&] {
             if (blockIdx.x < n1) {
-                run_item<true, EVEN1, TT, WR>(a, a.s[0], lds, &s_ok, wide, item1, blockIdx.x - item1 * a.s[0].tiles_pad, ent1);
+                run_item<true, EVEN1, TT, WR>(a, a.s[0], lds, &s_ok, wide, n, item1, blockIdx.x - item1 * a.s[0].tiles_pad, ent1);
             } else if (blockIdx.x - n1 < n2) {
                 const unsigned id = blockIdx.x - n1, item = a.s[1].pad_div(id);
-                run_item<false, EVEN2, TT, WR>(a, a.s[1], lds, &s_ok, wide, item, id - item * a.s[1].tiles_pad, load_const(a.blocks, 1 + item));
+                run_item<false, EVEN2, TT, WR>(a, a.s[1], lds, &s_ok, wide, n, item, id - item * a.s[1].tiles_pad, load_const(a.blocks, 1 + item));
             }
         };
         if constexpr (!WRAP) {
@@ -1191,8 +1218,8 @@ void ffn_stream_kernel(StreamArgs a) {
                 asm volatile("" : "+s"(g.KS), "+s"(g.tiles), "+s"(g.tiles_pad), "+s"(g.items));
                 const unsigned item = item0 + l * lanes;
                 const int4 ent = load_const(a.blocks, 1 + item);
-                if (s1) run_item<true, EVEN1, TT, WR>(a, g, lds, &s_ok, wide, item, id0 - item0 * tp, ent);
-                else run_item<false, EVEN2, TT, WR>(a, g, lds, &s_ok, wide, item, id0 - item0 * tp, ent);
+                if (s1) run_item<true, EVEN1, TT, WR>(a, g, lds, &s_ok, wide, n, item, id0 - item0 * tp, ent);
+                else run_item<false, EVEN2, TT, WR>(a, g, lds, &s_ok, wide, n, item, id0 - item0 * tp, ent);
             }
         }
     }
@@ -1246,15 +1273,16 @@ void ffn_stream_shared_kernel(SharedArgs p) {
     // the routed slots are cut as in a launch of their own; the shared slot's chain may also hide behind the routed stream
     const int wide = shared ? wide_on(head_s, (p.set[1].s[0].tiles + kWaves - 1) / kWaves, min_s, ks1, ks2_s, stream_ns(blocks_r, ks1, ks2_r))
                             : wide_on(head_r, (p.set[0].s[0].tiles + kWaves - 1) / kWaves, min_r, ks1, ks2_r);
+    const WideBlocks n = {shared ? head_s.x + static_cast<int>(blocks_r) : head_r.x, shared ? head_s.z : head_r.z};
     if (id < n1s + n1r) {
         if (item1 >= (first ? blocks_s : blocks_r)) return;
         const unsigned tile = (first ? id : id - n1s) - item1 * a.s[0].tiles_pad;
-        run_item<true, EVEN1, TT, WR>(a, a.s[0], lds, &s_ok, wide, item1, tile, ent1);
+        run_item<true, EVEN1, TT, WR>(a, a.s[0], lds, &s_ok, wide, n, item1, tile, ent1);
     } else {
         const unsigned id2 = id - (n1s + n1r) - (shared ? 0 : n2s);
         if (!shared && id2 >= n2r) return;
         const unsigned item = a.s[1].pad_div(id2);
-        run_item<false, EVEN2, TT, WR>(a, a.s[1], lds, &s_ok, wide, item, id2 - item * a.s[1].tiles_pad, load_const(a.blocks, 1 + item));
+        run_item<false, EVEN2, TT, WR>(a, a.s[1], lds, &s_ok, wide, n, item, id2 - item * a.s[1].tiles_pad, load_const(a.blocks, 1 + item));
     }
 }
 
@@ -1340,7 +1368,7 @@ __device__ __forceinline__ void run_big(const BigArgs &p, char *lds, int *s_ok, 
         b = x * each + (x < more ? x : more) + place;
         r = static_cast<int>(p.group_div[STAGE1 ? 0 : 1](b));        // a slot of nb blocks has nb * groups items: its block r has the slot of item b
     }
-    const int wr = rows128 ? 128 : 64;
+    const int shift = rows128 ? 7 : 6, wr = 1 << shift;              // rows of a wide block
     const BigItem it = find_entry(a.blocks, n_blocks, wide, cut, wr, r, moe::lane_id());
     if (it.index < 0) return;
     const int lo = it.ent.w, hi = it.ent.z;
@@ -1348,9 +1376,9 @@ __device__ __forceinline__ void run_big(const BigArgs &p, char *lds, int *s_ok, 
         run_stream_item<STAGE1, EVEN, 4>(a, g, lds, s_ok, it.index, static_cast<int>(id) - b * g.tiles_pad, it.ent);
         return;
     }
-    const int nb = (hi - lo + wr - 1) / wr, nth = (it.ent.y - lo) / wr, at = b - (r - nth) * groups, group = at / nb, block = at % nb;
+    const int nb = (hi - lo + wr - 1) >> shift, nth = (it.ent.y - lo) >> shift, at = b - (r - nth) * groups, group = at / nb, block = at % nb;
     const int row0 = lo + block * wr, m = hi - row0 < wr ? hi - row0 : wr;
-    const int item = it.index + (block - nth) * (wr / 64);
+    const int item = it.index + ((block - nth) << (shift - 6));
     if (m > 64) wide_item2<STAGE1, 8>(a, g, lds, s_ok, item, group, groups, it.ent.x, row0, m);
     else wide_item2<STAGE1, 4>(a, g, lds, s_ok, item, group, groups, it.ent.x, row0, m);
 }
