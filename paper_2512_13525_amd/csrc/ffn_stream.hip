@@ -1458,7 +1458,7 @@ int launch_ffn_stream(const FfnCall &c, int T, int d_h, hipStream_t st) {
     const long long items = ffn_max_blocks(T, c.k, c.C);
     if (items > kMaxItems) return MOE_ESHAPE;
     const StreamArgs a = stream_args(c, T, d_h);
-    if (ffn_is_big(T, d_h, c.d_e)) {
+    if (ffn_is_big(T, c.k, c.C, d_h, c.d_e)) {
         BigArgs p;
         p.a = a;
         for (int i = 0; i < 2; ++i) {
@@ -1492,7 +1492,7 @@ int launch_ffn_stream(const FfnCall &c, int T, int d_h, hipStream_t st) {
 constexpr long long kSharedMaxBlocks = 224;
 bool ffn_stream_takes_shared(const FfnCall &c, const FfnCall &sh, int T, int d_h) {
     const long long items = ffn_max_blocks(T, c.k, c.C), items_s = ffn_max_blocks(T, sh.k, sh.C);
-    if (ffn_is_big(T, d_h, c.d_e) || ffn_is_big(T, d_h, sh.d_e) || items > kSharedMaxBlocks || items_s > kFfnLaneBlocks || (c.d_e / 32) % 2 != (sh.d_e / 32) % 2) return false;
+    if (ffn_is_big(T, c.k, c.C, d_h, c.d_e) || ffn_is_big(T, sh.k, sh.C, d_h, sh.d_e) || items > kSharedMaxBlocks || items_s > kFfnLaneBlocks || (c.d_e / 32) % 2 != (sh.d_e / 32) % 2) return false;
     const StreamArgs r = stream_args(c, T, d_h), s = stream_args(sh, T, d_h);
     return items * (r.s[0].tiles_pad + r.s[1].tiles_pad) + items_s * (s.s[0].tiles_pad + s.s[1].tiles_pad) <= 0x7fffffffLL;
 }

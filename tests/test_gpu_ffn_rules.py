@@ -293,3 +293,41 @@ def test_one_long_slot_as_tiled_gemms_time(d_h, d_e, limit):
         B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, wide_min)
         t.append(device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws)))
     assert t[0] < limit * t[1], t
+
+
+@pytest.mark.parametrize("T", [3584, 3585])                             # 56 requests a slot, and a few more
+def test_large_batch_of_short_slots(T):
+    """Both sides of the average from which a large batch takes the launch for large batches, slots of up to 300 requests and
+    empty ones among them, rows against the oracle, twice on one workspace."""
+    counts, k, d_h, d_e = [(40, 64, 65, 17, 0, 70, 300, 5)[s % 8] for s in range(64)], 1, 96, 160
+    d = Dispatch(counts[:48] + [0] * 16, T, k, seed=T)
+    cfg = W.MoEConfig("short", E=d.C, k=k, d_h=d_h, d_e=d_e, T=T, n_inst=1, C=d.C, zipf_s=0.0, seed=23)
+    X = W.activations(cfg)
+    W13, W2 = (np.stack(w) for w in zip(*(W.expert_weights(cfg, e) for e in range(d.C))))
+    want = ffn.grouped_ffn(X, W13, W2, d.off, d.perm, k)
+    d13, d2, dX = to_device_bf16(W13), to_device_bf16(W2), to_device_bf16(X)
+    p13, p2 = torch.empty_like(d13), torch.empty_like(d2)
+    B.moe_pack_weights_bf16(d13, d2, d.C, d_h, d_e, p13, p2)
+    ws, Yp = d.buffers(d_h, d_e)
+    for _ in range(2):
+        Yp.fill_(123.0)
+        d.run(dX, p13, p2, d_h, d_e, Yp, ws)
+        torch.cuda.synchronize()
+        got = Yp.cpu().numpy()
+        assert (got[d.n:] == 123.0).all()
+        num, den = np.linalg.norm(got[:d.n] - want, axis=1), np.linalg.norm(want, axis=1)
+        assert (num <= 2.5 * TOL_BF16 * den + 1e-30).all(), int(np.argmax(num / den))
+        assert B.moe_workspace_status(ws) == 0
+
+
+def test_large_batch_of_short_slots_time():
+    """200 slots of 20 requests take as long at 2048 tokens as at 2047 (within 1.12; 1.36 times as long in the launch for large
+    batches)."""
+    t = []
+    w = random_weights(200, 512, 256)
+    for T in (2047, 2048):
+        d = Dispatch([20] * 200, T, 4)
+        X = torch.empty((T, 512), dtype=torch.bfloat16, device="cuda").normal_()
+        ws, Yp = d.buffers(512, 256)
+        t.append(device_time(lambda: d.run(X, *w, 512, 256, Yp, ws)))
+    assert t[1] < 1.12 * t[0], t
