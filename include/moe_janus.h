@@ -402,13 +402,14 @@ int moe_grouped_ffn_static(const void *X_dev, const void *W13_dev, const void *W
  *                                    workgroups per block) >= this value (default 256; by default
  *                                    also from 64 such workgroups on when the launch has enough
  *                                    other experts to stream to hide them).
+ *                                    In the launch for large batches (from 2048 tokens on, and from 384
+ *                                    on where T x d_h x d_e >= 12e9; not where T*k <= 56*C) they are
+ *                                    blocks of 128 rows instead when (number of 128-row blocks) x
+ *                                    ceil(d_e / 64) >= this value; by default they are tiled GEMMs
+ *                                    there unless they are a few blocks that nothing hides, of 128
+ *                                    rows when (number of 128-row blocks) x ceil(d_e / 128) >= 176.
  *                                    Otherwise they are cut into streaming items like every other
- *                                    slot.  In large batches (from 2048 tokens on, and below where
- *                                    T x d_h x d_e >= 12e9) they are tiled GEMMs unless they are a few blocks that
- *                                    nothing hides, over blocks of 128 rows when
- *                                    (number of 128-row blocks) x ceil(d_e / 128) >= this
- *                                    value (default 176), else of 64 rows; any value > 0 makes
- *                                    them tiled GEMMs.  Results do not depend on it beyond rounding order.
+ *                                    slot.  Results do not depend on it beyond rounding order.
  */
 #define MOE_WS_OPT_SPIN_LIMIT            0
 #define MOE_WS_OPT_WIDE_MIN_WORKGROUPS   1

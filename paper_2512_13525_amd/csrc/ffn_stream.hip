@@ -1307,6 +1307,7 @@ struct BigArgs {
     StreamArgs a;
     int groups[2];                       // workgroups of a wide block: groups of eight packed tiles of a stage
     FastDiv group_div[2];                // division by groups
+    int groups_sum, pads_sum;            // groups and tiles_pad of both stages together
 };
 
 // Blocks of 128 rows from this many first-stage workgroups of them on, else of 64 rows (us, blocks of 128 and of 64 rows:
@@ -1350,11 +1351,39 @@ __device__ __forceinline__ BigItem find_entry(const int32_t *blocks, int n, bool
     return {make_int4(0, 0, 0, 0), -1};
 }
 
+// A 64-row block of a wide slot as streaming items after all (a caller's threshold says so): eight tiles of it one after the other by one
+// workgroup, since the grid has no ids for every tile.  One kind of item per stage, for a full block.
+template <bool STAGE1, bool EVEN>
+__device__ __forceinline__ void run_untiled(const StreamArgs &a, const StageArgs &g_, char *lds, int *s_ok, int item, int group, int slot,
+                                            int row0, int row_end) {
+    constexpr int TT = 4;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE), lane = threadIdx.x % MOE_WAVE;
+    const int t0 = group * 2 * kWaves, t1 = t0 + 2 * kWaves < g_.tiles ? t0 + 2 * kWaves : g_.tiles;
+#pragma unroll 1
+    for (int tile = t0; tile < t1; ++tile) {
+        StageArgs g = g_;                                            // opaque copies, as in the loop over a long list
+        asm volatile("" : "+s"(g.KS), "+s"(g.tiles));
+        if (tile > t0) __syncthreads();                              // the LDS buffer is reused
+        const char *w = g.Wp + (static_cast<size_t>(slot) * g.tiles + tile) * g.KS * 2048;
+        if constexpr (STAGE1) {
+            stream_item_lines<8, TT, false, EVEN>(a, g, lds, w, tile, row0, row_end, wave, lane);
+            __syncthreads();
+            store_act<TT>(a, lds, TT, item, tile, row0, row_end);
+            announce_tiles(a, item, g.tiles);
+        } else if (stream_item_down<4, TT, 1, false, 1>(a, g, lds, s_ok, w, 0, item, tile, g.tiles, wave, lane)) {
+            __syncthreads();
+            store_rows<TT>(a, g, lds, 2, 4, tile, row0, row_end);
+        } else {
+            store_nan_rows(a, g, tile, row0, row_end - row0 < TT * 16 ? row_end - row0 : TT * 16);
+        }
+    }
+}
+
 // n_blocks: entries of the list; n_wide: blocks of the wide slots; id: of the stage's wide or streaming ids.  A block is named by its
 // first entry of the list: that entry's control lines and, with 128 rows, the `act` of that entry and the next.
 template <bool STAGE1, bool EVEN>
-__device__ __forceinline__ void run_big(const BigArgs &p, char *lds, int *s_ok, bool wide, int cut, bool rows128, int n_blocks,
-                                        int n_wide, unsigned id) {
+__device__ __forceinline__ void run_big(const BigArgs &p, char *lds, int *s_ok, bool wide, int cut, bool tiled, bool rows128,
+                                        int n_blocks, int n_wide, unsigned id) {
     const StreamArgs &a = p.a;
     const StageArgs &g = a.s[STAGE1 ? 0 : 1];
     const int groups = p.groups[STAGE1 ? 0 : 1];
@@ -1379,7 +1408,8 @@ __device__ __forceinline__ void run_big(const BigArgs &p, char *lds, int *s_ok, 
     const int nb = (hi - lo + wr - 1) >> shift, nth = (it.ent.y - lo) >> shift, at = b - (r - nth) * groups, group = at / nb, block = at % nb;
     const int row0 = lo + block * wr, m = hi - row0 < wr ? hi - row0 : wr;
     const int item = it.index + ((block - nth) << (shift - 6));
-    if (m > 64) wide_item2<STAGE1, 8>(a, g, lds, s_ok, item, group, groups, it.ent.x, row0, m);
+    if (!tiled) run_untiled<STAGE1, EVEN>(a, g, lds, s_ok, item, group, it.ent.x, row0, hi);
+    else if (m > 64) wide_item2<STAGE1, 8>(a, g, lds, s_ok, item, group, groups, it.ent.x, row0, m);
     else wide_item2<STAGE1, 4>(a, g, lds, s_ok, item, group, groups, it.ent.x, row0, m);
 }
 
@@ -1392,9 +1422,16 @@ void ffn_big_kernel(BigArgs p) {
     const int4 head = load_const(p.a.blocks, 0);
     const int wide_min = load_const(p.a.ctrl, 0).w;
     if (!list_fits(head, 64, p.a.ctrl)) return;
-    const bool rows128 = head.w * p.groups[0] >= (wide_min > 0 ? wide_min : kBigMinWorkgroups);
+    // The surplus of the worst-case grid leaves before anything else is worked out (30000 workgroups at T = 8192, d_h = 4096, d_e = 1536: a layer
+    // with 36 blocks 152.9 us without this line, 148.7 with it).
+    if (blockIdx.x >= 16u + head.z * p.groups_sum + (head.x - head.z + kBigMaxCut) * p.pads_sum) return;
+    // a caller's threshold: as in the other launches for blocks of 64 rows, the same for blocks of 128, which it takes before them
+    const int groups64 = (p.a.s[0].tiles + kWaves - 1) / kWaves;
+    const bool rows128 = wide_min > 0 ? head.w * groups64 >= wide_min : head.w * p.groups[0] >= kBigMinWorkgroups;
     // a few blocks that nothing hides are cut into streaming items as in the other launches (wide_on)
-    const bool any = wide_min > 0 || head.z > kBigMaxCut || wide_on(head, (p.a.s[0].tiles + kWaves - 1) / kWaves, 0, p.a.s[0].KS, p.a.s[1].KS);
+    const bool tiled = wide_min > 0 ? head.z * groups64 >= wide_min
+                                    : head.z > kBigMaxCut || wide_on(head, groups64, 0, p.a.s[0].KS, p.a.s[1].KS);
+    const bool any = tiled || head.z > kBigMaxCut;                   // ids of their own for the wide slots' blocks
     const int cut = any ? kWideMin : 0x7fffffff;
     const int n_wide = any ? (rows128 ? head.w : head.z) : 0;
     const unsigned n_stream = head.x - (any ? head.z : 0);
@@ -1402,14 +1439,14 @@ void ffn_big_kernel(BigArgs p) {
     const unsigned w1 = (n_wide * p.groups[0] + 7u) & ~7u, s1 = n_stream * p.a.s[0].tiles_pad;
     if (id < w1 + s1) {
         const bool wide = id < w1;
-        run_big<true, EVEN1>(p, lds, &s_ok, wide, cut, rows128, head.x, n_wide, wide ? id : id - w1);
+        run_big<true, EVEN1>(p, lds, &s_ok, wide, cut, tiled, rows128, head.x, n_wide, wide ? id : id - w1);
         return;
     }
     id -= w1 + s1;
     const unsigned w2 = (n_wide * p.groups[1] + 7u) & ~7u, s2 = n_stream * p.a.s[1].tiles_pad;
     if (id < w2 + s2) {
         const bool wide = id < w2;
-        run_big<false, EVEN2>(p, lds, &s_ok, wide, cut, rows128, head.x, n_wide, wide ? id : id - w2);
+        run_big<false, EVEN2>(p, lds, &s_ok, wide, cut, tiled, rows128, head.x, n_wide, wide ? id : id - w2);
     }
 }
 
@@ -1465,8 +1502,10 @@ int launch_ffn_stream(const FfnCall &c, int T, int d_h, hipStream_t st) {
             p.groups[i] = (a.s[i].tiles + 2 * kWaves - 1) / (2 * kWaves);
             p.group_div[i] = fast_div(p.groups[i]);
         }
+        p.groups_sum = p.groups[0] + p.groups[1];
+        p.pads_sum = a.s[0].tiles_pad + a.s[1].tiles_pad;
         if (items * p.groups[0] > 0x7fffffffLL || items * p.groups[1] > 0x7fffffffLL) return MOE_ESHAPE;
-        const long long grid = items * (p.groups[0] + p.groups[1]) + 16 + static_cast<long long>(c.C + kBigMaxCut) * (a.s[0].tiles_pad + a.s[1].tiles_pad);
+        const long long grid = items * p.groups_sum + 16 + static_cast<long long>(c.C + kBigMaxCut) * p.pads_sum;
         if (grid > 0x7fffffffLL) return MOE_ESHAPE;
         const bool l1 = a.s[0].KS % 2 == 0, l2 = a.s[1].KS % 2 == 0;
         const dim3 blocks(static_cast<unsigned>(grid)), threads(kThreads);

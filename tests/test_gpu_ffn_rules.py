@@ -41,6 +41,12 @@ class Dispatch:
     def run(self, X, W13p, W2p, d_h, d_e, Yp, ws):
         B.moe_grouped_ffn(X, W13p, W2p, self.T, self.k, self.C, d_h, d_e, B.MOE_DTYPE_BF16, *self.dev, Yp, ws)
 
+    def wide_min(self, form, d_e):
+        """The option's value that makes the slots with more than 64 requests what `form` says in the launch for large batches."""
+        per_block = -(-d_e // 64)
+        assert form != "64 rows" or self.list[3] < self.list[2] or not self.list[2]
+        return {"rule": 0, "128 rows": 1, "64 rows": max(1, int(self.list[2]) * per_block), "streaming": 1 << 20}[form]
+
     def gemm_workgroups(self, d_e):
         """First-stage workgroups over blocks of 128 rows, what the rule of the tiled-GEMM launches goes by."""
         return int(self.list[3]) * -(-(d_e // 16) // 4)
@@ -215,7 +221,7 @@ def test_f32_row_tiles(counts, T, k, d_h, d_e):
     assert (num <= 6e-6 * den + 1e-30).all(), float((num / den).max())
 
 
-@pytest.mark.parametrize("wide_min", [0, 1, 1 << 20])                    # the rule's choice, blocks of 128 rows, blocks of 64 rows
+@pytest.mark.parametrize("form", ["rule", "128 rows", "64 rows", "streaming"])
 @pytest.mark.parametrize("counts,k,d_h,d_e", [
     ([64, 65, 0, 128, 129, 1, 192, 193, 257], 1, 64, 32),                # edges of both kinds of block; fewest K-steps
     ([66, 63, 300, 17, 130], 1, 96, 160),                                # odd numbers of K-steps: a half K-tile at the end
@@ -224,7 +230,7 @@ def test_f32_row_tiles(counts, T, k, d_h, d_e):
     ([s % 65 for s in range(130)], 4, 128, 64),                          # no wide slot
     ([2048], 1, 512, 1056),                                              # many blocks of one slot on every XCD
 ])
-def test_launch_for_large_batches(counts, k, d_h, d_e, wide_min):
+def test_launch_for_large_batches(counts, k, d_h, d_e, form):
     """Batches from 2048 tokens on: wide blocks of 64 and of 128 rows and streaming items found from the slots' offsets, rows
     against the oracle, three times on one workspace."""
     T = 2048
@@ -237,7 +243,7 @@ def test_launch_for_large_batches(counts, k, d_h, d_e, wide_min):
     p13, p2 = torch.empty_like(d13), torch.empty_like(d2)
     B.moe_pack_weights_bf16(d13, d2, d.C, d_h, d_e, p13, p2)
     ws, Yp = d.buffers(d_h, d_e)
-    B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, wide_min)
+    B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, d.wide_min(form, d_e))
     for _ in range(3):
         Yp.fill_(123.0)
         d.run(to_device_bf16(X), p13, p2, d_h, d_e, Yp, ws)
@@ -256,7 +262,7 @@ def test_launch_for_large_batches(counts, k, d_h, d_e, wide_min):
 ])
 def test_large_batch_takes_its_rows_from_the_list(counts, k):
     """The bf16 path takes every row range from the block list, in large batches too: offsets that say something else change
-    nothing (blocks of 128 rows, of 64 rows and the rule's choice)."""
+    nothing (the rule's choice, blocks of 128 and of 64 rows, streaming items)."""
     T, d_h, d_e = 2048, 64, 96
     d = Dispatch(counts, T, k, seed=3)
     cfg = W.MoEConfig("list", E=d.C, k=k, d_h=d_h, d_e=d_e, T=T, n_inst=1, C=d.C, zipf_s=0.0, seed=17)
@@ -268,8 +274,8 @@ def test_large_batch_takes_its_rows_from_the_list(counts, k):
     B.moe_pack_weights_bf16(d13, d2, d.C, d_h, d_e, p13, p2)
     ws, Yp = d.buffers(d_h, d_e)
     other = torch.zeros_like(d.dev[0])
-    for wide_min in (0, 1, int(d.list[3]) * 2 + 1):
-        B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, wide_min)
+    for form in ("rule", "128 rows", "64 rows", "streaming"):
+        B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, d.wide_min(form, d_e))
         Yp.fill_(123.0)
         B.moe_grouped_ffn(dX, p13, p2, T, k, d.C, d_h, d_e, B.MOE_DTYPE_BF16, other, *d.dev[1:], Yp, ws)
         torch.cuda.synchronize()
@@ -331,3 +337,28 @@ def test_large_batch_of_short_slots_time():
         ws, Yp = d.buffers(512, 256)
         t.append(device_time(lambda: d.run(X, *w, 512, 256, Yp, ws)))
     assert t[1] < 1.12 * t[0], t
+
+
+@pytest.mark.parametrize("d_h,d_e", [(128, 192), (96, 160)])            # even and odd numbers of K-steps, a last group of two tiles
+def test_threshold_keeps_slots_streaming_in_large_batches(d_h, d_e):
+    """A threshold that no batch reaches keeps all slots in streaming items in the launch for large batches as in the other: the
+    same bits at 2048 tokens as at 2047 (blocks of more than 32 rows; both launches then split K the same way)."""
+    counts, k = [128, 100, 64, 120, 0, 192, 33, 500], 1
+    d = Dispatch(counts, 2047, k, seed=31)
+    cfg = W.MoEConfig("threshold", E=d.C, k=k, d_h=d_h, d_e=d_e, T=2048, n_inst=1, C=d.C, zipf_s=0.0, seed=37)
+    X = to_device_bf16(W.activations(cfg))
+    W13, W2 = (to_device_bf16(np.stack(w)) for w in zip(*(W.expert_weights(cfg, e) for e in range(d.C))))
+    p13, p2 = torch.empty_like(W13), torch.empty_like(W2)
+    B.moe_pack_weights_bf16(W13, W2, d.C, d_h, d_e, p13, p2)
+    got = []
+    for T in (2047, 2048):
+        d.T = T
+        ws, Yp = d.buffers(d_h, d_e)
+        B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, 1 << 20)
+        for _ in range(2):
+            Yp.fill_(123.0)
+            d.run(X, p13, p2, d_h, d_e, Yp, ws)
+            torch.cuda.synchronize()
+            got.append(Yp[:d.n].clone())
+            assert (Yp[d.n:] == 123.0).all() and B.moe_workspace_status(ws) == 0
+    assert all(torch.equal(got[0], g) for g in got[1:])
