@@ -14,7 +14,9 @@ from helpers import device_time, expected_blocks
 pytestmark = pytest.mark.gpu
 
 TOL_BF16 = 2e-2                  # relative, of a layer in bf16
-GEMM_MIN_TOKENS, GEMM_MIN_WORKGROUPS = 2048, 512
+LARGE_MIN_TOKENS = 2048          # from here on the launch for large batches ...
+ROWS128_MIN_WORKGROUPS = 176     # ... with tiled GEMMs over blocks of 128 rows from this many first-stage workgroups of them on
+MAX_CUT = 8                      # ... and up to this many blocks of 64 rows as streaming items where nothing hides them
 
 
 class Dispatch:
@@ -47,9 +49,11 @@ class Dispatch:
         assert form != "64 rows" or self.list[3] < self.list[2] or not self.list[2]
         return {"rule": 0, "128 rows": 1, "64 rows": max(1, int(self.list[2]) * per_block), "streaming": 1 << 20}[form]
 
-    def gemm_workgroups(self, d_e):
-        """First-stage workgroups over blocks of 128 rows, what the rule of the tiled-GEMM launches goes by."""
-        return int(self.list[3]) * -(-(d_e // 16) // 4)
+    def form(self, d_e):
+        """What the launch for large batches makes of the slots with more than 64 requests (small layers: nothing hides them)."""
+        if self.list[2] <= MAX_CUT and int(self.list[2]) * -(-d_e // 64) < 64:
+            return "streaming"
+        return "128 rows" if int(self.list[3]) * -(-d_e // 128) >= ROWS128_MIN_WORKGROUPS else "64 rows"
 
 
 def random_weights(C, d_h, d_e):
@@ -61,15 +65,17 @@ def random_weights(C, d_h, d_e):
 LONG = [(130, 65, 64, 17, 200, 66)[s % 6] for s in range(150)]           # 325 blocks of 64 rows: the list wraps twice
 
 
-@pytest.mark.parametrize("counts,T,k,d_h,d_e,own_launches", [
-    ([65 + s % 64 for s in range(63)] + [64, 9, 0, 33], 2048, 4, 160, 512, False),
-    ([65 + s % 64 for s in range(64)] + [64, 9, 0, 33], 2048, 4, 160, 512, True),
-    (LONG, 2048, 8, 96, 512, True), (LONG, 2047, 8, 96, 512, False)])
-def test_tiled_gemm_launches_by_their_own_rule(counts, T, k, d_h, d_e, own_launches):
-    """Slots with more than 64 requests by launches of their own from 2048 tokens and 512 first-stage workgroups on, inside the
-    streaming launch below: both sides of the line with the rule's own threshold, rows against the oracle."""
+@pytest.mark.parametrize("counts,T,k,d_h,d_e,form", [
+    ([65 + s % 64 for s in range(43)] + [64, 9, 0, 33], 2048, 4, 160, 512, "64 rows"),       # 172 workgroups of 128-row blocks
+    ([65 + s % 64 for s in range(44)] + [64, 9, 0, 33], 2048, 4, 160, 512, "128 rows"),      # 176
+    ([65, 128, 100, 70, 64, 0, 20], 2048, 1, 160, 256, "streaming"),                         # eight blocks of 64 rows
+    ([129, 192, 150, 64, 0, 20], 2048, 1, 160, 256, "64 rows"),                              # nine
+    (LONG, 2048, 8, 96, 512, "128 rows"), (LONG, 2047, 8, 96, 512, None)])
+def test_large_batches_by_their_own_rule(counts, T, k, d_h, d_e, form):
+    """Both sides of the lines that the launch for large batches draws by itself, and of the token count from which it runs, rows
+    against the oracle."""
     d = Dispatch(counts, T, k, seed=T)
-    assert (T >= GEMM_MIN_TOKENS and d.gemm_workgroups(d_e) >= GEMM_MIN_WORKGROUPS) == own_launches
+    assert (d.form(d_e) if T >= LARGE_MIN_TOKENS else None) == form
     cfg = W.MoEConfig("rules", E=d.C, k=k, d_h=d_h, d_e=d_e, T=T, n_inst=1, C=d.C, zipf_s=0.0, seed=21)
     X = W.activations(cfg)
     W13, W2 = (np.stack(w) for w in zip(*(W.expert_weights(cfg, e) for e in range(d.C))))
@@ -89,20 +95,20 @@ def test_tiled_gemm_launches_by_their_own_rule(counts, T, k, d_h, d_e, own_launc
         assert B.moe_workspace_status(ws) == 0
 
 
-@pytest.mark.parametrize("C,rows,d_h,d_e", [(64, 78, 1024, 512), (20, 78, 7168, 2048), (20, 206, 3072, 1024)])
-def test_tiled_gemm_line_time(C, rows, d_h, d_e):
-    """Past the line the launches of their own are what the rule takes: its time is theirs (within 1.12; inside the streaming
-    launch these batches take 1.13 to 1.35 times as long)."""
-    T, k = 2048, 8
-    d = Dispatch([rows] * C, T, k)
-    assert GEMM_MIN_WORKGROUPS <= d.gemm_workgroups(d_e) < 1280
+@pytest.mark.parametrize("C,rows,d_h,d_e,other,limit", [(32, 128, 2048, 768, "64 rows", 0.96), (20, 78, 7168, 2048, "64 rows", 0.93),
+                                                        (3, 128, 4096, 1536, "128 rows", 0.75)])
+def test_line_of_the_block_size_time(C, rows, d_h, d_e, other, limit):
+    """What the rule takes is faster than the other size of block (0.90, 0.86 and 0.59 of its time)."""
+    d = Dispatch([rows] * C, 2048, 8)
+    assert (d.list[3] * -(-d_e // 128) >= ROWS128_MIN_WORKGROUPS) == (other == "64 rows")
     w = random_weights(C, d_h, d_e)
-    X = torch.empty((T, d_h), dtype=torch.bfloat16, device="cuda").normal_()
+    X = torch.empty((2048, d_h), dtype=torch.bfloat16, device="cuda").normal_()
     ws, Yp = d.buffers(d_h, d_e)
-    rule = device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws), n=5)
-    B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, 1)
-    own = device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws), n=5)
-    assert rule < 1.12 * own, (rule, own)
+    t = []
+    for form in ("rule", other):
+        B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, d.wide_min(form, d_e))
+        t.append(device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws), n=5))
+    assert t[0] < limit * t[1], t
 
 
 @pytest.mark.parametrize("rows", [36, 48])
@@ -126,13 +132,13 @@ def test_short_list_of_a_batch_that_could_have_a_long_one_time():
     C, rows, k, d_h, d_e = 36, 100, 8, 7168, 2048
     w = random_weights(C, d_h, d_e)
     t = {}
-    for T in (600, 1500):
+    for T in (600, 760):
         d = Dispatch([rows] * C, T, k)
-        assert d.list[0] <= 128 and (B.moe_max_blocks(T, k, C) > 128) == (T == 1500)
+        assert d.list[0] <= 128 and (B.moe_max_blocks(T, k, C) > 128) == (T == 760) and T * d_h * d_e < 12e9
         X = torch.empty((T, d_h), dtype=torch.bfloat16, device="cuda").normal_()
         ws, Yp = d.buffers(d_h, d_e)
         t[T] = device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws), n=5)
-    assert t[1500] < 1.09 * t[600], t
+    assert t[760] < 1.09 * t[600], t
 
 
 @pytest.mark.parametrize("counts,T,k,d_h,d_e,d_s,wide_min", [
@@ -362,3 +368,92 @@ def test_threshold_keeps_slots_streaming_in_large_batches(d_h, d_e):
             got.append(Yp[:d.n].clone())
             assert (Yp[d.n:] == 123.0).all() and B.moe_workspace_status(ws) == 0
     assert all(torch.equal(got[0], g) for g in got[1:])
+
+
+def test_large_by_its_work_below_2048_tokens():
+    """384 to 2047 tokens take the launch for large batches where T x d_h x d_e >= 12e9: one slot of several blocks, one short, one
+    without requests; alone, and with a shared expert, which is then a call of its own."""
+    counts, T, k, d_h, d_e, d_s = [200, 30, 0, 70], 900, 1, 7168, 2048, 64
+    assert T * d_h * d_e >= 12e9 and T * k > 56 * len(counts)
+    d, sh = Dispatch(counts, T, k), Dispatch([T], T, 1)
+    B.moe_shared_dispatch(T, *sh.dev)
+    cfg = W.MoEConfig("work", E=d.C, k=k, d_h=d_h, d_e=d_e, T=T, n_inst=1, C=d.C, zipf_s=0.0, seed=41)
+    X = W.activations(cfg)
+    W13, W2 = (np.stack(w) for w in zip(*(W.expert_weights(cfg, e) for e in range(d.C))))
+    ws13, ws2 = W.shared_expert_weights(cfg, d_s)
+    want = [ffn.grouped_ffn(X, W13, W2, d.off, d.perm, k), ffn.expert_ffn(X, ws13, ws2)]
+    packed = []
+    for w13, w2, n, width in ((W13, W2, d.C, d_e), (ws13[None], ws2[None], 1, d_s)):
+        a, b = to_device_bf16(w13), to_device_bf16(w2)
+        packed.append((torch.empty_like(a), torch.empty_like(b)))
+        B.moe_pack_weights_bf16(a, b, n, d_h, width, *packed[-1])
+    (ws, Yp), (s_ws, Ys) = d.buffers(d_h, d_e), sh.buffers(d_h, d_s)
+    X = to_device_bf16(X)
+
+    def check(got, ref):
+        num, den = np.linalg.norm(got - ref, axis=1), np.linalg.norm(ref, axis=1)
+        assert (num <= 2.5 * TOL_BF16 * den + 1e-30).all()
+
+    for shared in (False, True):
+        Yp.fill_(123.0)
+        if shared:
+            B.moe_grouped_ffn_shared(X, *packed[0], T, k, d.C, d_h, d_e, B.MOE_DTYPE_BF16, *d.dev, Yp, ws, *packed[1], d_s, *sh.dev,
+                                     Ys, s_ws)
+        else:
+            d.run(X, *packed[0], d_h, d_e, Yp, ws)
+        torch.cuda.synchronize()
+        check(Yp[:d.n].cpu().numpy(), want[0])
+        assert (Yp[d.n:] == 123.0).all() and B.moe_workspace_status(ws) == 0
+    check(Ys.cpu().numpy(), want[1])
+    assert B.moe_workspace_status(s_ws) == 0
+
+
+@pytest.mark.parametrize("form,victim", [("128 rows", 2), ("64 rows", 3), ("streaming", 3), ("rule", 8)])
+def test_wait_overrun_in_the_launch_for_large_batches(form, victim):
+    """A block of the launch for large batches that never becomes ready: NaN in its rows, the others as they are, status bit 0, and
+    after moe_workspace_init the bits of a clean run.  As for the other launches the host pre-loads the block's first-stage
+    counter, so that nobody completes it, and allows a few thousand polls."""
+    counts, T, k, d_h, d_e = [30, 64, 192, 129, 20, 200], 2048, 1, 192, 160
+    d = Dispatch(counts, T, k, seed=2)
+    entries = d.list.reshape(-1, 4)[1:]
+    cfg = W.MoEConfig("late", E=d.C, k=k, d_h=d_h, d_e=d_e, T=T, n_inst=1, C=d.C, zipf_s=0.0, seed=43)
+    X = to_device_bf16(W.activations(cfg))
+    W13, W2 = (to_device_bf16(np.stack(w)) for w in zip(*(W.expert_weights(cfg, e) for e in range(d.C))))
+    p13, p2 = torch.empty_like(W13), torch.empty_like(W2)
+    B.moe_pack_weights_bf16(W13, W2, d.C, d_h, d_e, p13, p2)
+    ws, Yp = d.buffers(d_h, d_e)
+
+    def run():
+        B.moe_workspace_set_option(ws, B.MOE_WS_OPT_WIDE_MIN_WORKGROUPS, d.wide_min(form, d_e))
+        Yp.fill_(123.0)
+        d.run(X, p13, p2, d_h, d_e, Yp, ws)
+        torch.cuda.synchronize()
+        assert (Yp[d.n:] == 123.0).all()
+        return Yp[:d.n].cpu().numpy(), B.moe_workspace_status(ws)
+
+    clean, status = run()
+    assert status == 0
+    slot, row, hi, _ = (int(v) for v in entries[victim])
+    rows = np.arange(row, min(hi, row + (128 if form == "128 rows" else 64)))
+    ws.view(torch.int32)[(victim + 1) * 256] = 1000
+    B.moe_workspace_set_option(ws, B.MOE_WS_OPT_SPIN_LIMIT, 5000)
+    got, status = run()
+    assert status == 1 and np.isnan(got[rows]).all()
+    others = np.setdiff1d(np.arange(d.n), rows)
+    np.testing.assert_array_equal(got[others], clean[others])
+    B.moe_workspace_init(ws)
+    again, status = run()
+    assert status == 0
+    np.testing.assert_array_equal(again, clean)
+
+
+def test_large_batch_refuses_a_list_of_other_blocks():
+    """A list cut into blocks of 32 rows is refused by the launch for large batches: status bit 1, nothing written."""
+    d = Dispatch([100, 40, 300], 2048, 1)
+    X = torch.zeros((2048, 64), dtype=torch.bfloat16, device="cuda")
+    w = random_weights(d.C, 64, 64)
+    ws, Yp = d.buffers(64, 64)
+    d.dev[2][1] = 32
+    d.run(X, *w, 64, 64, Yp, ws)
+    torch.cuda.synchronize()
+    assert B.moe_workspace_status(ws) == 2 and (Yp == 123.0).all()

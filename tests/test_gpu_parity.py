@@ -196,8 +196,8 @@ FFN_CFGS = [W.tiny(), small(), small("multi_tile", T=300, k=4, E=8, n_inst=2, C=
             small("f32_ragged", dtype="f32", T=21, d_h=36, d_e=20),
             W.dsv2lite(), W.qwen3(32), W.qwen3(256), W.qwen3(1024), W.stress(64, 1.25, 0.8),
             W.stress(2048, 1.25, 0.8), W.dsv3(512),
-            # token-heavy points of the stress sweep, lists that wrap around: T = 4096 has 360 first-stage workgroups of
-            # 128-row blocks (tiled GEMMs inside the streaming launch), T = 8192 has 576 (launches of their own, from 512 on)
+            # token-heavy points of the stress sweep in the launch for large batches: T = 4096 has 180 first-stage workgroups of
+            # 128-row blocks, T = 8192 has 288 (blocks of 128 rows from 176 on)
             W.stress(4096, 1.25, 0.8), W.stress(8192, 1.25, 0.8)]
 
 
@@ -675,8 +675,8 @@ def test_steps_replayed_from_a_hip_graph_match_eager():
 @pytest.mark.parametrize("cfg", [W.qwen3(1024), W.stress(2048, 1.25, 0.8), W.dsv3(512)], ids=lambda c: f"{c.name}-T{c.T}")
 def test_layer_parity_with_wide_blocks_forced_on(cfg):
     """Full-size layers whose hottest slots hold more than 64 requests, with those slots computed as
-    tiled-GEMM blocks (forced on: these batches have too few such blocks for the rule; blocks of 64
-    rows, and of 128 rows in the launch for batches of at least 2048 tokens)."""
+    tiled-GEMM blocks (forced on, whatever the rule says: blocks of 64 rows, and of 128 rows in the launch for large
+    batches, which the second takes)."""
     orc = OracleRun(cfg, only_activated=True)
     assert (orc.slot_count > 64).any()
     step = LayerStep(cfg, orc.lay, orc.g_self)
