@@ -341,7 +341,7 @@ int moe_pack_weights_bf16(const void *W13_dev, const void *W2_dev, int C, int d_
  * to bf16 once.  A slot's rows are cut into blocks of R = moe_block_rows(T) rows, each a streaming
  * item per channel tile (a slot with one block has its weights read from memory exactly once); in
  * batches with many slots of more than 64 requests those slots are computed as tiled GEMMs over
- * larger blocks by workgroups of the same launch (MOE_WS_OPT_WIDE_MIN_WORKGROUPS below).
+ * blocks of 64 or 128 rows by workgroups of the same launch (MOE_WS_OPT_WIDE_MIN_WORKGROUPS below).
  * The bf16 path is one launch in which the workgroups of the second stage
  * wait for flags raised by the first.  The wait is bounded: a workgroup whose wait runs out
  * (which means the control region was not cleared, or the GPU was shared with work that starved
@@ -440,8 +440,9 @@ int moe_combine_shared(const float *Yp_dev, const int32_t *pos_dev, const float 
 
 /* moe_grouped_ffn for the routed experts and for the shared expert (width d_s, the dispatch of moe_shared_dispatch, a
  * workspace of moe_workspace_bytes(T, 1, 1, d_h, d_s, dtype) bytes of its own, initialised like the other): Yp and Ys are what the
- * two calls give, up to the order in which a slot's K-steps are added.  One launch where it can be (bf16, T < 2048,
- * moe_max_blocks(T, k, C) <= 224, d_e / 32 and d_s / 32 both even or both odd), so that the shared expert runs beside the
+ * two calls give, up to the order in which a slot's K-steps are added.  One launch where it can be (bf16, moe_max_blocks(T, k, C)
+ * <= 224, d_e / 32 and d_s / 32 both even or both odd, neither set in the launch for large batches: T < 2048 and, from 384 tokens
+ * on, T x d_h x d_s < 12e9 and either T x d_h x d_e < 12e9 or T*k <= 56*C), so that the shared expert runs beside the
  * routed experts' weight stream; otherwise the two calls one after the other.  Nothing is launched when an argument of
  * either set is refused.
  */

@@ -90,13 +90,13 @@ void launch_ffn_stream_shared(const FfnCall &c, const FfnCall &sh, int T, int d_
 
 // Batches that take the launch for large batches (ffn_big_kernel; block lists of 64 rows): from 2048 tokens on, and below
 // where T x d_h x d_e is large, unless the slots have few requests even if all of them are local.  Us a layer in that launch and in the
-// streaming launch: T = 2040, d_h = 4096, d_e = 1536 164 and 197; T = 1000, d_h = 7168, d_e = 2048 275 and 276, T = 2040 356 and 362;
+// streaming launch: T = 2040, d_h = 4096, d_e = 1536 170 and 197; T = 1000, d_h = 7168, d_e = 2048 275 and 276, T = 2040 356 and 362;
 // but T = 1000, d_h = 4096, d_e = 1536 155 and 152; d_h = 2048, d_e = 1408 97 and 89; T = 2000 120 and 114.  From 2048 tokens on it is the
 // faster one where the batch has many wide blocks, which the host cannot know (64 slots of 250 rows, d_h = 1024, d_e = 512 102 and 131;
 // T = 8000, d_h = 2048, d_e = 768, zipf 1 126 and 157); but 64 to 131 requests a slot, of which a quarter is local, 3-12 % slower.
 // At most 56 requests a slot on average leave few slots with more than 64, and streaming items want the third workgroup a CU: 200
-// slots of 20 rows, d_h = 512, d_e = 256 57 and 42; 128 of 33 (T = 2500, k = 2: 50 a slot), d_h = 1024, d_e = 512 94 and 79; popular slots of
-// up to 400 rows cost at most 5 % (160 slots, 52 on average, zipf 0.6, d_h = 7168, d_e = 256 521 and 546).  With 63 on average, all
+// slots of 20 rows, d_h = 512, d_e = 256 57 and 42; 100 of 50, d_h = 1024, d_e = 512 94 and 79; popular slots of
+// up to 400 rows cost at most 5 % (160 slots, 52 on average, zipf 0.6, d_h = 7168, d_e = 256 516 and 545).  With 63 on average, all
 // local, half of the slots are wide: 132 slots, d_h = 4096, d_e = 1536 1028 and 1201.
 constexpr int kBigMinTokens = 2048;
 constexpr long long kBigWork = 12000000000LL;

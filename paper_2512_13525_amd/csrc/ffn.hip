@@ -12,7 +12,7 @@
 // workgroup's share of a matrix is one contiguous run of 2 KiB steps read with fully coalesced
 // 128-bit loads straight into MFMA registers.
 //
-// fp32 path (correctness configuration): plain wave-per-output-row dot products, two kernels.
+// fp32 path (correctness configuration): tiles of 16 rows x 16 channels on the fp32 matrix cores, two launches.
 #include <stdlib.h>
 
 #include <mutex>

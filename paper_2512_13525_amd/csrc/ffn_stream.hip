@@ -30,8 +30,8 @@
 //
 // Both stages run in ONE launch: the stage-2 workgroups have the higher ids, so the hardware
 // starts them only after every stage-1 workgroup has been started, and they fill the compute
-// units that the tail of stage 1 leaves idle.  A stage-2 workgroup first puts its weight loads in
-// flight and then waits until the 16-channel tiles of its block of `act` rows are all written: a
+// units that the tail of stage 1 leaves idle.  A streaming workgroup of stage 2 first puts its weight loads
+// in flight (a tiled-GEMM one requests nothing yet) and then waits until the 16-channel tiles of its block of `act` rows are all written: a
 // counter per block in the workspace is bumped by each stage-1 workgroup once its stores are
 // acknowledged; the workgroup that completes the count raises the block's ready flags, which the
 // stage-2 workgroups poll (bounded; on an overrun the workgroup raises the workspace's error word,
@@ -328,11 +328,12 @@ __device__ __forceinline__ void stream_item_lines(const StreamArgs &a, const Sta
 
     // Weights run D super-steps ahead (ring wr); the token rows DB super-steps: the loads of
     // super-step q+DB are issued in iteration q *before* the weights of q+D.  Loads return in order,
-    // so waiting for the token rows of the next super-step also waits for every older weight load:
-    // with DB = 1 only the newest super-step of weights stays in flight across that wait, with
-    // DB = 2 (where the registers allow it: blocks of up to 16 rows, 32 in the 64-row kernel) two do.  The steady-state
-    // loop has no branch, so the compiler counts outstanding loads exactly; before and after it
-    // loads are only issued for super-steps that exist.
+    // so waiting for the token rows of the next super-step also waits for every older weight load.
+    // At the top of the loop the compiler allows for the way into it, where the first weights are in front of the first
+    // token rows: every D-th super-step waits until nothing or (DB = 1) the rows of one are in flight.  Waiting for the first rows
+    // ahead of the loop instead, so that 4 to 16 loads stay in flight, is level or slower (four layer steps with five blocks of up
+    // to 5 rows 91.4 and 92.3 us, with 17 of up to 32 rows 154.0 and 155.7; d_h = 7168, T = 512 222.2 and 223.6).
+    // Before and after the loop loads are only issued for super-steps that exist.
     constexpr int DB = (NH <= 4) ? D : 1;                        // D: the two rings share their positions
     bf16x8 wr[D][2][2];
     bf16x8 br[DB][NH];
@@ -1180,7 +1181,7 @@ void ffn_stream_kernel(StreamArgs a) {
             own_item();
         } else {
             if (n_blocks <= lanes) {
-                own_item();              // as without WRAP: the loop's copy of the items is up to 14 % slower on full 64-row blocks
+                own_item();              // as without WRAP: the loop's copy of the tiled-GEMM items is up to 4 % slower
                 return;
             }
             if (blockIdx.x >= n1 + n2) return;
@@ -1231,9 +1232,9 @@ void ffn_stream_kernel(StreamArgs a) {
 // two launches 168 + 77 us).  Its first-stage workgroups have the lowest ids, because their chains are the longest, and
 // the numbers of its blocks and of those ids follow from T; then the routed first stage, and the second stages in
 // the same order, so that again no workgroup waits for one with a higher id.  Every block has workgroups of its own, and
-// the second stages have the same parity of K-steps.  Layer steps with a shared expert, two FFN launches and one, us: T = 256
-// as above 285 -> 243, T = 8 96 -> 83; d_h = 2048, d_e = 1408, shared width 1408: T = 8 (two layers) 88 -> 69, T = 128 67 -> 59,
-// T = 512 107 -> 89, T = 1000 140 -> 119.
+// the second stages have the same parity of K-steps.  Layer steps with a shared expert, two FFN launches and one, us, means of three
+// inputs: T = 256 as above 282 -> 234, T = 8 109 -> 95; d_h = 2048, d_e = 1408, shared width 1408: T = 8 43 -> 34, T = 128 63 -> 56,
+// T = 512 101 -> 83, T = 1000 127 -> 111.
 struct SharedArgs {
     StreamArgs set[2];
     unsigned shared_blocks;              // the shared list's number of blocks, at most
@@ -1293,16 +1294,17 @@ void launch_shared(const SharedArgs &p, int block_rows, unsigned blocks, hipStre
 }
 
 // ---------------------------------------------------------------------------------------------
-// Batches of at least kBigMinTokens tokens: every slot with more than kWideMin requests as wide blocks of two packed tiles a
+// Batches that ffn_is_big() takes: every slot with more than kWideMin requests as wide blocks of two packed tiles a
 // wavefront, the others as streaming items (one block each), in one launch of two workgroups a CU with the registers for both.
 // The blocks are looked up in the list by their number among the wide or the streaming ones (find_entry), not by their place in it: a wide
 // block has as many ids as it has groups of tiles, and only a slot can have a streaming block, so the worst-case grid stays small (32000 workgroups at T = 8192, k = 8, C = 16,
 // d_h = 4096, d_e = 1536, where ids for every tile of every block of 64 rows would be 166000) and no workgroup has to walk a list.
 // Wide blocks come first: their chains are the longest and hide behind the streams.  Against blocks of 128 rows x four tiles in two
-// launches of their own before the streaming launch, us a layer: T = 8192, d_h = 4096,
-// d_e = 1536 388 -> 303, T = 3000 232 -> 193; d_h = 2048, d_e = 1408, T = 2500 151 -> 128; d_e = 768, T = 4000 98 -> 90; 64 slots of 250 rows,
-// d_h = 1024, d_e = 512 144 -> 102.  Slower where nothing is wide and the slots are many (128 slots of 64 rows, d_h = 2048, d_e = 768
-// 307 -> 317; 200 of 20 rows, d_h = 512, d_e = 256 54 -> 58).
+// launches of their own before the streaming launch, us of these launches, least and most of five inputs: T = 8192, d_h = 4096,
+// d_e = 1536 180 and 645 -> 148 and 536, T = 3000 127 and 164 -> 108 and 141; d_h = 2048, d_e = 1408, T = 3000 77 and 207 -> 63 and 148;
+// d_e = 768, T = 4000 57 and 181 -> 50 and 114.  Slower where nearly nothing is wide, the slots are many and ffn_is_big() cannot tell (128
+// slots of 64 rows, T*k = 128*C, d_h = 2048, d_e = 768 304 -> 309; 199 of 40 rows and one of 300, T*k = 82*C, d_h = 7168, d_e = 256
+// 655 -> 737), and where a few blocks are all there is (one slot of 500 rows, d_h = d_e = 2048 35 -> 39).
 struct BigArgs {
     StreamArgs a;
     int groups[2];                       // workgroups of a wide block: groups of eight packed tiles of a stage
@@ -1525,9 +1527,11 @@ int launch_ffn_stream(const FfnCall &c, int T, int d_h, hipStream_t st) {
 }
 
 // Routed blocks that the launch of two sets has workgroups for.  It has no loop over a long list, and the surplus of its grid
-// costs more the larger the bound is (us a step with the shared expert, two launches and one: bound 131, d_h = 7168,
-// T = 380 330 and 271; 161, T = 900 392 and 380; 204, d_h = 2048, d_e = 768, T = 1500 97.0 and 90.5; 195, d_e = 1408,
-// T = 1900 172.5 and 164.1; 267, d_e = 768, T = 2000 110.8 and 113.0; 286, d_h = 7168, T = 2000 608 and 616).
+// costs more the larger the bound is (us a step with the shared expert, two launches and one, means of three inputs: bound 131,
+// d_h = 7168, d_e = 2048, T = 380 358 and 292; 157, d_h = 2048, d_e = 1408, T = 1500 158 and 144; 195, T = 1900 179 and 168; 204,
+// d_e = 768, T = 1500 104 and 93; 203, d_h = 4096, d_e = 1536, T = 1500 225 and 221; 267, d_h = 2048, d_e = 768, T = 2000 111 and 113).  A set
+// that takes the launch for large batches keeps a call of its own (d_h = 7168, d_e = 2048, shared width 2048: T = 900 389, in one
+// launch of streaming and 64-row items 399; T = 1500 516 and 549).
 constexpr long long kSharedMaxBlocks = 224;
 bool ffn_stream_takes_shared(const FfnCall &c, const FfnCall &sh, int T, int d_h) {
     const long long items = ffn_max_blocks(T, c.k, c.C), items_s = ffn_max_blocks(T, sh.k, sh.C);

@@ -127,18 +127,18 @@ def test_partly_filled_last_block_time(rows):
 
 
 def test_short_list_of_a_batch_that_could_have_a_long_one_time():
-    """The same slots in a batch whose list could be longer than the workgroups' own blocks (128) take little longer (1.04
-    times, token rows spread over more tokens; 1.14 when they run through the loop that walks long lists)."""
-    C, rows, k, d_h, d_e = 36, 100, 8, 7168, 2048
+    """The same slots in a batch whose list could be longer than the workgroups' own blocks (128) take no longer (1.007 times,
+    token rows spread over more tokens; 1.036 when they run through the loop that walks long lists)."""
+    C, rows, k, d_h, d_e = 36, 100, 8, 2048, 1408
     w = random_weights(C, d_h, d_e)
     t = {}
-    for T in (600, 760):
+    for T in (600, 1500, 600, 1500):
         d = Dispatch([rows] * C, T, k)
-        assert d.list[0] <= 128 and (B.moe_max_blocks(T, k, C) > 128) == (T == 760) and T * d_h * d_e < 12e9
+        assert d.list[0] <= 128 and (B.moe_max_blocks(T, k, C) > 128) == (T == 1500) and T * d_h * d_e < 12e9
         X = torch.empty((T, d_h), dtype=torch.bfloat16, device="cuda").normal_()
         ws, Yp = d.buffers(d_h, d_e)
-        t[T] = device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws), n=5)
-    assert t[760] < 1.09 * t[600], t
+        t[T] = min(t.get(T, 1e9), device_time(lambda: d.run(X, *w, d_h, d_e, Yp, ws), n=5))
+    assert t[1500] < 1.025 * t[600], t
 
 
 @pytest.mark.parametrize("counts,T,k,d_h,d_e,d_s,wide_min", [
