@@ -514,6 +514,20 @@ __device__ __forceinline__ void aebs_block(const SchedTables &tb, SchedShared &s
 }
 
 // ------------------------------------------------------------------ a4: dispatch in one workgroup
+// The lanes of `among` whose v (below 2^bits) is this lane's; meaningless in other lanes.  A ballot per bit, whatever the number of
+// different values.
+__device__ __forceinline__ uint64_t lanes_alike(int v, int bits, uint64_t among) {
+    uint32_t lo = static_cast<uint32_t>(among), hi = static_cast<uint32_t>(among >> 32);
+    int w = static_cast<int>(static_cast<uint32_t>(v) << (32 - bits));
+    for (int b = 0; b < bits; ++b, w = static_cast<int>(static_cast<uint32_t>(w) << 1)) {   // wave-uniform; the bit is w's sign
+        const uint64_t ones = __ballot(w < 0);
+        const uint32_t mine = static_cast<uint32_t>(w >> 31);
+        lo &= ~(static_cast<uint32_t>(ones) ^ mine);
+        hi &= ~(static_cast<uint32_t>(ones >> 32) ^ mine);
+    }
+    return static_cast<uint64_t>(hi) << 32 | lo;
+}
+
 struct PermShared {
     int cnt[kFrontWaves][MOE_MAX_SLOTS];     // pass A: counts; pass B: running bases
     int total[MOE_MAX_SLOTS];
@@ -559,6 +573,43 @@ __device__ __forceinline__ void scan_slots(PermShared &sh, int C, int block_rows
         sh.off[C] = carry;
         slot_off[C] = carry;
         sh.blk_base[C] = hcarry + lcarry;
+    }
+}
+
+// The same for batches of few requests (below 32768, so that the counts of blocks fit 16 bits): the totals come from total_of(s) and go
+// to slot_count as well, and one scan carries both classes' blocks.
+template <typename TotalOf>
+__device__ __forceinline__ void scan_slots_packed(PermShared &sh, int C, int block_rows, TotalOf total_of,
+                                                  int32_t *__restrict__ slot_count, int32_t *__restrict__ slot_off, int lane) {
+    int carry = 0, bcarry = 0, wide = 0;                              // blocks: heavy slots' << 16 | light slots'; wide: 64-row << 16 | 128-row
+    for (int s0 = 0; s0 < C; s0 += MOE_WAVE) {
+        const int s = s0 + lane;
+        const int v = s < C ? total_of(s) : 0;
+        const int nb = (v + block_rows - 1) / block_rows;
+        wide += v > 64 ? ((v + 63) / 64) << 16 | (v + 127) / 128 : 0;
+        const bool heavy = v > kHeavyRows;
+        const int b = heavy ? nb << 16 : nb;
+        const int incl = wave_incl_scan_i32(v), bincl = wave_incl_scan_i32(b);
+        if (s < C) {
+            sh.off[s] = carry + incl - v;
+            slot_off[s] = carry + incl - v;
+            slot_count[s] = v;
+            // light slots are placed relative to the end of the heavy class, added below
+            const int at = bcarry + bincl - b;
+            sh.blk_base[s] = heavy ? at >> 16 : -(at & 0xffff) - 1;
+        }
+        carry += __builtin_amdgcn_readlane(incl, MOE_WAVE - 1);
+        bcarry += __builtin_amdgcn_readlane(bincl, MOE_WAVE - 1);
+    }
+    for (int s = lane; s < C; s += MOE_WAVE)
+        if (sh.blk_base[s] < 0) sh.blk_base[s] = (bcarry >> 16) + (-sh.blk_base[s] - 1);
+    wide = __builtin_amdgcn_readlane(wave_incl_scan_i32(wide), MOE_WAVE - 1);
+    if (lane == 0) {
+        sh.n_wide = wide >> 16;
+        sh.n_wide128 = wide & 0xffff;
+        sh.off[C] = carry;
+        slot_off[C] = carry;
+        sh.blk_base[C] = (bcarry >> 16) + (bcarry & 0xffff);
     }
 }
 

@@ -242,7 +242,7 @@ int launch_gate(const void *X, const void *Wr, const float *bias, float *logits,
 // Decode-size tail (up to kRegPairs requests): Alg. 1 and the counting sort with every request id
 // held in registers.  Wavefront w owns requests [w*gpw*64, (w+1)*gpw*64), the mapping the sort needs,
 // so the ids are read from memory exactly once and everything after that runs out of LDS and registers.
-constexpr int kGpwMax = 8;                                            // 64-request groups per wavefront (compiled for 1, 2, 4 and 8)
+constexpr int kGpwMax = 8;                                            // 64-request groups per wavefront (1 and 2: front_tail_few; 4 and 8: front_tail_small)
 constexpr int kRegPairs = moe::kFrontWaves * kGpwMax * MOE_WAVE;      // 8192
 constexpr int kSlotOfLds = 8192;                                      // E*n_inst entries of slot_of kept in LDS
 // A batch of a few tokens is routed by one workgroup: the ids stay in LDS, and the publication, the ticket and the
@@ -257,6 +257,7 @@ struct SmallShared {
     moe::SchedShared sched;
     moe::PermShared perm;
     alignas(16) int16_t slot_of[kSlotOfLds];
+    int16_t expert_of[MOE_MAX_SLOTS];                                 // of this instance's slots; unspecified where a slot is empty
 };
 
 // The tail's layout tables in LDS, its flags and counters cleared.  Every workgroup prepares this while
@@ -294,10 +295,10 @@ __device__ __forceinline__ void stage_small(const FrontArgs &a, SmallShared &sh,
     reinterpret_cast<uint4 *>(&sh.perm.cnt[0][0])[i] = make_uint4(0u, 0u, 0u, 0u);
 }
 
-// ids_lds: the batch's request ids in LDS (one-workgroup launch), or null: they were written by other
-// workgroups and are read with agent-scope loads.  VPL >= n_words; GPW >= 64-request groups per wavefront.
+// VPL >= n_words; GPW >= 64-request groups per wavefront.  The request ids were written by other workgroups and are read with
+// agent-scope loads.
 template <int VPL, int GPW>
-__device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared &sh, int n_pairs, const int32_t *ids_lds) {
+__device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared &sh, int n_pairs) {
     const int tid = threadIdx.x;
     const int wave = tid / MOE_WAVE, lane = tid % MOE_WAVE;
     const int E = a.E, n_inst = a.n_inst, C = a.C;
@@ -310,7 +311,7 @@ __device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared
         const int p = (wave * gpw + g) * MOE_WAVE + lane;
         id[g] = -1;
         if (g < gpw && p < n_pairs)
-            id[g] = ids_lds ? ids_lds[p] : __hip_atomic_load(a.ids + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            id[g] = __hip_atomic_load(a.ids + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     // ---- Step 1
 #pragma unroll
@@ -421,12 +422,123 @@ __device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared
     }
 }
 
+// The tail of batches with one or two requests a thread (GPW).  An expert has at most one slot on this instance, so which of its slots a
+// request would go to and the request's place there do not wait for Alg. 1: they are worked out with Step 1, and the counts' prefix over
+// the wavefronts beside Step 2; what follows Step 2 is the scan over the slots that it kept, on the second wavefront beside the stores of
+// Step 3, and the stores.  Bound by the instructions of its 16 wavefronts, four to a SIMD of one CU.  Against front_tail_small, which has two
+// passes over the requests and two more barriers behind Step 2: four layer steps at d_h = 2048, k = 8 with T = 8 95.0 -> 93.3 us, with T = 256
+// 164.1 -> 162.6; the gate and this launch at E = 64, k = 6, T = 300 12.3 -> 11.4 us.  With four and more requests a thread the ranks ahead of
+// Step 2 take what they save behind it (E = 256, k = 8, T = 512 behind the gate 23.5 and 23.7 us), so those batches keep front_tail_small.
+// ids_lds: the batch's request ids in LDS (one-workgroup launch), or null: they were written by other workgroups.  VPL >= n_words.
+template <int VPL, int GPW>
+__device__ __forceinline__ void front_tail_few(const FrontArgs &a, SmallShared &sh, int n_pairs, const int32_t *ids_lds) {
+    const int tid = threadIdx.x;
+    const int wave = tid / MOE_WAVE, lane = tid % MOE_WAVE;
+    const int E = a.E, n_inst = a.n_inst, C = a.C, p0 = wave * GPW * MOE_WAVE + lane;   // request g of this thread: p0 + g * MOE_WAVE
+    int id[GPW];
+#pragma unroll
+    for (int g = 0; g < GPW; ++g) {
+        const int p = p0 + g * MOE_WAVE;
+        id[g] = -1;
+        if (p < n_pairs) id[g] = ids_lds ? ids_lds[p] : __hip_atomic_load(a.ids + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+
+    // ---- Step 1; the slot of the request's expert here, or -1, and the request's place among its wavefront's for that slot
+    int sl[GPW], rank[GPW];
+#pragma unroll
+    for (int g = 0; g < GPW; ++g) {
+        sl[g] = -1;
+        if (id[g] >= 0) {
+            sh.sched.flag[id[g]] = 1u;
+            sl[g] = sh.slot_of[id[g] * n_inst + a.g_self];
+        }
+    }
+    int *run = &sh.perm.cnt[wave][0];                                 // this wavefront's requests of each slot so far
+#pragma unroll
+    for (int g = 0; g < GPW; ++g) {
+        const uint64_t same = moe::lanes_alike(sl[g], 32 - __builtin_clz(C), __ballot(sl[g] >= 0));
+        rank[g] = 0;
+        if (sl[g] >= 0) {
+            const int before = g > 0 ? run[sl[g]] : 0;
+            rank[g] = before + __popcll(same & moe::lanemask_lt());
+            if (lane == __builtin_ctzll(same)) run[sl[g]] = before + __popcll(same);
+        }
+        if (g + 1 < GPW) {                                            // the next group reads what this one's first lanes wrote
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        }
+    }
+    __syncthreads();
+
+    // ---- Step 2 (first wavefront), slot_of in LDS; the prefix over the wavefronts meanwhile
+    if (wave == 0) {
+        const auto rep_of = [&](int e, int g) {
+            const int single = sh.sched.single_rid[e], multi = (g < 0 ? 0 : g) * C + sh.slot_of[e * n_inst + (g < 0 ? 0 : g)];
+            return g >= 0 ? multi : single;
+        };
+        const int load = moe::aebs_select_wave<VPL, VPL>(sh.sched.flag, sh.sched.host_mask, sh.sched.multi_mask,
+                                                    sh.sched.single_mask, E, n_inst, a.n_words, lane, rep_of, sh.sched.rep,
+                                                    a.act_rep);
+        if (lane < n_inst) a.load[lane] = load;
+    } else {
+        for (int s = tid - MOE_WAVE; s < C; s += moe::kFrontThreads - MOE_WAVE) {
+            int run = 0;
+#pragma unroll
+            for (int w = 0; w < moe::kFrontWaves; ++w) {
+                const int c = sh.perm.cnt[w][s];
+                sh.perm.cnt[w][s] = run;
+                run += c;
+            }
+            sh.perm.total[s] = run;
+        }
+        for (int e = tid - MOE_WAVE; e < E; e += moe::kFrontThreads - MOE_WAVE) {
+            const int s = sh.slot_of[e * n_inst + a.g_self];
+            if (s >= 0) sh.expert_of[s] = static_cast<int16_t>(e);
+        }
+    }
+    __syncthreads();
+
+    // ---- Step 3; the second wavefront places the slots that Alg. 1 kept
+    const int rid_lo = a.g_self * C;
+    if (wave == 1) {
+        const auto total_of = [&](int s) {
+            const int e = sh.expert_of[s] & (MOE_MAX_EXPERTS - 1);    // unspecified for an empty slot, whose total is 0
+            return sh.sched.rep[e] == rid_lo + s ? sh.perm.total[s] : 0;
+        };
+        moe::scan_slots_packed(sh.perm, C, a.block_rows, total_of, a.slot_count, a.slot_off, lane);
+    }
+    int row[GPW];
+#pragma unroll
+    for (int g = 0; g < GPW; ++g) {
+        row[g] = -1;
+        if (id[g] >= 0) {
+            const int r = sh.sched.rep[id[g]];
+            a.rid[p0 + g * MOE_WAVE] = r;
+            if (sl[g] >= 0 && r == rid_lo + sl[g]) row[g] = rank[g] + sh.perm.cnt[wave][sl[g]];
+        }
+    }
+    __syncthreads();
+    moe::list_blocks(sh.perm, C, a.block_rows, a.blocks);
+#pragma unroll
+    for (int g = 0; g < GPW; ++g) {
+        if (id[g] >= 0) {
+            const int p = p0 + g * MOE_WAVE;
+            if (row[g] >= 0) {
+                row[g] += sh.perm.off[sl[g]];
+                a.perm[row[g]] = p;
+            }
+            a.pos[p] = row[g];
+        }
+    }
+}
+
 template <int VPL>
 __device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared &sh, int n_pairs) {
-    if (n_pairs <= kRegPairs / 8) front_tail_small<VPL, 1>(a, sh, n_pairs, nullptr);
-    else if (n_pairs <= kRegPairs / 4) front_tail_small<VPL, 2>(a, sh, n_pairs, nullptr);
-    else if (n_pairs <= kRegPairs / 2) front_tail_small<VPL, 4>(a, sh, n_pairs, nullptr);
-    else front_tail_small<VPL, kGpwMax>(a, sh, n_pairs, nullptr);
+    if (n_pairs <= kRegPairs / 8) front_tail_few<VPL, 1>(a, sh, n_pairs, nullptr);
+    else if (n_pairs <= kRegPairs / 4) front_tail_few<VPL, 2>(a, sh, n_pairs, nullptr);
+    else if (n_pairs <= kRegPairs / 2) front_tail_small<VPL, 4>(a, sh, n_pairs);
+    else front_tail_small<VPL, kGpwMax>(a, sh, n_pairs);
 }
 
 template <int VPL>
@@ -476,7 +588,7 @@ void front_kernel(FrontArgs a) {
     if (small && early) stage_small(a, sh.small, tp);
     if (solo) {
         __syncthreads();
-        front_tail_small<VPL, 1>(a, sh.small, n_pairs, s_ids);
+        front_tail_few<VPL, 1>(a, sh.small, n_pairs, s_ids);
         return;
     }
     if (a.act_bits) {

@@ -69,6 +69,47 @@ def test_front_sizes(n_inst, C, E, T):
         assert int(s.sync[:33].abs().sum().item()) == 0
 
 
+@pytest.mark.parametrize("n_inst,C,E", [(1, 256, 200), (2, 1, 2), (2, 64, 90), (4, 65, 150)])
+@pytest.mark.parametrize("T", [1, 63, 65, 1023, 1024, 1025, 2047, 2048, 2049])
+def test_front_of_few_requests(n_inst, C, E, T):
+    """Up to 1024 and 2048 requests (one and two a thread, one expert a token: the edges lie on T) the sort starts before Alg. 1
+    has decided: every instance's dispatch against the oracle, with one slot an instance, all of them, empty slots among the others,
+    experts with a slot on several instances (kept on one of them) and requests that all name one expert."""
+    k = 1
+    rng = np.random.default_rng([n_inst, C, E, T])
+    lay = np.full(n_inst * C, -1, dtype=np.int32)
+    for e in range(E):                                               # homes round-robin, then second replicas as far as slots go
+        lay[(e % n_inst) * C + e // n_inst] = e
+    if C > 1:
+        for e in range(0, E, 3):
+            g = (e + 1) % n_inst
+            free = np.nonzero(lay[g * C:(g + 1) * C] < 0)[0]
+            if n_inst > 1 and len(free) > 2:
+                lay[g * C + free[-1]] = e
+    pl = scheduling.make_placement(lay, E, n_inst, C)
+    for hot in (False, True):
+        logits = rng.standard_normal((T, E)).astype(np.float32)
+        if hot:
+            logits[:, E // 2] += 20.0
+        ids, _ = routing.route_softmax(logits, k)
+        O, act_rep, load = scheduling.aebs(ids, pl)
+        for g in range(n_inst):
+            count, off, perm = dispatch.permute(O, g, C)
+            cfg = W.MoEConfig("few", E=E, k=k, d_h=32, d_e=32, T=T, n_inst=n_inst, C=C, zipf_s=0.0, seed=1)
+            s = LayerStep(cfg, lay, g)
+            for t in (s.rid, s.slot_count, s.slot_off, s.perm, s.pos, s.blocks):
+                t.fill_(-5)
+            s.front(torch.from_numpy(logits).cuda())
+            torch.cuda.synchronize()
+            pos = np.full(T * k, -1)
+            pos[perm] = np.arange(len(perm))
+            for got, want in ((s.rid, O), (s.act_rep, act_rep), (s.load, load), (s.slot_count, count), (s.slot_off, off), (s.pos, pos)):
+                np.testing.assert_array_equal(got.cpu().numpy().reshape(np.shape(want)), want)
+            np.testing.assert_array_equal(s.perm.cpu().numpy()[:len(perm)], perm)
+            blk = expected_blocks(off, B.moe_block_rows(T))
+            np.testing.assert_array_equal(s.blocks.cpu().numpy()[:len(blk)], blk)
+
+
 @pytest.mark.parametrize("E,k", [(64, 9), (64, 10), (128, 8), (256, 32), (512, 8), (576, 8), (704, 32), (768, 3), (1024, 8)])
 def test_front_selects_like_route(E, k):
     """Ids and weights of the front and of moe_route, bit for bit, on logits full of ties, for every number of keys a lane that
