@@ -579,7 +579,7 @@ __device__ __forceinline__ bool stream_item_down(const StreamArgs &a, const Stag
 // its leading entry as [K-tile of stage 2 = 64 channels][row][128 bytes]: every 128-byte line has one
 // writing workgroup, and stage 2 reads a K-tile of all rows as one contiguous run.  The hand-off is
 // the one of the streaming items: counter and flags of the leading entry.
-template <bool STAGE1, int RT>
+template <bool STAGE1, int RT, bool AHEAD>
 __device__ __forceinline__ void wide_item(const StreamArgs &a, const StageArgs &g, char *lds, int *s_ok,
                                           int item, int group, int n_groups, int slot, int row0, int m, bool drain) {
     constexpr int kRing = 2;                                         // K-tiles of both operands in flight
@@ -669,20 +669,33 @@ __device__ __forceinline__ void wide_item(const StreamArgs &a, const StageArgs &
         }                                                                                        \
         asm volatile("" ::: "memory");                                                           \
     } while (0)
-    // the multiply of one K-step: row tiles in groups of up to four (LDS reads of a group, then its MFMAs)
-#define MOE_WIDE_MMA_STEP(set, ss)                                                               \
+    // A K-tile's products.  AHEAD: the second K-step's fragments are read between the first one's products, one behind each row tile's,
+    // instead of ahead of its own, where every wavefront waits for LDS a second time (layer steps, us: d_h = 2048, d_e = 1408, T = 1000 108.7 ->
+    // 107.7, without popular experts 102.8 -> 101.6; d_e = 768, T = 1500 73.7 -> 72.7; d_h = 4096, d_e = 1536, T = 700 level).
+#define MOE_WIDE_READ(set, ss, r)                                                                \
+    b_[r] = *reinterpret_cast<const bf16x8 *>(lds + ((set) & 1) * kBufBytes + (r) * 2048 + rd_row + (((4 * (ss) + rd_g) ^ rd_sw) * 16))
+#define MOE_WIDE_MMA(set, full)                                                                  \
     do {                                                                                         \
-        _Pragma("unroll") for (int r0_ = 0; r0_ < RT; r0_ += 4) {                                \
-            bf16x8 b_[4];                                                                        \
-            _Pragma("unroll") for (int r4 = 0; r4 < 4; ++r4)                                     \
-                if (r0_ + r4 < RT)                                                               \
-                    b_[r4] = *reinterpret_cast<const bf16x8 *>(                                  \
-                        lds + ((set) & 1) * kBufBytes + (r0_ + r4) * 2048 + rd_row + (((4 * (ss) + rd_g) ^ rd_sw) * 16)); \
-            _Pragma("unroll") for (int r4 = 0; r4 < 4; ++r4)                                     \
-                if (r0_ + r4 < RT) {                                                             \
-                    acc[r0_ + r4][0] = mfma16(areg[set][ss][0], b_[r4], acc[r0_ + r4][0]);       \
-                    acc[r0_ + r4][1] = mfma16(areg[set][ss][1], b_[r4], acc[r0_ + r4][1]);       \
-                }                                                                                \
+        bf16x8 b_[RT];                                                                           \
+        _Pragma("unroll") for (int r = 0; r < RT; ++r) MOE_WIDE_READ(set, 0, r);                 \
+        if constexpr (AHEAD) { asm volatile("" ::: "memory"); __builtin_amdgcn_sched_barrier(0); } \
+        _Pragma("unroll") for (int r = 0; r < RT; ++r) {                                         \
+            acc[r][0] = mfma16(areg[set][0][0], b_[r], acc[r][0]);                               \
+            acc[r][1] = mfma16(areg[set][0][1], b_[r], acc[r][1]);                               \
+            if constexpr (AHEAD) {                                                               \
+                if (full) MOE_WIDE_READ(set, 1, r);                                              \
+                asm volatile("" ::: "memory");                                                   \
+                __builtin_amdgcn_sched_barrier(0);                                               \
+            }                                                                                    \
+        }                                                                                        \
+        if (full) {                                                                              \
+            if constexpr (!AHEAD) {                                                              \
+                _Pragma("unroll") for (int r = 0; r < RT; ++r) MOE_WIDE_READ(set, 1, r);         \
+            }                                                                                    \
+            _Pragma("unroll") for (int r = 0; r < RT; ++r) {                                     \
+                acc[r][0] = mfma16(areg[set][1][0], b_[r], acc[r][0]);                           \
+                acc[r][1] = mfma16(areg[set][1][1], b_[r], acc[r][1]);                           \
+            }                                                                                    \
         }                                                                                        \
     } while (0)
     // The LDS buffer written here was last read in the multiply of K-tile i-2, which every wavefront
@@ -692,8 +705,7 @@ __device__ __forceinline__ void wide_item(const StreamArgs &a, const StageArgs &
         MOE_WIDE_STAGE(set);                                                                     \
         MOE_WIDE_LOAD_B(set, (i) + kRing);                                                       \
         lds_barrier();                                                                           \
-        MOE_WIDE_MMA_STEP(set, 0);                                                               \
-        if (full) MOE_WIDE_MMA_STEP(set, 1);                                                     \
+        MOE_WIDE_MMA(set, full);                                                                 \
         asm volatile("" ::: "memory");                                                           \
         MOE_WIDE_LOAD_A(set, (i) + kRing);                                                       \
     } while (0)
@@ -731,7 +743,8 @@ __device__ __forceinline__ void wide_item(const StreamArgs &a, const StageArgs &
 #undef MOE_WIDE_LOAD_A
 #undef MOE_WIDE_LOAD_B
 #undef MOE_WIDE_STAGE
-#undef MOE_WIDE_MMA_STEP
+#undef MOE_WIDE_READ
+#undef MOE_WIDE_MMA
 #undef MOE_WIDE_STEP
 
     // lane l holds, per row tile, 4 consecutive channels (l/16)*4.. of row (l%16) of the tile
@@ -1035,8 +1048,9 @@ __device__ __forceinline__ void run_wide(const StreamArgs &a, const StageArgs &g
     const bool drain = wide_drains<BR>(n, a.s[1].tiles);
     // up to 16 rows as two row tiles (one kind of item less; slots of 72 rows: 58 -> 61 us at d_h = 2048, d_e = 768, 173 -> 163 at
     // d_h = 4096, d_e = 1536)
-    if (rt <= 2) wide_item<STAGE1, 2>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m, drain);
-    else wide_item<STAGE1, 4>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m, drain);
+    constexpr bool kAhead = BR == 64;                                // the 32-row launch has no registers for it (up to 14 spilled)
+    if (rt <= 2) wide_item<STAGE1, 2, kAhead>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m, drain);
+    else wide_item<STAGE1, 4, kAhead>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m, drain);
 }
 
 // EVEN: this stage has an even number of K-steps
