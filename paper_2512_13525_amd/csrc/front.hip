@@ -422,6 +422,14 @@ __device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared
     }
 }
 
+// What a wavefront's lanes did to LDS before this comes before what they do after it.  The lanes run in step, but the compiler orders only
+// each lane's own accesses.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // The tail of batches with one or two requests a thread (GPW).  An expert has at most one slot on this instance, so which of its slots a
 // request would go to and the request's place there do not wait for Alg. 1: they are worked out with Step 1, and the counts' prefix over
 // the wavefronts beside Step 2; what follows Step 2 is the scan over the slots that it kept, on the second wavefront beside the stores of
@@ -457,17 +465,14 @@ __device__ __forceinline__ void front_tail_few(const FrontArgs &a, SmallShared &
 #pragma unroll
     for (int g = 0; g < GPW; ++g) {
         const uint64_t same = moe::lanes_alike(sl[g], 32 - __builtin_clz(C), __ballot(sl[g] >= 0));
-        rank[g] = 0;
-        if (sl[g] >= 0) {
-            const int before = g > 0 ? run[sl[g]] : 0;
-            rank[g] = before + __popcll(same & moe::lanemask_lt());
-            if (lane == __builtin_ctzll(same)) run[sl[g]] = before + __popcll(same);
+        int before = 0;
+        if (g > 0) {
+            wave_lds_order();                                         // what the previous group's first lanes wrote
+            if (sl[g] >= 0) before = run[sl[g]];
+            wave_lds_order();                                         // every lane of a slot has read before its first lane writes
         }
-        if (g + 1 < GPW) {                                            // the next group reads what this one's first lanes wrote
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        }
+        rank[g] = before + __popcll(same & moe::lanemask_lt());
+        if (sl[g] >= 0 && lane == __builtin_ctzll(same)) run[sl[g]] = before + __popcll(same);
     }
     __syncthreads();
 

@@ -110,6 +110,34 @@ def test_front_of_few_requests(n_inst, C, E, T):
             np.testing.assert_array_equal(s.blocks.cpu().numpy()[:len(blk)], blk)
 
 
+@pytest.mark.parametrize("n_inst,C,E,k,T", [(1, 7, 7, 3, 342), (1, 7, 7, 3, 682), (2, 5, 8, 2, 1024), (1, 1, 1, 1, 2048), (1, 256, 256, 8, 129),
+                                             (1, 256, 256, 8, 256)])
+def test_front_of_several_requests_a_token(n_inst, C, E, k, T):
+    """Every instance's dispatch, work list and replica ids against the oracle where a slot's requests lie in both groups of a wavefront
+    (1025 to 2048 requests: the second group's ranks go on where the first one's end), from one slot to 256."""
+    cfg = W.MoEConfig("several", E=E, k=k, d_h=32, d_e=32, T=T, n_inst=n_inst, C=C, zipf_s=0.5, seed=T)
+    lay = W.build_placement(cfg)
+    pl = scheduling.make_placement(lay, E, n_inst, C)
+    logits = W.router_logits(cfg)
+    ids, _ = routing.route_softmax(logits, k)
+    O, act_rep, load = scheduling.aebs(ids, pl)
+    for g in range(n_inst):
+        count, off, perm = dispatch.permute(O, g, C)
+        pos = np.full(T * k, -1)
+        pos[perm] = np.arange(len(perm))
+        s = LayerStep(cfg, lay, g)
+        for t in (s.topk_ids, s.rid, s.act_rep, s.load, s.slot_count, s.slot_off, s.perm, s.pos, s.blocks):
+            t.fill_(-5)
+        s.front(torch.from_numpy(logits).cuda())
+        torch.cuda.synchronize()
+        for got, want in ((s.topk_ids, ids), (s.rid, O), (s.act_rep, act_rep), (s.load, load), (s.slot_count, count), (s.slot_off, off),
+                          (s.pos, pos)):
+            np.testing.assert_array_equal(got.cpu().numpy().reshape(np.shape(want)), want)
+        np.testing.assert_array_equal(s.perm.cpu().numpy()[:len(perm)], perm)
+        blk = expected_blocks(off, B.moe_block_rows(T))
+        np.testing.assert_array_equal(s.blocks.cpu().numpy()[:len(blk)], blk)
+
+
 @pytest.mark.parametrize("E,k", [(64, 9), (64, 10), (128, 8), (256, 32), (512, 8), (576, 8), (704, 32), (768, 3), (1024, 8)])
 def test_front_selects_like_route(E, k):
     """Ids and weights of the front and of moe_route, bit for bit, on logits full of ties, for every number of keys a lane that
