@@ -244,6 +244,7 @@ int launch_gate(const void *X, const void *Wr, const float *bias, float *logits,
 // so the ids are read from memory exactly once and everything after that runs out of LDS and registers.
 constexpr int kGpwMax = 8;                                            // 64-request groups per wavefront (1 and 2: front_tail_few; 4 and 8: front_tail_small)
 constexpr int kRegPairs = moe::kFrontWaves * kGpwMax * MOE_WAVE;      // 8192
+constexpr int kFewPairs = 2 * moe::kFrontWaves * MOE_WAVE;            // 2048: up to two requests a thread
 constexpr int kSlotOfLds = 8192;                                      // E*n_inst entries of slot_of kept in LDS
 // A batch of a few tokens is routed by one workgroup: the ids stay in LDS, and the publication, the ticket and the
 // read-back (0.3 + 0.45 + 0.9 us at T = 8) fall away.  Its wavefronts take turns on the four SIMDs, so each further four
@@ -434,8 +435,9 @@ __device__ __forceinline__ void wave_lds_order() {
 // request would go to and the request's place there do not wait for Alg. 1: they are worked out with Step 1, and the counts' prefix over
 // the wavefronts beside Step 2; what follows Step 2 is the scan over the slots that it kept, on the second wavefront beside the stores of
 // Step 3, and the stores.  Bound by the instructions of its 16 wavefronts, four to a SIMD of one CU.  Against front_tail_small, which has two
-// passes over the requests and two more barriers behind Step 2: four layer steps at d_h = 2048, k = 8 with T = 8 95.0 -> 93.3 us, with T = 256
-// 164.1 -> 162.6; the gate and this launch at E = 64, k = 6, T = 300 12.3 -> 11.4 us.  With four and more requests a thread the ranks ahead of
+// passes over the requests and two more barriers behind Step 2, both in a kernel with all tails, us, this launch alone: E = 128, k = 8, T = 8
+// 6.45 -> 6.3, T = 128 7.8 -> 7.3, T = 256 8.3 -> 8.15; E = 256, k = 8, T = 256 9.35 -> 8.9 (with groups of experts 10.9 and 10.9, T = 160 10.55
+// and 10.65); E = 64, k = 6, T = 341 8.2 -> 7.7.  With four and more requests a thread the ranks ahead of
 // Step 2 take what they save behind it (E = 256, k = 8, T = 512 behind the gate 23.5 and 23.7 us), so those batches keep front_tail_small.
 // ids_lds: the batch's request ids in LDS (one-workgroup launch), or null: they were written by other workgroups.  VPL >= n_words.
 template <int VPL, int GPW>
@@ -538,15 +540,17 @@ __device__ __forceinline__ void front_tail_few(const FrontArgs &a, SmallShared &
     }
 }
 
-template <int VPL>
-__device__ __forceinline__ void front_tail_small(const FrontArgs &a, SmallShared &sh, int n_pairs) {
-    if (n_pairs <= kRegPairs / 8) front_tail_few<VPL, 1>(a, sh, n_pairs, nullptr);
-    else if (n_pairs <= kRegPairs / 4) front_tail_few<VPL, 2>(a, sh, n_pairs, nullptr);
-    else if (n_pairs <= kRegPairs / 2) front_tail_small<VPL, 4>(a, sh, n_pairs);
-    else front_tail_small<VPL, kGpwMax>(a, sh, n_pairs);
-}
+// What the last workgroup does.  A kernel for each, because the code of the tails that a batch does not run costs it scalar registers (256
+// experts: 16 spilled in the selection, none here) and a longer way through the code.  All tails in one kernel and one each, us, this launch
+// alone: E = 256, k = 8, T = 64 10.1 -> 9.7, T = 512 13.15 -> 12.9; E = 1000, k = 8, T = 700 24.4 -> 20.9; E = 64, k = 6, T = 1000 14.7 -> 14.5,
+// T = 3000 19.2 -> 19.0; 101 sizes 0.86 to 1.01, median 0.98.
+enum class Tail {
+    Few,      // up to kFewPairs requests, layout table in LDS: front_tail_few
+    Small,    // up to kRegPairs requests, layout table in LDS: front_tail_small
+    Large,    // the others
+};
 
-template <int VPL>
+template <int VPL, Tail TAIL>
 __global__ __launch_bounds__(moe::kFrontThreads)
 void front_kernel(FrontArgs a) {
     // the tails' LDS; the decode-size tail's is prepared while the tokens are routed, so the routing rows and
@@ -558,18 +562,19 @@ void front_kernel(FrontArgs a) {
     };
     __shared__ Shared sh;
     __shared__ float row[moe::kFrontWaves][VPL * MOE_WAVE];
-    __shared__ int32_t s_ids[kSoloTokens * MOE_MAX_TOPK];
+    __shared__ int32_t s_ids[TAIL == Tail::Few ? kSoloTokens * MOE_MAX_TOPK : 1];
     __shared__ int s_last;
     __shared__ uint32_t s_bits[kBitWords];                            // experts this workgroup's tokens selected
 
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / MOE_WAVE);
     const int lane = moe::lane_id();
     const int n_pairs = a.T * a.k;
-    const bool small = n_pairs <= kRegPairs && a.E * a.n_inst <= kSlotOfLds;
-    const bool solo = a.solo != 0;                                    // this is the only workgroup
+    constexpr bool small = TAIL != Tail::Large;
+    const bool solo = TAIL == Tail::Few && a.solo != 0;               // this is the only workgroup
+    const bool bits = TAIL == Tail::Large && a.act_bits;
     TablePrefetch tp{};
     if (small) tp = prefetch_tables(a);
-    if (a.act_bits) {
+    if (bits) {
         if (threadIdx.x < kBitWords) s_bits[threadIdx.x] = 0u;
         __syncthreads();
     }
@@ -583,7 +588,7 @@ void front_kernel(FrontArgs a) {
             int32_t *ids = a.ids + static_cast<size_t>(t) * a.k;
             float *w = a.w + static_cast<size_t>(t) * a.k;
             moe::route_token<VPL, true>(lg, a.E, a.k, a.cfg, row[wave], lane, ids, w, solo ? s_ids + t * a.k : nullptr,
-                                        a.act_bits ? s_bits : nullptr);
+                                        bits ? s_bits : nullptr);
         }
     }
     // Wavefronts that route nothing prepare the tail meanwhile; where all route only the last workgroup does.  Against every
@@ -591,12 +596,14 @@ void front_kernel(FrontArgs a) {
     // experts and from 1025 tokens on up to 2 % slower (E = 128, k = 4, T = 2048 13.6 -> 13.8), below that 0 to 3 % faster.
     const bool early = solo || a.tok_per_wg < moe::kFrontWaves;
     if (small && early) stage_small(a, sh.small, tp);
-    if (solo) {
-        __syncthreads();
-        front_tail_few<VPL, 1>(a, sh.small, n_pairs, s_ids);
-        return;
+    if constexpr (TAIL == Tail::Few) {
+        if (solo) {
+            __syncthreads();
+            front_tail_few<VPL, 1>(a, sh.small, n_pairs, s_ids);
+            return;
+        }
     }
-    if (a.act_bits) {
+    if (bits) {
         // Step 1 of Alg. 1, spread over the routing workgroups: one atomic per non-empty word
         __syncthreads();
         if (threadIdx.x < kBitWords && s_bits[threadIdx.x])
@@ -613,34 +620,40 @@ void front_kernel(FrontArgs a) {
     __syncthreads();
     if (!s_last) return;
 
-    if (small) {
+    if constexpr (small) {
         if (!early) {
             stage_small(a, sh.small, tp);
             __syncthreads();
         }
-        front_tail_small<VPL>(a, sh.small, n_pairs);
-        return;
-    }
-    if (a.act_bits) {
-        // Step 2 from the bitset the routing workgroups left; Step 3 and the sort follow in two launches
-        moe::aebs_stage_tables(a.tb, sh.sched, a.E, a.n_inst, a.n_words);
-        for (int e = threadIdx.x; e < a.E; e += moe::kFrontThreads) {
-            const uint32_t word = __hip_atomic_load(a.act_bits + (e >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sh.sched.flag[e] = (word >> (e & 31)) & 1u;
+        if constexpr (TAIL == Tail::Few) {
+            if (n_pairs <= kFewPairs / 2) front_tail_few<VPL, 1>(a, sh.small, n_pairs, nullptr);
+            else front_tail_few<VPL, 2>(a, sh.small, n_pairs, nullptr);
+        } else {
+            if (n_pairs <= kRegPairs / 2) front_tail_small<VPL, kGpwMax / 2>(a, sh.small, n_pairs);
+            else front_tail_small<VPL, kGpwMax>(a, sh.small, n_pairs);
         }
+    } else {
+        if (bits) {
+            // Step 2 from the bitset the routing workgroups left; Step 3 and the sort follow in two launches
+            moe::aebs_stage_tables(a.tb, sh.sched, a.E, a.n_inst, a.n_words);
+            for (int e = threadIdx.x; e < a.E; e += moe::kFrontThreads) {
+                const uint32_t word = __hip_atomic_load(a.act_bits + (e >> 5), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                sh.sched.flag[e] = (word >> (e & 31)) & 1u;
+            }
+            __syncthreads();
+            if (threadIdx.x < kBitWords)                                  // ready for the next call
+                __hip_atomic_store(a.act_bits + threadIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            moe::aebs_select<VPL>(a.tb, sh.sched, a.E, a.n_inst, a.C, a.n_words, a.act_rep, a.load);
+            return;
+        }
+        const int vec_ok = ((reinterpret_cast<uintptr_t>(a.ids) | reinterpret_cast<uintptr_t>(a.rid)) & 15) == 0;
+        moe::aebs_block<VPL>(a.tb, sh.sched, a.E, a.n_inst, a.C, a.n_words, a.ids, n_pairs, vec_ok, true,
+                        a.rid, a.act_rep, a.load);
+        // rid is re-read below by other wavefronts of this workgroup
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         __syncthreads();
-        if (threadIdx.x < kBitWords)                                  // ready for the next call
-            __hip_atomic_store(a.act_bits + threadIdx.x, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        moe::aebs_select<VPL>(a.tb, sh.sched, a.E, a.n_inst, a.C, a.n_words, a.act_rep, a.load);
-        return;
+        moe::permute_block(sh.perm, a.rid, n_pairs, a.g_self, a.C, a.slot_count, a.slot_off, a.perm, a.pos, a.blocks, a.block_rows);
     }
-    const int vec_ok = ((reinterpret_cast<uintptr_t>(a.ids) | reinterpret_cast<uintptr_t>(a.rid)) & 15) == 0;
-    moe::aebs_block<VPL>(a.tb, sh.sched, a.E, a.n_inst, a.C, a.n_words, a.ids, n_pairs, vec_ok, true,
-                    a.rid, a.act_rep, a.load);
-    // rid is re-read below by other wavefronts of this workgroup
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    moe::permute_block(sh.perm, a.rid, n_pairs, a.g_self, a.C, a.slot_count, a.slot_off, a.perm, a.pos, a.blocks, a.block_rows);
 }
 
 // Step 3 of Alg. 1 for one chunk of requests and the chunk's per-slot counts.
@@ -671,14 +684,20 @@ template <int VPL>
 int launch_front(const FrontArgs &a_in, const char *what, hipStream_t st) {
     FrontArgs a = a_in;
     // every routing workgroup takes a ticket from one counter: keep them to about a hundred
-    a.solo = static_cast<long long>(a.T) * a.k <= kRegPairs && a.E * a.n_inst <= kSlotOfLds && a.T <= solo_tokens(a.E, a.k);
+    const long long n_pairs = static_cast<long long>(a.T) * a.k;
+    const Tail tail = n_pairs > kRegPairs || a.E * a.n_inst > kSlotOfLds ? Tail::Large : n_pairs > kFewPairs ? Tail::Small : Tail::Few;
+    static_assert(kSoloTokens * MOE_MAX_TOPK <= kFewPairs, "a batch of one workgroup is one of few requests");
+    a.solo = tail == Tail::Few && a.T <= solo_tokens(a.E, a.k);
     a.tok_per_wg = a.solo ? moe::kFrontWaves : a.T <= 512 ? 4 : a.T <= 1024 ? 8 : moe::kFrontWaves;
     // past one workgroup per CU the counter and the bit set cost more than a second token on every wavefront
     // (T = 8192, E = 256: front 32 -> 28 us; E = 128 30 -> 26)
     a.tok_per_wave = a.act_bits && a.T > kFrontTwoTokens ? 2 : 1;
     const int per = a.tok_per_wg * a.tok_per_wave;
     const int blocks = a.T > 0 ? (a.T + per - 1) / per : 1;
-    hipLaunchKernelGGL(front_kernel<VPL>, dim3(blocks), dim3(moe::kFrontThreads), 0, st, a);
+    const dim3 grid(blocks), threads(moe::kFrontThreads);
+    if (tail == Tail::Few) hipLaunchKernelGGL((front_kernel<VPL, Tail::Few>), grid, threads, 0, st, a);
+    else if (tail == Tail::Small) hipLaunchKernelGGL((front_kernel<VPL, Tail::Small>), grid, threads, 0, st, a);
+    else hipLaunchKernelGGL((front_kernel<VPL, Tail::Large>), grid, threads, 0, st, a);
     if (a.act_bits) {
         hipLaunchKernelGGL(front_count_kernel, dim3(a.n_chunks), dim3(moe::kFrontThreads), 0, st, a);
         hipLaunchKernelGGL(front_scatter_kernel, dim3(a.n_chunks), dim3(moe::kFrontThreads), 0, st, a);
