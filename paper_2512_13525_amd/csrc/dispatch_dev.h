@@ -514,7 +514,7 @@ __device__ __forceinline__ void aebs_block(const SchedTables &tb, SchedShared &s
 }
 
 // ------------------------------------------------------------------ a4: dispatch in one workgroup
-// The lanes of `among` whose v (below 2^bits) is this lane's; meaningless in other lanes.  A ballot per bit, whatever the number of
+// The lanes of `among` whose v (below 2^bits, bits >= 1) is this lane's; meaningless in other lanes.  A ballot per bit, whatever the number of
 // different values.
 __device__ __forceinline__ uint64_t lanes_alike(int v, int bits, uint64_t among) {
     uint32_t lo = static_cast<uint32_t>(among), hi = static_cast<uint32_t>(among >> 32);

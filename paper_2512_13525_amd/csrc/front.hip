@@ -464,9 +464,10 @@ __device__ __forceinline__ void front_tail_few(const FrontArgs &a, SmallShared &
         }
     }
     int *run = &sh.perm.cnt[wave][0];                                 // this wavefront's requests of each slot so far
+    const int slot_bits = C > 1 ? 32 - __builtin_clz(C - 1) : 1;
 #pragma unroll
     for (int g = 0; g < GPW; ++g) {
-        const uint64_t same = moe::lanes_alike(sl[g], 32 - __builtin_clz(C), __ballot(sl[g] >= 0));
+        const uint64_t same = moe::lanes_alike(sl[g], slot_bits, __ballot(sl[g] >= 0));
         int before = 0;
         if (g > 0) {
             wave_lds_order();                                         // what the previous group's first lanes wrote
@@ -510,9 +511,11 @@ __device__ __forceinline__ void front_tail_few(const FrontArgs &a, SmallShared &
     const int rid_lo = a.g_self * C;
     if (wave == 1) {
         const auto total_of = [&](int s) {
+            static_assert((MOE_MAX_EXPERTS & (MOE_MAX_EXPERTS - 1)) == 0, "the mask keeps any value inside rep");
             const int e = sh.expert_of[s] & (MOE_MAX_EXPERTS - 1);    // unspecified for an empty slot, whose total is 0
             return sh.sched.rep[e] == rid_lo + s ? sh.perm.total[s] : 0;
         };
+        static_assert(kFewPairs < 32768, "scan_slots_packed counts blocks in 16 bits");
         moe::scan_slots_packed(sh.perm, C, a.block_rows, total_of, a.slot_count, a.slot_off, lane);
     }
     int row[GPW];
