@@ -54,6 +54,8 @@ def test_front_sizes(n_inst, C, E, T):
     O, act_rep, load = scheduling.aebs(ids, pl)
     g = int(np.argmax(load))
     count, off, perm = dispatch.permute(O, g, C)
+    pos = np.full(T * k, -1)
+    pos[perm] = np.arange(len(perm))
     s = LayerStep(cfg, lay, g)
     for _ in range(2):
         for t in (s.topk_ids, s.rid, s.act_rep, s.load, s.slot_count, s.slot_off, s.perm, s.pos, s.blocks):
@@ -61,7 +63,7 @@ def test_front_sizes(n_inst, C, E, T):
         s.front(torch.from_numpy(logits).cuda())
         torch.cuda.synchronize()
         for got, want in ((s.topk_ids, ids), (s.rid, O), (s.act_rep, act_rep), (s.load, load), (s.slot_count, count),
-                          (s.slot_off, off)):
+                          (s.slot_off, off), (s.pos, pos)):
             np.testing.assert_array_equal(got.cpu().numpy().reshape(np.shape(want)), want)
         np.testing.assert_array_equal(s.perm.cpu().numpy()[:len(perm)], perm)
         blk = expected_blocks(off, B.moe_block_rows(T))
@@ -133,6 +135,36 @@ def test_front_of_several_requests_a_token(n_inst, C, E, k, T):
         for got, want in ((s.topk_ids, ids), (s.rid, O), (s.act_rep, act_rep), (s.load, load), (s.slot_count, count), (s.slot_off, off),
                           (s.pos, pos)):
             np.testing.assert_array_equal(got.cpu().numpy().reshape(np.shape(want)), want)
+        np.testing.assert_array_equal(s.perm.cpu().numpy()[:len(perm)], perm)
+        blk = expected_blocks(off, B.moe_block_rows(T))
+        np.testing.assert_array_equal(s.blocks.cpu().numpy()[:len(blk)], blk)
+
+
+@pytest.mark.parametrize("n_inst,C,E", [(4, 100, 300), (5, 140, 680), (8, 130, 1000)])
+@pytest.mark.parametrize("T", [8, 9, 128, 129, 256, 257, 512, 513, 1024, 1025])
+def test_front_of_many_experts(n_inst, C, E, T):
+    """8, 12 and 16 keys a lane with every tail (k = 8: the edges of 1024, 2048, 4096 and 8192 requests lie on T; one workgroup up to 8
+    tokens), the layout table in LDS: everything the front writes against the oracle, for the straggler and for the last instance."""
+    k = 8
+    cfg = W.MoEConfig("many", E=E, k=k, d_h=32, d_e=32, T=T, n_inst=n_inst, C=C, zipf_s=1.0, seed=T)
+    lay = W.build_placement(cfg)
+    pl = scheduling.make_placement(lay, E, n_inst, C)
+    logits = W.router_logits(cfg)
+    ids, w = routing.route_softmax(logits, k)
+    O, act_rep, load = scheduling.aebs(ids, pl)
+    for g in sorted({int(np.argmax(load)), n_inst - 1}):
+        count, off, perm = dispatch.permute(O, g, C)
+        pos = np.full(T * k, -1)
+        pos[perm] = np.arange(len(perm))
+        s = LayerStep(cfg, lay, g)
+        for t in (s.topk_ids, s.topk_w, s.rid, s.act_rep, s.load, s.slot_count, s.slot_off, s.perm, s.pos, s.blocks):
+            t.fill_(-5)
+        s.front(torch.from_numpy(logits).cuda())
+        torch.cuda.synchronize()
+        for got, want in ((s.topk_ids, ids), (s.rid, O), (s.act_rep, act_rep), (s.load, load), (s.slot_count, count), (s.slot_off, off),
+                          (s.pos, pos)):
+            np.testing.assert_array_equal(got.cpu().numpy().reshape(np.shape(want)), want)
+        np.testing.assert_allclose(s.topk_w.cpu().numpy(), w, rtol=1e-5, atol=1e-30)   # fp32 exp and a sum of 8
         np.testing.assert_array_equal(s.perm.cpu().numpy()[:len(perm)], perm)
         blk = expected_blocks(off, B.moe_block_rows(T))
         np.testing.assert_array_equal(s.blocks.cpu().numpy()[:len(blk)], blk)
