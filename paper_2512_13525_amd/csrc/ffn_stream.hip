@@ -670,8 +670,9 @@ __device__ __forceinline__ void wide_item(const StreamArgs &a, const StageArgs &
         asm volatile("" ::: "memory");                                                           \
     } while (0)
     // A K-tile's products.  AHEAD: the second K-step's fragments are read between the first one's products, one behind each row tile's,
-    // instead of ahead of its own, where every wavefront waits for LDS a second time (layer steps, us: d_h = 2048, d_e = 1408, T = 1000 108.7 ->
-    // 107.7, without popular experts 102.8 -> 101.6; d_e = 768, T = 1500 73.7 -> 72.7; d_h = 4096, d_e = 1536, T = 700 level).
+    // instead of ahead of its own, where every wavefront waits for LDS a second time.  This launch alone, us: 32 blocks and no streams 82.8 ->
+    // 81.6 (d_h = 2048, d_e = 1408, T = 1000) and 55.1 -> 54.0 (d_e = 768, T = 1500); 58 blocks beside streams (d_e = 1408, T = 1500) 105.6 ->
+    // 103.5 with runs of one side 1.4 apart; up to 26 blocks beside streams (T = 500 to 1000, also d_h = 4096 and 7168) level, 0.99 to 1.00.
 #define MOE_WIDE_READ(set, ss, r)                                                                \
     b_[r] = *reinterpret_cast<const bf16x8 *>(lds + ((set) & 1) * kBufBytes + (r) * 2048 + rd_row + (((4 * (ss) + rd_g) ^ rd_sw) * 16))
 #define MOE_WIDE_MMA(set, full)                                                                  \
@@ -1048,7 +1049,10 @@ __device__ __forceinline__ void run_wide(const StreamArgs &a, const StageArgs &g
     const bool drain = wide_drains<BR>(n, a.s[1].tiles);
     // up to 16 rows as two row tiles (one kind of item less; slots of 72 rows: 58 -> 61 us at d_h = 2048, d_e = 768, 173 -> 163 at
     // d_h = 4096, d_e = 1536)
-    constexpr bool kAhead = BR == 64;                                // the 32-row launch has no registers for it (up to 14 spilled)
+    // The 32-row launch is without it: compiled for long lists it would spill 3 or 14 registers.  Its other instantiations would not; steps
+    // there measured 0.98 to 1.00 with it (d_h = 2048, d_e = 1408, T = 256 63.1 -> 61.9 us; d_h = 7168 with a shared expert, T = 256
+    // 226.9 -> 225.4; eleven others level).
+    constexpr bool kAhead = BR == 64;
     if (rt <= 2) wide_item<STAGE1, 2, kAhead>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m, drain);
     else wide_item<STAGE1, 4, kAhead>(a, g, lds, s_ok, item, pair.group, groups, slot, row0, m, drain);
 }
