@@ -594,11 +594,10 @@ void front_kernel(FrontArgs a) {
                                         bits ? s_bits : nullptr);
         }
     }
-    // Wavefronts that route nothing prepare the tail meanwhile; where all route only the last workgroup does.  Against every
-    // workgroup preparing it: E = 512, k = 4, T = 1500 16.5 -> 16.1 us, E = 384, k = 2, T = 3000 14.0 -> 13.8; with up to 256
-    // experts and from 1025 tokens on up to 2 % slower (E = 128, k = 4, T = 2048 13.6 -> 13.8), below that 0 to 3 % faster.
-    const bool early = solo || a.tok_per_wg < moe::kFrontWaves;
-    if (small && early) stage_small(a, sh.small, tp);
+    // Wavefronts that route nothing prepare the tail meanwhile, and so do those that have routed.  Against only the last workgroup preparing
+    // it where all wavefronts route: E = 256, k = 4, T = 1025 12.7 -> 12.0 us, E = 128, k = 4, T = 1600 14.3 -> 14.0, E = 384, k = 2, T = 4000
+    // 20.5 -> 20.3, none of 24 sizes slower.
+    if (small) stage_small(a, sh.small, tp);
     if constexpr (TAIL == Tail::Few) {
         if (solo) {
             __syncthreads();
@@ -624,10 +623,6 @@ void front_kernel(FrontArgs a) {
     if (!s_last) return;
 
     if constexpr (small) {
-        if (!early) {
-            stage_small(a, sh.small, tp);
-            __syncthreads();
-        }
         if constexpr (TAIL == Tail::Few) {
             if (n_pairs <= kFewPairs / 2) front_tail_few<VPL, 1>(a, sh.small, n_pairs, nullptr);
             else front_tail_few<VPL, 2>(a, sh.small, n_pairs, nullptr);
