@@ -594,10 +594,12 @@ void front_kernel(FrontArgs a) {
                                         bits ? s_bits : nullptr);
         }
     }
-    // Wavefronts that route nothing prepare the tail meanwhile, and so do those that have routed.  Against only the last workgroup preparing
-    // it where all wavefronts route: E = 256, k = 4, T = 1025 12.7 -> 12.0 us, E = 128, k = 4, T = 1600 14.3 -> 14.0, E = 384, k = 2, T = 4000
-    // 20.5 -> 20.3, none of 24 sizes slower.
-    if (small) stage_small(a, sh.small, tp);
+    // Wavefronts that route nothing prepare the tail meanwhile, and so do those that have routed: against only the last workgroup preparing
+    // it where all wavefronts route, E = 256, k = 4, T = 1025 12.7 -> 11.9 us, E = 128, k = 4, T = 1600 14.3 -> 14.05, E = 384, k = 2, T = 4000
+    // 20.5 -> 20.3, none of 24 sizes slower.  Few requests are past 1024 tokens only with k = 1, and there the last workgroup does it: every
+    // one would take 2 to 3 % off them, but without this test the code for all batches of few requests came out 0.5 to 2 % slower.
+    const bool early = TAIL == Tail::Small || solo || a.tok_per_wg < moe::kFrontWaves;
+    if (small && early) stage_small(a, sh.small, tp);
     if constexpr (TAIL == Tail::Few) {
         if (solo) {
             __syncthreads();
@@ -623,6 +625,10 @@ void front_kernel(FrontArgs a) {
     if (!s_last) return;
 
     if constexpr (small) {
+        if (!early) {
+            stage_small(a, sh.small, tp);
+            __syncthreads();
+        }
         if constexpr (TAIL == Tail::Few) {
             if (n_pairs <= kFewPairs / 2) front_tail_few<VPL, 1>(a, sh.small, n_pairs, nullptr);
             else front_tail_few<VPL, 2>(a, sh.small, n_pairs, nullptr);
@@ -688,7 +694,7 @@ int launch_front(const FrontArgs &a_in, const char *what, hipStream_t st) {
     a.solo = tail == Tail::Few && a.T <= solo_tokens(a.E, a.k);
     a.tok_per_wg = a.solo ? moe::kFrontWaves : a.T <= 512 ? 4 : a.T <= 1024 ? 8 : moe::kFrontWaves;
     // past one workgroup per CU the counter and the bit set cost more than a second token on every wavefront
-    // (T = 8192, E = 256: front 32 -> 28 us; E = 128 30 -> 26)
+    // (T = 8192, k = 8, this launch and the two behind it: E = 256 30.6 -> 26.2 us; E = 128 31.8 -> 27.6)
     a.tok_per_wave = a.act_bits && a.T > kFrontTwoTokens ? 2 : 1;
     const int per = a.tok_per_wg * a.tok_per_wave;
     const int blocks = a.T > 0 ? (a.T + per - 1) / per : 1;
@@ -715,7 +721,7 @@ int launch_front_for(const FrontArgs &a, const char *what, hipStream_t st) {
     if (vpl <= 2) return launch_front<2>(a, what, st);
     if (vpl <= 4) return launch_front<4>(a, what, st);
     if (vpl <= 8) return launch_front<8>(a, what, st);
-    if (vpl <= 12) return launch_front<12>(a, what, st);      // E = 640, k = 16, T = 55: 19.5 us, 22.1 with the code for 1024 experts
+    if (vpl <= 12) return launch_front<12>(a, what, st);      // E = 640, k = 16, T = 55: 14.7 us, 17.2 with the code for 1024 experts
     return launch_front<16>(a, what, st);
 }
 
