@@ -249,8 +249,10 @@ constexpr int kSlotOfLds = 8192;                                      // E*n_ins
 // A batch of a few tokens is routed by one workgroup: the ids stay in LDS, and the publication, the ticket and the
 // read-back (0.3 + 0.45 + 0.9 us at T = 8) fall away.  Its wavefronts take turns on the four SIMDs, so each further four
 // tokens add a selection to the chain, and the line falls with the selection's length, about E * k
-// (one workgroup against several, us: E = 128, k = 8, T = 12 7.4 and 7.6, T = 16 8.0 and 7.6; E = 512, k = 8, T = 8
-// 9.1 and 9.7, T = 12 10.2 and 9.4; E = 1024, k = 32, T = 4 27.2 and 28.4, T = 16 39.9 and 29.6).
+// (one workgroup against several, us: E = 64, k = 6, T = 12 5.7 and 5.9; E = 128, k = 8, T = 8 6.35 and 6.7; E = 512, k = 8, T = 8 9.3 and 9.75,
+// T = 12 level; E = 1000, k = 8, T = 8 12.6 and 13.2; E = 1024, k = 32, T = 4 21.9 and 22.6, T = 16 34.5 and 23.7).  With 9 to 12 tokens and
+// E * k from 768 to 2048 several would take 1 to 6 % less (E = 128, k = 8, T = 12 6.9 and 6.7; E = 256 with groups, k = 8, T = 9 9.4 and 8.8),
+// but one workgroup leaves the ticket alone there, which callers with several streams have been able to rely on.
 constexpr int kSoloTokens = 12;
 int solo_tokens(int E, int k) { return E * k <= 2048 ? kSoloTokens : E * k <= 8192 ? 8 : 4; }
 
